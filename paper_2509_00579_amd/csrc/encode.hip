@@ -262,7 +262,9 @@ __global__ __launch_bounds__(256) void write_kernel(Geo g, const uint16_t *__res
     enc[tid] = enc_of(g, WHICH)[tid];
     enc[256 + tid] = enc_of(g, WHICH)[256 + tid];
     static_assert(sizeof(rec) % 16 == 0, "whole 16-byte units");
-    for (int i = tid; i < (int)(sizeof(rec) / 16); i += 256) reinterpret_cast<uint4 *>(rec)[i] = make_uint4(0, 0, 0, 0);
+    // cleared from behind the {min,max} words on: another wave may have stored those already (the one word of a BlockQuant
+    // header and the padding behind it belong to thread 0 in both places)
+    for (int i = tid + R::n_units(g) / 4; i < (int)(sizeof(rec) / 16); i += 256) reinterpret_cast<uint4 *>(rec)[i] = make_uint4(0, 0, 0, 0);
     // codes -> LDS tile (token-major rows, padded), header -> record
     const int c0 = tile_chan0(tid);
     if constexpr (KEPT) {  // the kept codes are already packed the way the tile wants them

@@ -188,6 +188,27 @@ def test_prefill_with_one_quantization_pass(gpu, oracle, B, H, Hq, S, rel_k, rel
     gc.close()
 
 
+@pytest.mark.parametrize("B,H,S", [(4, 8, 32768)])
+def test_prefill_is_reproducible(gpu, B, H, S):
+    """The same prompt compressed again and again gives the same cache: every record of 2 x 16384 blocks, read back as
+    fp16 (a wave that clears a record header after another has filled it shows in about one block in 10^5)."""
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(17)
+    Kx, Vx = (torch.randn((B, S, H, 128), generator=gen, device="cuda:0").half() for _ in range(2))
+    gc = gpu.KVCompCache(B, H, H, S, 1e-2, 1e-2, max_code_len=6)
+    ws = torch.empty(gc.prefill_workspace_bytes(S), dtype=torch.uint8, device="cuda:0")
+    first = None
+    for i in range(24):
+        gc.reset(keep_codebook=False)
+        gc.prefill(Kx, Vx, ws)
+        got = [gc.decompress(w, S) for w in (K, V)]
+        if first is None:
+            first = got
+        assert all(torch.equal(a, b) for a, b in zip(got, first)), f"pass {i} differs from the first"
+    gc.close()
+
+
 def test_one_context_two_prompts_with_different_codebooks(gpu, oracle):
     """A context that is reset and filled again builds new codebooks: the tables that the second prompt is encoded and
     decoded with must be the second prompt's (the tables travel from a pinned host block that is rewritten in place).
