@@ -25,6 +25,8 @@
 //    reduction" of Section 3.3.2) inside the same launch.
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "huff_decode.cuh"
 #include "kvcomp_internal.h"
 #include "split_combine.cuh"
@@ -789,116 +791,184 @@ __device__ __forceinline__ void tile_state_to_area(const TileSoft<G> &ts, float 
 
 
 // The buffered fp16 tokens (Section 3.2.3: the newest vectors take part too), in units of 16 tokens; this wave takes
-// units first_unit, first_unit + unit_step, ...  Token r of the buffer sits in slot (res_head + r) mod res_tokens;
-// res_head is a multiple of 64, so a unit never wraps.
-// A unit is read with 4 coalesced loads per tensor (one instruction = 4 rows of 256 bytes: lane = row l/16, 16-byte
-// piece l%16), K and V together and all in flight at once: a single wave has nothing else to hide the memory
-// latency with, and small units spread the buffer over many waves.  Scores of row 4i + l/16 are formed by a sum over
-// the row's 16 lanes, which is also the layout the V rows arrive in; the channel sums are then folded over the four
-// row groups and handed to the lanes that own them (lane l: channels 2l, 2l+1).
+// units first_unit, first_unit + unit_step, ...  Token r of the buffer (oldest = 0) sits in slot
+// (res_head + r) mod res_tokens; res_head is a multiple of 64, so a unit never wraps.
+// A unit is read with four 16-byte loads per lane and tensor, K and V together and all in flight at once: a single wave
+// has nothing else to hide the memory latency with, and small units spread the buffer over many waves.
+//   scores : v_mfma_f32_16x16x32_f16, tokens x heads.  Lane l supplies K row l % 16 and query head l % 16, channels
+//            32 i + 8 (l / 16) .. +7 in step i, and receives head l % 16 of the tokens 4 (l / 16) .. +3.
+//   p . V  : lane l holds channels 8 (l % 16) .. +7 of those same four tokens, so a numerator reaches the 16 lanes that
+//            multiply with it by a broadcast inside their row of 16, which rides on the FMA.
+// All heads of a group share the loads, the matrix instructions and one running softmax per unit; only the FMAs of p . V
+// grow with the group.  (One head after the other on the vector ALU, with its own reductions and lane exchanges, a unit
+// took 5 us for groups of 4: the waves that had one finished last.)
 // When the append of the newest token is fused into the launch (new_row >= 0), its row comes from k_new / v_new
-// instead of the buffer, and the 16 lanes that read it store it into its buffer slot for the launches to come: one
+// instead of the buffer, and the lanes that read it store it into its buffer slot for the launches to come: one
 // wave of the grid per (batch, head) owns that row, so there is one writer and no reader of the slot in this launch.
+// The result is merged into the wave's parked state (`area`, see soft_to_area).
 // Out of line: it runs once, after the decode loop, and must not weigh on that loop's registers.
 constexpr int kUnitTokens = 16;
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// acc + (w of lane N of this lane's row of 16) * x: the broadcast is a DPP modifier of the FMA's first operand.  w must
+// not have been written by a VALU instruction in the two wait states before (row_operand()).
+template <int N>
+__device__ __forceinline__ float fma_row(float w, float x, float acc) {
+    static_assert(N >= 0 && N < 8, "lane of the row");
+#define KVC_FMA_ROW(n) if constexpr (N == n) asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:" #n " row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(w), "v"(x))
+    KVC_FMA_ROW(0); KVC_FMA_ROW(1); KVC_FMA_ROW(2); KVC_FMA_ROW(3); KVC_FMA_ROW(4); KVC_FMA_ROW(5); KVC_FMA_ROW(6); KVC_FMA_ROW(7);
+#undef KVC_FMA_ROW
+    return acc;
+}
+__device__ __forceinline__ void row_operand(float &a, float &b, float &c, float &d) {
+    asm volatile("s_nop 1" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+}
+// w of lane n of this lane's row of 16
+template <int N>
+__device__ __forceinline__ float row_bcast(float w) { return dpp_f<0x150 + N>(w); }
+template <int G, int N = 0, class F>
+__device__ __forceinline__ void for_heads(F &&f) {  // f(integral constant) for the heads 0 .. G-1
+    if constexpr (N < G) {
+        f(std::integral_constant<int, N>());
+        for_heads<G, N + 1>(f);
+    }
+}
+// a + b over the two halves / the neighbouring rows of the wave: the first half (even rows) receives a's sum, the second
+// (odd rows) b's
+__device__ __forceinline__ float fold_halves(float a, float b) {
+    const v2u r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+__device__ __forceinline__ float fold_rows(float a, float b) {
+    const v2u r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+__device__ __forceinline__ float max_over_rows(float v) {  // over the four rows of 16, per lane of the row
+    v2u r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+    r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+}
+
 template <int G>
 __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens, int B, int H, int b, int h,
                                              int res_head, int n_res, int first_unit, int unit_step,
-                                             const float *qf, float scale, int lane, const uint16_t *k_new,
+                                             const uint16_t *q0, float scale, int lane, const uint16_t *k_new,
                                              const uint16_t *v_new, int new_row, float *area) {
-    Soft<G> st;
-    area_to_soft<G>(area, lane, st);
     const size_t res_tensor = (size_t)B * res_tokens * H * kD;
-    const size_t row4 = (size_t)4 * H * kD;  // elements from one load to the next
     const int n_units = (n_res + kUnitTokens - 1) / kUnitTokens;
-    const int grp = lane >> 4, sub = lane & 15;
-    const bool hi2 = (grp & 2) != 0, hi1 = (grp & 1) != 0;
-    const int owner = 16 * (lane & 3) + (lane >> 2);  // after the fold: the lane that holds channels 2*lane, 2*lane+1
+    const int col = lane & 15, grp = lane >> 4;
+    uint4 qb[4];  // head `col` of the group (zeros beyond it)
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+        qb[i] = col < G ? *reinterpret_cast<const uint4 *>(q0 + col * kD + 32 * i + 8 * grp) : make_uint4(0, 0, 0, 0);
+    float m = -INFINITY, l = 0.f;  // running maximum of head `col`; its sum, this lane's share
+    float av[G][8];                // channels 8 col .. +7 of every head, this row's tokens
+#pragma unroll
+    for (int g = 0; g < G; g++)
+#pragma unroll
+        for (int k = 0; k < 8; k++) av[g][k] = 0.f;
     for (int u = first_unit; u < n_units; u += unit_step) {
         const int n_tok = min(kUnitTokens, n_res - u * kUnitTokens);
         int slot0 = res_head + u * kUnitTokens;
         if (slot0 >= res_tokens) slot0 -= res_tokens;
-        const size_t buf_off = (((size_t)b * res_tokens + slot0 + grp) * H + h) * kD + 8 * sub;
-        const size_t new_off = ((size_t)b * H + h) * kD + 8 * sub;
-        const int row0 = u * kUnitTokens + grp;  // number of this lane's first row in the buffer, oldest token = 0
+        const int new_tok = new_row - u * kUnitTokens;  // the appended token's number inside the unit, if it is in there
+        const size_t new_off = ((size_t)b * H + h) * kD;
+        const size_t buf0 = (((size_t)b * res_tokens + slot0) * H + h) * kD, row = (size_t)H * kD;
         uint4 rk[4], rv[4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const uint16_t *src = row0 + 4 * i == new_row ? k_new + new_off : res + buf_off + i * row4;
-            rk[i] = 4 * i + grp < n_tok ? *reinterpret_cast<const uint4 *>(src) : make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const uint16_t *src = row0 + 4 * i == new_row ? v_new + new_off : res + res_tensor + buf_off + i * row4;
-            rv[i] = 4 * i + grp < n_tok ? *reinterpret_cast<const uint4 *>(src) : make_uint4(0, 0, 0, 0);
-        }
-        if (new_row >= 0) {
-            uint16_t *wr = const_cast<uint16_t *>(res) + buf_off;
+        {
+            const uint16_t *src = (col == new_tok ? k_new + new_off : res + buf0 + col * row) + 8 * grp;
 #pragma unroll
             for (int i = 0; i < 4; i++)
-                if (row0 + 4 * i == new_row) {
-                    *reinterpret_cast<uint4 *>(wr + i * row4) = rk[i];
-                    *reinterpret_cast<uint4 *>(wr + res_tensor + i * row4) = rv[i];
-                }
+                rk[i] = col < n_tok ? *reinterpret_cast<const uint4 *>(src + 32 * i) : make_uint4(0, 0, 0, 0);
         }
-#pragma unroll 1
-        for (int gg = 0; gg < G; gg++) {
-            float qv[8];
 #pragma unroll
-            for (int k = 0; k < 8; k++) qv[k] = qf[gg * kD + 8 * sub + k];
-            float sc[4], mloc = -INFINITY;
+        for (int i = 0; i < 4; i++) {
+            const int t = 4 * grp + i;
+            const uint16_t *src = (t == new_tok ? v_new + new_off : res + res_tensor + buf0 + t * row) + 8 * col;
+            rv[i] = t < n_tok ? *reinterpret_cast<const uint4 *>(src) : make_uint4(0, 0, 0, 0);
+        }
+        if (new_row >= 0 && new_tok >= 0 && new_tok < kUnitTokens) {
+            uint16_t *wr = const_cast<uint16_t *>(res) + buf0 + new_tok * row;
+            if (col == new_tok) {
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const uint32_t w[4] = {rk[i].x, rk[i].y, rk[i].z, rk[i].w};
-                float d = 0.f;
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    d = fmaf(qv[2 * k], h2f(w[k] & 0xffffu), d);
-                    d = fmaf(qv[2 * k + 1], h2f(w[k] >> 16), d);
-                }
-                d += dpp_f<kDppXor1>(d);
-                d += dpp_f<kDppXor2>(d);
-                d += dpp_f<kDppHalfMirror>(d);
-                d += dpp_f<kDppMirror>(d);  // the row's 16 lanes all hold its dot product
-                sc[i] = 4 * i + grp < n_tok ? scale * d : -INFINITY;
-                mloc = fmaxf(mloc, sc[i]);
+                for (int i = 0; i < 4; i++) *reinterpret_cast<uint4 *>(wr + 32 * i + 8 * grp) = rk[i];
             }
-            mloc = wave_max(mloc);
-            const float mnew = fmaxf(st.m[gg], mloc);
-            const float alpha = __expf(st.m[gg] - mnew);
-            float psum = 0.f;
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                sc[i] = __expf(sc[i] - mnew);
-                psum += sc[i];
+            for (int i = 0; i < 4; i++)
+                if (4 * grp + i == new_tok) *reinterpret_cast<uint4 *>(wr + res_tensor + 8 * col) = rv[i];
+        }
+        v4f s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            s = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, rk[i]), __builtin_bit_cast(v8h, qb[i]), s, 0, 0, 0);
+        float p[4] = {s.x, s.y, s.z, s.w}, mu = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            p[r] = 4 * grp + r < n_tok ? scale * p[r] : -INFINITY;
+            mu = fmaxf(mu, p[r]);
+        }
+        const float mnew = fmaxf(m, max_over_rows(mu));
+        if (u != first_unit && __builtin_amdgcn_ballot_w64(mnew > m) != 0) {
+            const float alpha = __expf(m - mnew);
+            l *= alpha;
+            for_heads<G>([&](auto gc) {
+                constexpr int g = decltype(gc)::value;
+                const float ag = row_bcast<g>(alpha);
+#pragma unroll
+                for (int k = 0; k < 8; k++) av[g][k] *= ag;
+            });
+        }
+        m = mnew;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            p[r] = __expf(p[r] - m);
+            l += p[r];
+        }
+        row_operand(p[0], p[1], p[2], p[3]);
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint32_t w[4] = {rv[i].x, rv[i].y, rv[i].z, rv[i].w};
+            float x[8];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                x[2 * k] = h2f(w[k] & 0xffffu);
+                x[2 * k + 1] = h2f(w[k] >> 16);
             }
-            st.l[gg] = st.l[gg] * alpha + (sub == 0 ? psum : 0.f);  // each row counted once
-            st.bv[gg] *= alpha;
-            st.m[gg] = mnew;
-            float av[8];
+            for_heads<G>([&](auto gc) {
+                constexpr int g = decltype(gc)::value;
 #pragma unroll
-            for (int k = 0; k < 8; k++) av[k] = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const uint32_t w[4] = {rv[i].x, rv[i].y, rv[i].z, rv[i].w};
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    av[2 * k] = fmaf(sc[i], h2f(w[k] & 0xffffu), av[2 * k]);
-                    av[2 * k + 1] = fmaf(sc[i], h2f(w[k] >> 16), av[2 * k + 1]);
-                }
-            }
-            // fold the four row groups: groups 0,1 keep elements 0..3 and groups 2,3 elements 4..7, then each group r
-            // keeps elements 2r, 2r+1 -- the channels 8*sub + 2r, +1 summed over all 16 rows
-            float w4[4], w2[2];
-#pragma unroll
-            for (int k = 0; k < 4; k++) w4[k] = (hi2 ? av[4 + k] : av[k]) + __shfl_xor(hi2 ? av[k] : av[4 + k], 32);
-#pragma unroll
-            for (int k = 0; k < 2; k++) w2[k] = (hi1 ? w4[2 + k] : w4[k]) + __shfl_xor(hi1 ? w4[k] : w4[2 + k], 16);
-            st.acc[gg][0] = st.acc[gg][0] * alpha + __shfl(w2[0], owner);
-            st.acc[gg][1] = st.acc[gg][1] * alpha + __shfl(w2[1], owner);
+                for (int k = 0; k < 8; k++) av[g][k] = fma_row<g>(p[i], x[k], av[g][k]);
+            });
         }
     }
-    soft_to_area<G>(st, area, lane);
+    // merge with the parked state: head `col` in the lanes of its column
+    l = fold_halves(l, l);
+    l = fold_rows(l, l);
+    float fa = 1.f, fb = 0.f;
+    if (col < G) {
+        float *ml = area + G * kD + 3 * col;
+        const float ma = ml[0], mx = fmaxf(ma, m);
+        fa = __expf(ma - mx);  // 0 for a state that is still empty
+        fb = __expf(m - mx);
+        const float l1 = fmaf(ml[1], fa, l * fb), bv1 = ml[2] * fa;
+        wave_sync();
+        if (grp == 0) { ml[0] = mx; ml[1] = l1; ml[2] = bv1; }
+    }
+    // fold the four rows: lane (grp, col) ends up with channels 8 col + 2 grp, +1 of all tokens
+    for_heads<G>([&](auto gc) {
+        constexpr int g = decltype(gc)::value;
+        float w4[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) w4[k] = fold_halves(av[g][k], av[g][4 + k]);
+        const float o0 = fold_rows(w4[0], w4[2]), o1 = fold_rows(w4[1], w4[3]);
+        float2 *at = reinterpret_cast<float2 *>(area + g * kD + 8 * col + 2 * grp);
+        const float2 old = *at;
+        const float a = row_bcast<g>(fa), c = row_bcast<g>(fb);
+        *at = make_float2(fmaf(old.x, a, o0 * c), fmaf(old.y, a, o1 * c));
+    });
+    wave_sync();
 }
 
 // A record on its way from global memory to the wave's LDS staging area: the first 8 KiB travel through
@@ -1174,8 +1244,8 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         if (first * kUnitTokens < a.n_res) {
             if (!parked) soft_to_area<G>(st, area, lane);
             parked = true;
-            buffered_tokens<G>(g.res, g.res_tokens, g.B, g.H, b, h, a.res_head, a.n_res, first, n_waves * a.n_splits, qf,
-                               a.scale, lane, a.k_new, a.v_new, a.new_row, area);
+            buffered_tokens<G>(g.res, g.res_tokens, g.B, g.H, b, h, a.res_head, a.n_res, first, n_waves * a.n_splits,
+                               a.q + ((size_t)b * g.Hq + (size_t)h * G) * kD, a.scale, lane, a.k_new, a.v_new, a.new_row, area);
         }
     }
     if (parked) area_to_soft<G>(area, lane, st);

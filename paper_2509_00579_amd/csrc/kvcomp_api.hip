@@ -439,10 +439,11 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
         n_splits = std::min(by_chip, by_work);
     }
     n_splits = std::max(1, std::min({n_splits, (int)kMaxSplits, std::max(ctx->n_blocks, 1)}));
-    // waves of a workgroup: no more than its split has block pairs (a short sequence leaves wave slots empty rather
-    // than CUs), at least enough for the buffered tokens' units to spread
+    // waves of a workgroup: as many as its split has block pairs and units of buffered tokens (a short sequence leaves wave
+    // slots empty rather than CUs); the kernel gives the units to the waves without a block first
     const int bps = ctx->n_blocks > 0 ? (ctx->n_blocks + n_splits - 1) / n_splits : 0;
-    int n_waves = std::max(1, std::min(max_waves, std::max(bps, std::min(4, (ctx->n_res + 15) / 16))));
+    const int units = (ctx->n_res + 15) / 16, units_per_split = (units + n_splits - 1) / n_splits;
+    const int n_waves = std::max(1, std::min(max_waves, bps + units_per_split));
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (ctx->profiling) {
         if (ctx->events_used + 2 > ctx->events.size()) {

@@ -387,6 +387,28 @@ def test_append_fused_into_the_attention_launch(gpu, oracle, B, H, Hq, window, S
     gc.close()
 
 
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("n0", [1, 14, 30, 60])
+def test_buffered_tokens_at_unit_edges(gpu, oracle, G, n0):
+    """Nothing but buffered fp16 tokens, which are read in units of 16: counts around the edges of a unit, the newest token
+    (still in the caller's tensor) first and last of its unit.  fp16 inputs, exact products, fp32 sums of at most 128 and
+    63 terms: 2^-24 * (128 + 63) * the sum of magnitudes, below 3e-5 for these inputs."""
+    B, H = 2, 2
+    Kx, Vx, oc, gc = _both(gpu, oracle, B, H, H * G, 64, n0, 128, 1e-2, 1e-2, seed=41 + n0)
+    kn, vn = W.make_new_tokens(B, H, 3, 43)
+    q = W.make_queries(B, H * G, 3, 44)
+    for t in range(3):
+        oc.append_token(kn[t], vn[t])
+        out = gc.append_attn_decode(_dev(kn[t]), _dev(vn[t]), _dev(q[t]), SCALE).cpu().numpy()
+        ref = oc.attn_decode(q[t], SCALE)
+        assert np.abs(out - ref).max() <= 3e-5 * max(1.0, np.abs(ref).max()), (t, np.abs(out - ref).max())
+        again = gc.attn_decode(_dev(q[t]), SCALE).cpu().numpy()  # the token is in its slot now
+        assert np.array_equal(out, again)
+    held = np.concatenate([Vx[:, :n0], vn.transpose(1, 0, 2, 3)], axis=1)
+    assert np.array_equal(gc.residual(V)[0].view(np.uint16), held.view(np.uint16))
+    gc.close()
+
+
 def test_many_sequence_splits(gpu, oracle):
     """One long sequence with a single KV head: the library splits it 128 ways (its maximum) so that the chip is
     filled; every split count gives the oracle's result, also when the last split is short or the buffer holds
