@@ -4,23 +4,20 @@
 // of one token with a lookup table -- each slice from both ends, four independent decode chains of 32 symbols per
 // lane -- and accumulates q.k in registers; the wave then updates a running softmax and decodes the V record of the
 // same block, every lane owning two channels (two slices, again four chains) and accumulating p.v in registers.  No
-// decompressed value ever leaves the registers (Section 3.3.2): groups of 4 and 8 query heads keep the decoded
-// quantization codes packed four to a register and hand them to the matrix cores from there.
+// decompressed value ever leaves the registers (Section 3.3.2): the decoded quantization codes are packed four to a
+// register and handed to the matrix cores from there.
 //
 // What differs from the paper's kernel, and why (gfx950):
 //  * lookup-table decode instead of the bit-serial tree walk of Section 3.3.1: all 64 lanes of a wave advance in
 //    symbol lock-step (same trip count for every lane, no divergence), so the dequantization weight of the current
-//    symbol is the same for the whole wave.  For groups of 1 and 2 query heads it reaches the FMA through a DPP quad
-//    broadcast of values fetched from LDS once per four steps, which keeps it off the VALU and nearly off the LDS pipe
-//    that the table lookups load; for groups of 4 and 8 the wave packs the decoded bytes into registers and multiplies
-//    them with the weights of all heads on int8 MFMA (see "tile path" below).  The table is
-//    indexed by as many stream bits as the longest code word of the codebook, and one 32-bit window serves several
-//    symbols (floor(31 / table width)) with no refill test in between;
+//    symbol is the same for the whole wave and the products with it fit the matrix cores: int8 codes times the signed
+//    byte digits of integer weights, exact in int32 (groups of 1 and 2 query heads: "a dot product per lane"; groups of 4
+//    and 8: "tile path").  The table is indexed by as many stream bits as the longest code word of the codebook, and one
+//    32-bit window serves several symbols (floor(31 / table width)) with no refill test in between;
 //  * the dequantization is folded into the weights: q.k' = sum_c q_c min_c + sum_c (q_c step_c) code_tc, and
-//    p.v'  = sum_t p_t min_t + sum_t (p_t step_t) code_tc: one convert and one FMA per decoded symbol;
+//    p.v'  = sum_t p_t min_t + sum_t (p_t step_t) code_tc;
 //  * K and V of a block are handled by the same wave back to back with an online softmax, so scores never go to
-//    memory; while one record is decoded the next one is already on its way from HBM into registers (tile path:
-//    straight into LDS while the products of the previous record run);
+//    memory; the next record goes from HBM straight into LDS while the last products of the previous one run;
 //  * the sequence is split over workgroups; the workgroup that finishes last merges the splits (the "sum
 //    reduction" of Section 3.3.2) inside the same launch.
 #include <hip/hip_fp16.h>
@@ -40,11 +37,22 @@ struct FusedArgs {
     float scale;
     int n_blocks, res_head, n_res, blocks_per_split, n_splits, stage_bytes;
     uint32_t mask[2];   // table index mask of each tensor, already scaled to the byte offset of an entry
+    float bias[2];      // what the decode tables' symbols are short of: 128 with more than 128 levels, else 0
     // append fused into this launch: the newest buffered token (number new_row of the buffer, oldest = 0) is not in the
     // buffer yet but in k_new / v_new [B][H][128]; the wave that reads it also stores it there.  new_row < 0: none.
     const uint16_t *k_new, *v_new;
     int new_row;
 };
+
+// How far a score may exceed the softmax reference of groups of 1 and 2 heads before the state is rescaled.  A block's
+// integer weights are scaled by that block's largest numerator, so nothing is lost below e^8 = 2981.
+constexpr float kLazyMaxDot = 8.f;
+
+constexpr int kTileMinG = 4;  // smallest query-head group on the tile path
+
+// Symbols reach the matrix cores as int8: as they are with up to 128 levels, minus 128 (FusedArgs::bias) beyond.  Code
+// words of up to 7 bits leave at most 128 levels.
+template <int LB> constexpr bool kBiased = LB > 7;
 
 // softmax state of one wave for G query heads
 template <int G>
@@ -54,282 +62,26 @@ struct Soft {
 #pragma unroll
         for (int g = 0; g < G; g++) { m[g] = -INFINITY; l[g] = 0.f; bv[g] = 0.f; acc[g][0] = 0.f; acc[g][1] = 0.f; }
     }
-    // s: this lane's score (-inf for an invalid lane).  Returns p and rescales the running sums.
+    // s: this lane's score.  Returns its softmax numerator.  The reference m is the same in all lanes and moves only when
+    // a score exceeds it by more than kLazyMaxDot (m = -inf before the first block): most blocks then need no maximum
+    // over the wave and no rescaling of the sums.
     __device__ __forceinline__ float update(int g, float s) {
-        const float mloc = wave_max(s);
-        const float mnew = fmaxf(m[g], mloc);
-        const float alpha = __expf(m[g] - mnew);
-        const float p = __expf(s - mnew);
-        l[g] = l[g] * alpha + p;
-        bv[g] *= alpha;
-        acc[g][0] *= alpha;
-        acc[g][1] *= alpha;
-        m[g] = mnew;
+        if (__builtin_amdgcn_ballot_w64(s - m[g] > kLazyMaxDot) != 0) {
+            const float mnew = fmaxf(m[g], wave_max(s));
+            const float alpha = __expf(m[g] - mnew);
+            l[g] *= alpha;
+            bv[g] *= alpha;
+            acc[g][0] *= alpha;
+            acc[g][1] *= alpha;
+            m[g] = mnew;
+        }
+        const float p = __expf(s - m[g]);
+        l[g] += p;
         return p;
     }
 };
 
-// ---- accumulation of one round of decoded symbols -----------------------------------------------------------------
-// The folded weight of the current symbol is wave-uniform.
-//
-// Query-head groups of 1 and 2: every fourth step, lane i of each quad of lanes fetches the weight of step s + i from
-// LDS (four addresses, no bank conflict); the FMA of step s + i then takes it through a quad broadcast.  No
-// instruction is spent on the broadcast itself.  (Groups of 4 and 8: the tile path further down.)
-constexpr int kTileMinG = 4;  // smallest query-head group on the tile path
-
-// acc + (w of lane Q of this lane's quad) * symbol: the quad broadcast is a DPP modifier of the FMA's first operand,
-// no instruction of its own.  w must not have been written by a VALU instruction in the two instructions before
-// (it comes from an LDS read).
-template <int Q>
-__device__ __forceinline__ float fma_quad_c(float w, float sym, float acc) {
-    static_assert(Q >= 0 && Q < 4, "quad lane");
-    if constexpr (Q == 0) asm("v_fmac_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(w), "v"(sym));
-    if constexpr (Q == 1) asm("v_fmac_f32_dpp %0, %1, %2 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(w), "v"(sym));
-    if constexpr (Q == 2) asm("v_fmac_f32_dpp %0, %1, %2 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(w), "v"(sym));
-    if constexpr (Q == 3) asm("v_fmac_f32_dpp %0, %1, %2 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(w), "v"(sym));
-    return acc;
-}
-__device__ __forceinline__ float fma_quad(float w, int q, float sym, float acc) {
-    switch (q & 3) {
-        case 0: return fma_quad_c<0>(w, sym, acc);
-        case 1: return fma_quad_c<1>(w, sym, acc);
-        case 2: return fma_quad_c<2>(w, sym, acc);
-        default: return fma_quad_c<3>(w, sym, acc);
-    }
-}
-
-// K, groups of 1 and 2: symbol index `up` of chain au/bu is channel up / 64+up, index `dn` of chain ad/bd is channel
-// dn / 64+dn.  wl = weights + (lane & 3) * G, wdn = weights - (lane & 3) * G, weights laid out [channel][head].
-// CNT table entries of SP symbols each, the first of them symbol `first` of its chain.
-template <int G, int CNT, int SP>
-__device__ __forceinline__ void k_accum(const float *wl, const float *wdn, float (&wq)[4][G], int first,
-                                        const uint32_t (&fau)[CNT], const uint32_t (&fad)[CNT],
-                                        const uint32_t (&fbu)[CNT], const uint32_t (&fbd)[CNT], float (&acc)[G]) {
-#pragma unroll
-    for (int k = 0; k < CNT * SP; k++) {
-        const int up = first + k, dn = kSliceLen - 1 - up;  // symbol index inside the slice
-        const int q = up & 3;
-        if (q == 0) {
-#pragma unroll
-            for (int g = 0; g < G; g++) {
-                wq[0][g] = wl[up * G + g];
-                wq[1][g] = wdn[dn * G + g];
-                wq[2][g] = wl[(kSliceLen + up) * G + g];
-                wq[3][g] = wdn[(kSliceLen + dn) * G + g];
-            }
-        }
-        const bool second = SP == 2 && (k & 1);
-        const float s0 = second ? sym2_f32(fau[k / SP]) : sym_f32(fau[k / SP]);
-        const float s1 = second ? sym2_f32(fad[k / SP]) : sym_f32(fad[k / SP]);
-        const float s2 = second ? sym2_f32(fbu[k / SP]) : sym_f32(fbu[k / SP]);
-        const float s3 = second ? sym2_f32(fbd[k / SP]) : sym_f32(fbd[k / SP]);
-#pragma unroll
-        for (int g = 0; g < G; g++) {
-            acc[g] = fma_quad(wq[0][g], q, s0, acc[g]);
-            acc[g] = fma_quad(wq[1][g], q, s1, acc[g]);
-            acc[g] = fma_quad(wq[2][g], q, s2, acc[g]);
-            acc[g] = fma_quad(wq[3][g], q, s3, acc[g]);
-        }
-    }
-}
-
-// V, groups of 1 and 2: symbol index = token; chains au/ad belong to channel 2*lane, bu/bd to channel 2*lane+1.
-template <int G, int CNT, int SP>
-__device__ __forceinline__ void v_accum(const float *wl, const float *wdn, float (&wq)[2][G], int first,
-                                        const uint32_t (&fau)[CNT], const uint32_t (&fad)[CNT],
-                                        const uint32_t (&fbu)[CNT], const uint32_t (&fbd)[CNT], float (&acc)[G][2]) {
-#pragma unroll
-    for (int k = 0; k < CNT * SP; k++) {
-        const int up = first + k, dn = kSliceLen - 1 - up;  // token index inside the block
-        const int q = up & 3;
-        if (q == 0) {
-#pragma unroll
-            for (int g = 0; g < G; g++) {
-                wq[0][g] = wl[up * G + g];
-                wq[1][g] = wdn[dn * G + g];
-            }
-        }
-        const bool second = SP == 2 && (k & 1);
-        const float s0 = second ? sym2_f32(fau[k / SP]) : sym_f32(fau[k / SP]);
-        const float s1 = second ? sym2_f32(fad[k / SP]) : sym_f32(fad[k / SP]);
-        const float s2 = second ? sym2_f32(fbu[k / SP]) : sym_f32(fbu[k / SP]);
-        const float s3 = second ? sym2_f32(fbd[k / SP]) : sym_f32(fbd[k / SP]);
-#pragma unroll
-        for (int g = 0; g < G; g++) {
-            acc[g][0] = fma_quad(wq[0][g], q, s0, acc[g][0]);
-            acc[g][0] = fma_quad(wq[1][g], q, s1, acc[g][0]);
-            acc[g][1] = fma_quad(wq[0][g], q, s2, acc[g][1]);
-            acc[g][1] = fma_quad(wq[1][g], q, s3, acc[g][1]);
-        }
-    }
-}
-
-// ---- K block: lane = token; its two slices are channels 0..63 and 64..127 ------------------------------------------
-// hdr32: the record (LDS or global); wts: this wave's LDS weight area.  Leaves scale * q.k' of this lane's token in
-// score[].  LB: the table width the kernel is compiled for (see DecodeMode).
-template <int G, int LB>
-__device__ __forceinline__ void k_block(const uint32_t *hdr32, const char *lut, uint32_t mask, float *wts,
-                                        const float (&qreg)[G][2], float two_eb, float scale, int lane, int kmm,
-                                        float (&score)[G]) {
-    using M = DecodeMode<LB>;
-    constexpr int SP = M::kSymsPerLookup, NL = M::kLookupsPerWindow;
-    // lane c holds the folded weights q_c * step_c of channels c and c + 64.  kmm = bytes of the {min,max} pairs in
-    // the header: 512 (one pair per channel) or 16 (BlockQuant: one pair for the whole block)
-    const bool per_channel = kmm == kMinMaxBytesK;
-    const uint32_t mm0 = hdr32[per_channel ? lane : 0], mm1 = hdr32[per_channel ? lane + 64 : 0];
-    const float mn0 = h2f(mm0 & 0xffffu), mn1 = h2f(mm1 & 0xffffu);
-    const float st0 = two_eb * (h2f(mm0 >> 16) - mn0), st1 = two_eb * (h2f(mm1 >> 16) - mn1);
-    float w0[G], w1[G], acc[G];
-#pragma unroll
-    for (int g = 0; g < G; g++) {
-        w0[g] = qreg[g][0] * st0;
-        w1[g] = qreg[g][1] * st1;
-        acc[g] = 0.f;
-    }
-    const uint32_t sb = hdr32[kmm / 4 + lane];  // bit counts of slices 2*lane and 2*lane+1
-    const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
-    const uint32_t *wm1 = hdr32 + (kmm + 2 * kSlices) / 4 - 1;
-    constexpr int kRounds = M::kLookupsPerChain / NL, kTail = M::kLookupsPerChain - kRounds * NL;
-    static_assert(G < kTileMinG, "groups of 4 and 8 take the tile path");
-    Quad<M::J> qd;
-    {
-#pragma unroll
-        for (int g = 0; g < G; g++) {  // LDS layout [channel][head]
-            wts[lane * G + g] = w0[g];
-            wts[(kSliceLen + lane) * G + g] = w1[g];
-        }
-        const float *wl = wts + (lane & 3) * G, *wdn = wts - (lane & 3) * G;
-        float wq[4][G];
-        wave_sync();
-        qd.open(wm1, start, sb & 0xffffu, sb >> 16);
-        // fully unrolled: the step number decides at compile time which quad lane holds the weight, and the
-        // scheduler may overlap the table lookups of one round with the accumulation of the previous one
-#pragma unroll
-        for (int r = 0; r < kRounds; r++) {
-            uint32_t fau[NL], fad[NL], fbu[NL], fbd[NL];
-            qd.template step<NL>(wm1, lut, mask, fau, fad, fbu, fbd);
-            k_accum<G, NL, SP>(wl, wdn, wq, r * NL * SP, fau, fad, fbu, fbd, acc);
-        }
-        if constexpr (kTail > 0) {
-            uint32_t fau[kTail ? kTail : 1], fad[kTail ? kTail : 1], fbu[kTail ? kTail : 1], fbd[kTail ? kTail : 1];
-            qd.template step<(kTail ? kTail : 1)>(wm1, lut, mask, fau, fad, fbu, fbd);
-            k_accum<G, (kTail ? kTail : 1), SP>(wl, wdn, wq, kRounds * NL * SP, fau, fad, fbu, fbd, acc);
-        }
-    }
-    // the constant part of the dot product, sum_c q_c min_c, is shared by all tokens of the block
-#pragma unroll
-    for (int g = 0; g < G; g++) score[g] = scale * (acc[g] + wave_sum(qreg[g][0] * mn0 + qreg[g][1] * mn1));
-}
-
-// ---- V block: lane = channels 2*lane and 2*lane+1 (its two slices) -------------------------------------------------
-// p[g] = softmax numerator of token `lane`.
-template <int G, int LB>
-__device__ __forceinline__ void v_block(const uint32_t *hdr32, const char *lut, uint32_t mask, float *wts,
-                                        const float (&p)[G], float two_eb, int lane, Soft<G> &st) {
-    using M = DecodeMode<LB>;
-    constexpr int SP = M::kSymsPerLookup, NL = M::kLookupsPerWindow;
-    // lane t holds the folded weight p_t * step_t of token t
-    const uint32_t mm = hdr32[lane];
-    const float mn = h2f(mm & 0xffffu);
-    const float step = two_eb * (h2f(mm >> 16) - mn);
-    float w[G];
-#pragma unroll
-    for (int g = 0; g < G; g++) {
-        w[g] = p[g] * step;
-        st.bv[g] += p[g] * mn;
-    }
-    const uint32_t sb = hdr32[kMinMaxBytesV / 4 + lane];
-    const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
-    const uint32_t *wm1 = hdr32 + kHdrBytesV / 4 - 1;
-    constexpr int kRounds = M::kLookupsPerChain / NL, kTail = M::kLookupsPerChain - kRounds * NL;
-    static_assert(G < kTileMinG, "groups of 4 and 8 take the tile path");
-    Quad<M::J> qd;
-    {
-#pragma unroll
-        for (int g = 0; g < G; g++) wts[lane * G + g] = w[g];  // LDS layout [token][head]
-        const float *wl = wts + (lane & 3) * G, *wdn = wts - (lane & 3) * G;
-        float wq[2][G];
-        wave_sync();
-        qd.open(wm1, start, sb & 0xffffu, sb >> 16);
-#pragma unroll
-        for (int r = 0; r < kRounds; r++) {
-            uint32_t fau[NL], fad[NL], fbu[NL], fbd[NL];
-            qd.template step<NL>(wm1, lut, mask, fau, fad, fbu, fbd);
-            v_accum<G, NL, SP>(wl, wdn, wq, r * NL * SP, fau, fad, fbu, fbd, st.acc);
-        }
-        if constexpr (kTail > 0) {
-            uint32_t fau[kTail ? kTail : 1], fad[kTail ? kTail : 1], fbu[kTail ? kTail : 1], fbd[kTail ? kTail : 1];
-            qd.template step<(kTail ? kTail : 1)>(wm1, lut, mask, fau, fad, fbu, fbd);
-            v_accum<G, (kTail ? kTail : 1), SP>(wl, wdn, wq, kRounds * NL * SP, fau, fad, fbu, fbd, st.acc);
-        }
-    }
-}
-
-// Rare path: a record larger than the LDS staging area is decoded straight from global memory.  Kept out of line so
-// that it costs the common path no registers.
-template <int G, int LB>
-__device__ __noinline__ void k_block_global(const uint32_t *rec, const char *lut, uint32_t mask, float *wts,
-                                            const float (&qreg)[G][2], float two_eb, float scale, int lane, int kmm,
-                                            float (&score)[G]) {
-    k_block<G, LB>(rec, lut, mask, wts, qreg, two_eb, scale, lane, kmm, score);
-}
-template <int G, int LB>
-__device__ __noinline__ void v_block_global(const uint32_t *rec, const char *lut, uint32_t mask, float *wts,
-                                            const float (&p)[G], float two_eb, int lane, Soft<G> &st) {
-    v_block<G, LB>(rec, lut, mask, wts, p, two_eb, lane, st);
-}
-
-// ---- groups of 4 and 8 query heads, tile path ---------------------------------------------------------------------
-// With several query heads per KV head the update of the accumulators is a matrix product, (heads x symbols) weights
-// times the decoded block, and the decode itself is the same for all heads.  The wave therefore only packs the
-// decoded symbols, four table entries to a register -- less work than one conversion and one FMA per symbol and
-// head -- and multiplies them with the folded weights on v_mfma_i32_32x32x16_i8, whose result tiles (32 rows of
-// weights x 32 columns) give the path its name:
-//   * the table holds the symbols biased by -128 (symbol ^ 0x80 read as int8), so a register of packed symbols is an
-//     MFMA operand as it is, with no conversion; the operand wants 32 columns x 16 positions from 64 lanes that hold
-//     one slice each, which one v_permlane32_swap_b32 per register arranges (step_operands);
-//   * a weight w is scaled by a per-block power of two to an integer W below 2^22 and split into three signed bytes,
-//     W = sum_j d_j 256^j; row 4 * head + j of the A operand holds digit j, the products are exact in int32, and the
-//     digit rows of a head land in the same lane of the result, where they are recombined in fp32;
-//   * sum_c W_c (s_c - 128) misses 128 * sum_c W_c, which joins the constant term of the block.
-// Lane l of the result tiles holds column l % 32 (token of a K block, channel of a V block) for the heads
-// l / 32 + 2 i: the running softmax state lives in that layout and is converted to the per-channel layout of the
-// other paths once, after the last block.
-typedef int v16i __attribute__((ext_vector_type(16)));
-
-template <int G>
-struct TileSoft {
-    static constexpr int HL = G / 2;  // heads per lane: l / 32 + 2 i
-    float m[HL], l[HL], bv[HL], acc[HL][4];  // l, bv: this lane's share; acc[i][ct]: channel 32 ct + l % 32
-    __device__ __forceinline__ void init() {
-#pragma unroll
-        for (int i = 0; i < HL; i++) {
-            m[i] = -INFINITY; l[i] = 0.f; bv[i] = 0.f;
-#pragma unroll
-            for (int c = 0; c < 4; c++) acc[i][c] = 0.f;
-        }
-    }
-};
-
-// maximum / sum over the 32 lanes of this lane's half of the wave
-__device__ __forceinline__ float half_max(float v, bool upper) {
-    v = fmaxf(v, dpp_f<kDppXor1>(v));
-    v = fmaxf(v, dpp_f<kDppXor2>(v));
-    v = fmaxf(v, dpp_f<kDppHalfMirror>(v));
-    v = fmaxf(v, dpp_f<kDppMirror>(v));
-    const float lo = fmaxf(bcast(v, 0), bcast(v, 16)), hi = fmaxf(bcast(v, 32), bcast(v, 48));
-    return upper ? hi : lo;
-}
-__device__ __forceinline__ float half_sum(float v, bool upper) {
-    v += dpp_f<kDppXor1>(v);
-    v += dpp_f<kDppXor2>(v);
-    v += dpp_f<kDppHalfMirror>(v);
-    v += dpp_f<kDppMirror>(v);
-    const float lo = bcast(v, 0) + bcast(v, 16), hi = bcast(v, 32) + bcast(v, 48);
-    return upper ? hi : lo;
-}
-
-// bytes 1 of four table entries (the biased symbols) as one word, first entry in the lowest byte
+// bytes 1 of four table entries (the symbols) as one word, first entry in the lowest byte
 __device__ __forceinline__ uint32_t pack_syms(uint32_t e0, uint32_t e1, uint32_t e2, uint32_t e3) {
     const uint32_t lo = __builtin_amdgcn_perm(e1, e0, 0x0c0c0501u), hi = __builtin_amdgcn_perm(e3, e2, 0x0c0c0501u);
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
@@ -345,7 +97,7 @@ template <int NE>
 struct ChainSyms {
     uint32_t au[NE], ad[NE], bu[NE], bd[NE];
 };
-// The decoded symbols (biased bytes) of the lane's two slices, four per word, in ascending position inside the slice:
+// The decoded symbols of the lane's two slices, four per word, in ascending position inside the slice:
 // word j of a slice holds positions 4j .. 4j+3.  The up chain delivers words 0, 1, .. and the down chain 15, 14, ..
 struct SliceWords {
     uint32_t a[16], b[16];
@@ -401,6 +153,259 @@ __device__ __forceinline__ void decode_span(Quad<DecodeMode<LB>::J> &qd, const u
 // first symbol that the second span of a block decodes when the products run after each half: the first half's
 // windows are whole, so they may reach into the second half
 constexpr int tile_first_span(int NS) { return (16 + NS - 1) / NS * NS; }
+
+// ---- groups of 1 and 2 query heads: a dot product per lane on the matrix cores ------------------------------------
+// Every lane needs the products of ITS OWN decoded symbols with wave-uniform weights (K: token x channels, V: channel x
+// tokens).  v_mfma_i32_16x16x64_i8 computes D[row][col] = sum over the lane groups g = 0..3 of A[lane (g,row)] .
+// B[lane (g,col)], 16 bytes a lane, and lane (g,col) receives rows 4g .. 4g+3 of column col.  With A non-zero only in
+// the lanes (g,row) with row / 4 == g the groups do not mix: register j of lane l is the dot product of digit row j of the
+// weights with lane l's own 16 symbols.  No lane exchange, no conversion and no FMA per symbol: the wave packs the decoded
+// symbols four to a register and issues one matrix instruction per 16 of them.
+//   * A weight w is scaled by a power of two (per block and head) to an integer |W| <= 2^30 and split into four signed
+//     bytes, W = sum_j d_j 256^j, the four rows that a lane group owns; the products are exact in int32 and the four sums
+//     are joined in fp32.  30 bits hold every fp32 weight down to 2^-6 of the block's largest exactly.
+//   * the table holds the symbols as int8, from 128 levels on minus `bias` = 128; x' = min + step * code =
+//     (min + bias * step) + step * (code - bias), so the bias only enters the constant term.
+// 32 heads x 32768 tokens: 1098 instead of 1454 vector instructions per block pair, 58.6 -> 53.5 us a step together with
+// the shorter prologue (the LDS pipe is the busier unit: 82 % of the busy cycles, its table lookups conflict); groups of 2,
+// 3 x 8 heads x 12345 tokens, code words of up to 12 bits: 40.7 -> 32.0 us.  A conversion and an FMA per symbol and head,
+// as before, spent half of the loop's vector instructions on them.
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// the 4 x 4 bytes of a quad of lanes transposed: lane q of the result holds byte q of the four lanes' words, lane 0's in
+// the lowest byte
+struct QuadTranspose {
+    uint32_t sel1, sel2;
+    __device__ __forceinline__ explicit QuadTranspose(int lane)
+        : sel1((lane & 1) ? 0x03070105u : 0x06020400u), sel2((lane & 2) ? 0x03020706u : 0x05040100u) {}
+    __device__ __forceinline__ uint32_t operator()(uint32_t u) const {
+        const uint32_t v = __builtin_amdgcn_perm(dpp_u<kDppXor1>(u), u, sel1);
+        return __builtin_amdgcn_perm(dpp_u<kDppXor2>(v), v, sel2);
+    }
+};
+// power of two f = 2^up that brings the largest |weight| of the wave into [2^29, 2^30); *inv = 1 / f.  All in scalar
+// registers: the bit patterns of non-negative floats are ordered like the floats.
+__device__ __forceinline__ uint32_t wave_max_bits(float v) {
+    v = fmaxf(v, dpp_f<kDppXor1>(v));
+    v = fmaxf(v, dpp_f<kDppXor2>(v));
+    v = fmaxf(v, dpp_f<kDppHalfMirror>(v));
+    v = fmaxf(v, dpp_f<kDppMirror>(v));
+    const uint32_t u = __float_as_uint(v);
+    const uint32_t a = __builtin_amdgcn_readlane(u, 0), b = __builtin_amdgcn_readlane(u, 16),
+                   c = __builtin_amdgcn_readlane(u, 32), d = __builtin_amdgcn_readlane(u, 48);
+    return max(max(a, b), max(c, d));
+}
+__device__ __forceinline__ float dot_scale(float amax, float *inv) {
+    const int e = (int)(wave_max_bits(amax) >> 23) - 126;  // amax = m * 2^e, m in [0.5, 1)
+    const int up = min(30 - e, 120);
+    *inv = __uint_as_float((uint32_t)(127 - up) << 23);
+    return __uint_as_float((uint32_t)(127 + up) << 23);
+}
+// bytes 0..3: the signed digits of W
+__device__ __forceinline__ uint32_t four_digits(float w) { return ((uint32_t)(int)w + 0x00808080u) ^ 0x00808080u; }
+__device__ __forceinline__ float join_four(const v4i &d) {
+    return fmaf(fmaf(fmaf((float)d.w, 256.f, (float)d.z), 256.f, (float)d.y), 256.f, (float)d.x);
+}
+// Where a lane reads its piece of the A operand: digit row lane % 4 if its matrix row belongs to its lane group, else
+// zeros.  digits: this head's four rows in the wave's LDS area; zeros: kDigitRow zero bytes.
+__device__ __forceinline__ const uint8_t *a_piece(const uint8_t *digits, const uint8_t *zeros, int lane) {
+    const int row = lane & 15;
+    return (row >> 2) == (lane >> 4) ? digits + (row & 3) * kDigitRow : zeros;
+}
+__device__ __forceinline__ v4i a_step(const uint8_t *piece, int pos) { return *reinterpret_cast<const v4i *>(piece + pos); }
+__device__ __forceinline__ v4i b_step(const uint32_t (&w)[16], int step) {
+    const v4i r = {(int)w[4 * step], (int)w[4 * step + 1], (int)w[4 * step + 2], (int)w[4 * step + 3]};
+    return r;
+}
+// where this lane's word of digits goes after the transposition: row lane % 4, columns 4 (lane / 4) .. + 3
+__device__ __forceinline__ uint32_t *digit_slot(uint8_t *digits, int lane) {
+    return reinterpret_cast<uint32_t *>(digits + (lane & 3) * kDigitRow + (lane & ~3));
+}
+
+// ---- K block: lane = token; its two slices are channels 0..63 and 64..127 ------------------------------------------
+// hdr32: the record (LDS or global); digits: this wave's LDS weight area.  Leaves scale * q.k' of this lane's token in
+// score[].  LB: the table width the kernel is compiled for (see DecodeMode).
+template <int G, int LB, class F>
+__device__ __forceinline__ void k_block(const uint32_t *hdr32, const char *lut, uint32_t mask, uint8_t *digits,
+                                        const uint8_t *zeros, const float (&qreg)[G][2], float two_eb, float bias,
+                                        float scale, int lane, int kmm, float (&score)[G], F &&record_done) {
+    static_assert(G < kTileMinG, "groups of 4 and 8 take the tile path");
+    // lane c holds the weights of channels c and c + 64.  kmm = bytes of the {min,max} pairs in the header: 512 (one pair
+    // per channel) or 16 (BlockQuant: one pair for the whole block)
+    const bool per_channel = kmm == kMinMaxBytesK;
+    const uint32_t mm0 = hdr32[per_channel ? lane : 0], mm1 = hdr32[per_channel ? lane + 64 : 0];
+    const float mn0 = h2f(mm0 & 0xffffu), mn1 = h2f(mm1 & 0xffffu);
+    const float st0 = two_eb * (h2f(mm0 >> 16) - mn0), st1 = two_eb * (h2f(mm1 >> 16) - mn1);
+    const QuadTranspose transpose(lane);
+    float cst[G], inv[G];
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+        const float w0 = qreg[g][0] * st0, w1 = qreg[g][1] * st1;
+        const float f = dot_scale(fmaxf(fabsf(w0), fabsf(w1)), &inv[g]);
+        uint32_t *slot = digit_slot(digits + g * 4 * kDigitRow, lane);
+        slot[0] = transpose(four_digits(w0 * f));
+        slot[kSliceLen / 4] = transpose(four_digits(w1 * f));
+        // the constant part of the dot product is shared by all tokens of the block
+        cst[g] = qreg[g][0] * fmaf(bias, st0, mn0) + qreg[g][1] * fmaf(bias, st1, mn1);
+    }
+    const uint32_t sb = hdr32[kmm / 4 + lane];  // bit counts of slices 2*lane and 2*lane+1
+    const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
+    const uint32_t *wm1 = hdr32 + (kmm + 2 * kSlices) / 4 - 1;
+    Quad<DecodeMode<LB>::J> qd;
+    wave_sync();
+    qd.open(wm1, start, sb & 0xffffu, sb >> 16);
+    ChainSyms<DecodeMode<LB>::kLookupsPerChain> syms;
+    SliceWords pw;
+    const uint8_t *piece[G];
+    v4i d[G];
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+        piece[g] = a_piece(digits + g * 4 * kDigitRow, zeros, lane);
+        d[g] = v4i{0, 0, 0, 0};
+    }
+    auto products = [&](int ks) {
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            d[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_step(piece[g], 16 * ks), b_step(pw.a, ks), d[g], 0, 0, 0);
+            d[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_step(piece[g], kSliceLen + 16 * ks), b_step(pw.b, ks), d[g], 0, 0, 0);
+        }
+    };
+    constexpr int kP = tile_first_span(DecodeMode<LB>::kSymsPerWindow);
+    decode_span<LB, 0, kP>(qd, wm1, lut, mask, syms, pw);
+    products(0);
+    products(3);
+    decode_span<LB, kP, kHalf>(qd, wm1, lut, mask, syms, pw);
+    wave_sync();
+    record_done();
+    products(1);
+    products(2);
+#pragma unroll
+    for (int g = 0; g < G; g++) score[g] = scale * fmaf(inv[g], join_four(d[g]), wave_sum(cst[g]));
+}
+
+// ---- V block: lane = channels 2*lane and 2*lane+1 (its two slices) -------------------------------------------------
+// p[g] = softmax numerator of token `lane`.
+template <int G, int LB, class F>
+__device__ __forceinline__ void v_block(const uint32_t *hdr32, const char *lut, uint32_t mask, uint8_t *digits,
+                                        const uint8_t *zeros, const float (&p)[G], float two_eb, float bias, int lane,
+                                        Soft<G> &st, F &&record_done) {
+    static_assert(G < kTileMinG, "groups of 4 and 8 take the tile path");
+    // lane t holds the folded weight p_t * step_t of token t
+    const uint32_t mm = hdr32[lane];
+    const float mn = h2f(mm & 0xffffu);
+    const float step = two_eb * (h2f(mm >> 16) - mn);
+    const QuadTranspose transpose(lane);
+    float inv[G];
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+        const float w = p[g] * step;
+        const float f = dot_scale(w, &inv[g]);
+        *digit_slot(digits + g * 4 * kDigitRow, lane) = transpose(four_digits(w * f));
+        st.bv[g] = fmaf(p[g], fmaf(bias, step, mn), st.bv[g]);
+    }
+    const uint32_t sb = hdr32[kMinMaxBytesV / 4 + lane];
+    const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
+    const uint32_t *wm1 = hdr32 + kHdrBytesV / 4 - 1;
+    Quad<DecodeMode<LB>::J> qd;
+    wave_sync();
+    qd.open(wm1, start, sb & 0xffffu, sb >> 16);
+    ChainSyms<DecodeMode<LB>::kLookupsPerChain> syms;
+    SliceWords pw;
+    const uint8_t *piece[G];
+    v4i d[G][2];
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+        piece[g] = a_piece(digits + g * 4 * kDigitRow, zeros, lane);
+        d[g][0] = d[g][1] = v4i{0, 0, 0, 0};
+    }
+    auto products = [&](int ks) {
+#pragma unroll
+        for (int g = 0; g < G; g++) {
+            const v4i a = a_step(piece[g], 16 * ks);
+            d[g][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b_step(pw.a, ks), d[g][0], 0, 0, 0);
+            d[g][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b_step(pw.b, ks), d[g][1], 0, 0, 0);
+        }
+    };
+    constexpr int kP = tile_first_span(DecodeMode<LB>::kSymsPerWindow);
+    decode_span<LB, 0, kP>(qd, wm1, lut, mask, syms, pw);
+    products(0);
+    products(3);
+    decode_span<LB, kP, kHalf>(qd, wm1, lut, mask, syms, pw);
+    wave_sync();
+    record_done();
+    products(1);
+    products(2);
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+        st.acc[g][0] = fmaf(inv[g], join_four(d[g][0]), st.acc[g][0]);
+        st.acc[g][1] = fmaf(inv[g], join_four(d[g][1]), st.acc[g][1]);
+    }
+}
+
+// Rare path: a record larger than the LDS staging area is decoded straight from global memory.  Kept out of line so
+// that it costs the common path no registers.
+template <int G, int LB>
+__device__ __noinline__ void k_block_global(const uint32_t *rec, const char *lut, uint32_t mask, uint8_t *digits,
+                                            const uint8_t *zeros, const float (&qreg)[G][2], float two_eb, float bias,
+                                            float scale, int lane, int kmm, float (&score)[G]) {
+    k_block<G, LB>(rec, lut, mask, digits, zeros, qreg, two_eb, bias, scale, lane, kmm, score, [] {});
+}
+template <int G, int LB>
+__device__ __noinline__ void v_block_global(const uint32_t *rec, const char *lut, uint32_t mask, uint8_t *digits,
+                                            const uint8_t *zeros, const float (&p)[G], float two_eb, float bias, int lane,
+                                            Soft<G> &st) {
+    v_block<G, LB>(rec, lut, mask, digits, zeros, p, two_eb, bias, lane, st, [] {});
+}
+
+// ---- groups of 4 and 8 query heads, tile path ---------------------------------------------------------------------
+// With several query heads per KV head the update of the accumulators is a matrix product, (heads x symbols) weights
+// times the decoded block, and the decode itself is the same for all heads.  The wave therefore only packs the
+// decoded symbols, four table entries to a register -- less work than one conversion and one FMA per symbol and
+// head -- and multiplies them with the folded weights on v_mfma_i32_32x32x16_i8, whose result tiles (32 rows of
+// weights x 32 columns) give the path its name:
+//   * a register of packed symbols is an MFMA operand as it is, with no conversion; the operand wants 32 columns x 16 positions from 64 lanes that hold
+//     one slice each, which one v_permlane32_swap_b32 per register arranges (step_operands);
+//   * a weight w is scaled by a per-block power of two to an integer W below 2^22 and split into three signed bytes,
+//     W = sum_j d_j 256^j; row 4 * head + j of the A operand holds digit j, the products are exact in int32, and the
+//     digit rows of a head land in the same lane of the result, where they are recombined in fp32;
+//   * with more than 128 levels the table holds symbol - 128: sum_c W_c (s_c - 128) misses 128 * sum_c W_c, which joins
+//     the constant term of the block.
+// Lane l of the result tiles holds column l % 32 (token of a K block, channel of a V block) for the heads
+// l / 32 + 2 i: the running softmax state lives in that layout and is converted to the per-channel layout of the
+// other paths once, after the last block.
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+template <int G>
+struct TileSoft {
+    static constexpr int HL = G / 2;  // heads per lane: l / 32 + 2 i
+    float m[HL], l[HL], bv[HL], acc[HL][4];  // l, bv: this lane's share; acc[i][ct]: channel 32 ct + l % 32
+    __device__ __forceinline__ void init() {
+#pragma unroll
+        for (int i = 0; i < HL; i++) {
+            m[i] = -INFINITY; l[i] = 0.f; bv[i] = 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; c++) acc[i][c] = 0.f;
+        }
+    }
+};
+
+// maximum / sum over the 32 lanes of this lane's half of the wave
+__device__ __forceinline__ float half_max(float v, bool upper) {
+    v = fmaxf(v, dpp_f<kDppXor1>(v));
+    v = fmaxf(v, dpp_f<kDppXor2>(v));
+    v = fmaxf(v, dpp_f<kDppHalfMirror>(v));
+    v = fmaxf(v, dpp_f<kDppMirror>(v));
+    const float lo = fmaxf(bcast(v, 0), bcast(v, 16)), hi = fmaxf(bcast(v, 32), bcast(v, 48));
+    return upper ? hi : lo;
+}
+__device__ __forceinline__ float half_sum(float v, bool upper) {
+    v += dpp_f<kDppXor1>(v);
+    v += dpp_f<kDppXor2>(v);
+    v += dpp_f<kDppHalfMirror>(v);
+    v += dpp_f<kDppMirror>(v);
+    const float lo = bcast(v, 0) + bcast(v, 16), hi = bcast(v, 32) + bcast(v, 48);
+    return upper ? hi : lo;
+}
 
 // The B operands of v_mfma_i32_32x32x16_i8 for one step of 16 positions (words w[0..3] of a slice) straight from
 // registers.  Lane l of the operand supplies column l % 32 and positions 8 (l / 32) .. +7.  With one slice per lane and
@@ -484,7 +489,7 @@ constexpr float kLazyMax = 2.f;
 // request the next record, whose loads then travel while few registers are live.
 template <int G, int LB, class F>
 __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *lut, uint32_t mask2, uint8_t *tile,
-                                             const float *qf, float two_eb, float scale, int lane, int kmm,
+                                             const float *qf, float two_eb, float bias, float scale, int lane, int kmm,
                                              TileSoft<G> &ts, float (&p)[G / 2][2], F &&record_done) {
     constexpr int HL = G / 2;
     // everything derived from the lane number is recomputed per block (a few instructions) instead of being kept in
@@ -529,13 +534,13 @@ __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *
                 qm = fmaf(qa[i][c], mn[c], qm);
                 dg[c] = magic_digits(bits);
             }
-            const float wsum = (float)(int)(wbits - 4u * kMagicBits);
+            if constexpr (kBiased<LB>) qm = fmaf(bias * inv, (float)(int)(wbits - 4u * kMagicBits), qm);
             uint32_t rows[3];
             transpose_digits(dg[0], dg[1], dg[2], dg[3], rows);
             const int head = hv + 2 * i;
 #pragma unroll
             for (int j = 0; j < 3; j++) *reinterpret_cast<uint32_t *>(tile + (3 * head + j) * kARowK + 4 * x) = rows[j];
-            cst[i] = half_sum(fmaf(128.f * inv, wsum, qm), upper);
+            cst[i] = half_sum(qm, upper);
         }
         wave_sync();
 #pragma unroll
@@ -627,8 +632,8 @@ __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *
 // V block.  p: softmax numerators of tokens l%32 and 32 + l%32 for this lane's heads.
 template <int G, int LB, class F>
 __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *lut, uint32_t mask2, uint8_t *tile,
-                                             const float (&p)[G / 2][2], float two_eb, int lane, TileSoft<G> &ts,
-                                             F &&record_done) {
+                                             const float (&p)[G / 2][2], float two_eb, float bias, int lane,
+                                             TileSoft<G> &ts, F &&record_done) {
     constexpr int HL = G / 2;
     asm volatile("" : "+v"(lane));
     const int x = lane & 31, hv = lane >> 5;
@@ -663,8 +668,8 @@ __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *
 #pragma unroll
                 for (int j = 0; j < 3; j++) tile[(3 * head + j) * kARowV + 32 * t + x] = (uint8_t)(dg >> (8 * j));
             }
-            const float wsum = (float)(int)(wbits - 2u * kMagicBits);
-            ts.bv[i] += fmaf(128.f * inv, wsum, fmaf(p[i][0], mn[0], p[i][1] * mn[1]));
+            if constexpr (kBiased<LB>) ts.bv[i] = fmaf(bias * inv, (float)(int)(wbits - 2u * kMagicBits), ts.bv[i]);
+            ts.bv[i] += fmaf(p[i][0], mn[0], p[i][1] * mn[1]);
         }
         wave_sync();
 #pragma unroll
@@ -724,14 +729,15 @@ __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *
 // record sizes) is decoded straight from global memory, out of line.
 template <int G, int LB>
 __device__ __noinline__ void k_tile_block_global(const uint32_t *rec, const char *lut, uint32_t mask2, uint8_t *tile,
-                                                 const float *qf, float two_eb, float scale, int lane, int kmm,
+                                                 const float *qf, float two_eb, float bias, float scale, int lane, int kmm,
                                                  TileSoft<G> &ts, float (&p)[G / 2][2]) {
-    k_tile_block<G, LB>(rec, lut, mask2, tile, qf, two_eb, scale, lane, kmm, ts, p, [] {});
+    k_tile_block<G, LB>(rec, lut, mask2, tile, qf, two_eb, bias, scale, lane, kmm, ts, p, [] {});
 }
 template <int G, int LB>
 __device__ __noinline__ void v_tile_block_global(const uint32_t *rec, const char *lut, uint32_t mask2, uint8_t *tile,
-                                                 const float (&p)[G / 2][2], float two_eb, int lane, TileSoft<G> &ts) {
-    v_tile_block<G, LB>(rec, lut, mask2, tile, p, two_eb, lane, ts, [] {});
+                                                 const float (&p)[G / 2][2], float two_eb, float bias, int lane,
+                                                 TileSoft<G> &ts) {
+    v_tile_block<G, LB>(rec, lut, mask2, tile, p, two_eb, bias, lane, ts, [] {});
 }
 
 // A wave's softmax state parked in LDS, G * 128 + 3 * G floats: o[g][channel] then {m, l, bv} per head with l and bv
@@ -971,57 +977,20 @@ __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens
     wave_sync();
 }
 
-// A record on its way from global memory to the wave's LDS staging area: the first 8 KiB travel through
-// registers (loads issued early, stored to LDS later), the rest is copied at commit time.
-constexpr int kPrefetchRegs = 8;
-// The part of a record beyond what travels through registers (records above 8 KiB: only with code words near the
-// 12-bit limit).  Out of line so that its address arithmetic is not hoisted into the kernel's register budget.
-__device__ __noinline__ void copy_rest(uint4 *stage, const uint4 *src, uint32_t n16, int lane) {
-    for (uint32_t i = lane + 64 * kPrefetchRegs; i < n16; i += 64) stage[i] = src[i];
+// A record goes from global memory straight into the wave's staging area with LDS-direct loads (lane l of load i delivers
+// its 16 bytes to byte 1024 i + 16 l; in the last one the lanes beyond the record are masked out), issued when the
+// previous record has been decoded: no register holds it on the way.
+__device__ __forceinline__ void load_lds16(const uint4 *src, uint8_t *dst) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
 }
-
-struct Prefetch {
-    uint4 r[kPrefetchRegs];
-    const uint4 *src;
-    uint32_t n16;
-    __device__ __forceinline__ void issue(const uint8_t *rec, uint32_t size16, int lane) {
-        src = reinterpret_cast<const uint4 *>(rec);
-        n16 = size16;
-#pragma unroll
-        for (int i = 0; i < kPrefetchRegs; i++) {
-            const uint32_t at = min((uint32_t)(lane + 64 * i), size16 - 1u);  // clamped: every load is in bounds
-            r[i] = src[at];
-        }
-    }
-    __device__ __forceinline__ void commit(uint4 *stage, int lane) const {
-#pragma unroll
-        for (int i = 0; i < kPrefetchRegs; i++)
-            if (lane + 64 * i < n16) stage[lane + 64 * i] = r[i];
-        if (n16 > 64u * kPrefetchRegs) copy_rest(stage, src, n16, lane);
-    }
-};
-
-// The tile path's variant: the record goes from global memory straight into the staging area with LDS-direct loads
-// (lane l of load i delivers its 16 bytes to byte 1024 i + 16 l; lanes beyond the record are masked out), issued when
-// the previous record has been decoded -- no register holds it on the way.  The rest of a record above 8 KiB is copied
-// at wait time.
-struct DirectStage {
-    const uint4 *src;
-    uint32_t n16;
-    __device__ __forceinline__ void issue(const uint8_t *rec, uint32_t size16, uint8_t *stage, int lane) {
-        src = reinterpret_cast<const uint4 *>(rec);
-        n16 = size16;
-#pragma unroll
-        for (int i = 0; i < kPrefetchRegs; i++)
-            if (lane + 64 * i < size16)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + lane + 64 * i),
-                                                 (__attribute__((address_space(3))) void *)(stage + 1024 * i), 16, 0, 0);
-    }
-    __device__ __forceinline__ void wait(uint4 *stage4, int lane) const {
-        __builtin_amdgcn_s_waitcnt(0);  // vmcnt(0): the loads have written the LDS
-        if (n16 > 64u * kPrefetchRegs) copy_rest(stage4, src, n16, lane);
-    }
-};
+__device__ __forceinline__ void stage_record(const uint8_t *rec, uint32_t size16, uint8_t *stage, int lane) {
+    const uint4 *src = reinterpret_cast<const uint4 *>(rec);
+    const uint32_t n_full = size16 >> 6, rest = size16 & 63u;
+    for (uint32_t i = 0; i < n_full; i++) load_lds16(src + 64 * i + lane, stage + 1024 * i);
+    if ((uint32_t)lane < rest) load_lds16(src + 64 * n_full + lane, stage + 1024 * n_full);
+}
+__device__ __forceinline__ void wait_record() { __builtin_amdgcn_s_waitcnt(0); }  // vmcnt(0): the loads have written the LDS
 
 // One workgroup per CU, as many waves as the registers allow per SIMD (fused_waves_per_simd): 4 (128 VGPRs), 3 (168)
 // or 2 (256).  The host may launch fewer waves per workgroup (short sequences,
@@ -1034,7 +1003,8 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     using M = DecodeMode<LB>;
     constexpr bool kTile = G >= kTileMinG;  // packed symbols in registers, int8 MFMA
     __shared__ __attribute__((aligned(16))) uint8_t lut_s[2][M::kTableBytes];
-    __shared__ __attribute__((aligned(16))) float qf[G * kD];
+    __shared__ __attribute__((aligned(16))) float qf[kTile ? G * kD : 4];
+    __shared__ __attribute__((aligned(16))) uint8_t zeros[kTile ? 16 : kDigitRow];  // lanes that hold no digit row read it
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // per wave: staging area + weights
     const int tid = threadIdx.x, lane = tid & 63, n_threads = blockDim.x;
     // the wave number and everything derived from it (block numbers, table entries, record addresses) are scalars
@@ -1042,7 +1012,8 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     const int n_waves = __builtin_amdgcn_readfirstlane(n_threads >> 6);
     uint8_t *stage = smem + (size_t)wave * a.stage_bytes;
     constexpr int kWeightBytes = (int)fused_weight_bytes(G);
-    float *wts = reinterpret_cast<float *>(smem + (size_t)n_waves * a.stage_bytes + (size_t)wave * kWeightBytes);
+    // the wave's weight area: digit rows of the A operand
+    uint8_t *tile = smem + (size_t)n_waves * a.stage_bytes + (size_t)wave * kWeightBytes;
     const char *lutK = reinterpret_cast<const char *>(&lut_s[0][0]);
     const char *lutV = reinterpret_cast<const char *>(&lut_s[1][0]);
 
@@ -1061,72 +1032,79 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     const BlockEntry *tabK = g.table + ((size_t)0 * g.B * g.H + bh) * g.max_blocks;
     const BlockEntry *tabV = g.table + ((size_t)1 * g.B * g.H + bh) * g.max_blocks;
     const uint32_t stage16 = (uint32_t)a.stage_bytes / 16 - 1;  // one unit of slack for the streams' look-ahead
-    uint4 *stage4 = reinterpret_cast<uint4 *>(stage);
     const uint32_t *stage32 = reinterpret_cast<const uint32_t *>(stage);
 
-    // Prologue.  The first Block Offsets Array entries are requested before the decode tables and the query so that
-    // their round trip overlaps; the first K record is requested before the workgroup barrier.
+    // Prologue: everything the first block needs is requested before anything is waited for -- the Block Offsets Array
+    // entries, the decode tables (LDS-direct, the waves share them), the query, then the first K record -- so that the
+    // workgroup starts after two trips to memory (entry, record).  As loops of load, wait, LDS store the tables and the
+    // query cost a workgroup of four waves 3.4 us.
     int j = j0 + wave;
     BlockEntry eK = {0, 0}, eV = {0, 0};
     if (j < j1) {
         eK = tabK[j];
         eV = tabV[j];
     }
-    for (int t = 0; t < 2; t++) {
-        // pair table: 4096 entries of 4 bytes; otherwise 2^(longest code word of this tensor) entries of 2 bytes
-        const uint4 *src = M::kPair ? reinterpret_cast<const uint4 *>(pair_of(g, t))
-                                    : reinterpret_cast<const uint4 *>(lut_of(g, t));
-        uint4 *dst = reinterpret_cast<uint4 *>(&lut_s[t][0]);
-        const int n16 = M::kPair ? M::kTableBytes / 16 : max(1, (2 << g.lut_bits[t]) / 16);
-        const uint32_t flip = !kTile ? 0u : M::kPair ? 0x00808000u : 0x80008000u;  // the MFMA operands hold symbol - 128 as int8
-        for (int i = tid; i < n16; i += n_threads) {
-            uint4 v = src[i];
-            v.x ^= flip; v.y ^= flip; v.z ^= flip; v.w ^= flip;
-            dst[i] = v;
+    const uint16_t *q0 = a.q + ((size_t)b * g.Hq + (size_t)h * G) * kD;
+    uint4 qv[kTile ? G / 4 : 1];           // tile path: 8 query values each, of this thread and of thread + n_threads
+    uint32_t qh[kTile ? 1 : G][2];         // else: q of channels lane and lane + 64
+    if constexpr (kTile) {
+#pragma unroll
+        for (int k = 0; k < G / 4; k++)    // at least 64 threads for G * 16 pieces
+            qv[k] = reinterpret_cast<const uint4 *>(q0)[min(tid + k * n_threads, G * kD / 8 - 1)];
+    } else {
+#pragma unroll
+        for (int gg = 0; gg < G; gg++) { qh[gg][0] = q0[gg * kD + lane]; qh[gg][1] = q0[gg * kD + lane + 64]; }
+    }
+    auto stage_table = [&](const uint4 *src, int bytes, uint8_t *to) {
+        for (int c = wave; 1024 * c < bytes; c += n_waves)
+            if (1024 * c + 16 * lane < bytes) load_lds16(src + 64 * c + lane, to + 1024 * c);
+    };
+    stage_table(M::kPair ? reinterpret_cast<const uint4 *>(pair_of(g, 0)) : reinterpret_cast<const uint4 *>(lut_of(g, 0)),
+                M::kTableBytes, &lut_s[0][0]);
+    stage_table(M::kPair ? reinterpret_cast<const uint4 *>(pair_of(g, 1)) : reinterpret_cast<const uint4 *>(lut_of(g, 1)),
+                M::kTableBytes, &lut_s[1][0]);
+    const uint32_t maskK = a.mask[0], maskV = a.mask[1];
+    if (j < j1 && eK.size16 <= stage16) stage_record(g.payload + (size_t)eK.off16 * 16, eK.size16, stage, lane);
+    float qreg[kTile ? 1 : G][2];          // the tile path reads its q from LDS once per block
+    if constexpr (kTile) {
+#pragma unroll
+        for (int k = 0; k < G / 4; k++) {
+            const int i = tid + k * n_threads;
+            float4 *dst = reinterpret_cast<float4 *>(qf + 8 * i);
+            if (i < G * kD / 8) {
+                dst[0] = make_float4(h2f(qv[k].x & 0xffffu), h2f(qv[k].x >> 16), h2f(qv[k].y & 0xffffu), h2f(qv[k].y >> 16));
+                dst[1] = make_float4(h2f(qv[k].z & 0xffffu), h2f(qv[k].z >> 16), h2f(qv[k].w & 0xffffu), h2f(qv[k].w >> 16));
+            }
+        }
+    } else {
+#pragma unroll
+        for (int gg = 0; gg < G; gg++) { qreg[gg][0] = h2f(qh[gg][0]); qreg[gg][1] = h2f(qh[gg][1]); }
+        if (tid < kDigitRow / 4) reinterpret_cast<uint32_t *>(zeros)[tid] = 0;
+    }
+    wait_record();
+    __syncthreads();
+    if constexpr (kBiased<LB>) {
+        if (a.bias[0] != 0.f || a.bias[1] != 0.f) {
+            uint32_t *tk = reinterpret_cast<uint32_t *>(&lut_s[0][0]), *tv = reinterpret_cast<uint32_t *>(&lut_s[1][0]);
+            if (a.bias[0] != 0.f)
+                for (int i = tid; i < M::kTableBytes / 4; i += n_threads) tk[i] ^= 0x80008000u;
+            if (a.bias[1] != 0.f)
+                for (int i = tid; i < M::kTableBytes / 4; i += n_threads) tv[i] ^= 0x80008000u;
+            __syncthreads();
         }
     }
-    const uint32_t maskK = a.mask[0], maskV = a.mask[1];
-    for (int i = tid; i < G * kD; i += n_threads) qf[i] = h2f(a.q[((size_t)b * g.Hq + (size_t)h * G) * kD + i]);
-    Prefetch pf;
-#pragma unroll
-    for (int i = 0; i < kPrefetchRegs; i++) pf.r[i] = make_uint4(0, 0, 0, 0);
-    pf.src = nullptr;
-    pf.n16 = 0;
-    DirectStage ds;
-    ds.src = nullptr;
-    ds.n16 = 0;
-    if (j < j1 && eK.size16 <= stage16) {
-        if constexpr (kTile) ds.issue(g.payload + (size_t)eK.off16 * 16, eK.size16, stage, lane);
-        else pf.issue(g.payload + (size_t)eK.off16 * 16, eK.size16, lane);
-    }
-    __syncthreads();
-    // q in registers: channels lane and lane + 64 (the tile path reads its q from LDS once per block)
     constexpr int kQ0 = kTile ? G / 2 : G;
-    float qreg[kTile ? 1 : G][2];
-    if constexpr (!kTile) {
-#pragma unroll
-        for (int gg = 0; gg < G; gg++) { qreg[gg][0] = qf[gg * kD + lane]; qreg[gg][1] = qf[gg * kD + lane + 64]; }
-    }
 
     Soft<G> st;
     st.init();
     TileSoft<kTile ? G : 2> ts;
     ts.init();
-    uint8_t *tile = reinterpret_cast<uint8_t *>(wts);
 
-    if (j < j1) {
-        if (eK.size16 <= stage16) {
-            if constexpr (kTile) ds.wait(stage4, lane);
-            else pf.commit(stage4, lane);
-        }
-        wave_sync();
-    }
     __builtin_amdgcn_s_setprio(3);
     while (j < j1) {
         float score[G], p[G];
         const bool k_staged = eK.size16 <= stage16, v_staged = eV.size16 <= stage16;
         const uint8_t *recK = g.payload + (size_t)eK.off16 * 16, *recV = g.payload + (size_t)eV.off16 * 16;
-        if (!kTile && v_staged) pf.issue(recV, eV.size16, lane);  // V record travels while K is decoded
         const int jn = j + n_waves;  // the next pair's Block Offsets Array entries travel with it
         BlockEntry eKn = {0, 0}, eVn = {0, 0};
         if (jn < j1) {
@@ -1134,33 +1112,35 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             eVn = tabV[jn];
         }
         float pt[kQ0][2];  // tile path: softmax numerators in the layout of the result tiles
+        // The next record is requested when the current one has been decoded: the staging area is free then, and its
+        // loads travel behind the last products and the softmax.
+        auto next_v = [&] { if (v_staged) stage_record(recV, eV.size16, stage, lane); };
         if constexpr (kTile) {
-            // The next record is requested when the current one has been decoded: its registers are then live across
-            // the products and the softmax only, not across a decode.
             if (k_staged) {
-                k_tile_block<G, LB>(stage32, lutK, maskK, tile, qf, g.two_eb[0], a.scale, lane, g.k_minmax_bytes, ts, pt,
-                                    [&] { if (v_staged) ds.issue(recV, eV.size16, stage, lane); });
+                k_tile_block<G, LB>(stage32, lutK, maskK, tile, qf, g.two_eb[0], a.bias[0], a.scale, lane, g.k_minmax_bytes,
+                                     ts, pt, next_v);
             } else {
                 TileSoft<G> ts_tmp = ts;
                 float p_tmp[kQ0][2];
                 k_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, tile, qf, g.two_eb[0],
-                                           a.scale, lane, g.k_minmax_bytes, ts_tmp, p_tmp);
+                                            a.bias[0], a.scale, lane, g.k_minmax_bytes, ts_tmp, p_tmp);
                 ts = ts_tmp;
 #pragma unroll
                 for (int i = 0; i < kQ0; i++) { pt[i][0] = p_tmp[i][0]; pt[i][1] = p_tmp[i][1]; }
-                if (v_staged) ds.issue(recV, eV.size16, stage, lane);
+                next_v();
             }
         } else {
         if (k_staged) {
-            k_block<G, LB>(stage32, lutK, maskK, wts, qreg, g.two_eb[0], a.scale, lane, g.k_minmax_bytes, score);
+            k_block<G, LB>(stage32, lutK, maskK, tile, zeros, qreg, g.two_eb[0], a.bias[0], a.scale, lane, g.k_minmax_bytes, score, next_v);
         } else {  // larger than the staging area: decode from global memory (copies keep the hot state in registers)
             float q_tmp[G][2], s_tmp[G];
 #pragma unroll
             for (int gg = 0; gg < G; gg++) { q_tmp[gg][0] = qreg[gg][0]; q_tmp[gg][1] = qreg[gg][1]; }
-            k_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, wts, q_tmp, g.two_eb[0], a.scale,
-                                  lane, g.k_minmax_bytes, s_tmp);
+            k_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, tile, zeros, q_tmp, g.two_eb[0],
+                                  a.bias[0], a.scale, lane, g.k_minmax_bytes, s_tmp);
 #pragma unroll
             for (int gg = 0; gg < G; gg++) score[gg] = s_tmp[gg];
+            next_v();
         }
         }
         if constexpr (!kTile) {
@@ -1168,49 +1148,43 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             for (int gg = 0; gg < G; gg++) p[gg] = st.update(gg, score[gg]);
         }
         wave_sync();  // every lane is done with the K record
-        if (v_staged) {
-            if constexpr (kTile) ds.wait(stage4, lane);
-            else pf.commit(stage4, lane);
-        }
+        if (v_staged) wait_record();
         wave_sync();
         eKn.off16 = __builtin_amdgcn_readfirstlane(eKn.off16);
         eKn.size16 = __builtin_amdgcn_readfirstlane(eKn.size16);
         eVn.off16 = __builtin_amdgcn_readfirstlane(eVn.off16);
         eVn.size16 = __builtin_amdgcn_readfirstlane(eVn.size16);
         const bool next_staged = jn < j1 && eKn.size16 <= stage16;
-        if (!kTile && next_staged) pf.issue(g.payload + (size_t)eKn.off16 * 16, eKn.size16, lane);
+        auto next_k = [&] { if (next_staged) stage_record(g.payload + (size_t)eKn.off16 * 16, eKn.size16, stage, lane); };
         if constexpr (kTile) {
             if (v_staged) {
-                v_tile_block<G, LB>(stage32, lutV, maskV, tile, pt, g.two_eb[1], lane, ts,
-                                    [&] { if (next_staged) ds.issue(g.payload + (size_t)eKn.off16 * 16, eKn.size16, stage, lane); });
+                v_tile_block<G, LB>(stage32, lutV, maskV, tile, pt, g.two_eb[1], a.bias[1], lane, ts, next_k);
             } else {
                 TileSoft<G> ts_tmp = ts;
                 float p_tmp[kQ0][2];
 #pragma unroll
                 for (int i = 0; i < kQ0; i++) { p_tmp[i][0] = pt[i][0]; p_tmp[i][1] = pt[i][1]; }
                 v_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, tile, p_tmp, g.two_eb[1],
-                                           lane, ts_tmp);
+                                            a.bias[1], lane, ts_tmp);
                 ts = ts_tmp;
-                if (next_staged) ds.issue(g.payload + (size_t)eKn.off16 * 16, eKn.size16, stage, lane);
+                next_k();
             }
         } else {
         if (v_staged) {
-            v_block<G, LB>(stage32, lutV, maskV, wts, p, g.two_eb[1], lane, st);
+            v_block<G, LB>(stage32, lutV, maskV, tile, zeros, p, g.two_eb[1], a.bias[1], lane, st, next_k);
         } else {
             Soft<G> st_tmp = st;
             float p_tmp[G];
 #pragma unroll
             for (int gg = 0; gg < G; gg++) p_tmp[gg] = p[gg];
-            v_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, wts, p_tmp, g.two_eb[1], lane,
-                                  st_tmp);
+            v_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, tile, zeros, p_tmp, g.two_eb[1],
+                                  a.bias[1], lane, st_tmp);
             st = st_tmp;
+            next_k();
         }
         }
         wave_sync();
-        if (jn < j1 && eKn.size16 <= stage16) {
-            if constexpr (kTile) ds.wait(stage4, lane);
-            else pf.commit(stage4, lane);
-        }
+        if (next_staged) wait_record();
         wave_sync();
         eK = eKn;
         eV = eVn;
@@ -1245,7 +1219,7 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             if (!parked) soft_to_area<G>(st, area, lane);
             parked = true;
             buffered_tokens<G>(g.res, g.res_tokens, g.B, g.H, b, h, a.res_head, a.n_res, first, n_waves * a.n_splits,
-                               a.q + ((size_t)b * g.Hq + (size_t)h * G) * kD, a.scale, lane, a.k_new, a.v_new, a.new_row, area);
+                               q0, a.scale, lane, a.k_new, a.v_new, a.new_row, area);
         }
     }
     if (parked) area_to_soft<G>(area, lane, st);
@@ -1339,6 +1313,7 @@ hipError_t launch_fused_attn(const Geo &g, const uint16_t *q, float scale, float
     a.blocks_per_split = n_blocks > 0 ? (n_blocks + n_splits - 1) / n_splits : 0;
     a.n_splits = n_blocks > 0 ? (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split : 1;
     a.stage_bytes = stage_bytes;
+    for (int t = 0; t < 2; t++) a.bias[t] = g.n_sym[t] > 128 ? 128.f : 0.f;
     const int bits_k = g.lut_bits[0], bits_v = g.lut_bits[1];
     const int longest = bits_k > bits_v ? bits_k : bits_v;
     if (longest < 1 || longest > kLutBits) return hipErrorInvalidValue;

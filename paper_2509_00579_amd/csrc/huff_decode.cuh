@@ -122,29 +122,13 @@ struct DownReader {
     }
 };
 
-// CNT table lookups in a window.  J = 1: 16-bit entries (symbol << 8) | code length, indexed by the next `bits` stream
-// bits, mask = ((1 << bits) - 1) << 1.  J = 2: 32-bit entries of the pair table, indexed by the next 12 stream bits
+// A table entry.  J = 1: 16-bit entries (symbol << 8) | code length, indexed by the next `bits` stream bits,
+// mask = ((1 << bits) - 1) << 1.  J = 2: 32-bit entries of the pair table, indexed by the next 12 stream bits
 // (mask = 0xfff << 2): byte 0 = length of two consecutive code words together, byte 1 = first symbol, byte 2 = second
-// symbol.  CNT * (index width) <= 32 - J is the caller's promise.  e[] receives the entries; returns the number of
-// bits used.
-template <int J, int CNT>
-__device__ __forceinline__ uint32_t lookup(uint32_t win, const char *lut, uint32_t mask, uint32_t (&e)[CNT]) {
-    uint32_t tot = 0;
-#pragma unroll
-    for (int k = 0; k < CNT; k++) {
-        if constexpr (J == 1) e[k] = *reinterpret_cast<const uint16_t *>(lut + (win & mask));
-        else e[k] = *reinterpret_cast<const uint32_t *>(lut + (win & mask));
-        win >>= (e[k] & 31u);
-        tot += e[k];  // low byte: running sum of code lengths (at most 31, never carries)
-    }
-    return tot & 0xffu;
-}
-
-// the symbols of a table entry as fp32 (one v_cvt_f32_ubyte1 / v_cvt_f32_ubyte2)
-__device__ __forceinline__ float sym_f32(uint32_t e) { return (float)((e >> 8) & 0xffu); }
-__device__ __forceinline__ float sym2_f32(uint32_t e) { return (float)((e >> 16) & 0xffu); }
-
-// The four chains of one lane (two slices x two directions) advance together, CNT lookups each.
+// symbol.  Lookups per window * index width <= 31 - J from four lookups on, else <= 32 - J, is the caller's promise.
+// The four chains of one lane (two slices x two directions) advance together, CNT lookups each.  The four lookups of a
+// round are issued back to back before any of their results is used: a wave then waits for the LDS once per round, not
+// once per lookup.  (Left to itself the compiler runs the chains of some blocks one after the other.)
 template <int J>
 struct Quad {
     UpReader<J> au, bu;
@@ -163,17 +147,42 @@ struct Quad {
         bu.open(wm1, b0);
         bd.open(wm1, b0 + bbits);
     }
+    __device__ __forceinline__ static uint32_t entry(const char *lut, uint32_t at) {
+        if constexpr (J == 1) return *reinterpret_cast<const uint16_t *>(lut + at);
+        else return *reinterpret_cast<const uint32_t *>(lut + at);
+    }
     template <int CNT>
     __device__ __forceinline__ void step(const uint32_t *wm1, const char *lut, uint32_t mask, uint32_t (&fau)[CNT],
                                          uint32_t (&fad)[CNT], uint32_t (&fbu)[CNT], uint32_t (&fbd)[CNT]) {
-        const uint32_t u0 = lookup<J, CNT>(au.window(wm1), lut, mask, fau);
-        const uint32_t u1 = lookup<J, CNT>(ad.window(wm1), lut, mask, fad);
-        const uint32_t u2 = lookup<J, CNT>(bu.window(wm1), lut, mask, fbu);
-        const uint32_t u3 = lookup<J, CNT>(bd.window(wm1), lut, mask, fbd);
-        au.advance(wm1, u0);
-        ad.advance(wm1, u1);
-        bu.advance(wm1, u2);
-        bd.advance(wm1, u3);
+        // From four lookups on the bits used are counted by a one in bit 31 of the window that the shifts move down (CNT
+        // code words leave it untouched); for fewer it is cheaper to add up the entries' length bytes.
+        constexpr bool kSentinel = CNT >= 4;
+        uint32_t w[4] = {au.window(wm1), ad.window(wm1), bu.window(wm1), bd.window(wm1)}, tot[4] = {0, 0, 0, 0};
+        if constexpr (kSentinel) {
+#pragma unroll
+            for (int c = 0; c < 4; c++) w[c] |= 0x80000000u;
+        }
+#pragma unroll
+        for (int k = 0; k < CNT; k++) {
+            uint32_t at[4], e[4];
+#pragma unroll
+            for (int c = 0; c < 4; c++) at[c] = w[c] & mask;
+#pragma unroll
+            for (int c = 0; c < 4; c++) e[c] = entry(lut, at[c]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                if (kSentinel || k + 1 < CNT) w[c] >>= (e[c] & 31u);
+                if (!kSentinel) tot[c] += e[c];
+            }
+            fau[k] = e[0]; fad[k] = e[1]; fbu[k] = e[2]; fbd[k] = e[3];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; c++) tot[c] = kSentinel ? (uint32_t)__builtin_clz(w[c]) : tot[c] & 0xffu;
+        au.advance(wm1, tot[0]);
+        ad.advance(wm1, tot[1]);
+        bu.advance(wm1, tot[2]);
+        bd.advance(wm1, tot[3]);
     }
 };
 

@@ -91,9 +91,10 @@ constexpr int fused_table_bits(int longest) {
     return longest <= 6 ? 6 : longest <= 7 ? 7 : longest <= 8 ? 8 : longest <= 10 ? 10 : 12;
 }
 constexpr int kLdsBytesPerCU = 160 * 1024;
-// Bytes of one wave's LDS area next to its staging area.  Groups of 1 and 2 heads: fp32 weights [128][G].  Groups of
-// 4 and 8: the area in which the A operand is laid out.
-constexpr size_t fused_weight_bytes(int G) { return G >= 4 ? (size_t)tile_bytes(G) : (size_t)G * kD * 4; }
+// Bytes of one wave's LDS area next to its staging area, in which the A operand is laid out.  Groups of 1 and 2 heads:
+// four digit rows per head; 16 bytes of padding put the rows into different banks.
+constexpr int kDigitRow = kD + 16;
+constexpr size_t fused_weight_bytes(int G) { return G >= 4 ? (size_t)tile_bytes(G) : (size_t)G * 4 * kDigitRow; }
 // LDS of one fused-kernel workgroup apart from the per-wave areas: the two decode tables, the query rows, the merge flag.
 constexpr size_t fused_lds_fixed(int G, int longest) {
     return (fused_table_bits(longest) == 6 ? (size_t)2 * kPairTableEntries * 4 : (size_t)4 << fused_table_bits(longest)) +

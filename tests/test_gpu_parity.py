@@ -409,6 +409,21 @@ def test_buffered_tokens_at_unit_edges(gpu, oracle, G, n0):
     gc.close()
 
 
+@pytest.mark.parametrize("G", [1, 2])
+@pytest.mark.parametrize("rel,limit", [(2e-3, 8), (2e-3, 12), (3.9e-3, 8), (3.95e-3, 7), (1e-2, 6), (0.25, 2)])
+def test_integer_dot_products_of_groups_of_1_and_2(gpu, oracle, G, rel, limit):
+    """Weights as 30-bit integers against decoded symbols as int8: 251, 129, 128, 51 and 3 levels (beyond 128 the symbols are
+    biased), channels ten times the others.  The weights carry fp32's 24 bits, the products are exact, the rest is fp32
+    sums over 128 channels and 195 tokens: 2^-24 * (128 + 195) * the sum of magnitudes (about 4) is 8e-5."""
+    B, H, S = 1, 2, 195
+    Kx, Vx, oc, gc = _both(gpu, oracle, B, H, H * G, S, S, 256, rel, rel, seed=51, limit=limit)
+    q = W.make_queries(B, H * G, 1, 52)[0]
+    out = gc.attn_decode(_dev(q), SCALE).cpu().numpy()
+    ref = oc.attn_decode(q, SCALE)
+    assert np.abs(out - ref).max() <= 8e-5 * max(1.0, np.abs(ref).max()), np.abs(out - ref).max()
+    gc.close()
+
+
 def test_many_sequence_splits(gpu, oracle):
     """One long sequence with a single KV head: the library splits it 128 ways (its maximum) so that the chip is
     filled; every split count gives the oracle's result, also when the last split is short or the buffer holds
