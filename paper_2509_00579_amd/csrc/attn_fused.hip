@@ -30,18 +30,42 @@
 
 namespace kvc {
 
+// Unsigned division by a number that the host knows: x / d = mulhi(x, mul) >> shift for x < 2^31 (round-up method); d = 1
+// is mul = 0.  Scalar instructions only, where the compiler's own division goes through the vector ALU's reciprocal.
+struct FastDiv {
+    uint32_t mul, shift;
+    void set(uint32_t d) {
+        uint32_t s = 0;
+        while ((1ull << s) < d) s++;
+        mul = d == 1 ? 0u : (uint32_t)((1ull << (31 + s)) / d + 1);
+        shift = s ? s - 1 : 0;
+    }
+    __device__ __forceinline__ uint32_t operator()(uint32_t x) const { return mul ? __umulhi(x, mul) >> shift : x; }
+};
+
+// Only what the kernel reads, what it reads first in front: the arguments sit in memory that the scalar cache has not seen,
+// and every 64-byte line of them costs a trip (about 1 us); early_args() sends for all three at once.
 struct FusedArgs {
-    Geo g;
+    const BlockEntry *table;
+    const uint8_t *tables, *payload;
     const uint16_t *q;
-    float *out;
-    float scale;
-    int n_blocks, res_head, n_res, blocks_per_split, n_splits, stage_bytes;
+    FastDiv by_splits, by_heads, by_waves;
+    int n_splits, H, max_blocks, n_blocks;
+    // second line
+    int blocks_per_split, stage_bytes, Hq, n_bh;
     uint32_t mask[2];   // table index mask of each tensor, already scaled to the byte offset of an entry
     float bias[2];      // what the decode tables' symbols are short of: 128 with more than 128 levels, else 0
-    // append fused into this launch: the newest buffered token (number new_row of the buffer, oldest = 0) is not in the
+    float two_eb[2], scale;
+    int k_minmax_bytes, n_res, res_head, res_tokens;
+    // Append fused into this launch: the newest buffered token (number new_row of the buffer, oldest = 0) is not in the
     // buffer yet but in k_new / v_new [B][H][128]; the wave that reads it also stores it there.  new_row < 0: none.
-    const uint16_t *k_new, *v_new;
     int new_row;
+    // third line
+    float *out, *partials;
+    uint32_t *counters;
+    const uint16_t *res, *k_new, *v_new;
+    int B;
+    __device__ __forceinline__ void early_args() const { asm volatile("" ::"s"(new_row), "s"(B)); }
 };
 
 // How far a score may exceed the softmax reference of groups of 1 and 2 heads before the state is rescaled.  A block's
@@ -1017,20 +1041,19 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     const char *lutK = reinterpret_cast<const char *>(&lut_s[0][0]);
     const char *lutV = reinterpret_cast<const char *>(&lut_s[1][0]);
 
-    const Geo &g = a.g;
+    a.early_args();
     // Workgroups go to the eight XCDs round-robin by their linear number, and each XCD has its own L2.  Numbering the
     // (batch-head, split) pairs so that an XCD gets a contiguous range of them keeps the splits of one head -- whose
     // records are neighbours in memory and share cache lines at their ends, and whose partials the last of them
     // merges -- behind one L2.
     int item = blockIdx.x;
     if ((gridDim.x & (kXCDs - 1)) == 0) item = (item & (kXCDs - 1)) * (gridDim.x / kXCDs) + item / kXCDs;
-    const int bh = item / a.n_splits, split = item - bh * a.n_splits;
-    const int b = bh / g.H, h = bh - b * g.H;
+    const int bh = (int)a.by_splits((uint32_t)item), split = item - bh * a.n_splits;
+    const int b = (int)a.by_heads((uint32_t)bh), h = bh - b * a.H;
 
     const int j0 = split * a.blocks_per_split;
     const int j1 = min(j0 + a.blocks_per_split, a.n_blocks);
-    const BlockEntry *tabK = g.table + ((size_t)0 * g.B * g.H + bh) * g.max_blocks;
-    const BlockEntry *tabV = g.table + ((size_t)1 * g.B * g.H + bh) * g.max_blocks;
+    const BlockEntry *tabK = a.table + (size_t)bh * a.max_blocks, *tabV = tabK + (size_t)a.n_bh * a.max_blocks;
     const uint32_t stage16 = (uint32_t)a.stage_bytes / 16 - 1;  // one unit of slack for the streams' look-ahead
     const uint32_t *stage32 = reinterpret_cast<const uint32_t *>(stage);
 
@@ -1044,7 +1067,7 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         eK = tabK[j];
         eV = tabV[j];
     }
-    const uint16_t *q0 = a.q + ((size_t)b * g.Hq + (size_t)h * G) * kD;
+    const uint16_t *q0 = a.q + ((size_t)b * a.Hq + (size_t)h * G) * kD;
     uint4 qv[kTile ? G / 4 : 1];           // tile path: 8 query values each, of this thread and of thread + n_threads
     uint32_t qh[kTile ? 1 : G][2];         // else: q of channels lane and lane + 64
     if constexpr (kTile) {
@@ -1059,12 +1082,11 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         for (int c = wave; 1024 * c < bytes; c += n_waves)
             if (1024 * c + 16 * lane < bytes) load_lds16(src + 64 * c + lane, to + 1024 * c);
     };
-    stage_table(M::kPair ? reinterpret_cast<const uint4 *>(pair_of(g, 0)) : reinterpret_cast<const uint4 *>(lut_of(g, 0)),
-                M::kTableBytes, &lut_s[0][0]);
-    stage_table(M::kPair ? reinterpret_cast<const uint4 *>(pair_of(g, 1)) : reinterpret_cast<const uint4 *>(lut_of(g, 1)),
-                M::kTableBytes, &lut_s[1][0]);
+    constexpr int kTabOff = M::kPair ? kTabPairOff : kTabLutOff;
+    stage_table(reinterpret_cast<const uint4 *>(a.tables + kTabOff), M::kTableBytes, &lut_s[0][0]);
+    stage_table(reinterpret_cast<const uint4 *>(a.tables + kTensorTablesBytes + kTabOff), M::kTableBytes, &lut_s[1][0]);
     const uint32_t maskK = a.mask[0], maskV = a.mask[1];
-    if (j < j1 && eK.size16 <= stage16) stage_record(g.payload + (size_t)eK.off16 * 16, eK.size16, stage, lane);
+    if (j < j1 && eK.size16 <= stage16) stage_record(a.payload + (size_t)eK.off16 * 16, eK.size16, stage, lane);
     float qreg[kTile ? 1 : G][2];          // the tile path reads its q from LDS once per block
     if constexpr (kTile) {
 #pragma unroll
@@ -1100,11 +1122,13 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     TileSoft<kTile ? G : 2> ts;
     ts.init();
 
+    const int total = j < j1 ? (int)a.by_waves((uint32_t)(j1 - j + n_waves - 1)) : 0;  // this wave's block pairs
+    int left = total;
     __builtin_amdgcn_s_setprio(3);
     while (j < j1) {
         float score[G], p[G];
         const bool k_staged = eK.size16 <= stage16, v_staged = eV.size16 <= stage16;
-        const uint8_t *recK = g.payload + (size_t)eK.off16 * 16, *recV = g.payload + (size_t)eV.off16 * 16;
+        const uint8_t *recK = a.payload + (size_t)eK.off16 * 16, *recV = a.payload + (size_t)eV.off16 * 16;
         const int jn = j + n_waves;  // the next pair's Block Offsets Array entries travel with it
         BlockEntry eKn = {0, 0}, eVn = {0, 0};
         if (jn < j1) {
@@ -1117,13 +1141,13 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         auto next_v = [&] { if (v_staged) stage_record(recV, eV.size16, stage, lane); };
         if constexpr (kTile) {
             if (k_staged) {
-                k_tile_block<G, LB>(stage32, lutK, maskK, tile, qf, g.two_eb[0], a.bias[0], a.scale, lane, g.k_minmax_bytes,
+                k_tile_block<G, LB>(stage32, lutK, maskK, tile, qf, a.two_eb[0], a.bias[0], a.scale, lane, a.k_minmax_bytes,
                                      ts, pt, next_v);
             } else {
                 TileSoft<G> ts_tmp = ts;
                 float p_tmp[kQ0][2];
-                k_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, tile, qf, g.two_eb[0],
-                                            a.bias[0], a.scale, lane, g.k_minmax_bytes, ts_tmp, p_tmp);
+                k_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, tile, qf, a.two_eb[0],
+                                            a.bias[0], a.scale, lane, a.k_minmax_bytes, ts_tmp, p_tmp);
                 ts = ts_tmp;
 #pragma unroll
                 for (int i = 0; i < kQ0; i++) { pt[i][0] = p_tmp[i][0]; pt[i][1] = p_tmp[i][1]; }
@@ -1131,13 +1155,13 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             }
         } else {
         if (k_staged) {
-            k_block<G, LB>(stage32, lutK, maskK, tile, zeros, qreg, g.two_eb[0], a.bias[0], a.scale, lane, g.k_minmax_bytes, score, next_v);
+            k_block<G, LB>(stage32, lutK, maskK, tile, zeros, qreg, a.two_eb[0], a.bias[0], a.scale, lane, a.k_minmax_bytes, score, next_v);
         } else {  // larger than the staging area: decode from global memory (copies keep the hot state in registers)
             float q_tmp[G][2], s_tmp[G];
 #pragma unroll
             for (int gg = 0; gg < G; gg++) { q_tmp[gg][0] = qreg[gg][0]; q_tmp[gg][1] = qreg[gg][1]; }
-            k_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, tile, zeros, q_tmp, g.two_eb[0],
-                                  a.bias[0], a.scale, lane, g.k_minmax_bytes, s_tmp);
+            k_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, tile, zeros, q_tmp, a.two_eb[0],
+                                  a.bias[0], a.scale, lane, a.k_minmax_bytes, s_tmp);
 #pragma unroll
             for (int gg = 0; gg < G; gg++) score[gg] = s_tmp[gg];
             next_v();
@@ -1155,29 +1179,29 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         eVn.off16 = __builtin_amdgcn_readfirstlane(eVn.off16);
         eVn.size16 = __builtin_amdgcn_readfirstlane(eVn.size16);
         const bool next_staged = jn < j1 && eKn.size16 <= stage16;
-        auto next_k = [&] { if (next_staged) stage_record(g.payload + (size_t)eKn.off16 * 16, eKn.size16, stage, lane); };
+        auto next_k = [&] { if (next_staged) stage_record(a.payload + (size_t)eKn.off16 * 16, eKn.size16, stage, lane); };
         if constexpr (kTile) {
             if (v_staged) {
-                v_tile_block<G, LB>(stage32, lutV, maskV, tile, pt, g.two_eb[1], a.bias[1], lane, ts, next_k);
+                v_tile_block<G, LB>(stage32, lutV, maskV, tile, pt, a.two_eb[1], a.bias[1], lane, ts, next_k);
             } else {
                 TileSoft<G> ts_tmp = ts;
                 float p_tmp[kQ0][2];
 #pragma unroll
                 for (int i = 0; i < kQ0; i++) { p_tmp[i][0] = pt[i][0]; p_tmp[i][1] = pt[i][1]; }
-                v_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, tile, p_tmp, g.two_eb[1],
+                v_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, tile, p_tmp, a.two_eb[1],
                                             a.bias[1], lane, ts_tmp);
                 ts = ts_tmp;
                 next_k();
             }
         } else {
         if (v_staged) {
-            v_block<G, LB>(stage32, lutV, maskV, tile, zeros, p, g.two_eb[1], a.bias[1], lane, st, next_k);
+            v_block<G, LB>(stage32, lutV, maskV, tile, zeros, p, a.two_eb[1], a.bias[1], lane, st, next_k);
         } else {
             Soft<G> st_tmp = st;
             float p_tmp[G];
 #pragma unroll
             for (int gg = 0; gg < G; gg++) p_tmp[gg] = p[gg];
-            v_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, tile, zeros, p_tmp, g.two_eb[1],
+            v_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, tile, zeros, p_tmp, a.two_eb[1],
                                   a.bias[1], lane, st_tmp);
             st = st_tmp;
             next_k();
@@ -1192,11 +1216,10 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         {   // The SIMD issues from its oldest wave first, so its resident waves finish one after the other and the
             // last one runs alone, unable to fill the VALU.  Waves that are behind get the issue slots instead:
             // the priority falls with the share of the work that is done, and the waves finish together.
-            const int total = (j1 - j0 - wave + n_waves - 1) / n_waves, left = (j1 - j + n_waves - 1) / n_waves;
-            const int q4 = total > 0 ? (4 * left + total - 1) / total : 0;  // 4 .. 0
-            if (q4 >= 4) __builtin_amdgcn_s_setprio(3);
-            else if (q4 == 3) __builtin_amdgcn_s_setprio(2);
-            else if (q4 == 2) __builtin_amdgcn_s_setprio(1);
+            const int left4 = 4 * --left;
+            if (left4 > 3 * total) __builtin_amdgcn_s_setprio(3);
+            else if (left4 > 2 * total) __builtin_amdgcn_s_setprio(2);
+            else if (left4 > total) __builtin_amdgcn_s_setprio(1);
             else __builtin_amdgcn_s_setprio(0);
         }
     }
@@ -1212,13 +1235,12 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     // the buffered fp16 tokens in units of 16: unit u goes to split n_splits-1 - u % n_splits (the last split is the
     // short one), there to the waves in turn, starting after the wave that took the split's last block
     if (a.n_res > 0) {
-        int turn = (wave - (j1 - j0)) % n_waves;
-        if (turn < 0) turn += n_waves;
+        const int turn = j - j1;  // 0 for the wave whose turn the next block would be
         const int first = a.n_splits - 1 - split + a.n_splits * turn;
         if (first * kUnitTokens < a.n_res) {
             if (!parked) soft_to_area<G>(st, area, lane);
             parked = true;
-            buffered_tokens<G>(g.res, g.res_tokens, g.B, g.H, b, h, a.res_head, a.n_res, first, n_waves * a.n_splits,
+            buffered_tokens<G>(a.res, a.res_tokens, a.B, a.H, b, h, a.res_head, a.n_res, first, n_waves * a.n_splits,
                                q0, a.scale, lane, a.k_new, a.v_new, a.new_row, area);
         }
     }
@@ -1239,32 +1261,45 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         }
     }
     __syncthreads();
-    const int row0 = b * g.Hq + h * G;
+    const int row0 = b * a.Hq + h * G;
     // the thread number is rebuilt from the lane and the (scalar) wave number: nothing of the prologue has to stay
     // in a register, or be spilled, across the decode loop for the sake of the merge
     const int tid_m = lane + 64 * wave, nt_m = 64 * n_waves;
     for (int i = tid_m; i < G * kD; i += nt_m) {
         const int gg = i / kD, c = i - gg * kD;
-        float M_ = -INFINITY;
-        for (int w = 0; w < n_waves; w++)
-            M_ = fmaxf(M_, reinterpret_cast<const float *>(smem + (size_t)w * a.stage_bytes)[gg * kPartialStride + kD]);
-        float L = 0.f, O = 0.f;
-        for (int w = 0; w < n_waves; w++) {
-            const float *cw = reinterpret_cast<const float *>(smem + (size_t)w * a.stage_bytes) + gg * kPartialStride;
-            const float mw = cw[kD];
-            const float f = mw == -INFINITY ? 0.f : __expf(mw - M_);
-            L += cw[kD + 1] * f;
-            O += cw[c] * f;
+        float M_ = -INFINITY, L = 0.f, O = 0.f;
+        for (int w0 = 0; w0 < n_waves; w0 += 4) {  // the LDS reads of four waves' states at a time
+            float mw[4], lw[4], ow[4], mx = M_;
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const float *cw = reinterpret_cast<const float *>(smem + (size_t)min(w0 + k, n_waves - 1) * a.stage_bytes) +
+                                  gg * kPartialStride;
+                mw[k] = w0 + k < n_waves ? cw[kD] : -INFINITY;
+                lw[k] = cw[kD + 1];
+                ow[k] = cw[c];
+                mx = fmaxf(mx, mw[k]);
+            }
+            if (mx == -INFINITY) continue;  // waves that had nothing to do
+            const float f0 = __expf(M_ - mx);
+            L *= f0;
+            O *= f0;
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const float f = __expf(mw[k] - mx);  // 0 for a wave that had nothing to do
+                L = fmaf(lw[k], f, L);
+                O = fmaf(ow[k], f, O);
+            }
+            M_ = mx;
         }
         if (a.n_splits == 1) {
             a.out[(size_t)(row0 + gg) * kD + c] = O / L;
         } else {
-            float *dst = g.partials + ((size_t)(row0 + gg) * kMaxSplits + split) * kPartialStride;
+            float *dst = a.partials + ((size_t)(row0 + gg) * kMaxSplits + split) * kPartialStride;
             store_agent(dst + c, O);
             if (c == 0) { store_agent(dst + kD, M_); store_agent(dst + kD + 1, L); }
         }
     }
-    if (a.n_splits > 1) finish_splits<G>(g.partials, g.counters + bh, row0, a.n_splits, a.out, tid_m, nt_m);
+    if (a.n_splits > 1) finish_splits<G>(a.partials, a.counters + bh, row0, a.n_splits, a.out, tid_m, nt_m);
 }
 
 template <int G, int LB>
@@ -1279,7 +1314,7 @@ static hipError_t launch_fused_gn(const FusedArgs &a, int n_waves, size_t lds, h
     }
     if (n_waves < 1 || n_waves > MaxWaves<G, LB>::value) return hipErrorInvalidValue;
     if (ev0) (void)hipEventRecord(ev0, s);
-    hipLaunchKernelGGL((fused_attn_kernel<G, LB>), dim3(a.n_splits * a.g.B * a.g.H), dim3(64 * n_waves), lds, s, a);
+    hipLaunchKernelGGL((fused_attn_kernel<G, LB>), dim3(a.n_splits * a.n_bh), dim3(64 * n_waves), lds, s, a);
     if (ev1) (void)hipEventRecord(ev1, s);
     return hipGetLastError();
 }
@@ -1303,7 +1338,19 @@ hipError_t launch_fused_attn(const Geo &g, const uint16_t *q, float scale, float
     a.k_new = k_new;
     a.v_new = v_new;
     a.new_row = k_new ? n_res - 1 : -1;  // n_res counts the token being appended
-    a.g = g;
+    a.table = g.table;
+    a.tables = g.tables;
+    a.payload = g.payload;
+    a.partials = g.partials;
+    a.counters = g.counters;
+    a.res = g.res;
+    a.res_tokens = g.res_tokens;
+    a.B = g.B;
+    a.H = g.H;
+    a.Hq = g.Hq;
+    a.n_bh = g.B * g.H;
+    a.max_blocks = g.max_blocks;
+    a.k_minmax_bytes = g.k_minmax_bytes;
     a.q = q;
     a.out = out;
     a.scale = scale;
@@ -1313,6 +1360,10 @@ hipError_t launch_fused_attn(const Geo &g, const uint16_t *q, float scale, float
     a.blocks_per_split = n_blocks > 0 ? (n_blocks + n_splits - 1) / n_splits : 0;
     a.n_splits = n_blocks > 0 ? (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split : 1;
     a.stage_bytes = stage_bytes;
+    a.by_splits.set((uint32_t)a.n_splits);
+    a.by_heads.set((uint32_t)g.H);
+    a.by_waves.set((uint32_t)n_waves);
+    for (int t = 0; t < 2; t++) a.two_eb[t] = g.two_eb[t];
     for (int t = 0; t < 2; t++) a.bias[t] = g.n_sym[t] > 128 ? 128.f : 0.f;
     const int bits_k = g.lut_bits[0], bits_v = g.lut_bits[1];
     const int longest = bits_k > bits_v ? bits_k : bits_v;
