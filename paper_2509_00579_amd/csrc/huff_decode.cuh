@@ -205,4 +205,99 @@ struct DecodeMode {
     static constexpr int kTableBytes = (kPair ? 4 : 2) << kIndexBits;     // per tensor
 };
 
+// bytes 1 of four table entries (the symbols) as one word, first entry in the lowest byte
+__device__ __forceinline__ uint32_t pack_syms(uint32_t e0, uint32_t e1, uint32_t e2, uint32_t e3) {
+    const uint32_t lo = __builtin_amdgcn_perm(e1, e0, 0x0c0c0501u), hi = __builtin_amdgcn_perm(e3, e2, 0x0c0c0501u);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+// the same from two entries of the pair table (bytes 1 and 2 of each are two consecutive symbols): e0's symbols in
+// the two lowest bytes; and with the four symbols in the opposite order (a chain that was read downwards)
+__device__ __forceinline__ uint32_t pack_pairs(uint32_t e0, uint32_t e1) { return __builtin_amdgcn_perm(e1, e0, 0x06050201u); }
+__device__ __forceinline__ uint32_t pack_pairs_rev(uint32_t e0, uint32_t e1) { return __builtin_amdgcn_perm(e1, e0, 0x01020506u); }
+
+// The table entries of a lane's four chains while they wait to be packed (fully unrolled code: an entry lives in a
+// register from its lookup to the packing of its word).  NE entries per chain: 32 one-symbol or 16 two-symbol ones.
+template <int NE>
+struct ChainSyms {
+    uint32_t au[NE], ad[NE], bu[NE], bd[NE];
+};
+// The decoded symbols of the lane's two slices, four per word, in ascending position inside the slice:
+// word j of a slice holds positions 4j .. 4j+3.  The up chain delivers words 0, 1, .. and the down chain 15, 14, ..
+struct SliceWords {
+    uint32_t a[16], b[16];
+};
+// Decodes symbols S0 .. S1-1 of this lane's four chains (whole windows from S0 on; the last window of a chain may be
+// short) and packs every word whose four symbols are there.
+template <int LB, int S0, int S1>
+__device__ __forceinline__ void decode_span(Quad<DecodeMode<LB>::J> &qd, const uint32_t *wm1, const char *lut, uint32_t mask,
+                                            ChainSyms<DecodeMode<LB>::kLookupsPerChain> &e, SliceWords &p) {
+    using M = DecodeMode<LB>;
+    constexpr int SP = M::kSymsPerLookup, NL = M::kLookupsPerWindow, NS = M::kSymsPerWindow;
+    static_assert(S0 % NS == 0 && S0 < S1 && S1 <= kHalf && (S1 % NS == 0 || S1 == kHalf), "whole windows");
+    auto pack_words = [&](int w0, int w1) {
+#pragma unroll
+        for (int w = w0; w < w1; w++) {
+            if constexpr (SP == 1) {
+                p.a[w] = pack_syms(e.au[4 * w], e.au[4 * w + 1], e.au[4 * w + 2], e.au[4 * w + 3]);
+                p.a[15 - w] = pack_syms(e.ad[4 * w + 3], e.ad[4 * w + 2], e.ad[4 * w + 1], e.ad[4 * w]);
+                p.b[w] = pack_syms(e.bu[4 * w], e.bu[4 * w + 1], e.bu[4 * w + 2], e.bu[4 * w + 3]);
+                p.b[15 - w] = pack_syms(e.bd[4 * w + 3], e.bd[4 * w + 2], e.bd[4 * w + 1], e.bd[4 * w]);
+            } else {
+                p.a[w] = pack_pairs(e.au[2 * w], e.au[2 * w + 1]);
+                p.a[15 - w] = pack_pairs_rev(e.ad[2 * w], e.ad[2 * w + 1]);
+                p.b[w] = pack_pairs(e.bu[2 * w], e.bu[2 * w + 1]);
+                p.b[15 - w] = pack_pairs_rev(e.bd[2 * w], e.bd[2 * w + 1]);
+            }
+        }
+    };
+    constexpr int kFull = (S1 - S0) / NS, kTailSyms = (S1 - S0) - kFull * NS, kTail = kTailSyms / SP;
+    static_assert(kTailSyms % SP == 0, "a span ends on a whole table entry");
+#pragma unroll
+    for (int r = 0; r < kFull; r++) {
+        uint32_t fau[NL], fad[NL], fbu[NL], fbd[NL];
+        qd.template step<NL>(wm1, lut, mask, fau, fad, fbu, fbd);
+        const int s = S0 + r * NS;
+#pragma unroll
+        for (int k = 0; k < NL; k++) {
+            e.au[s / SP + k] = fau[k]; e.ad[s / SP + k] = fad[k]; e.bu[s / SP + k] = fbu[k]; e.bd[s / SP + k] = fbd[k];
+        }
+        pack_words(s / 4, (s + NS) / 4);
+    }
+    if constexpr (kTail > 0) {
+        uint32_t fau[kTail ? kTail : 1], fad[kTail ? kTail : 1], fbu[kTail ? kTail : 1], fbd[kTail ? kTail : 1];
+        qd.template step<(kTail ? kTail : 1)>(wm1, lut, mask, fau, fad, fbu, fbd);
+        constexpr int s = S0 + kFull * NS;
+#pragma unroll
+        for (int k = 0; k < kTail; k++) {
+            e.au[s / SP + k] = fau[k]; e.ad[s / SP + k] = fad[k]; e.bu[s / SP + k] = fbu[k]; e.bd[s / SP + k] = fbd[k];
+        }
+        pack_words(s / 4, (s + kTailSyms) / 4);
+    }
+}
+// the 4 x 4 bytes of a quad of lanes transposed: lane q of the result holds byte q of the four lanes' words, lane 0's in
+// the lowest byte
+struct QuadTranspose {
+    uint32_t sel1, sel2;
+    __device__ __forceinline__ explicit QuadTranspose(int lane)
+        : sel1((lane & 1) ? 0x03070105u : 0x06020400u), sel2((lane & 2) ? 0x03020706u : 0x05040100u) {}
+    __device__ __forceinline__ uint32_t operator()(uint32_t u) const {
+        const uint32_t v = __builtin_amdgcn_perm(dpp_u<kDppXor1>(u), u, sel1);
+        return __builtin_amdgcn_perm(dpp_u<kDppXor2>(v), v, sel2);
+    }
+};
+// A record goes from global memory straight into the wave's staging area with LDS-direct loads (lane l of load i delivers
+// its 16 bytes to byte 1024 i + 16 l; in the last one the lanes beyond the record are masked out), issued when the
+// previous record has been decoded: no register holds it on the way.
+__device__ __forceinline__ void load_lds16(const uint4 *src, uint8_t *dst) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void stage_record(const uint8_t *rec, uint32_t size16, uint8_t *stage, int lane) {
+    const uint4 *src = reinterpret_cast<const uint4 *>(rec);
+    const uint32_t n_full = size16 >> 6, rest = size16 & 63u;
+    for (uint32_t i = 0; i < n_full; i++) load_lds16(src + 64 * i + lane, stage + 1024 * i);
+    if ((uint32_t)lane < rest) load_lds16(src + 64 * n_full + lane, stage + 1024 * n_full);
+}
+__device__ __forceinline__ void wait_record() { __builtin_amdgcn_s_waitcnt(0); }  // vmcnt(0): the loads have written the LDS
+
 }  // namespace kvc

@@ -101,6 +101,19 @@ constexpr size_t fused_lds_fixed(int G, int longest) {
            (size_t)G * kD * 4 + 512;
 }
 
+// Unsigned division by a number that the host knows: x / d = mulhi(x, mul) >> shift for x < 2^31 (round-up method); d = 1
+// is mul = 0.  Scalar instructions only, where the compiler's own division goes through the vector ALU's reciprocal.
+struct FastDiv {
+    uint32_t mul, shift;
+    void set(uint32_t d) {
+        uint32_t s = 0;
+        while ((1ull << s) < d) s++;
+        mul = d == 1 ? 0u : (uint32_t)((1ull << (31 + s)) / d + 1);
+        shift = s ? s - 1 : 0;
+    }
+    __device__ __forceinline__ uint32_t operator()(uint32_t x) const { return mul ? __umulhi(x, mul) >> shift : x; }
+};
+
 // ---- launches implemented in the .hip files ----
 hipError_t launch_decompress(const Geo &g, int which, uint16_t *out, int n_blocks, int res_head, int n_res, int seq_stride,
                              int stage_bytes, int tree_walk, hipStream_t s);

@@ -983,6 +983,27 @@ def test_stand_alone_decompression(gpu, oracle, B, H, S, k_mode, max_len):
     gc.close()
 
 
+@pytest.mark.parametrize("B,H,S,rel,limit", [(1, 3, 192, 2e-3, 8), (1, 1, 320, 2e-3, 12), (3, 1, 130, 1e-2, 6),
+                                             (1, 5, 64, 5e-3, 10), (1, 2, 63, 1e-2, 12)])
+def test_decompression_widths_and_partial_workgroups(gpu, oracle, B, H, S, rel, limit):
+    """Every table width, more than 128 levels (codes beyond int8), block counts that leave waves of the last workgroup
+    idle or that are none, and a flush between two decompressions with a statistics call, which reads the control words,
+    in between: a larger record than before must still find its staging area.  Bit for bit against the oracle."""
+    Kx, Vx, oc, gc = _both(gpu, oracle, B, H, H, max(S, 64), S, S + 64, rel, rel, seed=71, limit=limit)
+    kn, vn = W.make_new_tokens(B, H, 64, 72)
+    kn, vn = (kn * 50).astype(np.float16), (vn ** 3).astype(np.float16)  # rare codes: longer records
+    for step in range(2):
+        for which in (K, V):
+            got = gc.decompress(which, oc.n_blocks * 64 + oc.n_res).cpu().numpy()
+            np.testing.assert_array_equal(got.view(np.uint16), oc.decompress(which).view(np.uint16))
+        if step == 0:
+            for t in range(64):
+                oc.append_token(kn[t], vn[t])
+                gc.append_token(_dev(kn[t]), _dev(vn[t]))
+            gc.stats()
+    gc.close()
+
+
 @pytest.mark.parametrize("name,rel", [("c2", 1e-2), ("c2", 5e-3), ("c2", 2e-2), ("c3", 1e-2), ("c4", 1e-2)])
 def test_large_configs_full_size_sampled(gpu, oracle, name, rel):
     """The long-context (with its error-bound sweep), grouped-query and 70B-shaped workloads at their full prompt
