@@ -191,8 +191,9 @@ kvcomp_status kvcomp_get_residual(kvcomp_ctx *ctx, int which, uint16_t *h_buf, i
  * ((b*seq_stride + t)*n_kv_heads + h)*128 + c, for t < tokens in the cache: blocks reconstructed as
  * fp16(min + float(code)*width) (binary32 multiply and add, one rounding), then the buffered tokens unchanged.
  * d_out: DEVICE, caller-owned, 16-byte aligned, batch*seq_stride*n_kv_heads*128 fp16; seq_stride >= tokens
- * (KVCOMP_ERR_CAPACITY otherwise).  Synchronises the stream once (it reads the largest record size, and reports
- * the flags described at kvcomp_get_stats). */
+ * (KVCOMP_ERR_CAPACITY otherwise).  Stream-ordered.  If an append has compressed a block since the last synchronising
+ * call, the call synchronises the stream once before it launches (it reads the largest record size, and reports the
+ * flags described at kvcomp_get_stats). */
 kvcomp_status kvcomp_decompress(kvcomp_ctx *ctx, int which, void *d_out, int seq_stride, void *stream);
 
 /* The same call with the decoder of Section 3.3.1 instead of the table decoder: a branch-free walk of the

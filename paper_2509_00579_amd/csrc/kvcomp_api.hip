@@ -47,6 +47,8 @@ struct kvcomp_ctx {
     uint8_t len[2][256];
     uint32_t code[2][256];
     uint32_t max_size16;
+    bool flushed;           // a flush was queued after the control words were last read: largest record and flags may have changed
+    bool flush_captured;    // a flush was captured into a graph: it may run again at any time
     int tune_splits, tune_stage, tune_waves;
     bool profiling;
     std::vector<hipEvent_t> events;  // pairs
@@ -66,6 +68,8 @@ namespace {
 kvcomp_status read_ctrl(kvcomp_ctx *ctx, hipStream_t s) {
     HIP_TRY(hipMemcpyAsync(ctx->h_ctrl, ctx->geo.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    ctx->flushed = false;
+    ctx->max_size16 = std::max(ctx->max_size16, ctx->h_ctrl->max_size16);
     return KVCOMP_OK;
 }
 
@@ -127,6 +131,7 @@ kvcomp_status kvcomp_create(const kvcomp_config *cfg, void *d_arena, size_t aren
     c->have_codebook = false;
     c->n_blocks = c->n_res = c->res_head = 0;
     c->max_size16 = 0;
+    c->flushed = c->flush_captured = false;
     c->tune_splits = c->tune_stage = c->tune_waves = 0;
     c->profiling = false;
     c->events_used = 0;
@@ -400,6 +405,10 @@ kvcomp_status kvcomp_append_token(kvcomp_ctx *ctx, const void *d_k_new, const vo
         const uint16_t *rk = g.res + (size_t)ctx->res_head * g.H * kD;
         const uint16_t *rv = rk + (size_t)g.B * g.res_tokens * g.H * kD;
         HIP_TRY(launch_encode(g, rk, rv, g.res_tokens, 1, ctx->n_blocks, s));
+        ctx->flushed = true;
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(s, &capture));
+        if (capture != hipStreamCaptureStatusNone) ctx->flush_captured = true;
         ctx->n_blocks++;
         ctx->n_res -= kBT;
         ctx->res_head = (ctx->res_head + kBT) % g.res_tokens;
@@ -621,12 +630,13 @@ static kvcomp_status decompress_impl(kvcomp_ctx *ctx, int which, void *d_out, in
     if (seq_stride < tokens) return fail(KVCOMP_ERR_CAPACITY, "seq_stride %d below the %d tokens in the cache", seq_stride, tokens);
     if (ctx->n_blocks && !ctx->have_codebook) return fail(KVCOMP_ERR_STATE, "no codebook");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (ctx->n_blocks) {  // the largest record may have grown through flushes since the last synchronising call
+    // The largest record may have grown, and flags may be up, through flushes since the control words were last read; where
+    // there was none the host knows both, and the stream goes on without a stop (10 us of an idle GPU per tensor).
+    if (ctx->n_blocks && (ctx->flushed || ctx->flush_captured)) {
         kvcomp_status st = read_ctrl(ctx, s);
         if (st) return st;
         st = check_flags(ctx, s);
         if (st) return st;
-        ctx->max_size16 = std::max(ctx->max_size16, ctx->h_ctrl->max_size16);
     }
     const int stage = (int)align_up((size_t)ctx->max_size16 * 16 + 16, 256);
     HIP_TRY(launch_decompress(ctx->geo, which, static_cast<uint16_t *>(d_out), ctx->n_blocks, ctx->res_head, ctx->n_res,
