@@ -1,8 +1,8 @@
 // The uncompressed comparison kernel (Section 4.3 compares the fused kernel with a plain fp16 matrix-vector
 // product): decode attention on the fp16 cache [B, S, H, 128], sequence split over workgroups with an online
 // softmax, merged inside the kernel like the fused path.  HBM-bound: every K and V byte is read once with 16-byte
-// loads.  Groups of 1 and 2 query heads form the scores on the vector ALU; groups of 4 and 8 (one K row serves
-// several heads, a small matrix product) on the matrix cores.
+// loads.  Groups of 1 and 2 query heads run on the vector ALU; groups of 4 and 8 (one K and one V row serve several heads:
+// two small matrix products) on the matrix cores.
 #include <hip/hip_fp16.h>
 
 #include <mutex>
@@ -182,60 +182,53 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_kernel(int B, i
 }
 
 // ---- groups of 4 and 8 query heads --------------------------------------------------------------------------------
-// Scores of 16 tokens x (up to 16) heads per v_mfma_f32_16x16x16_f16: S^T = K Q^T, A = K tile, B = Q^T.
-//   A: lane l holds row (token) l % 16, reduction slots 4 * (l / 16) .. + 3
-//   B: lane l holds column (head) l % 16, the same slots;  D: lane l holds column l % 16, rows 4 * (l / 16) .. + 3
-// Which channel a reduction slot stands for is free as long as A and B agree: step (i, hh) maps slot (l / 16, r) to
-// channel 8 * (l / 16 + 4 i) + 4 hh + r, so that a lane's A operands for two steps are one 16-byte load of its K row.
-// The P V product stays on the vector ALU (lane = 8 channels x one token in four, as in the kernel above); the
-// softmax numerators reach it through LDS.
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ half4_t as_half4(uint32_t lo, uint32_t hi) {
-    const uint2 v = make_uint2(lo, hi);
-    return __builtin_bit_cast(half4_t, v);
-}
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+// Both products run on v_mfma_f32_16x16x32_f16 with every operand straight from the registers it was loaded or computed in:
+//   A: lane l holds row l % 16, eight reduction slots of slot group l / 16;  B: column l % 16, the same slots;
+//   D: lane l holds column l % 16, rows 4 (l / 16) .. + 3.
+// Which index a slot stands for is free as long as A and B agree.
+//   scores: S^T = K Q^T, rows = 16 tokens, columns = query heads (repeated: column j is head j % G).  Step i maps slot
+//           (l / 16, r) to channel 8 (l / 16 + 4 i) + r: a lane's operand is one 16-byte load of its K row.
+//   p . V : O = P V, rows = heads, 32 tokens at a time.  A lane's eight scores of two tiles, tokens 16 tt + 4 (l / 16) + r,
+//           are the eight slots of its group, so the numerators are the A operand without leaving the lane.  V is loaded for
+//           those tokens, 8 channels of one token per load; the 8 x 8 halves of a lane are transposed in its registers (one
+//           v_perm_b32 per pair) into one B operand per channel: column l % 16 of tile ct is channel 8 (l % 16) + ct.
+//   A numerator has fp32's bits, an fp16 operand eleven of them: rows 0 .. G-1 hold p rounded to fp16, rows G .. 2G-1 what
+//   is left of it times 2^11 (the copies of the score columns are there for that), and the two are added at the end.
+// The loop keeps a tile of 64 V rows and the next tile of K rows on their way (16 to 32 KiB a wave, two waves per SIMD).
+// With p . V on the vector ALU, 8 FMAs per value for groups of 8, and the numerators through LDS, it was bound by the ALU:
+// 8 x 8 heads x 16384 tokens, groups of 8: 121 us (4.4 TB/s) -> 104 us (5.2 TB/s, what a large copy reaches); groups of 4,
+// 16 x 8 heads x 8192: 103 -> 99 us.
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr float kLowPart = 2048.f;     // scale of the second part of a numerator
+constexpr float kLazyMaxFp16 = 8.f;    // how far a score may exceed the softmax reference before the state is rescaled
 
 template <int G>
-__global__ __launch_bounds__(64 * kBWaves, G == 8 ? 2 : 3) void baseline_attn_gqa_kernel(
+__global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
     int B, int H, int Hq, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V, int seq,
     const uint16_t *__restrict__ q, float scale, float *__restrict__ partials, uint32_t *__restrict__ counters,
     float *__restrict__ out, int tokens_per_split, int split_stride) {
     static_assert(G == 4 || G == 8, "group size");
     __shared__ float comb[kBWaves][G][kPartialStride];
-    __shared__ __attribute__((aligned(16))) float p_s[kBWaves][64][G];  // numerators of the wave's current tokens
-    __shared__ float alpha_s[kBWaves][G];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int split = blockIdx.x, bh = blockIdx.y, b = bh / H, h = bh - b * H;
-    const int j = lane & 15, gq = lane >> 4;  // matrix column / row group;  V phase: channels 8 j .. + 7, tokens 4 i + gq
-    const int cc = j * 8;
-    half4_t qb[4][2];
+    const int j = lane & 15, gq = lane >> 4, part = j / G;
+    v8h qb[4];
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (j < G) v = *reinterpret_cast<const uint4 *>(q + ((size_t)b * Hq + (size_t)h * G + j) * kD + 8 * (gq + 4 * i));
-        qb[i][0] = as_half4(v.x, v.y);
-        qb[i][1] = as_half4(v.z, v.w);
-    }
-    float m = -INFINITY, lsum = 0.f;  // running maximum and sum of head j (lanes with j >= G idle along)
-    float acc[G][8];
+    for (int i = 0; i < 4; i++)
+        qb[i] = *reinterpret_cast<const v8h *>(q + ((size_t)b * Hq + (size_t)h * G + j % G) * kD + 8 * (gq + 4 * i));
+    float m = -INFINITY, lsum = 0.f;  // reference and sum of head j % G (this lane's tokens)
+    v4f acc[8];                       // channel 8 j + ct of rows 4 gq .. + 3
 #pragma unroll
-    for (int g = 0; g < G; g++)
-#pragma unroll
-        for (int k = 0; k < 8; k++) acc[g][k] = 0.f;
+    for (int ct = 0; ct < 8; ct++) acc[ct] = v4f{0.f, 0.f, 0.f, 0.f};
     const int t_begin = split * tokens_per_split;
     const int t_end = min(t_begin + tokens_per_split, seq);
     const size_t row = (size_t)H * kD;
     const uint16_t *Kb = K + ((size_t)b * seq * H + h) * kD + 8 * gq;
-    const uint16_t *Vb = V + ((size_t)b * seq * H + h) * kD + cc;
+    const uint16_t *Vb = V + ((size_t)b * seq * H + h) * kD + 8 * j;
 
-    uint4 kv[16];
+    uint4 kv[16], vv[16];
     auto load_k = [&](int t0) {
 #pragma unroll
         for (int tt = 0; tt < 4; tt++) {
@@ -246,82 +239,82 @@ __global__ __launch_bounds__(64 * kBWaves, G == 8 ? 2 : 3) void baseline_attn_gq
                                            : make_uint4(0, 0, 0, 0);
         }
     };
-    // Groups of 8 run two waves per SIMD anyway (their accumulators) and have the registers to request the next
-    // tile's K rows early; groups of 4 are better off with three waves per SIMD and no look-ahead (measured).
-    constexpr bool kAhead = G == 8;
-    int t0 = t_begin + wave * 64;
-    if (kAhead && t0 < t_end) load_k(t0);
-    for (; t0 < t_end; t0 += 64 * kBWaves) {
-        if (!kAhead) load_k(t0);
-        float s[16];
-        float ml = -INFINITY;
-#pragma unroll
-        for (int tt = 0; tt < 4; tt++) {
-            float4_t d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const uint4 &v = kv[tt * 4 + i];
-                d = __builtin_amdgcn_mfma_f32_16x16x16f16(as_half4(v.x, v.y), qb[i][0], d, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f32_16x16x16f16(as_half4(v.z, v.w), qb[i][1], d, 0, 0, 0);
-            }
-            const float dd[4] = {d.x, d.y, d.z, d.w};
-#pragma unroll
-            for (int r = 0; r < 4; r++) {  // token t0 + 16 tt + 4 gq + r, head j
-                s[tt * 4 + r] = t0 + 16 * tt + 4 * gq + r < t_end ? scale * dd[r] : -INFINITY;
-                ml = fmaxf(ml, s[tt * 4 + r]);
-            }
-        }
-        ml = fmaxf(ml, __shfl_xor(ml, 16));
-        ml = fmaxf(ml, __shfl_xor(ml, 32));
-        const float mnew = fmaxf(m, ml);  // finite: the tile holds at least one token
-        const float alpha = __expf(m - mnew);
-        m = mnew;
-        float ps = 0.f;
+    auto load_v = [&](int t0) {
 #pragma unroll
         for (int tt = 0; tt < 4; tt++)
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const float pv = __expf(s[tt * 4 + r] - mnew);
-                ps += pv;
-                if (j < G) p_s[wave][16 * tt + 4 * gq + r][j] = pv;
+                const int t = t0 + 16 * tt + 4 * gq + r;
+                vv[tt * 4 + r] = t < t_end ? *reinterpret_cast<const uint4 *>(Vb + (size_t)t * row) : make_uint4(0, 0, 0, 0);
             }
-        lsum = lsum * alpha + ps;
-        if (gq == 0 && j < G) alpha_s[wave][j] = alpha;
-        wave_lds_sync();
+    };
+    int t0 = t_begin + wave * 64;
+    if (t0 < t_end) load_k(t0);
+    for (; t0 < t_end; t0 += 64 * kBWaves) {
+        load_v(t0);
+        float s[16], ml = -INFINITY;
 #pragma unroll
-        for (int g = 0; g < G; g++) {
-            const float al = alpha_s[wave][g];
+        for (int tt = 0; tt < 4; tt++) {
+            v4f d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int k = 0; k < 8; k++) acc[g][k] *= al;
+            for (int i = 0; i < 4; i++)
+                d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, kv[tt * 4 + i]), qb[i], d, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; r++) s[tt * 4 + r] = scale * d[r];  // token t0 + 16 tt + 4 gq + r
         }
-        // the K rows of the next tile travel with the V rows of this one (the scores above were their last use)
-        if (kAhead && t0 + 64 * kBWaves < t_end) load_k(t0 + 64 * kBWaves);
-        constexpr int kChunk = G == 8 ? 8 : 16;  // V rows in flight per lane (register budget)
-#pragma unroll 1
-        for (int i0 = 0; i0 < 16; i0 += kChunk) {
-            uint4 vv[kChunk];
+        if (t0 + 64 * kBWaves < t_end) load_k(t0 + 64 * kBWaves);
+        if (t0 + 64 > t_end) {  // the last tile of the split
 #pragma unroll
-            for (int i = 0; i < kChunk; i++) {
-                const int t = t0 + 4 * (i0 + i) + gq;
-                vv[i] = t < t_end ? *reinterpret_cast<const uint4 *>(Vb + (size_t)t * row) : make_uint4(0, 0, 0, 0);
+            for (int n = 0; n < 16; n++)
+                if (t0 + 16 * (n >> 2) + 4 * gq + (n & 3) >= t_end) s[n] = -INFINITY;
+        }
+#pragma unroll
+        for (int n = 0; n < 16; n++) ml = fmaxf(ml, s[n]);
+        // The reference moves only when some score exceeds it by more than kLazyMaxFp16 (it is -inf at first: always then).
+        if (__builtin_amdgcn_ballot_w64(ml - m > kLazyMaxFp16) != 0) {
+            ml = fmaxf(ml, __shfl_xor(ml, 16));
+            ml = fmaxf(ml, __shfl_xor(ml, 32));
+            const float mnew = fmaxf(m, ml);  // finite: the tile holds at least one token
+            const float alpha = __expf(m - mnew);
+            m = mnew;
+            lsum *= alpha;
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const float ar = __shfl(alpha, 4 * gq + r);  // of row 4 gq + r, head (4 gq + r) % G
+#pragma unroll
+                for (int ct = 0; ct < 8; ct++) acc[ct][r] *= ar;
+            }
+        }
+        float ps = 0.f;
+#pragma unroll
+        for (int n = 0; n < 16; n++) {
+            s[n] = __expf(s[n] - m);
+            ps += s[n];
+        }
+        lsum += ps;
+#pragma unroll
+        for (int hh = 0; hh < 2; hh++) {  // tokens 0..31 and 32..63 of the tile
+            union { v8h v; uint32_t w[4]; } pa;
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const float p0 = s[8 * hh + 2 * k], p1 = s[8 * hh + 2 * k + 1];
+                const v2h hi = {(_Float16)p0, (_Float16)p1};
+                const v2h lo = {(_Float16)((p0 - (float)hi[0]) * kLowPart), (_Float16)((p1 - (float)hi[1]) * kLowPart)};
+                pa.w[k] = part == 0 ? __builtin_bit_cast(uint32_t, hi) : part == 1 ? __builtin_bit_cast(uint32_t, lo) : 0u;
             }
 #pragma unroll
-            for (int i = 0; i < kChunk; i++) {
-                float x[8];
-                unpack8(vv[i], x);
-                float pg[G];
+            for (int ct = 0; ct < 8; ct++) {
+                union { v8h v; uint32_t w[4]; } vb;
 #pragma unroll
-                for (int g4 = 0; g4 < G; g4 += 4) {
-                    const float4 t4 = *reinterpret_cast<const float4 *>(&p_s[wave][4 * (i0 + i) + gq][g4]);
-                    pg[g4] = t4.x; pg[g4 + 1] = t4.y; pg[g4 + 2] = t4.z; pg[g4 + 3] = t4.w;
+                for (int k = 0; k < 4; k++) {
+                    const uint4 &r0 = vv[8 * hh + 2 * k], &r1 = vv[8 * hh + 2 * k + 1];
+                    const uint32_t a = ct < 2 ? r0.x : ct < 4 ? r0.y : ct < 6 ? r0.z : r0.w;
+                    const uint32_t c = ct < 2 ? r1.x : ct < 4 ? r1.y : ct < 6 ? r1.z : r1.w;
+                    vb.w[k] = __builtin_amdgcn_perm(c, a, (ct & 1) ? 0x07060302u : 0x05040100u);
                 }
-#pragma unroll
-                for (int g = 0; g < G; g++)
-#pragma unroll
-                    for (int k = 0; k < 8; k++) acc[g][k] = fmaf(pg[g], x[k], acc[g][k]);
+                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa.v, vb.v, acc[ct], 0, 0, 0);
             }
         }
-        wave_lds_sync();  // the next tile overwrites p_s
     }
     lsum += __shfl_xor(lsum, 16);
     lsum += __shfl_xor(lsum, 32);
@@ -329,18 +322,14 @@ __global__ __launch_bounds__(64 * kBWaves, G == 8 ? 2 : 3) void baseline_attn_gq
         comb[wave][j][kD] = m;
         comb[wave][j][kD + 1] = lsum;
     }
+    // the second part of row 4 gq + r sits G rows further, in lane group gq + G / 4
 #pragma unroll
-    for (int g = 0; g < G; g++) {
+    for (int ct = 0; ct < 8; ct++)
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
-            acc[g][k] += __shfl_xor(acc[g][k], 16);
-            acc[g][k] += __shfl_xor(acc[g][k], 32);
+        for (int r = 0; r < 4; r++) {
+            const float v = fmaf(__shfl_xor(acc[ct][r], 4 * G), 1.f / kLowPart, acc[ct][r]);
+            if (4 * gq + r < G) comb[wave][4 * gq + r][8 * j + ct] = v;
         }
-        if (gq == 0) {
-#pragma unroll
-            for (int k = 0; k < 8; k++) comb[wave][g][cc + k] = acc[g][k];
-        }
-    }
     __syncthreads();
     merge_waves_and_splits<G>(comb, partials, counters, out, b, h, Hq, split, bh, tid, split_stride);
 }

@@ -809,6 +809,31 @@ def test_fp16_baseline_attention(gpu, oracle, B, H, Hq, S):
         _attn_close(out, ref)
 
 
+@pytest.mark.parametrize("G", [4, 8])
+@pytest.mark.parametrize("S", [1, 15, 17, 63, 65, 257, 700])
+def test_fp16_attention_of_large_groups_at_tile_edges(gpu, G, S):
+    """Groups of 4 and 8 on the uncompressed cache: sequence lengths around the 16-, 32- and 64-token pieces of a tile, and
+    scores that grow along the sequence, so that the softmax reference has to follow (by far more than its slack of 8)
+    with sums already made.  Against float64 on the CPU; the numerators are carried in two fp16 parts (2^-23), sums are
+    fp32: 1e-5 of the largest output."""
+    import torch
+    B, H = 2, 2
+    rng = np.random.default_rng(S * 10 + G)
+    Kx = rng.standard_normal((B, S, H, 128)).astype(np.float16)
+    Vx = rng.standard_normal((B, S, H, 128)).astype(np.float16)
+    q = rng.standard_normal((B, H * G, 128)).astype(np.float16)
+    for ramp in (0.0, 60.0):
+        Kr = (Kx + (ramp * np.linspace(0, 1, S)[None, :, None, None] * q[:, None, ::G, :] / 128)).astype(np.float16)
+        for n_splits in (0, 3):
+            out = gpu.BaselineFp16Attention(B, H, H * G)(_dev(Kr), _dev(Vx), _dev(q), 1.0, n_splits=n_splits).cpu().numpy()
+            k64, v64, q64 = (torch.from_numpy(x.astype(np.float64)) for x in (Kr, Vx, q))
+            for b in range(B):
+                for g in range(H * G):
+                    p = torch.softmax(k64[b, :, g // G] @ q64[b, g], 0)
+                    ref = (p @ v64[b, :, g // G]).numpy()
+                    assert np.abs(out[b, g] - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max()), (ramp, n_splits, b, g)
+
+
 def test_config1_full_size_sampled(gpu, oracle):
     """The benchmark workload (32 heads x 4096 tokens) in the launch configuration bench.py times."""
     w = W.CONFIGS["c1"]
