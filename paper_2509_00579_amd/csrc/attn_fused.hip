@@ -215,11 +215,12 @@ __device__ __forceinline__ void k_block(const uint32_t *hdr32, const char *lut, 
 }
 
 // ---- V block: lane = channels 2*lane and 2*lane+1 (its two slices) -------------------------------------------------
-// p[g] = softmax numerator of token `lane`.
-template <int G, int LB, class F>
+// p[g] = softmax numerator of token `lane`.  kLate: another wave is still computing them; they are fetched with
+// numerators(p) once the whole block has been decoded, and all products follow.
+template <int G, int LB, bool kLate, class F, class N>
 __device__ __forceinline__ void v_block(const uint32_t *hdr32, const char *lut, uint32_t mask, uint8_t *digits,
-                                        const uint8_t *zeros, const float (&p)[G], float two_eb, float bias, int lane,
-                                        Soft<G> &st, F &&record_done) {
+                                        const uint8_t *zeros, float (&p)[G], float two_eb, float bias, int lane,
+                                        Soft<G> &st, F &&record_done, N &&numerators) {
     static_assert(G < kTileMinG, "groups of 4 and 8 take the tile path");
     // lane t holds the folded weight p_t * step_t of token t
     const uint32_t mm = hdr32[lane];
@@ -227,13 +228,16 @@ __device__ __forceinline__ void v_block(const uint32_t *hdr32, const char *lut, 
     const float step = two_eb * (h2f(mm >> 16) - mn);
     const QuadTranspose transpose(lane);
     float inv[G];
+    auto weights = [&] {
 #pragma unroll
-    for (int g = 0; g < G; g++) {
-        const float w = p[g] * step;
-        const float f = dot_scale(w, &inv[g]);
-        *digit_slot(digits + g * 4 * kDigitRow, lane) = transpose(four_digits(w * f));
-        st.bv[g] = fmaf(p[g], fmaf(bias, step, mn), st.bv[g]);
-    }
+        for (int g = 0; g < G; g++) {
+            const float w = p[g] * step;
+            const float f = dot_scale(w, &inv[g]);
+            *digit_slot(digits + g * 4 * kDigitRow, lane) = transpose(four_digits(w * f));
+            st.bv[g] = fmaf(p[g], fmaf(bias, step, mn), st.bv[g]);
+        }
+    };
+    if constexpr (!kLate) weights();
     const uint32_t sb = hdr32[kMinMaxBytesV / 4 + lane];
     const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
     const uint32_t *wm1 = hdr32 + kHdrBytesV / 4 - 1;
@@ -259,11 +263,20 @@ __device__ __forceinline__ void v_block(const uint32_t *hdr32, const char *lut, 
     };
     constexpr int kP = tile_first_span(DecodeMode<LB>::kSymsPerWindow);
     decode_span<LB, 0, kP>(qd, wm1, lut, mask, syms, pw);
-    products(0);
-    products(3);
+    if constexpr (!kLate) {
+        products(0);
+        products(3);
+    }
     decode_span<LB, kP, kHalf>(qd, wm1, lut, mask, syms, pw);
     wave_sync();
     record_done();
+    if constexpr (kLate) {
+        numerators(p);
+        weights();
+        wave_sync();
+        products(0);
+        products(3);
+    }
     products(1);
     products(2);
 #pragma unroll
@@ -285,7 +298,10 @@ template <int G, int LB>
 __device__ __noinline__ void v_block_global(const uint32_t *rec, const char *lut, uint32_t mask, uint8_t *digits,
                                             const uint8_t *zeros, const float (&p)[G], float two_eb, float bias, int lane,
                                             Soft<G> &st) {
-    v_block<G, LB>(rec, lut, mask, digits, zeros, p, two_eb, bias, lane, st, [] {});
+    float pc[G];
+#pragma unroll
+    for (int g = 0; g < G; g++) pc[g] = p[g];
+    v_block<G, LB, false>(rec, lut, mask, digits, zeros, pc, two_eb, bias, lane, st, [] {}, [](float (&)[G]) {});
 }
 
 // ---- groups of 4 and 8 query heads, tile path ---------------------------------------------------------------------
@@ -560,21 +576,26 @@ __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *
     }
 }
 
-// V block.  p: softmax numerators of tokens l%32 and 32 + l%32 for this lane's heads.
-template <int G, int LB, class F>
+// V block.  p: softmax numerators of tokens l%32 and 32 + l%32 for this lane's heads.  kLate: see v_block.
+template <int G, int LB, bool kLate, class F, class N>
 __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *lut, uint32_t mask2, uint8_t *tile,
-                                             const float (&p)[G / 2][2], float two_eb, float bias, int lane,
-                                             TileSoft<G> &ts, F &&record_done) {
+                                             float (&p)[G / 2][2], float two_eb, float bias, int lane,
+                                             TileSoft<G> &ts, F &&record_done, N &&numerators) {
     constexpr int HL = G / 2;
     asm volatile("" : "+v"(lane));
     const int x = lane & 31, hv = lane >> 5;
     float inv;
     long a[4];
-    {
+    uint32_t minmax[2];
+    if constexpr (kLate) {  // the record's staging area may be reused before the weights are made
+        minmax[0] = hdr32[x];
+        minmax[1] = hdr32[32 + x];
+    }
+    auto weights = [&] {
         float mn[2], stp[2];
 #pragma unroll
         for (int t = 0; t < 2; t++) {
-            const uint32_t mm = hdr32[32 * t + x];
+            const uint32_t mm = kLate ? minmax[t] : hdr32[32 * t + x];
             mn[t] = h2f(mm & 0xffffu);
             stp[t] = two_eb * (h2f(mm >> 16) - mn[t]);
         }
@@ -609,7 +630,8 @@ __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *
             if ((x & 3) == 3 || x >= 4 * G) a[ks] = 0;
         }
         wave_sync();
-    }
+    };
+    if constexpr (!kLate) weights();
     // lane = channels lane (slice a) and 64 + lane (slice b), so that a result tile of 32 channels is one slice of 32
     // neighbouring lanes; slice s starts where the bits of slices 0 .. s-1 end
     const uint16_t *bits16 = reinterpret_cast<const uint16_t *>(hdr32 + kMinMaxBytesV / 4);
@@ -645,13 +667,21 @@ __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *
     };
     constexpr int kP = tile_first_span(DecodeMode<LB>::kSymsPerWindow);
     decode_span<LB, 0, kP>(qd, wm1, lut, mask2, syms, pw);
-    products(0, true);
-    products(3, false);
-    if constexpr (!kBoth) join();
+    if constexpr (!kLate) {
+        products(0, true);
+        products(3, false);
+        if constexpr (!kBoth) join();
+    }
     decode_span<LB, kP, kHalf>(qd, wm1, lut, mask2, syms, pw);
     wave_sync();
     record_done();
-    products(1, !kBoth);
+    if constexpr (kLate) {
+        numerators(p);
+        weights();
+        products(0, true);
+        products(3, false);
+    }
+    products(1, !kBoth && !kLate);
     products(2, false);
     join();
 }
@@ -668,7 +698,10 @@ template <int G, int LB>
 __device__ __noinline__ void v_tile_block_global(const uint32_t *rec, const char *lut, uint32_t mask2, uint8_t *tile,
                                                  const float (&p)[G / 2][2], float two_eb, float bias, int lane,
                                                  TileSoft<G> &ts) {
-    v_tile_block<G, LB>(rec, lut, mask2, tile, p, two_eb, bias, lane, ts, [] {});
+    float pc[G / 2][2];
+#pragma unroll
+    for (int i = 0; i < G / 2; i++) { pc[i][0] = p[i][0]; pc[i][1] = p[i][1]; }
+    v_tile_block<G, LB, false>(rec, lut, mask2, tile, pc, two_eb, bias, lane, ts, [] {}, [](float (&)[G / 2][2]) {});
 }
 
 // A wave's softmax state parked in LDS, G * 128 + 3 * G floats: o[g][channel] then {m, l, bv} per head with l and bv
@@ -914,13 +947,20 @@ __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens
 template <int G, int LB> struct MaxWaves { static constexpr int value = 4 * fused_waves_per_simd(G, LB); };
 
 // LB = the table width the kernel is compiled for (>= longest code word of both codebooks), see DecodeMode.
-template <int G, int LB>
+//
+// kPaired: a short cache leaves wave slots empty, and the time of a step is the serial chain of one wave: K record, softmax,
+// V record.  The two decodes do not depend on each other, so with 2 * blocks_per_split wave slots wave w decodes the K
+// record of the split's block w and wave blocks_per_split + w its V record at the same time; the softmax numerators go
+// from the first to the second through the first one's record area (free by then), announced by a flag in LDS.  The waves
+// behind them take the buffered tokens.  The V waves hold the state, the K waves end empty-handed.
+template <int G, int LB, bool kPaired>
 __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_kernel(FusedArgs a) {
     using M = DecodeMode<LB>;
     constexpr bool kTile = G >= kTileMinG;  // packed symbols in registers, int8 MFMA
     __shared__ __attribute__((aligned(16))) uint8_t lut_s[2][M::kTableBytes];
     __shared__ __attribute__((aligned(16))) float qf[kTile ? G * kD : 4];
     __shared__ __attribute__((aligned(16))) uint8_t zeros[kTile ? 16 : kDigitRow];  // lanes that hold no digit row read it
+    __shared__ uint32_t ready[kPaired ? 16 : 1];  // paired: wave w's numerators are in its record area
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // per wave: staging area + weights
     const int tid = threadIdx.x, lane = tid & 63, n_threads = blockDim.x;
     // the wave number and everything derived from it (block numbers, table entries, record addresses) are scalars
@@ -953,11 +993,14 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     // entries, the decode tables (LDS-direct, the waves share them), the query, then the first K record -- so that the
     // workgroup starts after two trips to memory (entry, record).  As loops of load, wait, LDS store the tables and the
     // query cost a workgroup of four waves 3.4 us.
+    const int n_pairs = a.blocks_per_split;
+    const bool is_v = kPaired && wave >= n_pairs;
     int j = j0 + wave;
+    if (is_v) j = wave < 2 * n_pairs ? j - n_pairs : j1;  // the waves behind the pairs own no block
     BlockEntry eK = {0, 0}, eV = {0, 0};
     if (j < j1) {
-        eK = tabK[j];
-        eV = tabV[j];
+        if (!is_v) eK = tabK[j];
+        if (!kPaired || is_v) eV = tabV[j];
     }
     const uint16_t *q0 = a.q + ((size_t)b * a.Hq + (size_t)h * G) * kD;
     uint4 qv[kTile ? G / 4 : 1];           // tile path: 8 query values each, of this thread and of thread + n_threads
@@ -978,7 +1021,8 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     stage_table(reinterpret_cast<const uint4 *>(a.tables + kTabOff), M::kTableBytes, &lut_s[0][0]);
     stage_table(reinterpret_cast<const uint4 *>(a.tables + kTensorTablesBytes + kTabOff), M::kTableBytes, &lut_s[1][0]);
     const uint32_t maskK = a.mask[0], maskV = a.mask[1];
-    if (j < j1 && eK.size16 <= stage16) stage_record(a.payload + (size_t)eK.off16 * 16, eK.size16, stage, lane);
+    const BlockEntry e0 = is_v ? eV : eK;
+    if (j < j1 && e0.size16 <= stage16) stage_record(a.payload + (size_t)e0.off16 * 16, e0.size16, stage, lane);
     float qreg[kTile ? 1 : G][2];          // the tile path reads its q from LDS once per block
     if constexpr (kTile) {
 #pragma unroll
@@ -994,6 +1038,9 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
 #pragma unroll
         for (int gg = 0; gg < G; gg++) { qreg[gg][0] = h2f(qh[gg][0]); qreg[gg][1] = h2f(qh[gg][1]); }
         if (tid < kDigitRow / 4) reinterpret_cast<uint32_t *>(zeros)[tid] = 0;
+    }
+    if constexpr (kPaired) {
+        if (tid < 16) ready[tid] = 0;
     }
     wait_record();
     __syncthreads();
@@ -1014,6 +1061,114 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     TileSoft<kTile ? G : 2> ts;
     ts.init();
 
+    if constexpr (kPaired) {
+        const uint8_t *rec = a.payload + (size_t)e0.off16 * 16;
+        const uint32_t *rec32 = reinterpret_cast<const uint32_t *>(rec);
+        const bool staged = e0.size16 <= stage16;
+        if (j < j1 && !is_v) {
+            __builtin_amdgcn_s_setprio(3);  // its V wave waits for it
+            float *box = reinterpret_cast<float *>(stage);
+            if constexpr (kTile) {
+                float p[kQ0][2];
+                if (staged) {
+                    k_tile_block<G, LB>(stage32, lutK, maskK, tile, qf, a.two_eb[0], a.bias[0], a.scale, lane,
+                                        a.k_minmax_bytes, ts, p, [] {});
+                } else {
+                    TileSoft<G> ts_tmp = ts;  // copies keep the hot state in registers
+                    float p_tmp[kQ0][2];
+                    k_tile_block_global<G, LB>(rec32, lutK, maskK, tile, qf, a.two_eb[0], a.bias[0], a.scale, lane,
+                                               a.k_minmax_bytes, ts_tmp, p_tmp);
+                    ts = ts_tmp;
+#pragma unroll
+                    for (int i = 0; i < kQ0; i++) { p[i][0] = p_tmp[i][0]; p[i][1] = p_tmp[i][1]; }
+                }
+                wave_sync();
+#pragma unroll
+                for (int i = 0; i < kQ0; i++) {
+                    box[(3 * i) * 64 + lane] = p[i][0];
+                    box[(3 * i + 1) * 64 + lane] = p[i][1];
+                    box[(3 * i + 2) * 64 + lane] = ts.m[i];
+                }
+            } else {
+                float score[G];
+                if (staged) {
+                    k_block<G, LB>(stage32, lutK, maskK, tile, zeros, qreg, a.two_eb[0], a.bias[0], a.scale, lane,
+                                   a.k_minmax_bytes, score, [] {});
+                } else {
+                    float q_tmp[G][2], s_tmp[G];
+#pragma unroll
+                    for (int gg = 0; gg < G; gg++) { q_tmp[gg][0] = qreg[gg][0]; q_tmp[gg][1] = qreg[gg][1]; }
+                    k_block_global<G, LB>(rec32, lutK, maskK, tile, zeros, q_tmp, a.two_eb[0], a.bias[0], a.scale, lane,
+                                          a.k_minmax_bytes, s_tmp);
+#pragma unroll
+                    for (int gg = 0; gg < G; gg++) score[gg] = s_tmp[gg];
+                }
+                wave_sync();
+#pragma unroll
+                for (int gg = 0; gg < G; gg++) {
+                    box[2 * gg * 64 + lane] = st.update(gg, score[gg]);
+                    box[(2 * gg + 1) * 64 + lane] = st.m[gg];
+                }
+            }
+            if (lane == 0) __hip_atomic_store(&ready[wave], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else if (j < j1) {
+            // The K wave of the pair is resident (a workgroup's waves start together) and sets its flag whatever its record
+            // holds, so the wait ends.
+            const int kw = wave - n_pairs;
+            const float *box = reinterpret_cast<const float *>(smem + (size_t)kw * a.stage_bytes);
+            auto wait_k = [&] {
+                while (__hip_atomic_load(&ready[kw], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u)
+                    __builtin_amdgcn_s_sleep(1);
+            };
+            if constexpr (kTile) {
+                float p[kQ0][2];
+                auto numerators = [&](float (&pp)[kQ0][2]) {
+                    wait_k();
+#pragma unroll
+                    for (int i = 0; i < kQ0; i++) {
+                        pp[i][0] = box[(3 * i) * 64 + lane];
+                        pp[i][1] = box[(3 * i + 1) * 64 + lane];
+                        ts.m[i] = box[(3 * i + 2) * 64 + lane];
+                        ts.l[i] = pp[i][0] + pp[i][1];
+                    }
+                };
+                if (staged) {
+                    v_tile_block<G, LB, true>(stage32, lutV, maskV, tile, p, a.two_eb[1], a.bias[1], lane, ts, [] {}, numerators);
+                } else {
+                    numerators(p);
+                    TileSoft<G> ts_tmp = ts;
+                    float p_tmp[kQ0][2];
+#pragma unroll
+                    for (int i = 0; i < kQ0; i++) { p_tmp[i][0] = p[i][0]; p_tmp[i][1] = p[i][1]; }
+                    v_tile_block_global<G, LB>(rec32, lutV, maskV, tile, p_tmp, a.two_eb[1], a.bias[1], lane, ts_tmp);
+                    ts = ts_tmp;
+                }
+            } else {
+                float p[G];
+                auto numerators = [&](float (&pp)[G]) {
+                    wait_k();
+#pragma unroll
+                    for (int gg = 0; gg < G; gg++) {
+                        pp[gg] = box[2 * gg * 64 + lane];
+                        st.m[gg] = box[(2 * gg + 1) * 64 + lane];
+                        st.l[gg] = pp[gg];
+                    }
+                };
+                if (staged) {
+                    v_block<G, LB, true>(stage32, lutV, maskV, tile, zeros, p, a.two_eb[1], a.bias[1], lane, st, [] {}, numerators);
+                } else {
+                    numerators(p);
+                    Soft<G> st_tmp = st;
+                    float p_tmp[G];
+#pragma unroll
+                    for (int gg = 0; gg < G; gg++) p_tmp[gg] = p[gg];
+                    v_block_global<G, LB>(rec32, lutV, maskV, tile, zeros, p_tmp, a.two_eb[1], a.bias[1], lane, st_tmp);
+                    st = st_tmp;
+                }
+            }
+        }
+    } else {
+    const auto no_numerators = [](auto &) {};
     const int total = j < j1 ? (int)a.by_waves((uint32_t)(j1 - j + n_waves - 1)) : 0;  // this wave's block pairs
     int left = total;
     __builtin_amdgcn_s_setprio(3);
@@ -1074,7 +1229,7 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         auto next_k = [&] { if (next_staged) stage_record(a.payload + (size_t)eKn.off16 * 16, eKn.size16, stage, lane); };
         if constexpr (kTile) {
             if (v_staged) {
-                v_tile_block<G, LB>(stage32, lutV, maskV, tile, pt, a.two_eb[1], a.bias[1], lane, ts, next_k);
+                v_tile_block<G, LB, false>(stage32, lutV, maskV, tile, pt, a.two_eb[1], a.bias[1], lane, ts, next_k, no_numerators);
             } else {
                 TileSoft<G> ts_tmp = ts;
                 float p_tmp[kQ0][2];
@@ -1087,7 +1242,7 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             }
         } else {
         if (v_staged) {
-            v_block<G, LB>(stage32, lutV, maskV, tile, zeros, p, a.two_eb[1], a.bias[1], lane, st, next_k);
+            v_block<G, LB, false>(stage32, lutV, maskV, tile, zeros, p, a.two_eb[1], a.bias[1], lane, st, next_k, no_numerators);
         } else {
             Soft<G> st_tmp = st;
             float p_tmp[G];
@@ -1115,41 +1270,45 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             else __builtin_amdgcn_s_setprio(0);
         }
     }
+    }
 
     // The record area is free now: the tile path changes the layout of its state through it, and a wave with buffered
     // tokens parks its state there across the out-of-line call.
-    float *area = reinterpret_cast<float *>(stage);
-    bool parked = false;
-    if constexpr (kTile) {
-        tile_state_to_area<G>(ts, area, lane);
-        parked = true;
-    }
-    // the buffered fp16 tokens in units of 16: unit u goes to split n_splits-1 - u % n_splits (the last split is the
-    // short one), there to the waves in turn, starting after the wave that took the split's last block
-    if (a.n_res > 0) {
-        const int turn = j - j1;  // 0 for the wave whose turn the next block would be
-        const int first = a.n_splits - 1 - split + a.n_splits * turn;
-        if (first * kUnitTokens < a.n_res) {
-            if (!parked) soft_to_area<G>(st, area, lane);
+    if (!kPaired || is_v) {  // a K wave of a pair has no state, and its area may still be read
+        float *area = reinterpret_cast<float *>(stage);
+        bool parked = false;
+        if constexpr (kTile) {
+            tile_state_to_area<G>(ts, area, lane);
             parked = true;
-            buffered_tokens<G>(a.res, a.res_tokens, a.B, a.H, b, h, a.res_head, a.n_res, first, n_waves * a.n_splits,
-                               q0, a.scale, lane, a.k_new, a.v_new, a.new_row, area);
         }
-    }
-    if (parked) area_to_soft<G>(area, lane, st);
-    wave_sync();
+        // the buffered fp16 tokens in units of 16: unit u goes to split n_splits-1 - u % n_splits (the last split is the
+        // short one), there to the waves in turn, starting after the wave that took the split's last block
+        if (a.n_res > 0) {
+            // 0 for the wave whose turn the next block would be; paired: for the first wave behind the pairs
+            const int turn = kPaired ? wave - 2 * n_pairs : j - j1, takers = kPaired ? n_waves - 2 * n_pairs : n_waves;
+            const int first = a.n_splits - 1 - split + a.n_splits * turn;
+            if (turn >= 0 && first * kUnitTokens < a.n_res) {
+                if (!parked) soft_to_area<G>(st, area, lane);
+                parked = true;
+                buffered_tokens<G>(a.res, a.res_tokens, a.B, a.H, b, h, a.res_head, a.n_res, first, takers * a.n_splits,
+                                   q0, a.scale, lane, a.k_new, a.v_new, a.new_row, area);
+            }
+        }
+        if (parked) area_to_soft<G>(area, lane, st);
+        wave_sync();
 
-    // merge the waves of this workgroup into one partial (o[128], m, l) per query head
-    float *comb = reinterpret_cast<float *>(stage);  // this wave's own staging area: G * 130 floats
+        // merge the waves of this workgroup into one partial (o[128], m, l) per query head
+        float *comb = reinterpret_cast<float *>(stage);  // this wave's own staging area: G * 130 floats
 #pragma unroll
-    for (int gg = 0; gg < G; gg++) {
-        const float l = wave_sum(st.l[gg]);
-        const float bv = wave_sum(st.bv[gg]);
-        comb[gg * kPartialStride + 2 * lane] = st.acc[gg][0] + bv;
-        comb[gg * kPartialStride + 2 * lane + 1] = st.acc[gg][1] + bv;
-        if (lane == 0) {
-            comb[gg * kPartialStride + kD] = st.m[gg];
-            comb[gg * kPartialStride + kD + 1] = l;
+        for (int gg = 0; gg < G; gg++) {
+            const float l = wave_sum(st.l[gg]);
+            const float bv = wave_sum(st.bv[gg]);
+            comb[gg * kPartialStride + 2 * lane] = st.acc[gg][0] + bv;
+            comb[gg * kPartialStride + 2 * lane + 1] = st.acc[gg][1] + bv;
+            if (lane == 0) {
+                comb[gg * kPartialStride + kD] = st.m[gg];
+                comb[gg * kPartialStride + kD + 1] = l;
+            }
         }
     }
     __syncthreads();
@@ -1160,7 +1319,7 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     for (int i = tid_m; i < G * kD; i += nt_m) {
         const int gg = i / kD, c = i - gg * kD;
         float M_ = -INFINITY, L = 0.f, O = 0.f;
-        for (int w0 = 0; w0 < n_waves; w0 += 4) {  // the LDS reads of four waves' states at a time
+        for (int w0 = kPaired ? n_pairs : 0; w0 < n_waves; w0 += 4) {  // the LDS reads of four waves' states at a time
             float mw[4], lw[4], ow[4], mx = M_;
 #pragma unroll
             for (int k = 0; k < 4; k++) {
@@ -1194,38 +1353,38 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     if (a.n_splits > 1) finish_splits<G>(a.partials, a.counters + bh, row0, a.n_splits, a.out, tid_m, nt_m);
 }
 
-template <int G, int LB>
+template <int G, int LB, bool kPaired>
 static hipError_t launch_fused_gn(const FusedArgs &a, int n_waves, size_t lds, hipEvent_t ev0, hipEvent_t ev1,
                                   hipStream_t s) {
     static size_t attr_set = 0;
     if (lds > attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&fused_attn_kernel<G, LB>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&fused_attn_kernel<G, LB, kPaired>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set = lds;
     }
     if (n_waves < 1 || n_waves > MaxWaves<G, LB>::value) return hipErrorInvalidValue;
     if (ev0) (void)hipEventRecord(ev0, s);
-    hipLaunchKernelGGL((fused_attn_kernel<G, LB>), dim3(a.n_splits * a.n_bh), dim3(64 * n_waves), lds, s, a);
+    hipLaunchKernelGGL((fused_attn_kernel<G, LB, kPaired>), dim3(a.n_splits * a.n_bh), dim3(64 * n_waves), lds, s, a);
     if (ev1) (void)hipEventRecord(ev1, s);
     return hipGetLastError();
 }
 
-template <int G>
+template <int G, bool kPaired>
 static hipError_t launch_fused_g(const FusedArgs &a, int longest, int n_waves, size_t lds, hipEvent_t ev0, hipEvent_t ev1,
                                  hipStream_t s) {
     switch (fused_table_bits(longest)) {
-        case 6: return launch_fused_gn<G, 6>(a, n_waves, lds, ev0, ev1, s);
-        case 7: return launch_fused_gn<G, 7>(a, n_waves, lds, ev0, ev1, s);
-        case 8: return launch_fused_gn<G, 8>(a, n_waves, lds, ev0, ev1, s);
-        case 10: return launch_fused_gn<G, 10>(a, n_waves, lds, ev0, ev1, s);
-        default: return launch_fused_gn<G, 12>(a, n_waves, lds, ev0, ev1, s);
+        case 6: return launch_fused_gn<G, 6, kPaired>(a, n_waves, lds, ev0, ev1, s);
+        case 7: return launch_fused_gn<G, 7, kPaired>(a, n_waves, lds, ev0, ev1, s);
+        case 8: return launch_fused_gn<G, 8, kPaired>(a, n_waves, lds, ev0, ev1, s);
+        case 10: return launch_fused_gn<G, 10, kPaired>(a, n_waves, lds, ev0, ev1, s);
+        default: return launch_fused_gn<G, 12, kPaired>(a, n_waves, lds, ev0, ev1, s);
     }
 }
 
 hipError_t launch_fused_attn(const Geo &g, const uint16_t *q, float scale, float *out, int n_blocks, int res_head,
                              int n_res, const uint16_t *k_new, const uint16_t *v_new, int n_splits, int n_waves,
-                             int stage_bytes, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
+                             bool paired, int stage_bytes, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
     FusedArgs a;
     a.k_new = k_new;
     a.v_new = v_new;
@@ -1267,11 +1426,17 @@ hipError_t launch_fused_attn(const Geo &g, const uint16_t *q, float scale, float
         a.mask[1] = ((1u << bits_v) - 1u) << 1;
     }
     const size_t lds = (size_t)n_waves * ((size_t)stage_bytes + fused_weight_bytes(g.G));
+    if (paired && (2 * a.blocks_per_split + (n_res > 0) > n_waves || n_waves > 16)) return hipErrorInvalidValue;
+    auto launch = [&](auto gc) {
+        constexpr int G = decltype(gc)::value;
+        return paired ? launch_fused_g<G, true>(a, longest, n_waves, lds, ev0, ev1, s)
+                      : launch_fused_g<G, false>(a, longest, n_waves, lds, ev0, ev1, s);
+    };
     switch (g.G) {
-        case 1: return launch_fused_g<1>(a, longest, n_waves, lds, ev0, ev1, s);
-        case 2: return launch_fused_g<2>(a, longest, n_waves, lds, ev0, ev1, s);
-        case 4: return launch_fused_g<4>(a, longest, n_waves, lds, ev0, ev1, s);
-        case 8: return launch_fused_g<8>(a, longest, n_waves, lds, ev0, ev1, s);
+        case 1: return launch(std::integral_constant<int, 1>());
+        case 2: return launch(std::integral_constant<int, 2>());
+        case 4: return launch(std::integral_constant<int, 4>());
+        case 8: return launch(std::integral_constant<int, 8>());
         default: return hipErrorInvalidValue;
     }
 }

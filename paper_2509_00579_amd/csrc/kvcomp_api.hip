@@ -452,7 +452,15 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     // slots empty rather than CUs); the kernel gives the units to the waves without a block first
     const int bps = ctx->n_blocks > 0 ? (ctx->n_blocks + n_splits - 1) / n_splits : 0;
     const int units = (ctx->n_res + 15) / 16, units_per_split = (units + n_splits - 1) / n_splits;
-    const int n_waves = std::max(1, std::min(max_waves, bps + units_per_split));
+    // A wave for each record of a pair where the wave slots would be empty.  It is the shorter chain against the SIMDs'
+    // sharing, so it ends at three waves per SIMD: 32 heads in 8 splits of n pairs, one query head per KV head, code words
+    // of up to 6 bits, n = 1 2 4 6 7 8: 8.9 8.8 9.7 11.3 12.4 13.0 us against 12.4 11.1 11.0 12.6 12.7 13.2; groups of 4,
+    // n = 2 4 6: 12.2 11.5 13.4 against 17.1 14.3 16.4; groups of 8: 16.6 14.7 16.7 against 24.5 19.4 20.5.  Groups of 1 and
+    // 2 with longer code words keep two waves per SIMD (their 128 registers do not hold a whole decoded block beside the
+    // lookups in flight): n = 4 6 8: 12.1 15.3 20.0 against 12.9 14.9 15.7.
+    const int paired_waves = std::min(max_waves, fused_table_bits(longest) == 6 || g.G >= 4 ? 12 : 8);
+    const bool paired = bps > 0 && 2 * bps + units_per_split <= paired_waves;
+    const int n_waves = std::max(1, std::min(max_waves, (paired ? 2 : 1) * bps + units_per_split));
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (ctx->profiling) {
         if (ctx->events_used + 2 > ctx->events.size()) {
@@ -472,7 +480,7 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
         ctx->events_used += 2;
     }
     HIP_TRY(launch_fused_attn(g, static_cast<const uint16_t *>(d_q), scale, d_out, ctx->n_blocks, ctx->res_head, ctx->n_res,
-                              k_new, v_new, n_splits, n_waves, stage, ev0, ev1, s));
+                              k_new, v_new, n_splits, n_waves, paired, stage, ev0, ev1, s));
     return KVCOMP_OK;
 }
 

@@ -133,7 +133,7 @@ hipError_t launch_append(const Geo &g, const uint16_t *k_new, const uint16_t *v_
 // reads it from there and stores it into its buffer slot (append fused into the launch)
 hipError_t launch_fused_attn(const Geo &g, const uint16_t *q, float scale, float *out, int n_blocks, int res_head,
                              int n_res, const uint16_t *k_new, const uint16_t *v_new, int n_splits, int n_waves,
-                             int stage_bytes, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);
+                             bool paired, int stage_bytes, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);
 hipError_t launch_baseline_attn(int B, int H, int Hq, const uint16_t *K, const uint16_t *V, int seq, const uint16_t *q,
                                 float scale, float *out, float *partials, uint32_t *counters, int n_splits,
                                 int split_stride, hipStream_t s);

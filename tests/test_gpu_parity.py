@@ -409,6 +409,23 @@ def test_buffered_tokens_at_unit_edges(gpu, oracle, G, n0):
     gc.close()
 
 
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("limit", [6, 12])
+def test_a_wave_for_each_record_of_a_pair(gpu, oracle, G, limit):
+    _say(f"K and V records of a pair on two waves, and on one; groups of {G}, code words of up to {limit} bits")
+    B, H = 1, 2
+    for S in (64, 64 * 4 + 63, 64 * 6 + 1, 64 * 9 + 40):  # 1, 4, 6 and 9 blocks: around every edge of the rule
+        _, _, oc, gc = _both(gpu, oracle, B, H, G * H, 64, S, S, 1e-2, 1e-2, 61, limit)
+        q = W.make_queries(B, G * H, 1, 61)[0]
+        ref = oc.attn_decode(q, SCALE)
+        for n_splits in (1, 2, 3, oc.n_blocks):  # last splits with fewer blocks among them
+            # waves: the library's choice; too few for the pairs; stage_bytes: as needed, and records from global memory
+            for waves, stage in ((0, 0), (1, 0), (3, 0), (0, 4608), (1, 4608)):
+                gc.set_tuning(n_splits=n_splits, waves=waves, stage_bytes=stage)
+                _attn_close(gc.attn_decode(_dev(q), SCALE).cpu().numpy(), ref)
+        gc.close()
+
+
 @pytest.mark.parametrize("G", [1, 2])
 @pytest.mark.parametrize("rel,limit", [(2e-3, 8), (2e-3, 12), (3.9e-3, 8), (3.95e-3, 7), (1e-2, 6), (0.25, 2)])
 def test_integer_dot_products_of_groups_of_1_and_2(gpu, oracle, G, rel, limit):
