@@ -27,7 +27,7 @@ constexpr int kBWaves = 4;
 // The waves of a workgroup have left (o[128], m, l) per query head in comb: merge them into the workgroup's partial
 // and, in the last workgroup of the (batch, kv head), the splits into the output.
 template <int G>
-__device__ __forceinline__ void merge_waves_and_splits(const float (&comb)[kBWaves][G][kPartialStride],
+__device__ __forceinline__ void merge_waves_and_splits(float (&comb)[kBWaves][G][kPartialStride],
                                                        float *__restrict__ partials, uint32_t *__restrict__ counters,
                                                        float *__restrict__ out, int b, int h, int Hq, int split, int bh,
                                                        int tid, int split_stride) {
@@ -51,7 +51,8 @@ __device__ __forceinline__ void merge_waves_and_splits(const float (&comb)[kBWav
         }
     }
     if (gridDim.x > 1)
-        finish_splits<G>(partials, counters + bh, b * Hq + h * G, (int)gridDim.x, out, tid, 64 * kBWaves, split_stride);
+        finish_splits<G>(partials, counters + bh, b * Hq + h * G, (int)gridDim.x, out, tid, 64 * kBWaves, &comb[0][0][0],
+                         split_stride);
 }
 
 

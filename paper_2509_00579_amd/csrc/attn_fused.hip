@@ -1350,7 +1350,8 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             if (c == 0) { store_agent(dst + kD, M_); store_agent(dst + kD + 1, L); }
         }
     }
-    if (a.n_splits > 1) finish_splits<G>(a.partials, a.counters + bh, row0, a.n_splits, a.out, tid_m, nt_m);
+    if (a.n_splits > 1) finish_splits<G>(a.partials, a.counters + bh, row0, a.n_splits, a.out, tid_m, nt_m,
+                                           reinterpret_cast<float *>(smem));
 }
 
 template <int G, int LB, bool kPaired>

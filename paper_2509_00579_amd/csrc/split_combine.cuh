@@ -10,6 +10,7 @@
 // stores to complete before the workgroup takes its ticket.
 #pragma once
 
+#include "huff_decode.cuh"
 #include "kvcomp_internal.h"
 
 namespace kvc {
@@ -22,10 +23,22 @@ __device__ __forceinline__ float load_agent(const float *p) {
 }
 
 // Called by all threads of the workgroup after they have written this workgroup's partials with store_agent() to
-// partials[(row0 + g) * split_stride + split].  nt = threads per workgroup.
+// partials[(row0 + g) * split_stride + split].  nt = threads per workgroup (whole waves); scratch: kPartialStride floats of
+// LDS per wave, free behind the caller's last barrier.
+//
+// The merge is the tail of the launch: one workgroup, bound by the latency of loads that pass the L2.  A wave merges one
+// head over a range of splits, with as many ranges as there are waves to a head: lane s holds {m, l} of the range's split
+// s (two splits when the range is that long), so the weight of every split is known after one reduction, and the two
+// accumulator words per lane and split are requested 16 splits at a time before anything is waited for.  Before, a
+// thread ran over all splits of one channel with a running maximum, three loads a split, and half or more of the threads
+// of a small workgroup ran over several channels one after the other.
+// Few heads over a long cache have the most splits.  us a step, before -> now: 1 head x 32768 tokens (128 splits) groups
+// of 1 18.0 -> 10.7, of 8 34.4 -> 22.8; 8 heads x 16384 (32) 16.0 -> 15.0 and 24.1 -> 21.5; 8 heads x 2048 (8) 8.6 -> 8.5
+// and 13.5 -> 12.1; fp16 kernel, groups of 8, 2 heads x 16384 (64) 30.9 -> 20.3, 8 x 8 heads x 16384 (4) 105.4 -> 103.3.
 template <int G>
 __device__ __forceinline__ void finish_splits(float *partials, uint32_t *counter, int row0, int n_splits, float *out,
-                                              int tid, int nt, int split_stride = kMaxSplits) {
+                                              int tid, int nt, float *scratch, int split_stride = kMaxSplits) {
+    static_assert(kMaxSplits <= 128, "a lane holds the state of two splits");
     __shared__ uint32_t s_last;
     // every wave: all of its (write-through) partial stores have completed before the barrier is passed
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -37,34 +50,79 @@ __device__ __forceinline__ void finish_splits(float *partials, uint32_t *counter
     }
     __syncthreads();
     if (!s_last) return;
-    // One pass over the splits with a running maximum; the loads of a batch of splits are issued together so that
-    // the merge costs a few memory round trips, not one per split.
-    constexpr int kBatch = 16;
-    for (int i = tid; i < G * kD; i += nt) {
-        const int g = i / kD, c = i - g * kD;
-        const float *p = partials + (size_t)(row0 + g) * split_stride * kPartialStride;
-        float M = -INFINITY, L = 0.f, O = 0.f;
-        for (int s0 = 0; s0 < n_splits; s0 += kBatch) {
-            float ms[kBatch], ls[kBatch], os[kBatch];
+    constexpr int kBatch = 16;  // ranges shorter than this only add their own merge
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = nt >> 6;
+    const int ranges = min(max(n_waves / G, 1), (n_splits + kBatch - 1) / kBatch);
+    const int per = (n_splits + ranges - 1) / ranges;
+    for (int item = wave; item < G * ranges; item += n_waves) {  // one round, unless there are fewer waves than heads
+        const int r = item / G, g = item - r * G, s0 = r * per, n = min(per, n_splits - s0);  // n < 1: an empty range
+        const float *p = partials + ((size_t)(row0 + g) * split_stride + s0) * kPartialStride;
+        float m0 = -INFINITY, m1 = -INFINITY, l0 = 0.f, l1 = 0.f;
+        if (lane < n) {
+            m0 = load_agent(p + lane * kPartialStride + kD);
+            l0 = load_agent(p + lane * kPartialStride + kD + 1);
+        }
+        if (lane + 64 < n) {
+            m1 = load_agent(p + (lane + 64) * kPartialStride + kD);
+            l1 = load_agent(p + (lane + 64) * kPartialStride + kD + 1);
+        }
+        float o[kBatch][2];
+        auto request = [&](int s) {
 #pragma unroll
             for (int k = 0; k < kBatch; k++) {
-                const int s = min(s0 + k, n_splits - 1);  // clamped: every load is in bounds
-                ms[k] = load_agent(p + s * kPartialStride + kD);
-                ls[k] = load_agent(p + s * kPartialStride + kD + 1);
-                os[k] = load_agent(p + s * kPartialStride + c);
-            }
-#pragma unroll
-            for (int k = 0; k < kBatch; k++) {
-                if (s0 + k < n_splits && ms[k] != -INFINITY) {
-                    const float Mn = fmaxf(M, ms[k]);
-                    const float fa = __expf(M - Mn), fb = __expf(ms[k] - Mn);
-                    L = L * fa + ls[k] * fb;
-                    O = O * fa + os[k] * fb;
-                    M = Mn;
+                o[k][0] = o[k][1] = 0.f;
+                if (s + k < n) {
+                    o[k][0] = load_agent(p + (s + k) * kPartialStride + lane);
+                    o[k][1] = load_agent(p + (s + k) * kPartialStride + lane + 64);
                 }
             }
+        };
+        request(0);
+        float mx = fmaxf(m0, m1);
+        mx = wave_max(mx);
+        // a split that had nothing to do (m = -inf) takes no part, whatever its words are
+        const unsigned long long live0 = __builtin_amdgcn_ballot_w64(m0 != -INFINITY),
+                                 live1 = __builtin_amdgcn_ballot_w64(m1 != -INFINITY);
+        const float f0 = m0 == -INFINITY ? 0.f : __expf(m0 - mx), f1 = m1 == -INFINITY ? 0.f : __expf(m1 - mx);
+        const float L = wave_sum(l0 * f0 + l1 * f1);
+        float O0 = 0.f, O1 = 0.f;
+        for (int s = 0; s < n; s += kBatch) {
+            if (s) request(s);
+#pragma unroll
+            for (int k = 0; k < kBatch; k++) {
+                const int at = (s + k) & 63;
+                const float w0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f0), at));
+                const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f1), at));
+                const float w = s + k < 64 ? w0 : w1;
+                const bool live = ((s + k < 64 ? live0 : live1) >> at) & 1;
+                O0 = fmaf(w, live ? o[k][0] : 0.f, O0);
+                O1 = fmaf(w, live ? o[k][1] : 0.f, O1);
+            }
         }
-        out[(size_t)(row0 + g) * kD + c] = O / L;
+        if (ranges == 1) {
+            out[(size_t)(row0 + g) * kD + lane] = O0 / L;
+            out[(size_t)(row0 + g) * kD + lane + 64] = O1 / L;
+        } else {
+            float *c = scratch + item * kPartialStride;  // item = wave here
+            c[lane] = O0;
+            c[lane + 64] = O1;
+            if (lane == 0) { c[kD] = mx; c[kD + 1] = L; }
+        }
+    }
+    if (ranges > 1) {
+        __syncthreads();
+        for (int i = tid; i < G * kD; i += nt) {
+            const int g = i / kD, c = i - g * kD;
+            float mx = -INFINITY, L = 0.f, O = 0.f;
+            for (int r = 0; r < ranges; r++) mx = fmaxf(mx, scratch[(r * G + g) * kPartialStride + kD]);
+            for (int r = 0; r < ranges; r++) {
+                const float *cr = scratch + (r * G + g) * kPartialStride;
+                const float f = cr[kD] == -INFINITY ? 0.f : __expf(cr[kD] - mx);
+                L = fmaf(cr[kD + 1], f, L);
+                O = fmaf(cr[c], f, O);
+            }
+            out[(size_t)(row0 + g) * kD + c] = O / L;
+        }
     }
     if (tid == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

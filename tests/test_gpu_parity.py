@@ -464,6 +464,23 @@ def test_many_sequence_splits(gpu, oracle):
     gc.close()
 
 
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_split_merge_at_range_edges(gpu, oracle, G):
+    _say(f"splits merged in one and in several ranges; groups of {G}")
+    B, H, S = 1, 1, 64 * 130
+    _, _, oc, gc = _both(gpu, oracle, B, H, G * H, 256, S, S, 1e-2, 1e-2, 62, 6)
+    q = W.make_queries(B, G * H, 1, 62)[0]
+    ref = np.asarray(oc.attn_decode(q, SCALE), np.float64)
+    # waves of a workgroup to a head, batches of 16 splits, the second split of a lane (beyond 64).  A split left out or
+    # with another's weight is off by 1e-2 and more; the integer weights of groups of 4 and 8 by up to 2e-4.
+    for n_splits in (2, 15, 16, 17, 33, 64, 65, 128):
+        for waves in (0, 1, 5):
+            gc.set_tuning(n_splits=n_splits, waves=waves)
+            out = gc.attn_decode(_dev(q), SCALE).cpu().numpy().astype(np.float64)
+            assert np.linalg.norm(out - ref) <= 2e-4 * np.linalg.norm(ref), (n_splits, waves)
+    gc.close()
+
+
 def _random_cases(n):
     rng = np.random.default_rng(2024)
     cases = []
