@@ -7,13 +7,16 @@
 //   1. size pass   : sum the code lengths of the block -> record size into the Block Offsets Array
 //   2. place       : the sizes are scanned in (tensor, batch, head, block) order starting at the arena tail
 //   3. write pass  : encode, write the record at its offset
+// Up to a few thousand records steps 1 and 2 are one launch (place_if_last).
 // Blocks that the fp16 buffer sheds during decoding are quantized by both passes from the buffer (the store side runs
 // once per token block while the fetch side runs every decode step, Section 3.3: the second read of 64 tokens is the
 // cheaper trade against a staging copy of the records).  A prompt goes through the histogram pass first, which keeps
 // the codes, the unit min/max and a histogram per block: its sizes come from the block histograms and its write pass
 // reads the kept codes.
 #include <algorithm>
+#include <type_traits>
 
+#include "huff_decode.cuh"
 #include "tile_quant.cuh"
 
 namespace kvc {
@@ -57,13 +60,18 @@ struct Kept {
     int blk_per_bh;
 };
 // ---- 1. size pass ------------------------------------------------------------------------------------------
+struct SizeShared {
+    QuantShared quant;
+    uint32_t enc[256];
+    uint32_t scratch[4];
+};
 template <int WHICH>
-__global__ __launch_bounds__(256) void size_kernel(Geo g, const uint16_t *__restrict__ X, int seq_stride,
-                                                    int n_blk_per_bh, int dst_blk0) {
-    __shared__ QuantShared sh;
-    __shared__ uint32_t enc[256];
-    __shared__ uint32_t scratch[4];
-    const int tid = threadIdx.x, blk = blockIdx.x;
+__device__ __forceinline__ void size_block(const Geo &g, const uint16_t *__restrict__ X, int seq_stride, int n_blk_per_bh,
+                                           int dst_blk0, int blk, SizeShared &shared) {
+    QuantShared &sh = shared.quant;
+    uint32_t (&enc)[256] = shared.enc;
+    uint32_t (&scratch)[4] = shared.scratch;
+    const int tid = threadIdx.x;
     const int bh = blk / n_blk_per_bh, j = blk - bh * n_blk_per_bh;
     enc[tid] = enc_of(g, WHICH)[tid];
     TileRegs r;
@@ -77,14 +85,21 @@ __global__ __launch_bounds__(256) void size_kernel(Geo g, const uint16_t *__rest
     const uint32_t total = block_sum(bits, scratch, tid);
     if (tid == 0) {
         const uint32_t s16 = record_size16(Rec<WHICH>::hdr_bytes(g), total);
-        g.table[((size_t)WHICH * g.B * g.H + bh) * g.max_blocks + dst_blk0 + j].size16 = s16;
+        __hip_atomic_store(&g.table[((size_t)WHICH * g.B * g.H + bh) * g.max_blocks + dst_blk0 + j].size16, s16, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);  // size_place_both_kernel reads it in another workgroup
     }
     if (bad) atomicOr(&g.ctrl->nonfinite, 1u);
+}
+template <int WHICH>
+__global__ __launch_bounds__(256) void size_kernel(Geo g, const uint16_t *__restrict__ X, int seq_stride,
+                                                    int n_blk_per_bh, int dst_blk0) {
+    __shared__ SizeShared sh;
+    size_block<WHICH>(g, X, seq_stride, n_blk_per_bh, dst_blk0, blockIdx.x, sh);
 }
 
 // The size pass from the block histograms that the histogram pass kept ([block][256] u16, blocks numbered
 // bh * kept_blk_per_bh + j): a record's payload is sum over the symbols of count x code length.  One wave per block,
-// lane l takes symbols 4l .. 4l+3.
+// lane l takes symbols 4l .. 4l+3.  For more blocks than size_place_kernel places (below).
 constexpr int kSizeBlocksPerWave = 4;
 template <int WHICH>
 __global__ __launch_bounds__(256) void size_from_hist_kernel(Geo g, const uint16_t *__restrict__ block_hist,
@@ -246,17 +261,148 @@ static void launch_place(const Geo &g, int n_blk_per_bh, int dst_blk0, int tenso
     hipLaunchKernelGGL(place_scan_kernel, dim3(chunks), dim3(kPlaceThreads), 0, s, g, n_blk_per_bh, dst_blk0, tensors);
 }
 
+// Size pass and placement in one launch: the workgroup that finishes last (a ticket; the sizes cross the XCDs as in
+// split_combine.cuh) scans all sizes and writes the offsets.  kPlaceRegs items per thread of that workgroup, item
+// c * THREADS + tid in register c, so that loads and stores of the table are coalesced as they are: a scan per wave and
+// register, then one of the wave totals.  A launch and the gap to it cost a short prompt or a flush more than these passes
+// take: 2 x 8 heads x 1000 tokens compressed and read back 128 -> 117 us, 96 tokens appended behind 2000 (three encodings of
+// six launches before, two now) 1120 -> 1093 us, 32 heads x 32768 within its noise.  Up to THREADS * kPlaceRegs records;
+// beyond, one workgroup would have to scan in several rounds, and the launches no longer show.
+constexpr int kPlaceRegs = 16;
+template <int THREADS>
+struct PlaceShared {
+    __attribute__((aligned(16))) uint32_t tot[kPlaceRegs * THREADS / 64];
+    uint32_t last, need;
+};
+// rows: the first row of Block Offsets Array entries; by_blk divides by n_blk_per_bh
+template <int THREADS>
+__device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, int n_items, int n_blk_per_bh, int dst_blk0,
+                                              const FastDiv &by_blk, PlaceShared<THREADS> &sh) {
+    constexpr int kWaves = THREADS / 64, kPerLane = kPlaceRegs * kWaves / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's sizes have arrived
+    __syncthreads();
+    if (tid == 0)
+        sh.last = __hip_atomic_fetch_add(&g.ctrl->place_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (!sh.last) return;
+    const uint32_t tail0 = g.ctrl->tail16;
+    auto entry = [&](int i) {
+        const int row = (int)by_blk((uint32_t)i);
+        return rows + (size_t)row * g.max_blocks + dst_blk0 + (i - row * n_blk_per_bh);
+    };
+    uint32_t size[kPlaceRegs], at[kPlaceRegs], biggest = 0;
+#pragma unroll
+    for (int k = 0; k < kPlaceRegs; k++) {
+        const int i = k * THREADS + tid;
+        size[k] = i < n_items ? __hip_atomic_load(&entry(i)->size16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kPlaceRegs; k++) {
+        at[k] = wave_excl_scan(size[k], lane);
+        if (lane == 63) sh.tot[k * kWaves + wave] = at[k] + size[k];
+        biggest = max(biggest, size[k]);
+    }
+    __syncthreads();
+    static_assert(kPerLane * 64 == kPlaceRegs * kWaves, "whole totals per lane");
+    if (wave == 0) {  // at most 2^14 records of at most 13 KiB: the sums stay far below 2^32 units
+        uint32_t t[kPerLane], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kPerLane; k++) {
+            t[k] = sh.tot[kPerLane * lane + k];
+            sum += t[k];
+        }
+        uint32_t before = wave_excl_scan(sum, lane);
+        if (lane == 63) sh.need = before + sum;
+#pragma unroll
+        for (int k = 0; k < kPerLane; k++) {
+            sh.tot[kPerLane * lane + k] = before;
+            before += t[k];
+        }
+    }
+    __syncthreads();
+    // a placement that would run past the arena: as in place_scan_kernel
+    const bool fits = (unsigned long long)tail0 + sh.need <= (unsigned long long)g.payload_cap16;
+#pragma unroll
+    for (int k = 0; k < kPlaceRegs; k++) {
+        const int i = k * THREADS + tid;
+        if (i < n_items) *entry(i) = {fits ? tail0 + sh.tot[k * kWaves + wave] + at[k] : 0u, size[k]};
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) biggest = max(biggest, (uint32_t)__shfl_xor(biggest, m));
+    if (fits && lane == 0 && biggest) atomicMax(&g.ctrl->max_size16, biggest);
+    if (tid == 0) {
+        if (fits) g.ctrl->tail16 = tail0 + sh.need;
+        else atomicOr(&g.ctrl->fault, kFaultArenaFull);
+        g.ctrl->place_ticket = 0;
+    }
+}
+
+// one tensor's sizes from the kept block histograms, and their placement
+constexpr int kSizePlaceThreads = 1024, kSizePlaceItems = kSizePlaceThreads * kPlaceRegs;
+template <int WHICH>
+__global__ __launch_bounds__(kSizePlaceThreads) void size_place_kernel(Geo g, const uint16_t *__restrict__ block_hist,
+                                                                       int kept_blk_per_bh, int n_blk_per_bh, FastDiv by_blk) {
+    constexpr int kWaves = kSizePlaceThreads / 64;
+    __shared__ PlaceShared<kSizePlaceThreads> sh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_items = g.B * g.H * n_blk_per_bh;
+    BlockEntry *table = g.table + (size_t)WHICH * g.B * g.H * g.max_blocks;
+    uint2 c[kSizeBlocksPerWave];
+    BlockEntry *e[kSizeBlocksPerWave];
+    const int item0 = (blockIdx.x * kWaves + wave) * kSizeBlocksPerWave;
+#pragma unroll
+    for (int k = 0; k < kSizeBlocksPerWave; k++) {
+        const int item = min(item0 + k, n_items - 1), bh = (int)by_blk((uint32_t)item), j = item - bh * n_blk_per_bh;
+        c[k] = *reinterpret_cast<const uint2 *>(block_hist + ((size_t)bh * kept_blk_per_bh + j) * 256 + 4 * lane);
+        e[k] = table + (size_t)bh * g.max_blocks + j;
+    }
+    uint32_t len[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) len[k] = enc_of(g, WHICH)[4 * lane + k] >> 16;
+#pragma unroll
+    for (int k = 0; k < kSizeBlocksPerWave; k++) {
+        uint32_t bits = (c[k].x & 0xffffu) * len[0] + (c[k].x >> 16) * len[1] + (c[k].y & 0xffffu) * len[2] + (c[k].y >> 16) * len[3];
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) bits += __shfl_xor(bits, m);
+        if (lane == 0 && item0 + k < n_items)
+            __hip_atomic_store(&e[k]->size16, record_size16(Rec<WHICH>::hdr_bytes(g), bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    place_if_last<kSizePlaceThreads>(g, table, n_items, n_blk_per_bh, 0, by_blk, sh);
+}
+
+// both tensors' sizes from the fp16 input, and their placement: K's workgroups, then V's
+constexpr int kSizePlaceBothItems = 256 * kPlaceRegs;
+__global__ __launch_bounds__(256) void size_place_both_kernel(Geo g, const uint16_t *__restrict__ XK,
+                                                              const uint16_t *__restrict__ XV, int seq_stride, int n_blk_per_bh,
+                                                              int dst_blk0, FastDiv by_blk) {
+    __shared__ SizeShared sh;
+    __shared__ PlaceShared<256> place;
+    const int total = g.B * g.H * n_blk_per_bh, blk = blockIdx.x;
+    if (blk < total) size_block<0>(g, XK, seq_stride, n_blk_per_bh, dst_blk0, blk, sh);
+    else size_block<1>(g, XV, seq_stride, n_blk_per_bh, dst_blk0, blk - total, sh);
+    place_if_last<256>(g, g.table, 2 * total, n_blk_per_bh, dst_blk0, by_blk, place);
+}
+
 // ---- 3. write pass -----------------------------------------------------------------------------------------
+template <bool KEPT>
+struct WriteShared {
+    __attribute__((aligned(16))) uint8_t code_tile[kCodeTileBytes];
+    __attribute__((aligned(16))) uint32_t rec[(kMaxRecordBytes + 15) / 16 * 4];
+    uint32_t enc[512];  // [0..256) first-bit-first, [256..512) last-bit-first
+    uint32_t wave_tot[4];
+    std::conditional_t<KEPT, int, QuantShared> quant;
+};
 template <int WHICH, bool KEPT>
-__global__ __launch_bounds__(256) void write_kernel(Geo g, const uint16_t *__restrict__ X, int seq_stride,
-                                                     int n_blk_per_bh, int dst_blk0, Kept kept) {
+__device__ __forceinline__ void write_block(const Geo &g, const uint16_t *__restrict__ X, int seq_stride, int n_blk_per_bh,
+                                            int dst_blk0, const Kept &kept, int blk, WriteShared<KEPT> &shared) {
     using R = Rec<WHICH>;
-    __shared__ QuantShared sh;
-    __shared__ uint32_t enc[512];  // [0..256) first-bit-first, [256..512) last-bit-first
-    __shared__ uint32_t wave_tot[4];
-    __shared__ __attribute__((aligned(16))) uint8_t code_tile[kCodeTileBytes];
-    __shared__ __attribute__((aligned(16))) uint32_t rec[(kMaxRecordBytes + 15) / 16 * 4];
-    const int tid = threadIdx.x, blk = blockIdx.x;
+    auto &enc = shared.enc;
+    auto &wave_tot = shared.wave_tot;
+    auto &code_tile = shared.code_tile;
+    auto &rec = shared.rec;
+    const int tid = threadIdx.x;
     const int bh = blk / n_blk_per_bh, j = blk - bh * n_blk_per_bh;
     if (g.ctrl->fault & kFaultArenaFull) return;  // the placement found no room (uniform over the workgroup)
     enc[tid] = enc_of(g, WHICH)[tid];
@@ -280,7 +426,7 @@ __global__ __launch_bounds__(256) void write_kernel(Geo g, const uint16_t *__res
     } else {
         TileRegs r;
         load_tile(X, seq_stride, g.H, bh / g.H, bh % g.H, j, tid, r);
-        quantize_tile<WHICH>(r, sh, tid, g.two_eb[WHICH], g.n_sym[WHICH], g.k_units);
+        quantize_tile<WHICH>(r, shared.quant, tid, g.two_eb[WHICH], g.n_sym[WHICH], g.k_units);
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const int t = tile_token(tid, i);
@@ -291,7 +437,7 @@ __global__ __launch_bounds__(256) void write_kernel(Geo g, const uint16_t *__res
     }
     if (tid < R::n_units(g)) {
         if constexpr (KEPT) rec[tid] = kept.minmax[((size_t)bh * kept.blk_per_bh + j) * R::n_units(g) + tid];
-        else rec[tid] = float_to_half_bits(sh.unit_mn[tid]) | (float_to_half_bits(sh.unit_mx[tid]) << 16);
+        else rec[tid] = float_to_half_bits(shared.quant.unit_mn[tid]) | (float_to_half_bits(shared.quant.unit_mx[tid]) << 16);
     }
     __syncthreads();
     // Each thread encodes 32 symbols, half of one slice (Section 3.2.2 stage 2).  K: slice s = token s/2, channels
@@ -375,10 +521,34 @@ __global__ __launch_bounds__(256) void write_kernel(Geo g, const uint16_t *__res
     for (uint32_t i = tid; i < n16 && i < e.size16; i += 256) dst[i] = src[i];
 }
 
+template <int WHICH, bool KEPT>
+__global__ __launch_bounds__(256) void write_kernel(Geo g, const uint16_t *__restrict__ X, int seq_stride,
+                                                     int n_blk_per_bh, int dst_blk0, Kept kept) {
+    __shared__ WriteShared<KEPT> sh;
+    write_block<WHICH, KEPT>(g, X, seq_stride, n_blk_per_bh, dst_blk0, kept, blockIdx.x, sh);
+}
+// both tensors from the fp16 input: K's workgroups, then V's
+__global__ __launch_bounds__(256) void write_both_kernel(Geo g, const uint16_t *__restrict__ XK,
+                                                         const uint16_t *__restrict__ XV, int seq_stride, int n_blk_per_bh,
+                                                         int dst_blk0) {
+    __shared__ WriteShared<false> sh;
+    const int total = g.B * g.H * n_blk_per_bh, blk = blockIdx.x;
+    const Kept none = {nullptr, nullptr, 0};
+    if (blk < total) write_block<0, false>(g, XK, seq_stride, n_blk_per_bh, dst_blk0, none, blk, sh);
+    else write_block<1, false>(g, XV, seq_stride, n_blk_per_bh, dst_blk0, none, blk - total, sh);
+}
+
 hipError_t launch_encode(const Geo &g, const uint16_t *XK, const uint16_t *XV, int seq_stride, int n_blk_per_bh,
                          int dst_blk0, hipStream_t s) {
     const int total = g.B * g.H * n_blk_per_bh;
     if (total <= 0) return hipSuccess;
+    if (2 * total <= kSizePlaceBothItems) {  // flushes and short prompts: two launches
+        FastDiv by_blk;
+        by_blk.set((uint32_t)n_blk_per_bh);
+        hipLaunchKernelGGL(size_place_both_kernel, dim3(2 * total), dim3(256), 0, s, g, XK, XV, seq_stride, n_blk_per_bh, dst_blk0, by_blk);
+        hipLaunchKernelGGL(write_both_kernel, dim3(2 * total), dim3(256), 0, s, g, XK, XV, seq_stride, n_blk_per_bh, dst_blk0);
+        return hipGetLastError();
+    }
     const Kept none = {nullptr, nullptr, 0};
     hipLaunchKernelGGL(size_kernel<0>, dim3(total), dim3(256), 0, s, g, XK, seq_stride, n_blk_per_bh, dst_blk0);
     hipLaunchKernelGGL(size_kernel<1>, dim3(total), dim3(256), 0, s, g, XV, seq_stride, n_blk_per_bh, dst_blk0);
@@ -396,17 +566,24 @@ hipError_t launch_encode_kept(const Geo &g, int which, const uint8_t *codes, con
                               int kept_blk_per_bh, int n_blk_per_bh, hipStream_t s) {
     const int total = g.B * g.H * n_blk_per_bh;
     if (total <= 0) return hipSuccess;
-    const int grid = std::min((total + 4 * kSizeBlocksPerWave - 1) / (4 * kSizeBlocksPerWave), 2048);
     const Kept k = {codes, mm, kept_blk_per_bh};
-    if (which == 0) {
-        hipLaunchKernelGGL(size_from_hist_kernel<0>, dim3(grid), dim3(256), 0, s, g, block_hist, kept_blk_per_bh, n_blk_per_bh);
-        launch_place(g, n_blk_per_bh, 0, 0, s);
-        hipLaunchKernelGGL((write_kernel<0, true>), dim3(total), dim3(256), 0, s, g, nullptr, 0, n_blk_per_bh, 0, k);
-    } else {
-        hipLaunchKernelGGL(size_from_hist_kernel<1>, dim3(grid), dim3(256), 0, s, g, block_hist, kept_blk_per_bh, n_blk_per_bh);
-        launch_place(g, n_blk_per_bh, 0, 1, s);
-        hipLaunchKernelGGL((write_kernel<1, true>), dim3(total), dim3(256), 0, s, g, nullptr, 0, n_blk_per_bh, 0, k);
-    }
+    auto run = [&](auto wc) {
+        constexpr int WHICH = decltype(wc)::value;
+        if (total <= kSizePlaceItems) {
+            FastDiv by_blk;
+            by_blk.set((uint32_t)n_blk_per_bh);
+            const int per_wg = kSizePlaceThreads / 64 * kSizeBlocksPerWave;
+            hipLaunchKernelGGL(size_place_kernel<WHICH>, dim3((total + per_wg - 1) / per_wg), dim3(kSizePlaceThreads), 0, s, g,
+                               block_hist, kept_blk_per_bh, n_blk_per_bh, by_blk);
+        } else {
+            const int grid = std::min((total + 4 * kSizeBlocksPerWave - 1) / (4 * kSizeBlocksPerWave), 2048);
+            hipLaunchKernelGGL(size_from_hist_kernel<WHICH>, dim3(grid), dim3(256), 0, s, g, block_hist, kept_blk_per_bh, n_blk_per_bh);
+            launch_place(g, n_blk_per_bh, 0, WHICH, s);
+        }
+        hipLaunchKernelGGL((write_kernel<WHICH, true>), dim3(total), dim3(256), 0, s, g, nullptr, 0, n_blk_per_bh, 0, k);
+    };
+    if (which == 0) run(std::integral_constant<int, 0>());
+    else run(std::integral_constant<int, 1>());
     return hipGetLastError();
 }
 

@@ -15,6 +15,7 @@ struct Ctrl {
     uint32_t nonfinite;     // set when an input value was Inf/NaN
     uint32_t fault;         // kFault* bits set by kernels that refused work; read and cleared at the synchronising calls
     uint32_t tail_base;     // the arena tail that the running placement starts from (tail16 moves at its end)
+    uint32_t place_ticket;  // workgroups of a size_place_kernel that have finished, zero between launches
     // filled by the statistics kernel only (kvcomp_get_stats)
     unsigned long long payload_bits[2];
     unsigned long long record16[2];  // sum of record sizes per tensor, 16-byte units

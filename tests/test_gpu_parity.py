@@ -209,6 +209,32 @@ def test_prefill_is_reproducible(gpu, B, H, S):
     gc.close()
 
 
+# up to 4096 records of both tensors / 16384 of one are placed by the size pass's last workgroup, more by launches of their own
+@pytest.mark.parametrize("B,H,n_blk", [(1, 1, 1), (3, 5, 7), (2, 16, 64), (2, 16, 65), (4, 32, 128), (4, 32, 129)])
+def test_placement_by_the_last_workgroup_and_by_launches(gpu, B, H, n_blk):
+    import torch
+    _say(f"placement of {B} x {H} x {n_blk} records a tensor")
+    S = 64 * n_blk
+    gen = torch.Generator(device="cuda:0").manual_seed(n_blk)
+    k, v = (torch.randn((B, S, H, 128), generator=gen, device="cuda:0").half() for _ in range(2))
+    gc = gpu.KVCompCache(B, H, H, S, 1e-2, 1e-2, max_code_len=6)
+    gc.prefill(k, v, torch.empty(gc.prefill_workspace_bytes(S), dtype=torch.uint8, device="cuda:0"))
+
+    def entries():
+        return [gc.block_entry(w, b, h, j) for w in (K, V) for b in range(B) for h in range(H) for j in range(n_blk)]
+
+    first = entries()  # sizes from the block histograms, one tensor after the other
+    at = 0
+    for off, size in first:
+        assert off == at and size > 0
+        at += size
+    assert gc.stats()["max_record_bytes"] == 16 * max(size for _, size in first)
+    gc.reset(keep_codebook=True)
+    gc.compress_blocks(k, v)  # sizes from the codes, both tensors at once
+    assert entries() == first
+    gc.close()
+
+
 def test_one_context_two_prompts_with_different_codebooks(gpu, oracle):
     """A context that is reset and filled again builds new codebooks: the tables that the second prompt is encoded and
     decoded with must be the second prompt's (the tables travel from a pinned host block that is rewritten in place).
