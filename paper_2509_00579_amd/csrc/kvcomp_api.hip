@@ -460,6 +460,12 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     // lookups in flight): n = 4 6 8: 12.1 15.3 20.0 against 12.9 14.9 15.7.
     const int paired_waves = std::min(max_waves, fused_table_bits(longest) == 6 || g.G >= 4 ? 12 : 8);
     const bool paired = bps > 0 && 2 * bps + units_per_split <= paired_waves;
+    // Sixteen waves (groups of 1 and 2) that have more than one pair each but not two leave a last round of a few waves that
+    // cannot fill the LDS pipe; twelve spread it better.  32 heads in 8 splits of n pairs, groups of 1, 16 against 12 waves,
+    // n = 16 18 20 24 28 30 34 64: 21.4 23.4 24.7 27.1 28.8 31.0 32.3 51.5 against 21.7 22.6 23.4 26.2 28.2 30.2 32.4 52.0 us;
+    // the same with code words of up to 12 bits (n = 20: 30.8 against 29.5) and for groups of 2.  Groups of 4 and 8 have
+    // twelve waves at most and gain less, each length at another number.
+    if (ctx->tune_waves <= 0 && max_waves == 16 && bps > 16 && bps < 32) max_waves = 12;
     const int n_waves = std::max(1, std::min(max_waves, (paired ? 2 : 1) * bps + units_per_split));
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (ctx->profiling) {
