@@ -953,6 +953,7 @@ template <int G, int LB> struct MaxWaves { static constexpr int value = 4 * fuse
 // record of the split's block w and wave blocks_per_split + w its V record at the same time; the softmax numerators go
 // from the first to the second through the first one's record area (free by then), announced by a flag in LDS.  The waves
 // behind them take the buffered tokens.  The V waves hold the state, the K waves end empty-handed.
+// 1 head x 1024 tokens 9.4 -> 7.9 us a step, 96 tokens appended to 2000 (8 heads, groups of 4) 1424 -> 1134 us.
 template <int G, int LB, bool kPaired>
 __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_kernel(FusedArgs a) {
     using M = DecodeMode<LB>;
