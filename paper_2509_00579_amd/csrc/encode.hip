@@ -280,6 +280,7 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
                                               const FastDiv &by_blk, PlaceShared<THREADS> &sh) {
     constexpr int kWaves = THREADS / 64, kPerLane = kPlaceRegs * kWaves / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t tail0 = g.ctrl->tail16;  // only the last workgroup moves it
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);  // this wave's sizes have arrived
     __syncthreads();
@@ -287,7 +288,6 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
         sh.last = __hip_atomic_fetch_add(&g.ctrl->place_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     __syncthreads();
     if (!sh.last) return;
-    const uint32_t tail0 = g.ctrl->tail16;
     auto entry = [&](int i) {
         const int row = (int)by_blk((uint32_t)i);
         return rows + (size_t)row * g.max_blocks + dst_blk0 + (i - row * n_blk_per_bh);
@@ -296,11 +296,14 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
 #pragma unroll
     for (int k = 0; k < kPlaceRegs; k++) {
         const int i = k * THREADS + tid;
+        size[k] = 0;
+        if (k * THREADS >= n_items) continue;  // uniform: few records need few of the registers
         size[k] = i < n_items ? __hip_atomic_load(&entry(i)->size16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     }
 #pragma unroll
     for (int k = 0; k < kPlaceRegs; k++) {
-        at[k] = wave_excl_scan(size[k], lane);
+        at[k] = 0;
+        if (k * THREADS < n_items) at[k] = wave_excl_scan(size[k], lane);  // uniform
         if (lane == 63) sh.tot[k * kWaves + wave] = at[k] + size[k];
         biggest = max(biggest, size[k]);
     }
@@ -327,7 +330,7 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
 #pragma unroll
     for (int k = 0; k < kPlaceRegs; k++) {
         const int i = k * THREADS + tid;
-        if (i < n_items) *entry(i) = {fits ? tail0 + sh.tot[k * kWaves + wave] + at[k] : 0u, size[k]};
+        if (k * THREADS < n_items && i < n_items) *entry(i) = {fits ? tail0 + sh.tot[k * kWaves + wave] + at[k] : 0u, size[k]};
     }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) biggest = max(biggest, (uint32_t)__shfl_xor(biggest, m));
