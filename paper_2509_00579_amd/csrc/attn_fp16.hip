@@ -230,15 +230,27 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
     const uint16_t *Vb = V + ((size_t)b * seq * H + h) * kD + 8 * j;
 
     uint4 kv[16], vv[16];
+    auto load_k16 = [&](int t16, uint4 (&k4)[4]) {  // 16 tokens
+        const int t = t16 + j;
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            k4[i] = t < t_end ? *reinterpret_cast<const uint4 *>(Kb + (size_t)t * row + 32 * i) : make_uint4(0, 0, 0, 0);
+    };
     auto load_k = [&](int t0) {
 #pragma unroll
         for (int tt = 0; tt < 4; tt++) {
-            const int t = t0 + 16 * tt + j;
+            uint4 k4[4];
+            load_k16(t0 + 16 * tt, k4);
 #pragma unroll
-            for (int i = 0; i < 4; i++)
-                kv[tt * 4 + i] = t < t_end ? *reinterpret_cast<const uint4 *>(Kb + (size_t)t * row + 32 * i)
-                                           : make_uint4(0, 0, 0, 0);
+            for (int i = 0; i < 4; i++) kv[tt * 4 + i] = k4[i];
         }
+    };
+    auto scores = [&](const uint4 (&k4)[4]) {
+        v4f d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, k4[i]), qb[i], d, 0, 0, 0);
+        return d;
     };
     auto load_v = [&](int t0) {
 #pragma unroll
@@ -256,10 +268,8 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
         float s[16], ml = -INFINITY;
 #pragma unroll
         for (int tt = 0; tt < 4; tt++) {
-            v4f d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-                d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, kv[tt * 4 + i]), qb[i], d, 0, 0, 0);
+            const uint4 k4[4] = {kv[tt * 4], kv[tt * 4 + 1], kv[tt * 4 + 2], kv[tt * 4 + 3]};
+            const v4f d = scores(k4);
 #pragma unroll
             for (int r = 0; r < 4; r++) s[tt * 4 + r] = scale * d[r];  // token t0 + 16 tt + 4 gq + r
         }
@@ -314,6 +324,40 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
                     vb.w[k] = __builtin_amdgcn_perm(c, a, (ct & 1) ? 0x07060302u : 0x05040100u);
                 }
                 acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa.v, vb.v, acc[ct], 0, 0, 0);
+            }
+        }
+    }
+    // An Inf in V times a numerator is Inf, but times the numerator's parts it is NaN wherever one of them is zero (or
+    // Inf - Inf where they differ in sign).  No finite V overflows the sums, so a sum that is not finite sends the wave over
+    // its tokens once more, with p . V in fp32 on the vector ALU against the final reference.
+    bool odd = false;
+#pragma unroll
+    for (int ct = 0; ct < 8; ct++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) odd |= !(fabsf(acc[ct][r]) < INFINITY);
+    if (__builtin_amdgcn_ballot_w64(odd) != 0) {
+#pragma unroll
+        for (int ct = 0; ct < 8; ct++) acc[ct] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int u0 = t_begin + wave * 64; u0 < t_end; u0 += (u0 & 48) == 48 ? 64 * kBWaves - 48 : 16) {  // 16 tokens at a time
+            uint4 k4[4];
+            load_k16(u0, k4);
+            v4f p = scores(k4);
+#pragma unroll
+            for (int r = 0; r < 4; r++) p[r] = __expf(scale * p[r] - m);  // token u0 + 4 gq + r
+            const int n = min(t_end - u0, 16);
+#pragma unroll 1
+            for (int t = 0; t < n; t++) {
+                float x[8];
+                unpack8(*reinterpret_cast<const uint4 *>(Vb + (size_t)(u0 + t) * row), x);
+                const float pt = (t & 2) ? (t & 1) ? p[3] : p[2] : (t & 1) ? p[1] : p[0];
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const float pr = __shfl(pt, 16 * (t >> 2) + 4 * gq + r);  // of row 4 gq + r
+#pragma unroll
+                    for (int ct = 0; ct < 8; ct++)
+                        if (4 * gq + r < G) acc[ct][r] = fmaf(pr, x[ct], acc[ct][r]);  // the rows of second parts stay zero
+                }
             }
         }
     }

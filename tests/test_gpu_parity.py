@@ -894,6 +894,30 @@ def test_fp16_attention_of_large_groups_at_tile_edges(gpu, G, S):
                     assert np.abs(out[b, g] - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max()), (ramp, n_splits, b, g)
 
 
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("S", [17, 300, 700])
+def test_fp16_attention_with_infinities_in_v(gpu, G, S):
+    """An Inf in V, which the uncompressed attention takes as it is: every head of the group gets Inf with its sign in that
+    channel, NaN where Infs of both signs meet or V holds a NaN, and the other channels do not notice.  The tokens are in the
+    first and last tile of a split, at the softmax reference and (ramp) far below the final one."""
+    import torch
+    B, H = 1, 2
+    rng = np.random.default_rng(S + G)
+    Kx = rng.standard_normal((B, S, H, 128)).astype(np.float16)
+    Vx = rng.standard_normal((B, S, H, 128)).astype(np.float16)
+    q = rng.standard_normal((B, H * G, 128)).astype(np.float16)
+    Vx[0, 0, :, 3], Vx[0, S - 1, :, 9], Vx[0, S // 2, 1, 127] = np.inf, -np.inf, np.inf
+    Vx[0, S // 3, :, 40], Vx[0, S - 2, :, 40], Vx[0, S // 2, :, 64] = np.inf, -np.inf, np.nan
+    for ramp in (0.0, 30.0):
+        Kr = (Kx + (ramp * np.linspace(0, 1, S)[None, :, None, None] * q[:, None, ::G, :] / 128)).astype(np.float16)
+        k64, v64, q64 = (torch.from_numpy(x.astype(np.float64)) for x in (Kr, Vx, q))
+        ref = np.stack([(torch.softmax(k64[0, :, g // G] @ q64[0, g] / 8, 0) @ v64[0, :, g // G]).numpy() for g in range(H * G)])
+        assert np.isposinf(ref[:, 3]).all() and np.isneginf(ref[:, 9]).all() and np.isnan(ref[:, [40, 64]]).all()
+        for n_splits in (0, 1, 3):
+            out = gpu.BaselineFp16Attention(B, H, H * G)(_dev(Kr), _dev(Vx), _dev(q), 0.125, n_splits=n_splits)
+            np.testing.assert_allclose(out.cpu().numpy()[0], ref, rtol=0, atol=1e-5, err_msg=f"{ramp} {n_splits}")
+
+
 def test_config1_full_size_sampled(gpu, oracle):
     """The benchmark workload (32 heads x 4096 tokens) in the launch configuration bench.py times."""
     w = W.CONFIGS["c1"]
