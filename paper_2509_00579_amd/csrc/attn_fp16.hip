@@ -193,17 +193,29 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_kernel(int B, i
 //           are the eight slots of its group, so the numerators are the A operand without leaving the lane.  V is loaded for
 //           those tokens, 8 channels of one token per load; the 8 x 8 halves of a lane are transposed in its registers (one
 //           v_perm_b32 per pair) into one B operand per channel: column l % 16 of tile ct is channel 8 (l % 16) + ct.
-//   A numerator has fp32's bits, an fp16 operand eleven of them: rows 0 .. G-1 hold p rounded to fp16, rows G .. 2G-1 what
-//   is left of it times 2^11 (the copies of the score columns are there for that), and the two are added at the end.
+//   A numerator is a fp32 number, an fp16 operand holds eleven bits of it above 2^-14 and fewer below: it goes in as four
+//   parts, each what the ones before left of it times 2^11 (truncated, so that the rest is exact and positive).  Three parts
+//   hold fp32's 24 bits of a numerator near 1, four hold them down to 2^-34.  The parts are the A rows G apart (the copies of
+//   the score columns are there for that) and are added at the end; groups of 8 have rows for two, and the other two take
+//   a second product per operand.  With two parts only, a numerator of e^-14 had 16 bits and one of e^-24 none.
 // The loop keeps a tile of 64 V rows and the next tile of K rows on their way (16 to 32 KiB a wave, two waves per SIMD).
 // With p . V on the vector ALU, 8 FMAs per value for groups of 8, and the numerators through LDS, it was bound by the ALU:
-// 8 x 8 heads x 16384 tokens, groups of 8: 121 us (4.4 TB/s) -> 104 us (5.2 TB/s, what a large copy reaches); groups of 4,
-// 16 x 8 heads x 8192: 103 -> 99 us.
+// 8 x 8 heads x 16384 tokens, groups of 8: 121 us (4.4 TB/s) -> 104 us (5.2 TB/s; a plain read reaches 6.0); groups of 4,
+// 16 x 8 heads x 8192: 103 -> 99 us.  Four parts instead of two cost nothing there (107.6 and 107.5 us in one run).
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-constexpr float kLowPart = 2048.f;     // scale of the second part of a numerator
+constexpr float kNextPart = 2048.f;    // scale of a numerator's part against the one before it
 constexpr float kLazyMaxFp16 = 8.f;    // how far a score may exceed the softmax reference before the state is rescaled
+
+// v + f * (v of the lane DIST further), valid in the lanes of the lower half (DIST 32) or of the even rows of 16 (DIST 16)
+template <int DIST>
+__device__ __forceinline__ float add_next(float v, float f) {
+    typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+    const uint32_t u = __float_as_uint(v);
+    const v2u r = DIST == 32 ? __builtin_amdgcn_permlane32_swap(u, u, false, false) : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return fmaf(__uint_as_float(r.y), f, __uint_as_float(r.x));
+}
 
 template <int G>
 __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
@@ -303,18 +315,30 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
             ps += s[n];
         }
         lsum += ps;
+        union { v8h v; uint32_t w[4]; } pa[2], pb[2];  // tokens 0..31 and 32..63 of the tile; pb: groups of 8
 #pragma unroll
-        for (int hh = 0; hh < 2; hh++) {  // tokens 0..31 and 32..63 of the tile
-            union { v8h v; uint32_t w[4]; } pa;
+        for (int k = 0; k < 8; k++) {
+            float p0 = s[2 * k], p1 = s[2 * k + 1];
+            uint32_t w[4];
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const float p0 = s[8 * hh + 2 * k], p1 = s[8 * hh + 2 * k + 1];
-                const v2h hi = {(_Float16)p0, (_Float16)p1};
-                const v2h lo = {(_Float16)((p0 - (float)hi[0]) * kLowPart), (_Float16)((p1 - (float)hi[1]) * kLowPart)};
-                pa.w[k] = part == 0 ? __builtin_bit_cast(uint32_t, hi) : part == 1 ? __builtin_bit_cast(uint32_t, lo) : 0u;
+            for (int i = 0; i < 4; i++) {
+                const v2h h = __builtin_bit_cast(v2h, __builtin_amdgcn_cvt_pkrtz(p0, p1));
+                w[i] = __builtin_bit_cast(uint32_t, h);
+                p0 = fmaf((float)h[0], -kNextPart, p0 * kNextPart);  // exact
+                p1 = fmaf((float)h[1], -kNextPart, p1 * kNextPart);
             }
+            if constexpr (G == 8) {
+                pa[k >> 2].w[k & 3] = part == 0 ? w[0] : w[1];
+                pb[k >> 2].w[k & 3] = part == 0 ? w[2] : w[3];
+            } else {
+                pa[k >> 2].w[k & 3] = part == 0 ? w[0] : part == 1 ? w[1] : part == 2 ? w[2] : w[3];
+            }
+        }
 #pragma unroll
-            for (int ct = 0; ct < 8; ct++) {
+        for (int ct = 0; ct < 8; ct++) {
+            v4f low = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int hh = 0; hh < 2; hh++) {
                 union { v8h v; uint32_t w[4]; } vb;
 #pragma unroll
                 for (int k = 0; k < 4; k++) {
@@ -323,19 +347,22 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
                     const uint32_t c = ct < 2 ? r1.x : ct < 4 ? r1.y : ct < 6 ? r1.z : r1.w;
                     vb.w[k] = __builtin_amdgcn_perm(c, a, (ct & 1) ? 0x07060302u : 0x05040100u);
                 }
-                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa.v, vb.v, acc[ct], 0, 0, 0);
+                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa[hh].v, vb.v, acc[ct], 0, 0, 0);
+                if constexpr (G == 8) low = __builtin_amdgcn_mfma_f32_16x16x32_f16(pb[hh].v, vb.v, low, 0, 0, 0);
+            }
+            if constexpr (G == 8) {
+#pragma unroll
+                for (int r = 0; r < 4; r++) acc[ct][r] = fmaf(low[r], 1.f / (kNextPart * kNextPart), acc[ct][r]);
             }
         }
     }
     // An Inf in V times a numerator is Inf, but times the numerator's parts it is NaN wherever one of them is zero (or
     // Inf - Inf where they differ in sign).  No finite V overflows the sums, so a sum that is not finite sends the wave over
     // its tokens once more, with p . V in fp32 on the vector ALU against the final reference.
-    bool odd = false;
+    v4f all = acc[0];
 #pragma unroll
-    for (int ct = 0; ct < 8; ct++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) odd |= !(fabsf(acc[ct][r]) < INFINITY);
-    if (__builtin_amdgcn_ballot_w64(odd) != 0) {
+    for (int ct = 1; ct < 8; ct++) all += acc[ct];
+    if (__builtin_amdgcn_ballot_w64(!(fabsf((all[0] + all[1]) + (all[2] + all[3])) < INFINITY)) != 0) {
 #pragma unroll
         for (int ct = 0; ct < 8; ct++) acc[ct] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
@@ -356,7 +383,7 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
                     const float pr = __shfl(pt, 16 * (t >> 2) + 4 * gq + r);  // of row 4 gq + r
 #pragma unroll
                     for (int ct = 0; ct < 8; ct++)
-                        if (4 * gq + r < G) acc[ct][r] = fmaf(pr, x[ct], acc[ct][r]);  // the rows of second parts stay zero
+                        if (4 * gq + r < G) acc[ct][r] = fmaf(pr, x[ct], acc[ct][r]);  // the rows of later parts stay zero
                 }
             }
         }
@@ -367,12 +394,14 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
         comb[wave][j][kD] = m;
         comb[wave][j][kD + 1] = lsum;
     }
-    // the second part of row 4 gq + r sits G rows further, in lane group gq + G / 4
+    // the next part of row 4 gq + r sits G rows further, in lane group gq + G / 4
 #pragma unroll
     for (int ct = 0; ct < 8; ct++)
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-            const float v = fmaf(__shfl_xor(acc[ct][r], 4 * G), 1.f / kLowPart, acc[ct][r]);
+            float v = acc[ct][r];
+            if constexpr (G == 4) v = add_next<16>(v, 1.f / kNextPart);
+            v = add_next<32>(v, G == 4 ? 1.f / (kNextPart * kNextPart) : 1.f / kNextPart);
             if (4 * gq + r < G) comb[wave][4 * gq + r][8 * j + ct] = v;
         }
     __syncthreads();

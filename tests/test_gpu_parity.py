@@ -874,8 +874,8 @@ def test_fp16_baseline_attention(gpu, oracle, B, H, Hq, S):
 def test_fp16_attention_of_large_groups_at_tile_edges(gpu, G, S):
     """Groups of 4 and 8 on the uncompressed cache: sequence lengths around the 16-, 32- and 64-token pieces of a tile, and
     scores that grow along the sequence, so that the softmax reference has to follow (by far more than its slack of 8)
-    with sums already made.  Against float64 on the CPU; the numerators are carried in two fp16 parts (2^-23), sums are
-    fp32: 1e-5 of the largest output."""
+    with sums already made.  Against float64 on the CPU; numerators and sums have fp32's
+    resolution: 1e-5 of the largest output."""
     import torch
     B, H = 2, 2
     rng = np.random.default_rng(S * 10 + G)
@@ -892,6 +892,26 @@ def test_fp16_attention_of_large_groups_at_tile_edges(gpu, G, S):
                     p = torch.softmax(k64[b, :, g // G] @ q64[b, g], 0)
                     ref = (p @ v64[b, :, g // G]).numpy()
                     assert np.abs(out[b, g] - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max()), (ramp, n_splits, b, g)
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_fp16_attention_of_small_numerators(gpu, G):
+    """Tokens whose numerators are far below the reference count with the resolution of fp32: the reference's tokens have V = 0,
+    the others a score 4, 14, 18 or 22 lower (numerators down to 2^-32) and a V of their own channel.  The scores are exact;
+    exp is off by half an ulp of the argument times log2 e (22 * 1.44 * 2^-24 = 1.9e-6) and an ulp of its own, the sums over
+    140 equal numerators by less than 140 * 2^-24: 1e-5 of every value.  Two fp16 parts would leave 1.5e-5 at 14, 1e-3 at 18."""
+    B, H, S = 1, 2, 140
+    depth = {5: 4.0, 21: 14.0, 70: 18.0, 139: 22.0}   # token -> how far below; in both halves and the last tile
+    Kx, Vx = (np.zeros((B, S, H, 128), np.float16) for _ in range(2))
+    q = np.zeros((B, H * G, 128), np.float16)
+    q[:, :, 11] = 1.0
+    norm = float(S - len(depth)) + sum(np.exp(-d) for d in depth.values())
+    ref = np.zeros(128)
+    for i, (t, d) in enumerate(depth.items()):
+        Kx[:, t, :, 11], Vx[:, t, :, 30 * i + 1] = -d, 32768.0
+        ref[30 * i + 1] = 32768.0 * np.exp(-d) / norm
+    out = gpu.BaselineFp16Attention(B, H, H * G)(_dev(Kx), _dev(Vx), _dev(q), 1.0).cpu().numpy()
+    assert (np.abs(out - ref) <= 1e-5 * ref).all(), out[0, 0][ref > 0] / ref[ref > 0]
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
