@@ -766,7 +766,10 @@ __device__ __forceinline__ void tile_state_to_area(const TileSoft<G> &ts, float 
 // A unit is read with four 16-byte loads per lane and tensor, K and V together and all in flight at once: a single wave
 // has nothing else to hide the memory latency with, and small units spread the buffer over many waves.
 //   scores : v_mfma_f32_16x16x32_f16, tokens x heads.  Lane l supplies K row l % 16 and query head l % 16, channels
-//            32 i + 8 (l / 16) .. +7 in step i, and receives head l % 16 of the tokens 4 (l / 16) .. +3.
+//            32 i + 8 (l / 16) .. +7 in step i, and receives head l % 16 of the tokens 4 (l / 16) .. +3.  Each step has an
+//            accumulator of its own and the four are added as a tree: a score is a fp32 sum over 128 channels, and its
+//            rounding decides the error of the output (one running accumulator: half as much error again, same time
+//            within 2 %).
 //   p . V  : lane l holds channels 8 (l % 16) .. +7 of those same four tokens, so a numerator reaches the 16 lanes that
 //            multiply with it by a broadcast inside their row of 16, which rides on the FMA.
 // All heads of a group share the loads, the matrix instructions and one running softmax per unit; only the FMAs of p . V
@@ -869,11 +872,13 @@ __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens
             for (int i = 0; i < 4; i++)
                 if (4 * grp + i == new_tok) *reinterpret_cast<uint4 *>(wr + res_tensor + 8 * col) = rv[i];
         }
-        v4f s = {0.f, 0.f, 0.f, 0.f};
+        v4f s[4];
 #pragma unroll
         for (int i = 0; i < 4; i++)
-            s = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, rk[i]), __builtin_bit_cast(v8h, qb[i]), s, 0, 0, 0);
-        float p[4] = {s.x, s.y, s.z, s.w}, mu = -INFINITY;
+            s[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, rk[i]), __builtin_bit_cast(v8h, qb[i]), v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        float p[4], mu = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; r++) p[r] = (s[0][r] + s[1][r]) + (s[2][r] + s[3][r]);
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             p[r] = 4 * grp + r < n_tok ? scale * p[r] : -INFINITY;

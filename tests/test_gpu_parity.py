@@ -436,6 +436,38 @@ def test_buffered_tokens_at_unit_edges(gpu, oracle, G, n0):
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_scores_of_buffered_tokens_are_summed_in_a_tree(gpu, G):
+    """The scores of the buffered tokens are fp32 sums over 128 channels, and with large ones they decide the error of the
+    output.  Summed as a tree (four sums of 32 channels, then the four), as numpy does here for the comparison, partial sums
+    stay small; one running sum over the four leaves half as much error again.  Everything else is float64 in the comparison,
+    so the kernel may exceed it by the rounding of its exp and sums: a quarter."""
+    B, H, S, seeds = 2, 4, 200, 12
+    err, tree = 0.0, 0.0
+    for seed in range(seeds):
+        Kx, Vx = W.make_kv(B, H, S, 300 + seed)
+        q = (2 * W.make_queries(B, H * G, 1, 300 + seed)[0].astype(np.float32)).astype(np.float16)
+        gc = gpu.KVCompCache(B, H, H * G, 256, 1e-2, 1e-2, buffer_tokens=256)
+        gc.prefill(_dev(Kx), _dev(Vx))
+        out = gc.attn_decode(_dev(q), SCALE).cpu().numpy().astype(np.float64)
+        gc.close()
+        for b in range(B):
+            for hq in range(H * G):
+                prod = Kx[b, :, hq // G].astype(np.float32) * q[b, hq].astype(np.float32)   # exact: 11 x 11 bits
+                exact = prod.astype(np.float64).sum(-1)
+                part = prod.reshape(S, 4, 32).transpose(0, 2, 1)
+                while part.shape[1] > 1:
+                    part = part[:, 0::2] + part[:, 1::2]
+                part = part[:, 0]
+                part = ((part[:, 0] + part[:, 1]) + (part[:, 2] + part[:, 3])).astype(np.float64)
+                ref, cmp = ((lambda p: p / p.sum() @ Vx[b, :, hq // G].astype(np.float64))(np.exp(SCALE * (s - exact.max())))
+                            for s in (exact, part))
+                err += ((out[b, hq] - ref) ** 2).sum()
+                tree += ((cmp - ref) ** 2).sum()
+    _say(f"  buffered scores, groups of {G}: error {np.sqrt(err / tree):.3f} of the tree's")
+    assert err <= 1.25 ** 2 * tree, np.sqrt(err / tree)
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
 @pytest.mark.parametrize("limit", [6, 12])
 def test_a_wave_for_each_record_of_a_pair(gpu, oracle, G, limit):
     _say(f"K and V records of a pair on two waves, and on one; groups of {G}, code words of up to {limit} bits")
