@@ -146,8 +146,8 @@ kvcomp_status kvcomp_append_token(kvcomp_ctx *ctx, const void *d_k_new, const vo
 /* Fetch stage (Section 3.3.2, Figure 1): one decode-attention step over the whole cache.  For every query head:
  * scores = scale * q.K'^T over all compressed blocks (Huffman decode + dequantize fused into the dot product) and
  * the buffered fp16 tokens, softmax over all of them, out = weights . V'.  Query head g reads KV head
- * g / (n_q_heads / n_kv_heads).  d_q: device fp16 [batch, n_q_heads, 128]; d_out: device fp32
- * [batch, n_q_heads, 128], caller-owned.  Stream-ordered, never synchronises.
+ * g / (n_q_heads / n_kv_heads).  d_q: device fp16 [batch, n_q_heads, 128], aligned to its elements (2 bytes); d_out:
+ * device fp32 [batch, n_q_heads, 128], caller-owned.  Stream-ordered, never synchronises.
  * Errors: STATE (empty cache), HIP. */
 kvcomp_status kvcomp_attn_decode(kvcomp_ctx *ctx, const void *d_q, float scale, float *d_out, void *stream);
 

@@ -61,9 +61,10 @@ def build(verbose: bool = False, extra_flags=(), out: pathlib.Path | None = None
     return lib
 
 
-def device_assembly(src: str) -> str:
-    """gfx950 assembly text of one source file, compiled with the library's flags (for checks on the generated code)."""
-    cmd = [_hipcc(), *FLAGS, "--cuda-device-only", "-S", str(CSRC / src), "-o", "-"]
+def device_assembly(src: str, llvm: bool = False) -> str:
+    """gfx950 assembly text (llvm: LLVM IR) of one source file, compiled with the library's flags (for checks on the generated
+    code)."""
+    cmd = [_hipcc(), *FLAGS, "--cuda-device-only", "-S", *(["-emit-llvm"] if llvm else []), str(CSRC / src), "-o", "-"]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True, check=True)
     return r.stdout
 

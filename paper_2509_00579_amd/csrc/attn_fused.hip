@@ -65,6 +65,15 @@ constexpr int kTileMinG = 4;  // smallest query-head group on the tile path
 // words of up to 7 bits leave at most 128 levels.
 template <int LB> constexpr bool kBiased = LB > 7;
 
+// Eight query values.  The query is the caller's and may start at any fp16 element (a view into a larger tensor), so the load
+// says that it is only 2-byte aligned; the hardware takes it as one 16-byte load all the same (the HSA ABI runs kernels in
+// unaligned access mode).
+__device__ __forceinline__ uint4 load_query(const uint16_t *p) {
+    typedef uint32_t piece_t __attribute__((ext_vector_type(4), aligned(2)));
+    const piece_t v = *(const __attribute__((address_space(1))) piece_t *)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // softmax state of one wave for G query heads
 template <int G>
 struct Soft {
@@ -835,7 +844,7 @@ __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens
     uint4 qb[4];  // head `col` of the group (zeros beyond it)
 #pragma unroll
     for (int i = 0; i < 4; i++)
-        qb[i] = col < G ? *reinterpret_cast<const uint4 *>(q0 + col * kD + 32 * i + 8 * grp) : make_uint4(0, 0, 0, 0);
+        qb[i] = col < G ? load_query(q0 + col * kD + 32 * i + 8 * grp) : make_uint4(0, 0, 0, 0);
     float m = -INFINITY, l = 0.f;  // running maximum of head `col`; its sum, this lane's share
     float av[G][8];                // channels 8 col .. +7 of every head, this row's tokens
 #pragma unroll
@@ -1014,7 +1023,7 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     if constexpr (kTile) {
 #pragma unroll
         for (int k = 0; k < G / 4; k++)    // at least 64 threads for G * 16 pieces
-            qv[k] = reinterpret_cast<const uint4 *>(q0)[min(tid + k * n_threads, G * kD / 8 - 1)];
+            qv[k] = load_query(q0 + 8 * min(tid + k * n_threads, G * kD / 8 - 1));
     } else {
 #pragma unroll
         for (int gg = 0; gg < G; gg++) { qh[gg][0] = q0[gg * kD + lane]; qh[gg][1] = q0[gg * kD + lane + 64]; }

@@ -484,6 +484,27 @@ def test_a_wave_for_each_record_of_a_pair(gpu, oracle, G, limit):
         gc.close()
 
 
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_query_at_any_element_of_a_larger_tensor(gpu, oracle, G):
+    """The query may start at any fp16 element: blocks and buffered tokens give the same bits as from an aligned copy."""
+    import torch
+    _say(f"queries at odd elements, groups of {G}")
+    B, H, S = 2, 2, 300
+    _, _, oc, gc = _both(gpu, oracle, B, H, G * H, S, S, S + 8, 1e-2, 1e-2, 63)
+    q = W.make_queries(B, G * H, 1, 63)[0]
+    want = gc.attn_decode(_dev(q), SCALE)
+    _attn_close(want.cpu().numpy(), oc.attn_decode(q, SCALE))
+    for first in (1, 2, 4, 7):
+        flat = torch.full((q.size + 8,), float("nan"), dtype=torch.float16, device="cuda:0")
+        view = flat[first:first + q.size].view(q.shape)
+        view.copy_(_dev(q))
+        assert torch.equal(gc.attn_decode(view, SCALE), want)
+    kn, vn = W.make_new_tokens(B, H, 1, 63)
+    oc.append_token(kn[0], vn[0])
+    _attn_close(gc.append_attn_decode(_dev(kn[0]), _dev(vn[0]), view, SCALE).cpu().numpy(), oc.attn_decode(q, SCALE))
+    gc.close()
+
+
 @pytest.mark.parametrize("G", [1, 2])
 @pytest.mark.parametrize("rel,limit", [(2e-3, 8), (2e-3, 12), (3.9e-3, 8), (3.95e-3, 7), (1e-2, 6), (0.25, 2)])
 def test_integer_dot_products_of_groups_of_1_and_2(gpu, oracle, G, rel, limit):

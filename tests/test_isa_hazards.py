@@ -136,3 +136,45 @@ def test_row_reductions_of_the_store_kernels_carry_their_wait_states(source):
             prev = lines[i - 1].split()
             assert prev[0] == "s_nop" and int(prev[1], 0) >= 1, (i, lines[i - 1], ins)
     assert found >= 8   # the V quantizer is in every store kernel of both files
+
+
+def _loads_through(body, roots):
+    """(bytes, alignment) of every load in `body` whose address is one of the pointers `roots` or computed from it."""
+    derived = set(roots)
+    grown = True
+    while grown:                            # phis may come before what they select
+        grown = False
+        for line in body:
+            m = re.match(r"\s*(%\S+) = (?:getelementptr|addrspacecast|phi|select|freeze)\b(.*)", line)
+            if m and m.group(1) not in derived and derived & set(re.findall(r"%[\w.]+", m.group(2))):
+                if "ptr" in m.group(2):
+                    derived.add(m.group(1))
+                    grown = True
+    size = {"i8": 1, "i16": 2, "i32": 4, "i64": 8, "half": 2}
+    out = []
+    for line in body:
+        m = re.match(r"\s*%\S+ = load (?:<(\d+) x (\w+)>|(\w+)), ptr(?: addrspace\(\d\))? (%[\w.]+), align (\d+)", line)
+        if m and m.group(4) in derived:
+            out.append((size[m.group(2) or m.group(3)] * int(m.group(1) or 1), int(m.group(5))))
+    return out
+
+
+def test_the_query_is_read_at_the_alignment_of_its_elements():
+    """kvcomp_attn_decode takes any fp16 pointer as d_q, so no load of the query may claim more than 2-byte alignment: in the
+    kernels (the pointer is the fourth of their argument block) and in the out-of-line code for the buffered tokens."""
+    ir = B.device_assembly("attn_fused.hip", llvm=True)
+    kernels = buffered = 0
+    for m in re.finditer(r"^define [^\n]*@(\S*(?:fused_attn_kernel|buffered_tokens)\w*)\(([^\n]*)\n(.*?)^}", ir, re.S | re.M):
+        body = m.group(3).splitlines()
+        if "fused_attn_kernel" in m.group(1):
+            kernels += 1
+            at = re.findall(r"(%\S+) = getelementptr inbounds(?: nuw)? i8, ptr addrspace\(4\) %0, i64 24\n", m.group(3))
+            roots = [x for a in at for x in re.findall(r"(%\S+) = load ptr, ptr addrspace\(4\) " + a + ",", m.group(3))]
+        else:
+            buffered += 1
+            roots = ["%10"]
+            assert len(re.findall(r"\bptr\b", m.group(2).split("%10")[0])) == 2, "the query is the second pointer"
+        loads = _loads_through(body, roots)
+        assert len(loads) > 0, m.group(1)
+        assert all(align <= 2 for _, align in loads), (m.group(1), loads)
+    assert kernels == 40 and buffered == 4
