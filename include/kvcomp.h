@@ -9,7 +9,7 @@
  *   - Pointers named d_* are DEVICE pointers (HIP global memory), pointers named h_* are HOST pointers.
  *   - The caller owns all device memory, including the arena handed to kvcomp_create; the library allocates no
  *     device memory.  `stream` arguments are a hipStream_t passed as void* (NULL = the default stream).
- *   - The stream-ordered calls may be captured into a HIP graph (they launch kernels only).  A replay repeats the
+ *   - The stream-ordered calls may be captured into a HIP graph (they launch kernels only; not kvcomp_decompress).  A replay repeats the
  *     device work, not the host-side bookkeeping of the context (block and buffer counts): replay a captured sequence
  *     only from the cache state its capture started from, and bring the context back to a known state with eager
  *     calls (kvcomp_reset + kvcomp_compress_blocks) before using it eagerly again.
@@ -193,7 +193,8 @@ kvcomp_status kvcomp_get_residual(kvcomp_ctx *ctx, int which, uint16_t *h_buf, i
  * d_out: DEVICE, caller-owned, 16-byte aligned, batch*seq_stride*n_kv_heads*128 fp16; seq_stride >= tokens
  * (KVCOMP_ERR_CAPACITY otherwise).  Stream-ordered.  If an append has compressed a block since the last synchronising
  * call, the call synchronises the stream once before it launches (it reads the largest record size, and reports the
- * flags described at kvcomp_get_stats). */
+ * flags described at kvcomp_get_stats).  It cannot be captured into a HIP graph unless the cache holds buffered tokens only
+ * (KVCOMP_ERR_HIP, and the capture goes on without it). */
 kvcomp_status kvcomp_decompress(kvcomp_ctx *ctx, int which, void *d_out, int seq_stride, void *stream);
 
 /* The same call with the decoder of Section 3.3.1 instead of the table decoder: a branch-free walk of the

@@ -644,6 +644,14 @@ static kvcomp_status decompress_impl(kvcomp_ctx *ctx, int which, void *d_out, in
     if (seq_stride < tokens) return fail(KVCOMP_ERR_CAPACITY, "seq_stride %d below the %d tokens in the cache", seq_stride, tokens);
     if (ctx->n_blocks && !ctx->have_codebook) return fail(KVCOMP_ERR_STATE, "no codebook");
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (ctx->n_blocks) {
+        // The staging area and the block count would be frozen into a graph, and a replay after further appends would leave
+        // blocks out.
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(s, &capture));
+        if (capture != hipStreamCaptureStatusNone)
+            return fail(KVCOMP_ERR_HIP, "kvcomp_decompress of compressed blocks cannot be captured into a graph");
+    }
     // The largest record may have grown, and flags may be up, through flushes since the control words were last read; where
     // there was none the host knows both, and the stream goes on without a stop (10 us of an idle GPU per tensor).
     if (ctx->n_blocks && (ctx->flushed || ctx->flush_captured)) {

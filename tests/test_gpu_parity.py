@@ -1186,6 +1186,33 @@ def test_decompression_widths_and_partial_workgroups(gpu, oracle, B, H, S, rel, 
     gc.close()
 
 
+def test_decompression_of_blocks_is_not_captured(gpu, oracle):
+    """A graph would freeze the staging area and the block count, so decompressing blocks under capture is refused; the capture
+    itself goes on, and decompressing buffered tokens alone can be captured."""
+    import torch
+    _say("decompression under stream capture")
+    _, _, oc, gc = _both(gpu, oracle, 1, 2, 2, 130, 130, 256, 1e-2, 1e-2, 73)
+    Kx, Vx, _, few = _both(gpu, oracle, 1, 2, 2, 64, 20, 256, 1e-2, 1e-2, 74)
+    out, tail = (torch.zeros((1, n, 2, 128), dtype=torch.float16, device="cuda:0") for n in (130, 20))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for tree_walk in (False, True):
+            with pytest.raises(gpu.KvcompError) as e:
+                gc.decompress(K, 130, out=out, tree_walk=tree_walk)
+            assert e.value.status == gpu.ERR_HIP
+        few.decompress(V, 20, out=tail)
+    for _ in range(3):
+        tail.zero_()
+        graph.replay()
+        assert np.array_equal(tail.cpu().numpy().view(np.uint16), Vx[:, :20].view(np.uint16))
+    assert torch.count_nonzero(out) == 0
+    got = gc.decompress(K, 130, out=out).cpu().numpy()
+    np.testing.assert_array_equal(got.view(np.uint16), oc.decompress(K).view(np.uint16))
+    gc.close()
+    few.close()
+
+
 @pytest.mark.parametrize("name,rel", [("c2", 1e-2), ("c2", 5e-3), ("c2", 2e-2), ("c3", 1e-2), ("c4", 1e-2)])
 def test_large_configs_full_size_sampled(gpu, oracle, name, rel):
     """The long-context (with its error-bound sweep), grouped-query and 70B-shaped workloads at their full prompt
