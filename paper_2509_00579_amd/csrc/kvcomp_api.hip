@@ -47,8 +47,9 @@ struct kvcomp_ctx {
     uint8_t len[2][256];
     uint32_t code[2][256];
     uint32_t max_size16;
-    bool flushed;           // a flush was queued after the control words were last read: largest record and flags may have changed
-    bool flush_captured;    // a flush was captured into a graph: it may run again at any time
+    bool flushed;              // a flush was queued behind the last look at the control words: largest record and flags may have changed
+    hipStream_t flush_stream;  // where: only a look at that stream's end sees it
+    bool flush_anytime;        // a flush may run at any time: it was captured into a graph, or flushes wait on two streams
     int tune_splits, tune_stage, tune_waves;
     bool profiling;
     std::vector<hipEvent_t> events;  // pairs
@@ -68,7 +69,7 @@ namespace {
 kvcomp_status read_ctrl(kvcomp_ctx *ctx, hipStream_t s) {
     HIP_TRY(hipMemcpyAsync(ctx->h_ctrl, ctx->geo.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    ctx->flushed = false;
+    if (s == ctx->flush_stream) ctx->flushed = false;
     ctx->max_size16 = std::max(ctx->max_size16, ctx->h_ctrl->max_size16);
     return KVCOMP_OK;
 }
@@ -131,7 +132,8 @@ kvcomp_status kvcomp_create(const kvcomp_config *cfg, void *d_arena, size_t aren
     c->have_codebook = false;
     c->n_blocks = c->n_res = c->res_head = 0;
     c->max_size16 = 0;
-    c->flushed = c->flush_captured = false;
+    c->flushed = c->flush_anytime = false;
+    c->flush_stream = nullptr;
     c->tune_splits = c->tune_stage = c->tune_waves = 0;
     c->profiling = false;
     c->events_used = 0;
@@ -335,6 +337,7 @@ static kvcomp_status finish_prompt(kvcomp_ctx *ctx, const uint16_t *K, const uin
     ctx->n_blocks = nb;
     ctx->n_res = seq - nb * kBT;
     ctx->res_head = 0;
+    ctx->flushed = false;  // the blocks are this call's
     ctx->max_size16 = ctx->h_ctrl->max_size16;
     return KVCOMP_OK;
 }
@@ -405,10 +408,11 @@ kvcomp_status kvcomp_append_token(kvcomp_ctx *ctx, const void *d_k_new, const vo
         const uint16_t *rk = g.res + (size_t)ctx->res_head * g.H * kD;
         const uint16_t *rv = rk + (size_t)g.B * g.res_tokens * g.H * kD;
         HIP_TRY(launch_encode(g, rk, rv, g.res_tokens, 1, ctx->n_blocks, s));
-        ctx->flushed = true;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        HIP_TRY(hipStreamIsCapturing(s, &capture));
-        if (capture != hipStreamCaptureStatusNone) ctx->flush_captured = true;
+        const bool known = hipStreamIsCapturing(s, &capture) == hipSuccess;  // the block is queued either way
+        if (!known || capture != hipStreamCaptureStatusNone || (ctx->flushed && ctx->flush_stream != s)) ctx->flush_anytime = true;
+        ctx->flushed = true;
+        ctx->flush_stream = s;
         ctx->n_blocks++;
         ctx->n_res -= kBT;
         ctx->res_head = (ctx->res_head + kBT) % g.res_tokens;
@@ -654,7 +658,7 @@ static kvcomp_status decompress_impl(kvcomp_ctx *ctx, int which, void *d_out, in
     }
     // The largest record may have grown, and flags may be up, through flushes since the control words were last read; where
     // there was none the host knows both, and the stream goes on without a stop (10 us of an idle GPU per tensor).
-    if (ctx->n_blocks && (ctx->flushed || ctx->flush_captured)) {
+    if (ctx->n_blocks && (ctx->flushed || ctx->flush_anytime)) {
         kvcomp_status st = read_ctrl(ctx, s);
         if (st) return st;
         st = check_flags(ctx, s);

@@ -1186,6 +1186,43 @@ def test_decompression_widths_and_partial_workgroups(gpu, oracle, B, H, S, rel, 
     gc.close()
 
 
+def test_decompression_after_a_flush_that_another_stream_did_not_wait_for(gpu, oracle):
+    """The control words are read on one stream while the flush that enlarges a record still waits on another: the
+    decompression behind the flush must look again."""
+    import torch
+    _say("statistics on a stream of their own while a flush waits")
+    B, H = 1, 2
+    Kx, Vx, oc, gc = _both(gpu, oracle, B, H, H, 64, 64, 192, 2e-3, 2e-3, seed=75, limit=12)
+    kn, vn = W.make_new_tokens(B, H, 64, 76)
+    kn, vn = (kn * 50).astype(np.float16), (vn ** 3).astype(np.float16)  # rare codes: longer records
+    dkn, dvn = _dev(kn), _dev(vn)
+    dK, dV = _dev(Kx), _dev(Vx)
+    largest = gc.stats()["max_record_bytes"]
+    for attempt in range(8):                   # two streams may share a hardware queue, and then nothing overtakes
+        gc.reset()
+        gc.compress_blocks(dK, dV)
+        torch.cuda.synchronize()
+        behind, aside = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(behind):
+            torch.cuda._sleep(20_000_000)      # some ten milliseconds
+            for t in range(64):
+                gc.append_token(dkn[t], dvn[t])
+        with torch.cuda.stream(aside):
+            overtook = gc.stats()["max_record_bytes"] == largest
+        with torch.cuda.stream(behind):
+            got = [gc.decompress(w, 128).cpu().numpy() for w in (K, V)]
+        assert gc.stats()["max_record_bytes"] > largest
+        if overtook:
+            break
+    else:
+        pytest.skip("no two streams that overtake each other")
+    for t in range(64):
+        oc.append_token(kn[t], vn[t])
+    for w in (K, V):
+        np.testing.assert_array_equal(got[w].view(np.uint16), oc.decompress(w).view(np.uint16))
+    gc.close()
+
+
 def test_decompression_of_blocks_is_not_captured(gpu, oracle):
     """A graph would freeze the staging area and the block count, so decompressing blocks under capture is refused; the capture
     itself goes on, and decompressing buffered tokens alone can be captured."""
