@@ -193,7 +193,9 @@ kvcomp_status kvcomp_get_residual(kvcomp_ctx *ctx, int which, uint16_t *h_buf, i
  * d_out: DEVICE, caller-owned, 16-byte aligned, batch*seq_stride*n_kv_heads*128 fp16; seq_stride >= tokens
  * (KVCOMP_ERR_CAPACITY otherwise).  Stream-ordered.  If an append has compressed a block since the last synchronising
  * call, the call synchronises the stream once before it launches (it reads the largest record size, and reports the
- * flags described at kvcomp_get_stats).  It cannot be captured into a HIP graph unless the cache holds buffered tokens only
+ * flags described at kvcomp_get_stats).  A block whose record does not fit the staging area (a damaged arena) comes out as
+ * NaN; kvcomp_get_stats, or the next decompression that is called after this one has run, reports it (KVCOMP_ERR_STATE).  It
+ * cannot be captured into a HIP graph unless the cache holds buffered tokens only
  * (KVCOMP_ERR_HIP, and the capture goes on without it). */
 kvcomp_status kvcomp_decompress(kvcomp_ctx *ctx, int which, void *d_out, int seq_stride, void *stream);
 

@@ -15,6 +15,7 @@ struct DecompArgs {
     uint16_t *out;
     int which, n_blocks, seq_stride, area_bytes, stage_bytes;
     int res_head, n_res;
+    uint32_t *host_refused;  // pinned host memory
     uint32_t mask2;
     FastDiv by_seq, by_heads;  // items of a sequence (heads * blocks), heads
 };
@@ -63,10 +64,16 @@ struct BlockOfWave {
         size16 = __builtin_amdgcn_readfirstlane(e.size16);
         rec = g.payload + (size_t)(uint32_t)__builtin_amdgcn_readfirstlane(e.off16) * 16;
         dst = a.out + (((size_t)b * a.seq_stride + (size_t)j * kBT) * g.H + h) * kD;
-        // a record larger than the staging area (the host sizes it from the largest record, so only a corrupted table gets
-        // here) is not decoded: the fault bit makes the next synchronising call fail
-        if (size16 * 16u + 16u > (uint32_t)a.stage_bytes) {
-            if (lane == 0) atomicOr(&g.ctrl->fault, kFaultStageSmall);
+        // A record larger than the staging area (the host sizes it from the largest record, so only a corrupted table gets
+        // here) is not decoded: its block is NaN, so that it cannot pass for data, and the next synchronising call, or the
+        // next decompression that is queued once this one has run, fails.
+        if (size16 >= (uint32_t)a.stage_bytes / 16) {
+            if (lane == 0) {
+                atomicOr(&g.ctrl->fault, kFaultStageSmall);
+                __hip_atomic_store(a.host_refused, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+            for (int t = lane >> 4; t < kBT; t += 4)
+                *reinterpret_cast<uint4 *>(dst + (size_t)t * g.H * kD + 8 * (lane & 15)) = make_uint4(~0u, ~0u, ~0u, ~0u);
             return false;
         }
         return true;
@@ -302,7 +309,7 @@ static hipError_t launch_dec_lb(const DecompArgs &a, size_t lds, int grid, hipSt
 }
 
 hipError_t launch_decompress(const Geo &g, int which, uint16_t *out, int n_blocks, int res_head, int n_res, int seq_stride,
-                             int stage_bytes, int tree_walk, hipStream_t s) {
+                             int stage_bytes, int tree_walk, uint32_t *host_refused, hipStream_t s) {
     DecompArgs a;
     a.g = g;
     a.out = out;
@@ -312,6 +319,7 @@ hipError_t launch_decompress(const Geo &g, int which, uint16_t *out, int n_block
     a.stage_bytes = stage_bytes;
     a.res_head = res_head;
     a.n_res = n_res;
+    a.host_refused = host_refused;
     const int bits = g.lut_bits[which];
     if (bits < 1 || bits > kLutBits) return hipErrorInvalidValue;
     a.mask2 = ((1u << bits) - 1u) << 1;

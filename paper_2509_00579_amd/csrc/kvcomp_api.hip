@@ -61,6 +61,8 @@ struct kvcomp_ctx {
     uint32_t *h_hist;  // [2][256]
     uint8_t *h_tables; // [2 tensors][kTensorTablesBytes], laid out like Geo::tables
     uint8_t *h_tables_dev;  // the same memory as kernels address it
+    volatile uint32_t *h_refused;  // set by a decompression that refused a block
+    uint32_t *h_refused_dev;
     hipEvent_t ev_hist[2];  // the histogram of K, of V has reached the host
 };
 
@@ -100,7 +102,7 @@ kvcomp_status check_flags(kvcomp_ctx *ctx, hipStream_t s) {
     if (fault & kFaultArenaFull)
         return fail(KVCOMP_ERR_CAPACITY, "a flush found the record arena full (a captured flush replayed without the "
                                          "eager calls in between?): its blocks were not written");
-    return fail(KVCOMP_ERR_STATE, "the decompressor met a record larger than its staging area: that block was skipped");
+    return fail(KVCOMP_ERR_STATE, "the decompressor met a record larger than its staging area: that block was filled with NaN");
 }
 
 }  // namespace
@@ -164,7 +166,7 @@ kvcomp_status kvcomp_create(const kvcomp_config *cfg, void *d_arena, size_t aren
     g.payload = c->arena + L.payload;
     g.payload_cap16 = (uint32_t)L.payload_cap16;
     void *pinned = nullptr;
-    const size_t pin_bytes = 256 + 2 * 256 * 4 + 2 * (size_t)kTensorTablesBytes;
+    const size_t refused_at = 256 + 2 * 256 * 4 + 2 * (size_t)kTensorTablesBytes, pin_bytes = refused_at + 64;
     hipError_t e = hipHostMalloc(&pinned, pin_bytes, hipHostMallocDefault);
     if (e != hipSuccess) {
         delete c;
@@ -183,6 +185,9 @@ kvcomp_status kvcomp_create(const kvcomp_config *cfg, void *d_arena, size_t aren
             return fail(KVCOMP_ERR_HIP, "hipHostGetDevicePointer: %s", hipGetErrorString(e));
         }
         c->h_tables_dev = static_cast<uint8_t *>(dev) + 256 + 2048;
+        c->h_refused = reinterpret_cast<volatile uint32_t *>(pb + refused_at);
+        c->h_refused_dev = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(dev) + refused_at);
+        *c->h_refused = 0;
     }
     c->ev_hist[0] = c->ev_hist[1] = nullptr;
     for (int w = 0; w < 2 && e == hipSuccess; w++) e = hipEventCreateWithFlags(&c->ev_hist[w], hipEventDisableTiming);
@@ -657,8 +662,10 @@ static kvcomp_status decompress_impl(kvcomp_ctx *ctx, int which, void *d_out, in
             return fail(KVCOMP_ERR_HIP, "kvcomp_decompress of compressed blocks cannot be captured into a graph");
     }
     // The largest record may have grown, and flags may be up, through flushes since the control words were last read; where
-    // there was none the host knows both, and the stream goes on without a stop (10 us of an idle GPU per tensor).
-    if (ctx->n_blocks && (ctx->flushed || ctx->flush_anytime)) {
+    // there was none the host knows both, and the stream goes on without a stop (10 us of an idle GPU per tensor).  An earlier
+    // decompression that refused a block says so in host memory.
+    if (ctx->n_blocks && (ctx->flushed || ctx->flush_anytime || *ctx->h_refused)) {
+        *ctx->h_refused = 0;
         kvcomp_status st = read_ctrl(ctx, s);
         if (st) return st;
         st = check_flags(ctx, s);
@@ -666,7 +673,7 @@ static kvcomp_status decompress_impl(kvcomp_ctx *ctx, int which, void *d_out, in
     }
     const int stage = (int)align_up((size_t)ctx->max_size16 * 16 + 16, 256);
     HIP_TRY(launch_decompress(ctx->geo, which, static_cast<uint16_t *>(d_out), ctx->n_blocks, ctx->res_head, ctx->n_res,
-                              seq_stride, stage, tree_walk, s));
+                              seq_stride, stage, tree_walk, ctx->h_refused_dev, s));
     return KVCOMP_OK;
 }
 

@@ -117,7 +117,7 @@ struct FastDiv {
 
 // ---- launches implemented in the .hip files ----
 hipError_t launch_decompress(const Geo &g, int which, uint16_t *out, int n_blocks, int res_head, int n_res, int seq_stride,
-                             int stage_bytes, int tree_walk, hipStream_t s);
+                             int stage_bytes, int tree_walk, uint32_t *host_refused, hipStream_t s);
 hipError_t launch_histogram(const Geo &g, int which, const uint16_t *X, int seq_stride, int n_blk_per_bh,
                             uint8_t *codes, uint32_t *minmax, uint16_t *block_hist, hipStream_t s);
 hipError_t launch_encode_kept(const Geo &g, int which, const uint8_t *codes, const uint32_t *mm, const uint16_t *block_hist,

@@ -1223,6 +1223,38 @@ def test_decompression_after_a_flush_that_another_stream_did_not_wait_for(gpu, o
     gc.close()
 
 
+@pytest.mark.parametrize("size16", [600, 0x10000000, 0xffffffff])
+@pytest.mark.parametrize("tree_walk", [False, True])
+def test_refused_block_is_reported_by_the_next_decompression(gpu, oracle, size16, tree_walk):
+    """A Block Offsets Array entry whose size exceeds every staging area (one written over here; the kernel's own check refuses
+    it, also where 16 * size wraps): the block comes out as NaN, the others as they are, and the next decompression, of
+    whichever tensor, reports it once."""
+    import torch
+    _say(f"damaged block entry, size {size16:#x}")
+    B, H, S = 2, 3, 200
+    _, _, oc, gc = _both(gpu, oracle, B, H, H, S, S, 256, 1e-2, 1e-2, 77)
+    off, size = gc.block_entry(K, 1, 2, 1)
+    table = gc.arena[: gc.arena.numel() // 8 * 8].view(torch.int64)
+    at = torch.nonzero(table == off + (size << 32)).flatten().tolist()
+    assert len(at) == 1
+    words = gc.arena[8 * at[0]:8 * at[0] + 8].view(torch.int32)
+    words[1] = size16 - (1 << 32 if size16 >> 31 else 0)
+    assert gc.block_entry(K, 1, 2, 1) == (off, size16)
+    want = oc.decompress(K).view(np.uint16).copy()
+    got = gc.decompress(K, S, tree_walk=tree_walk).cpu().numpy()
+    assert np.isnan(got[1, 64:128, 2]).all()
+    got[1, 64:128, 2] = want.view(np.float16)[1, 64:128, 2]
+    np.testing.assert_array_equal(got.view(np.uint16), want)
+    with pytest.raises(gpu.KvcompError) as e:
+        gc.decompress(V, S, tree_walk=tree_walk)
+    assert e.value.status == gpu.ERR_STATE
+    words[1] = size
+    for w in (K, V):
+        got = gc.decompress(w, S, tree_walk=tree_walk).cpu().numpy()
+        np.testing.assert_array_equal(got.view(np.uint16), oc.decompress(w).view(np.uint16))
+    gc.close()
+
+
 def test_decompression_of_blocks_is_not_captured(gpu, oracle):
     """A graph would freeze the staging area and the block count, so decompressing blocks under capture is refused; the capture
     itself goes on, and decompressing buffered tokens alone can be captured."""
