@@ -7,7 +7,7 @@
 //   1. size pass   : sum the code lengths of the block -> record size into the Block Offsets Array
 //   2. place       : the sizes are scanned in (tensor, batch, head, block) order starting at the arena tail
 //   3. write pass  : encode, write the record at its offset
-// Up to a few thousand records steps 1 and 2 are one launch (place_if_last).
+// As long as it pays, steps 1 and 2 are one launch (place_if_last).
 // Blocks that the fp16 buffer sheds during decoding are quantized by both passes from the buffer (the store side runs
 // once per token block while the fetch side runs every decode step, Section 3.3: the second read of 64 tokens is the
 // cheaper trade against a staging copy of the records).  A prompt goes through the histogram pass first, which keeps
@@ -262,23 +262,23 @@ static void launch_place(const Geo &g, int n_blk_per_bh, int dst_blk0, int tenso
 }
 
 // Size pass and placement in one launch: the workgroup that finishes last (a ticket; the sizes cross the XCDs as in
-// split_combine.cuh) scans all sizes and writes the offsets.  kPlaceRegs items per thread of that workgroup, item
+// split_combine.cuh) scans all sizes and writes the offsets.  REGS items per thread of that workgroup, item
 // c * THREADS + tid in register c, so that loads and stores of the table are coalesced as they are: a scan per wave and
 // register, then one of the wave totals.  A launch and the gap to it cost a short prompt or a flush more than these passes
 // take: 2 x 8 heads x 1000 tokens compressed and read back 128 -> 117 us, 96 tokens appended behind 2000 (three encodings of
-// six launches before, two now) 1120 -> 1093 us, 32 heads x 32768 within its noise.  Up to THREADS * kPlaceRegs records;
-// beyond, one workgroup would have to scan in several rounds, and the launches no longer show.
-constexpr int kPlaceRegs = 16;
-template <int THREADS>
+// six launches before, two now) 1120 -> 1093 us.  Up to THREADS * REGS records: the limits are where one launch stops
+// paying (kSizePlaceItems, kSizePlaceBothItems).
+template <int THREADS, int REGS>
 struct PlaceShared {
-    __attribute__((aligned(16))) uint32_t tot[kPlaceRegs * THREADS / 64];
+    static constexpr int kTotals = REGS * THREADS / 64, kPerLane = (kTotals + 63) / 64;
+    __attribute__((aligned(16))) uint32_t tot[64 * kPerLane];
     uint32_t last, need;
 };
 // rows: the first row of Block Offsets Array entries; by_blk divides by n_blk_per_bh
-template <int THREADS>
+template <int THREADS, int REGS>
 __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, int n_items, int n_blk_per_bh, int dst_blk0,
-                                              const FastDiv &by_blk, PlaceShared<THREADS> &sh) {
-    constexpr int kWaves = THREADS / 64, kPerLane = kPlaceRegs * kWaves / 64;
+                                              const FastDiv &by_blk, PlaceShared<THREADS, REGS> &sh) {
+    constexpr int kWaves = THREADS / 64, kTotals = PlaceShared<THREADS, REGS>::kTotals, kPerLane = PlaceShared<THREADS, REGS>::kPerLane;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t tail0 = g.ctrl->tail16;  // only the last workgroup moves it
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -292,28 +292,27 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
         const int row = (int)by_blk((uint32_t)i);
         return rows + (size_t)row * g.max_blocks + dst_blk0 + (i - row * n_blk_per_bh);
     };
-    uint32_t size[kPlaceRegs], at[kPlaceRegs], biggest = 0;
+    uint32_t size[REGS], at[REGS], biggest = 0;
 #pragma unroll
-    for (int k = 0; k < kPlaceRegs; k++) {
+    for (int k = 0; k < REGS; k++) {
         const int i = k * THREADS + tid;
         size[k] = 0;
         if (k * THREADS >= n_items) continue;  // uniform: few records need few of the registers
         size[k] = i < n_items ? __hip_atomic_load(&entry(i)->size16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     }
 #pragma unroll
-    for (int k = 0; k < kPlaceRegs; k++) {
+    for (int k = 0; k < REGS; k++) {
         at[k] = 0;
         if (k * THREADS < n_items) at[k] = wave_excl_scan(size[k], lane);  // uniform
         if (lane == 63) sh.tot[k * kWaves + wave] = at[k] + size[k];
         biggest = max(biggest, size[k]);
     }
     __syncthreads();
-    static_assert(kPerLane * 64 == kPlaceRegs * kWaves, "whole totals per lane");
-    if (wave == 0) {  // at most 2^14 records of at most 13 KiB: the sums stay far below 2^32 units
+    if (wave == 0) {  // at most 2^13 records of at most 13 KiB: the sums stay far below 2^32 units
         uint32_t t[kPerLane], sum = 0;
 #pragma unroll
         for (int k = 0; k < kPerLane; k++) {
-            t[k] = sh.tot[kPerLane * lane + k];
+            t[k] = kPerLane * lane + k < kTotals ? sh.tot[kPerLane * lane + k] : 0u;
             sum += t[k];
         }
         uint32_t before = wave_excl_scan(sum, lane);
@@ -328,7 +327,7 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
     // a placement that would run past the arena: as in place_scan_kernel
     const bool fits = (unsigned long long)tail0 + sh.need <= (unsigned long long)g.payload_cap16;
 #pragma unroll
-    for (int k = 0; k < kPlaceRegs; k++) {
+    for (int k = 0; k < REGS; k++) {
         const int i = k * THREADS + tid;
         if (k * THREADS < n_items && i < n_items) *entry(i) = {fits ? tail0 + sh.tot[k * kWaves + wave] + at[k] : 0u, size[k]};
     }
@@ -342,13 +341,15 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
     }
 }
 
-// one tensor's sizes from the kept block histograms, and their placement
-constexpr int kSizePlaceThreads = 1024, kSizePlaceItems = kSizePlaceThreads * kPlaceRegs;
+// one tensor's sizes from the kept block histograms, and their placement.  kvcomp_prefill, one launch against three, us by
+// records of a tensor: 512 94.7 and 102, 2048 138 and 150, 4096 167 and 178, 8192 238 and 243, 10240 277.8 and 276.3,
+// 16384 370 and 365: from there on one workgroup's scan takes longer than the launches.
+constexpr int kSizePlaceThreads = 1024, kSizePlaceRegs = 8, kSizePlaceItems = kSizePlaceThreads * kSizePlaceRegs;
 template <int WHICH>
 __global__ __launch_bounds__(kSizePlaceThreads) void size_place_kernel(Geo g, const uint16_t *__restrict__ block_hist,
                                                                        int kept_blk_per_bh, int n_blk_per_bh, FastDiv by_blk) {
     constexpr int kWaves = kSizePlaceThreads / 64;
-    __shared__ PlaceShared<kSizePlaceThreads> sh;
+    __shared__ PlaceShared<kSizePlaceThreads, kSizePlaceRegs> sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_items = g.B * g.H * n_blk_per_bh;
     BlockEntry *table = g.table + (size_t)WHICH * g.B * g.H * g.max_blocks;
@@ -372,20 +373,22 @@ __global__ __launch_bounds__(kSizePlaceThreads) void size_place_kernel(Geo g, co
         if (lane == 0 && item0 + k < n_items)
             __hip_atomic_store(&e[k]->size16, record_size16(Rec<WHICH>::hdr_bytes(g), bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    place_if_last<kSizePlaceThreads>(g, table, n_items, n_blk_per_bh, 0, by_blk, sh);
+    place_if_last(g, table, n_items, n_blk_per_bh, 0, by_blk, sh);
 }
 
-// both tensors' sizes from the fp16 input, and their placement: K's workgroups, then V's
-constexpr int kSizePlaceBothItems = 256 * kPlaceRegs;
+// both tensors' sizes from the fp16 input, and their placement: K's workgroups, then V's.  A workgroup is one record here, and
+// their tickets queue up at one address, 40 ns each.  kvcomp_compress_blocks, two launches against six, us by records of a
+// tensor: 64 34 and 50, 256 39 and 49, 384 49 and 52..60, 512 57..59 and 53..58, 1024 90 and 66, 2048 181 and 89.
+constexpr int kSizePlaceBothRegs = 3, kSizePlaceBothItems = 256 * kSizePlaceBothRegs;
 __global__ __launch_bounds__(256) void size_place_both_kernel(Geo g, const uint16_t *__restrict__ XK,
                                                               const uint16_t *__restrict__ XV, int seq_stride, int n_blk_per_bh,
                                                               int dst_blk0, FastDiv by_blk) {
     __shared__ SizeShared sh;
-    __shared__ PlaceShared<256> place;
+    __shared__ PlaceShared<256, kSizePlaceBothRegs> place;
     const int total = g.B * g.H * n_blk_per_bh, blk = blockIdx.x;
     if (blk < total) size_block<0>(g, XK, seq_stride, n_blk_per_bh, dst_blk0, blk, sh);
     else size_block<1>(g, XV, seq_stride, n_blk_per_bh, dst_blk0, blk - total, sh);
-    place_if_last<256>(g, g.table, 2 * total, n_blk_per_bh, dst_blk0, by_blk, place);
+    place_if_last(g, g.table, 2 * total, n_blk_per_bh, dst_blk0, by_blk, place);
 }
 
 // ---- 3. write pass -----------------------------------------------------------------------------------------

@@ -209,8 +209,9 @@ def test_prefill_is_reproducible(gpu, B, H, S):
     gc.close()
 
 
-# up to 4096 records of both tensors / 16384 of one are placed by the size pass's last workgroup, more by launches of their own
-@pytest.mark.parametrize("B,H,n_blk", [(1, 1, 1), (3, 5, 7), (2, 16, 64), (2, 16, 65), (4, 32, 128), (4, 32, 129)])
+# up to 768 records of both tensors / 8192 of one are placed by the size pass's last workgroup, more by launches of their own
+@pytest.mark.parametrize("B,H,n_blk", [(1, 1, 1), (3, 5, 7), (3, 16, 8), (5, 7, 11), (2, 16, 64), (2, 16, 65), (2, 32, 128), (3, 2731, 1),
+                                       (4, 32, 128), (4, 32, 129)])
 def test_placement_by_the_last_workgroup_and_by_launches(gpu, B, H, n_blk):
     import torch
     _say(f"placement of {B} x {H} x {n_blk} records a tensor")
