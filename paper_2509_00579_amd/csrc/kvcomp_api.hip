@@ -475,6 +475,11 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     // the same with code words of up to 12 bits (n = 20: 30.8 against 29.5) and for groups of 2.  Groups of 4 and 8 have
     // twelve waves at most and gain less, each length at another number.
     if (ctx->tune_waves <= 0 && max_waves == 16 && bps > 16 && bps < 32) max_waves = 12;
+    // Buffered tokens only: two waves per SIMD for groups of 1, 2 and 4.  More only get in each other's way; 4, 8, 12 and 16
+    // waves of groups of 1, 32 heads: 255 tokens 8.0 7.6 9.4 10.7 us, 1000 tokens 19.2 13.7 16.1 17.7, 4000 tokens 75.8 42.7
+    // 47.4 46.9; groups of 4 with 4, 8, 12: 255 10.3 9.2 11.0, 4000 88 48.4 50.0.  Groups of 8 have more work per load: 255
+    // tokens 14.4 12.9 13.8, 1000 33.6 26.4 26.6, 4000 136 83 75.5.
+    if (ctx->tune_waves <= 0 && ctx->n_blocks == 0 && g.G <= 4) max_waves = std::min(max_waves, 8);
     const int n_waves = std::max(1, std::min(max_waves, (paired ? 2 : 1) * bps + units_per_split));
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (ctx->profiling) {
