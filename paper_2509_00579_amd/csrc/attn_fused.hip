@@ -114,7 +114,10 @@ constexpr int tile_first_span(int NS) { return (16 + NS - 1) / NS * NS; }
 // symbols four to a register and issues one matrix instruction per 16 of them.
 //   * A weight w is scaled by a power of two (per block and head) to an integer |W| <= 2^30 and split into four signed
 //     bytes, W = sum_j d_j 256^j, the four rows that a lane group owns; the products are exact in int32 and the four sums
-//     are joined in fp32.  30 bits hold every fp32 weight down to 2^-6 of the block's largest exactly.
+//     are joined in fp32.  30 bits hold every fp32 weight down to 2^-6 of the block's largest exactly and smaller ones to
+//     half a unit, 2^-30 of the largest at most: less than what the rounding of a running fp32 sum over the symbols leaves.
+//     Error of the output against float64 over 8 x 4 x 4 heads x 2048 tokens: 0.34 (groups of 1) and 0.40 (2) of what a
+//     conversion and an FMA per symbol gave.
 //   * the table holds the symbols as int8, from 128 levels on minus `bias` = 128; x' = min + step * code =
 //     (min + bias * step) + step * (code - bias), so the bias only enters the constant term.
 // 32 heads x 32768 tokens: 1098 instead of 1454 vector instructions per block pair, 58.6 -> 53.5 us a step together with
@@ -141,8 +144,8 @@ __device__ __forceinline__ float dot_scale(float amax, float *inv) {
     *inv = __uint_as_float((uint32_t)(127 - up) << 23);
     return __uint_as_float((uint32_t)(127 + up) << 23);
 }
-// bytes 0..3: the signed digits of W
-__device__ __forceinline__ uint32_t four_digits(float w) { return ((uint32_t)(int)w + 0x00808080u) ^ 0x00808080u; }
+// bytes 0..3: the signed digits of W = w rounded to nearest (cut off, the weights' errors would all have one sign)
+__device__ __forceinline__ uint32_t four_digits(float w) { return ((uint32_t)(int)rintf(w) + 0x00808080u) ^ 0x00808080u; }
 __device__ __forceinline__ float join_four(const v4i &d) {
     return fmaf(fmaf(fmaf((float)d.w, 256.f, (float)d.z), 256.f, (float)d.y), 256.f, (float)d.x);
 }

@@ -521,6 +521,30 @@ def test_integer_dot_products_of_groups_of_1_and_2(gpu, oracle, G, rel, limit):
     gc.close()
 
 
+@pytest.mark.parametrize("G", [1, 2])
+def test_small_weights_beside_a_large_one_are_rounded(gpu, oracle, G):
+    """One channel's weight is 2^24 times the others', so that those are integers of about 100 on the block's scale (unit 2^-20).
+    Half of the tokens have code 50 in all 127 of them and differ from the other half by the error of the weights alone: rounded
+    to nearest, 0.29 * sqrt(127) * 50 units = 1.6e-4 of the score in the mean, cut off 0.5 * 127 * 50 units = 3e-3.  The output
+    moves by half of it: 5 of the former, 4e-4, is the bar."""
+    _say(f"small weights beside a large one, groups of {G}")
+    S = 64
+    Kx, Vx = np.zeros((1, S, 1, 128), np.float16), np.ones((1, S, 1, 128), np.float16)
+    Kx[0, 1::2, 0, 1:] = 1.0          # codes 0 and 50
+    Kx[0, 32:, 0, 0] = 1.0            # these tokens' scores are far below the others'
+    Vx[0, 1::2] = -1.0
+    q = np.random.default_rng(5).uniform(1e-3, 4e-3, (1, G, 128)).astype(np.float16)
+    q[..., 0] = -32768.0
+    oc = oracle.OracleCache(1, 1, G, S, 1e-2, 1e-2, 0, 12)
+    gc = gpu.KVCompCache(1, 1, G, S, 1e-2, 1e-2)
+    for c, dev in ((oc, lambda x: x), (gc, _dev)):
+        c.build_codebook(dev(Kx), dev(Vx))
+        c.compress_blocks(dev(Kx), dev(Vx))
+    err = np.abs(gc.attn_decode(_dev(q), 1.0).cpu().numpy() - oc.attn_decode(q, 1.0)).max()
+    assert err <= 4e-4, err
+    gc.close()
+
+
 def test_many_sequence_splits(gpu, oracle):
     """One long sequence with a single KV head: the library splits it 128 ways (its maximum) so that the chip is
     filled; every split count gives the oracle's result, also when the last split is short or the buffer holds
