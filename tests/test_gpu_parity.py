@@ -569,15 +569,18 @@ def test_many_sequence_splits(gpu, oracle):
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
-def test_split_merge_at_range_edges(gpu, oracle, G):
-    _say(f"splits merged in one and in several ranges; groups of {G}")
-    B, H, S = 1, 1, 64 * 130
+@pytest.mark.parametrize("n_blocks,splits", [(130, (2, 15, 17, 33, 65)), (128, (16, 32, 64, 128))])
+def test_split_merge_at_range_edges(gpu, oracle, G, n_blocks, splits):
+    _say(f"splits merged in one and in several ranges; groups of {G}, {n_blocks} blocks")
+    B, H, S = 1, 1, 64 * n_blocks
     _, _, oc, gc = _both(gpu, oracle, B, H, G * H, 256, S, S, 1e-2, 1e-2, 62, 6)
     q = W.make_queries(B, G * H, 1, 62)[0]
     ref = np.asarray(oc.attn_decode(q, SCALE), np.float64)
     # waves of a workgroup to a head, batches of 16 splits, the second split of a lane (beyond 64).  A split left out or
     # with another's weight is off by 1e-2 and more; the integer weights of groups of 4 and 8 by up to 2e-4.
-    for n_splits in (2, 15, 16, 17, 33, 64, 65, 128):
+    for n_splits in splits:
+        per_split = -(-n_blocks // n_splits)
+        assert -(-n_blocks // per_split) == n_splits, "the launch has as many splits as asked for"
         for waves in (0, 1, 5):
             gc.set_tuning(n_splits=n_splits, waves=waves)
             out = gc.attn_decode(_dev(q), SCALE).cpu().numpy().astype(np.float64)
@@ -1190,15 +1193,29 @@ def test_stand_alone_decompression(gpu, oracle, B, H, S, k_mode, max_len):
     gc.close()
 
 
+def _staging(oc):
+    """the staging area that the largest record of the cache asks for"""
+    largest = max((16 * int(oc.size16[w][:, :oc.n_blocks].max()) for w in (K, V)), default=0) if oc.n_blocks else 0
+    return (largest + 16 + 255) // 256 * 256
+
+
+def _rare_tokens(B, H, n, seed):
+    """tokens whose codes lie at both ends: long code words of a codebook that was built on normal samples"""
+    rng = np.random.default_rng(seed)
+    shape = (n, B, H, 128)
+    return [(rng.choice([-1.0, 1.0], shape) * rng.uniform(0.9, 1.0, shape)).astype(np.float16) for _ in range(2)]
+
+
+@pytest.mark.parametrize("look", [False, True])
 @pytest.mark.parametrize("B,H,S,rel,limit", [(1, 3, 192, 2e-3, 8), (1, 1, 320, 2e-3, 12), (3, 1, 130, 1e-2, 6),
                                              (1, 5, 64, 5e-3, 10), (1, 2, 63, 1e-2, 12)])
-def test_decompression_widths_and_partial_workgroups(gpu, oracle, B, H, S, rel, limit):
+def test_decompression_widths_and_partial_workgroups(gpu, oracle, B, H, S, rel, limit, look):
     """Every table width, more than 128 levels (codes beyond int8), block counts that leave waves of the last workgroup
-    idle or that are none, and a flush between two decompressions with a statistics call, which reads the control words,
-    in between: a larger record than before must still find its staging area.  Bit for bit against the oracle."""
+    idle or that are none, and a flush between two decompressions that makes a record outgrow the staging area of before, with
+    a statistics call, which reads the control words, in between (look) and without.  Bit for bit against the oracle."""
     Kx, Vx, oc, gc = _both(gpu, oracle, B, H, H, max(S, 64), S, S + 64, rel, rel, seed=71, limit=limit)
-    kn, vn = W.make_new_tokens(B, H, 64, 72)
-    kn, vn = (kn * 50).astype(np.float16), (vn ** 3).astype(np.float16)  # rare codes: longer records
+    kn, vn = _rare_tokens(B, H, 64, 72)
+    staging = _staging(oc)
     for step in range(2):
         for which in (K, V):
             got = gc.decompress(which, oc.n_blocks * 64 + oc.n_res).cpu().numpy()
@@ -1207,7 +1224,44 @@ def test_decompression_widths_and_partial_workgroups(gpu, oracle, B, H, S, rel, 
             for t in range(64):
                 oc.append_token(kn[t], vn[t])
                 gc.append_token(_dev(kn[t]), _dev(vn[t]))
-            gc.stats()
+            assert _staging(oc) > staging or limit == 8   # 251 levels in 8 bits: no code word is much longer than another
+            if look:
+                gc.stats()
+    gc.close()
+
+
+def test_decompression_after_replays_of_a_captured_flush(gpu, oracle):
+    """A flush inside a graph enlarges a record whenever the graph is replayed, and the host does not see it: decompression
+    looks at the control words every time from then on.  Replays start from the state of the capture and are followed by an
+    eager refill, as the interface asks."""
+    import torch
+    _say("decompression around replays of a captured flush")
+    B, H = 1, 2
+    Kx, Vx, oc, gc = _both(gpu, oracle, B, H, H, 64, 64, 192, 5e-3, 5e-3, seed=78, limit=10)
+    kn, vn = _rare_tokens(B, H, 64, 79)
+    dK, dV, dkn, dvn = _dev(Kx), _dev(Vx), _dev(kn), _dev(vn)
+    before = [oc.decompress(w).view(np.uint16).copy() for w in (K, V)]
+    staging = _staging(oc)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for t in range(64):
+            gc.append_token(dkn[t], dvn[t])
+    for t in range(64):
+        oc.append_token(kn[t], vn[t])
+    assert _staging(oc) > staging
+    for _ in range(3):
+        gc.reset()
+        gc.compress_blocks(dK, dV)
+        graph.replay()
+        for w in (K, V):    # the host's view: the first block
+            assert np.array_equal(gc.decompress(w, 64).cpu().numpy().view(np.uint16), before[w])
+        gc.reset()
+        gc.compress_blocks(dK, dV)
+        for t in range(64):
+            gc.append_token(dkn[t], dvn[t])
+        for w in (K, V):
+            np.testing.assert_array_equal(gc.decompress(w, 128).cpu().numpy().view(np.uint16), oc.decompress(w).view(np.uint16))
     gc.close()
 
 
