@@ -159,7 +159,8 @@ kvcomp_status kvcomp_attn_decode(kvcomp_ctx *ctx, const void *d_q, float scale, 
 kvcomp_status kvcomp_append_attn_decode(kvcomp_ctx *ctx, const void *d_k_new, const void *d_v_new, const void *d_q,
                                         float scale, float *d_out, void *stream);
 
-/* ---- metrics, parity and debug exports (these SYNCHRONISE `stream` and copy to HOST buffers) ------------- */
+/* ---- metrics, parity and debug exports -------------------------------------------------------------------
+ * Those with h_* buffers SYNCHRONISE `stream` and copy to them; kvcomp_decompress says when it does. */
 
 /* Also reports, once, what kernels flagged since the last synchronising call: NONFINITE (an appended token held Inf
  * or NaN), CAPACITY (a flush found the record arena full and wrote nothing: only a captured flush replayed without

@@ -198,7 +198,8 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_kernel(int B, i
 //   hold fp32's 24 bits of a numerator near 1, four hold them down to 2^-34.  The parts are the A rows G apart (the copies of
 //   the score columns are there for that) and are added at the end; groups of 8 have rows for two, and the other two take
 //   a second product per operand.  With two parts only, a numerator of e^-14 had 16 bits and one of e^-24 none.
-// The loop keeps a tile of 64 V rows and the next tile of K rows on their way (16 to 32 KiB a wave, two waves per SIMD).
+// The loop keeps a tile of 64 V rows and the next tile of K rows on their way (16 to 32 KiB a wave; registers for two waves
+// per SIMD, the host starts one unless there are more heads than CUs).
 // With p . V on the vector ALU, 8 FMAs per value for groups of 8, and the numerators through LDS, it was bound by the ALU:
 // 8 x 8 heads x 16384 tokens, groups of 8: 121 us (4.4 TB/s) -> 104 us (5.2 TB/s; a plain read reaches 6.0); groups of 4,
 // 16 x 8 heads x 8192: 103 -> 99 us.  Four parts instead of two cost nothing there (107.6 and 107.5 us in one run).

@@ -121,7 +121,8 @@ constexpr int tile_first_span(int NS) { return (16 + NS - 1) / NS * NS; }
 //   * the table holds the symbols as int8, from 128 levels on minus `bias` = 128; x' = min + step * code =
 //     (min + bias * step) + step * (code - bias), so the bias only enters the constant term.
 // 32 heads x 32768 tokens: 1098 instead of 1454 vector instructions per block pair, 58.6 -> 53.5 us a step together with
-// the shorter prologue (the LDS pipe is the busier unit: 82 % of the busy cycles, its table lookups conflict); groups of 2,
+// the shorter prologue (the LDS pipe is the busier unit: active in 82 % of the busy cycles, 5.8 cycles a wave-symbol of which
+// 4.0 are bank conflicts of the table lookups); groups of 2,
 // 3 x 8 heads x 12345 tokens, code words of up to 12 bits: 40.7 -> 32.0 us.  A conversion and an FMA per symbol and head,
 // as before, spent half of the loop's vector instructions on them.
 typedef int v4i __attribute__((ext_vector_type(4)));

@@ -450,7 +450,7 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     const int wgs_per_cu = std::max(1, std::min(reg_waves / max_waves,
                                                 (int)(kLdsBytesPerCU / (lds_fixed + max_waves * ((size_t)stage + per_wave_rest)))));
     int n_splits = ctx->tune_splits;
-    if (n_splits <= 0) {
+    if (n_splits <= 0) {  // measured with a wave per pair, not again with one per record
         const int bh = g.B * g.H;
         const int by_chip = std::max(1, kCUs * wgs_per_cu / bh);
         const int by_work = std::max(1, (ctx->n_blocks + 3) / 4);  // at least one block pair per SIMD of the CU
@@ -465,8 +465,9 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     // sharing, so it ends at three waves per SIMD: 32 heads in 8 splits of n pairs, one query head per KV head, code words
     // of up to 6 bits, n = 1 2 4 6 7 8: 8.9 8.8 9.7 11.3 12.4 13.0 us against 12.4 11.1 11.0 12.6 12.7 13.2; groups of 4,
     // n = 2 4 6: 12.2 11.5 13.4 against 17.1 14.3 16.4; groups of 8: 16.6 14.7 16.7 against 24.5 19.4 20.5.  Groups of 1 and
-    // 2 with longer code words keep two waves per SIMD (their 128 registers do not hold a whole decoded block beside the
-    // lookups in flight): n = 4 6 8: 12.1 15.3 20.0 against 12.9 14.9 15.7.
+    // 2 with longer code words end at two waves per SIMD: n = 4 6 8: 12.1 15.3 20.0 against 12.9 14.9 15.7.  Their kernels are
+    // compiled for the same sixteen waves as the unpaired ones, and a whole decoded block beside the lookups in flight does not
+    // fit the 128 registers of that (17 to 31 spilled); eight waves could have 256 each.
     const int paired_waves = std::min(max_waves, fused_table_bits(longest) == 6 || g.G >= 4 ? 12 : 8);
     const bool paired = bps > 0 && 2 * bps + units_per_split <= paired_waves;
     // Sixteen waves (groups of 1 and 2) that have more than one pair each but not two leave a last round of a few waves that

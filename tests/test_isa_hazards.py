@@ -1,9 +1,10 @@
 """Checks on the gfx950 assembly that hipcc generates for the fused kernel (no GPU needed).
 
-The query-weight broadcast of the fused kernel is a DPP modifier on v_fmac_f32, written as inline assembly.  The
-CDNA ISA asks for two wait states between a VALU instruction that writes a VGPR and a DPP instruction that reads
-it; the hardware does not interlock and the compiler's hazard recogniser does not look into inline assembly.  The
-weights come from LDS reads, so no such pair should exist: this test fails if a compiler change ever creates one.
+The products of the buffered tokens' softmax numerators with V take the numerator from another lane of the row with a DPP
+modifier on v_fmac_f32, written as inline assembly.  The CDNA ISA asks for two wait states between a VALU instruction that
+writes a VGPR and a DPP instruction that reads it; the hardware does not interlock and the compiler's hazard recogniser does
+not look into inline assembly.  An s_nop stands between the numerators and their first use, so no such pair should exist:
+this test fails if a compiler change ever creates one (a register copy in between, say).
 The walk follows the control flow backwards (fall-through and every branch into a label), not just the text order.
 """
 import re
