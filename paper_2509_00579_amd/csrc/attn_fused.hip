@@ -1349,12 +1349,15 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
                 ow[k] = cw[c];
                 mx = fmaxf(mx, mw[k]);
             }
+            // the loads stay together, in front of the branches (selects or loads behind them cost groups of 8 0.6 us)
+            asm volatile("" : "+v"(lw[0]), "+v"(lw[1]), "+v"(lw[2]), "+v"(lw[3]), "+v"(ow[0]), "+v"(ow[1]), "+v"(ow[2]), "+v"(ow[3]));
             if (mx == -INFINITY) continue;  // waves that had nothing to do
             const float f0 = __expf(M_ - mx);
             L *= f0;
             O *= f0;
 #pragma unroll
             for (int k = 0; k < 4; k++) {
+                if (w0 + k >= n_waves) break;  // uniform.  A copy of the last wave's sums: 0 times them is NaN if they are Inf
                 const float f = __expf(mw[k] - mx);  // 0 for a wave that had nothing to do
                 L = fmaf(lw[k], f, L);
                 O = fmaf(ow[k], f, O);

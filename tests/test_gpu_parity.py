@@ -469,6 +469,31 @@ def test_scores_of_buffered_tokens_are_summed_in_a_tree(gpu, G):
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("S", [20, 64 * 2 + 20])
+def test_infinities_in_the_v_of_buffered_tokens(gpu, oracle, G, S):
+    """A buffered token is taken as it is, Inf in V included: every head gets Inf in that channel, however many waves there are
+    to merge, and the other channels do not notice."""
+    _say(f"Inf in V of buffered tokens, groups of {G}, {S} tokens")
+    B, H = 1, 2
+    _, _, oc, gc = _both(gpu, oracle, B, H, G * H, 64, S, 256, 1e-2, 1e-2, 64)
+    kn, vn = W.make_new_tokens(B, H, 2, 64)
+    for t in range(2):
+        oc.append_token(kn[t], vn[t])
+    vn[0, 0, :, 5], vn[1, 0, :, 99] = np.inf, -np.inf
+    for t in range(2):
+        gc.append_token(_dev(kn[t]), _dev(vn[t]))
+    q = W.make_queries(B, G * H, 1, 64)[0]
+    ref = np.array(oc.attn_decode(q, SCALE))
+    ref[..., 5], ref[..., 99] = np.inf, -np.inf
+    for n_splits in (1, 2):
+        for waves in (0, 1, 2, 3, 4, 5, 6, 7, 8):
+            gc.set_tuning(n_splits=n_splits, waves=waves)
+            out = gc.attn_decode(_dev(q), SCALE).cpu().numpy()
+            np.testing.assert_allclose(out, ref, rtol=0, atol=1e-3, err_msg=f"{n_splits} {waves}")
+    gc.close()
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
 @pytest.mark.parametrize("limit", [6, 12])
 def test_a_wave_for_each_record_of_a_pair(gpu, oracle, G, limit):
     _say(f"K and V records of a pair on two waves, and on one; groups of {G}, code words of up to {limit} bits")
