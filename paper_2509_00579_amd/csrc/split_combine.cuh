@@ -80,7 +80,9 @@ __device__ __forceinline__ void finish_splits(float *partials, uint32_t *counter
         request(0);
         float mx = fmaxf(m0, m1);
         mx = wave_max(mx);
-        // a split that had nothing to do (m = -inf) takes no part, whatever its words are
+        // a split that had nothing to do, or whose tokens all score -inf (m = -inf), takes no part, whatever its words are
+        if (m0 == -INFINITY) l0 = 0.f;
+        if (m1 == -INFINITY) l1 = 0.f;
         const unsigned long long live0 = __builtin_amdgcn_ballot_w64(m0 != -INFINITY),
                                  live1 = __builtin_amdgcn_ballot_w64(m1 != -INFINITY);
         const float f0 = m0 == -INFINITY ? 0.f : __expf(m0 - mx), f1 = m1 == -INFINITY ? 0.f : __expf(m1 - mx);

@@ -1044,6 +1044,27 @@ def test_fp16_attention_with_infinities_in_v(gpu, G, S):
             np.testing.assert_allclose(out.cpu().numpy()[0], ref, rtol=0, atol=1e-5, err_msg=f"{ramp} {n_splits}")
 
 
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("n_splits,dead", [(2, [1]), (4, [0, 2]), (20, list(range(3, 19)))])
+def test_fp16_attention_of_splits_that_score_minus_infinity(gpu, G, n_splits, dead):
+    """Splits whose tokens all have score -Inf (K holds -Inf where every query is positive) take no part in the merge."""
+    import torch
+    B, H, S = 1, 2, 256 * n_splits
+    rng = np.random.default_rng(n_splits + G)
+    Kx, Vx = (rng.standard_normal((B, S, H, 128)).astype(np.float16) for _ in range(2))
+    q = rng.standard_normal((B, H * G, 128)).astype(np.float16)
+    q[..., 17] = 1.0
+    live = np.ones(S, bool)
+    for s in dead:
+        Kx[0, 256 * s:256 * (s + 1), :, 17] = -np.inf
+        live[256 * s:256 * (s + 1)] = False
+    out = gpu.BaselineFp16Attention(B, H, H * G)(_dev(Kx), _dev(Vx), _dev(q), 0.125, n_splits=n_splits).cpu().numpy()
+    k64, v64, q64 = (torch.from_numpy(x.astype(np.float64)) for x in (Kx[:, live], Vx[:, live], q))
+    for g in range(H * G):
+        ref = (torch.softmax(k64[0, :, g // G] @ q64[0, g] / 8, 0) @ v64[0, :, g // G]).numpy()
+        assert np.abs(out[0, g] - ref).max() <= 1e-5, g
+
+
 def test_config1_full_size_sampled(gpu, oracle):
     """The benchmark workload (32 heads x 4096 tokens) in the launch configuration bench.py times."""
     w = W.CONFIGS["c1"]
