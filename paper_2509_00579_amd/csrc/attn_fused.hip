@@ -909,9 +909,10 @@ __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens
             });
         }
         m = mnew;
+        const float ref = m == -INFINITY ? 0.f : m;  // so far every token scored -inf: numerators of 0
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-            p[r] = __expf(p[r] - m);
+            p[r] = __expf(p[r] - ref);
             l += p[r];
         }
         row_operand(p[0], p[1], p[2], p[3]);
@@ -938,8 +939,8 @@ __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens
     if (col < G) {
         float *ml = area + G * kD + 3 * col;
         const float ma = ml[0], mx = fmaxf(ma, m);
-        fa = __expf(ma - mx);  // 0 for a state that is still empty
-        fb = __expf(m - mx);
+        fa = ma == -INFINITY ? 0.f : __expf(ma - mx);  // 0 for a state that is still empty
+        fb = m == -INFINITY ? 0.f : __expf(m - mx);
         const float l1 = fmaf(ml[1], fa, l * fb), bv1 = ml[2] * fa;
         wave_sync();
         if (grp == 0) { ml[0] = mx; ml[1] = l1; ml[2] = bv1; }

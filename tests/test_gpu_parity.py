@@ -494,6 +494,28 @@ def test_infinities_in_the_v_of_buffered_tokens(gpu, oracle, G, S):
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("S", [16, 64 + 16, 64 * 3 + 32])
+def test_buffered_tokens_that_score_minus_infinity(gpu, oracle, G, S):
+    """Buffered tokens with score -Inf (K holds -Inf where every query is positive) take no part, also where they fill a unit
+    of 16 by themselves: the output is that of the cache without them."""
+    _say(f"buffered tokens that score -Inf, groups of {G}, {S} tokens")
+    B, H = 1, 2
+    _, _, oc, gc = _both(gpu, oracle, B, H, G * H, 64, S, 256, 1e-2, 1e-2, 65)
+    kn, vn = W.make_new_tokens(B, H, 17, 65)
+    kn[..., 30] = -np.inf
+    q = W.make_queries(B, G * H, 1, 65)[0]
+    q[..., 30] = 1.0
+    ref = np.array(oc.attn_decode(q, SCALE))
+    for t in range(17):                        # a unit of their own, then one behind it
+        _attn_close(gc.append_attn_decode(_dev(kn[t]), _dev(vn[t]), _dev(q), SCALE).cpu().numpy(), ref)
+    for n_splits in (1, 2):
+        for waves in (0, 1, 2, 3, 5, 8):
+            gc.set_tuning(n_splits=n_splits, waves=waves)
+            _attn_close(gc.attn_decode(_dev(q), SCALE).cpu().numpy(), ref)
+    gc.close()
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
 @pytest.mark.parametrize("limit", [6, 12])
 def test_a_wave_for_each_record_of_a_pair(gpu, oracle, G, limit):
     _say(f"K and V records of a pair on two waves, and on one; groups of {G}, code words of up to {limit} bits")
