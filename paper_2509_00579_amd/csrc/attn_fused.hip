@@ -898,8 +898,9 @@ __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens
             mu = fmaxf(mu, p[r]);
         }
         const float mnew = fmaxf(m, max_over_rows(mu));
+        const float ref = mnew == -INFINITY ? 0.f : mnew;  // so far every token scored -inf: numerators of 0
         if (u != first_unit && __builtin_amdgcn_ballot_w64(mnew > m) != 0) {
-            const float alpha = __expf(m - mnew);
+            const float alpha = __expf(m - ref);
             l *= alpha;
             for_heads<G>([&](auto gc) {
                 constexpr int g = decltype(gc)::value;
@@ -909,7 +910,6 @@ __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens
             });
         }
         m = mnew;
-        const float ref = m == -INFINITY ? 0.f : m;  // so far every token scored -inf: numerators of 0
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             p[r] = __expf(p[r] - ref);

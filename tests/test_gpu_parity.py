@@ -515,6 +515,28 @@ def test_buffered_tokens_that_score_minus_infinity(gpu, oracle, G, S):
     gc.close()
 
 
+@pytest.mark.parametrize("G", [2, 4, 8])
+def test_units_that_score_minus_infinity_for_one_head_only(gpu, oracle, G):
+    """Two units of buffered tokens on the wave that has the blocks: all tokens score -Inf for the even heads, those of the
+    second unit +Inf for the odd ones, whose reference moves.  The even heads' output is that of the blocks alone."""
+    _say(f"units that score -Inf for one head only, groups of {G}")
+    B, H = 1, 2
+    _, _, oc, gc = _both(gpu, oracle, B, H, G * H, 64, 64, 256, 1e-2, 1e-2, 66)
+    kn, vn = W.make_new_tokens(B, H, 32, 66)
+    kn[:16, ..., 30] = kn[16:, ..., 31] = -np.inf
+    q = W.make_queries(B, G * H, 1, 66)[0]
+    q[..., 30:32] = 1.0
+    q[:, 1::2, 31] = -1.0
+    ref = np.array(oc.attn_decode(q, SCALE))
+    for t in range(32):
+        gc.append_token(_dev(kn[t]), _dev(vn[t]))
+    for waves in (1, 2, 3, 8):
+        gc.set_tuning(n_splits=1, waves=waves)
+        out = gc.attn_decode(_dev(q), SCALE).cpu().numpy()
+        _attn_close(out[:, ::2], ref[:, ::2])
+    gc.close()
+
+
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 @pytest.mark.parametrize("limit", [6, 12])
 def test_a_wave_for_each_record_of_a_pair(gpu, oracle, G, limit):
