@@ -101,33 +101,31 @@ struct Soft {
     }
 };
 
-// first symbol that the second span of a block decodes when the products run after each half: the first half's
-// windows are whole, so they may reach into the second half
-constexpr int tile_first_span(int NS) { return (16 + NS - 1) / NS * NS; }
-
 // ---- groups of 1 and 2 query heads: a dot product per lane on the matrix cores ------------------------------------
 // Every lane needs the products of ITS OWN decoded symbols with wave-uniform weights (K: token x channels, V: channel x
-// tokens).  v_mfma_i32_16x16x64_i8 computes D[row][col] = sum over the lane groups g = 0..3 of A[lane (g,row)] .
-// B[lane (g,col)], 16 bytes a lane, and lane (g,col) receives rows 4g .. 4g+3 of column col.  With A non-zero only in
-// the lanes (g,row) with row / 4 == g the groups do not mix: register j of lane l is the dot product of digit row j of the
-// weights with lane l's own 16 symbols.  No lane exchange, no conversion and no FMA per symbol: the wave packs the decoded
-// symbols four to a register and issues one matrix instruction per 16 of them.
+// tokens).  v_mfma_i32_4x4x4_16b_i8 multiplies sixteen pairs of 4 x 4 matrices, one for each block of four lanes: register i
+// of lane l receives sum_k A[i][k] B[k][l % 4], where lane 4b + i holds row i of its block's A and lane l its own column of
+// B, four bytes each.  So B is a lane's four packed symbols as they are, A the four digit rows of the weights of these
+// four positions, and register i of every lane the dot product of digit row i with the lane's own symbols.  A must be the
+// same in all sixteen blocks, and the instruction's broadcast takes it from one of them: block b of ONE register holds
+// positions 4b .. 4b + 3, which is what one 4 x 4 byte transposition inside the quads of lanes leaves of a register that holds
+// the digits of position l in lane l.  Word w of a slice is multiplied with block w as soon as it is packed: no lane exchange, no
+// conversion, no FMA per symbol, no weights in LDS, and no word waits in a register.
 //   * A weight w is scaled by a power of two (per block and head) to an integer |W| <= 2^30 and split into four signed
-//     bytes, W = sum_j d_j 256^j, the four rows that a lane group owns; the products are exact in int32 and the four sums
+//     bytes, W = sum_j d_j 256^j, the four rows; the products are exact in int32 and the four sums
 //     are joined in fp32.  30 bits hold every fp32 weight down to 2^-6 of the block's largest exactly and smaller ones to
 //     half a unit, 2^-30 of the largest at most: less than what the rounding of a running fp32 sum over the symbols leaves.
 //     Error of the output against float64 over 8 x 4 x 4 heads x 2048 tokens: 0.34 (groups of 1) and 0.40 (2) of what a
 //     conversion and an FMA per symbol gave.
 //   * the table holds the symbols as int8, from 128 levels on minus `bias` = 128; x' = min + step * code =
 //     (min + bias * step) + step * (code - bias), so the bias only enters the constant term.
-// 32 heads x 32768 tokens: 1098 instead of 1454 vector instructions per block pair, 58.6 -> 53.5 us a step together with
-// the shorter prologue (the LDS pipe is the busier unit: active in 82 % of the busy cycles, 5.8 cycles a wave-symbol of which
-// 4.0 are bank conflicts of the table lookups); groups of 2,
-// 3 x 8 heads x 12345 tokens, code words of up to 12 bits: 40.7 -> 32.0 us.  A conversion and an FMA per symbol and head,
-// as before, spent half of the loop's vector instructions on them.
+// 32 heads x 32768 tokens, 16384 block pairs: a conversion and an FMA per symbol 58.6 us a step, v_mfma_i32_16x16x64_i8 with the
+// digits in LDS and three quarters of the A operand zero 50.6, this 50.8, with eight words of a half block fewer in registers:
+// groups of 2 with code words of up to 10 bits spilled 22 values and took 38.1 us (3 x 8 heads x 12345 tokens), now none and
+// 29.2.  The LDS pipe is what is full here (1290 of its cycles a block pair, three quarters of them table lookups).
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-// power of two f = 2^up that brings the largest |weight| of the wave into [2^29, 2^30); *inv = 1 / f.  All in scalar
+// power of two f = 2^up that brings the largest |weight| of the wave into [2^(BITS-1), 2^BITS); *inv = 1 / f.  All in scalar
 // registers: the bit patterns of non-negative floats are ordered like the floats.
 __device__ __forceinline__ uint32_t wave_max_bits(float v) {
     v = fmaxf(v, dpp_f<kDppXor1>(v));
@@ -139,159 +137,119 @@ __device__ __forceinline__ uint32_t wave_max_bits(float v) {
                    c = __builtin_amdgcn_readlane(u, 32), d = __builtin_amdgcn_readlane(u, 48);
     return max(max(a, b), max(c, d));
 }
-__device__ __forceinline__ float dot_scale(float amax, float *inv) {
+template <int BITS>
+__device__ __forceinline__ float int_scale(float amax, float *inv) {
     const int e = (int)(wave_max_bits(amax) >> 23) - 126;  // amax = m * 2^e, m in [0.5, 1)
-    const int up = min(30 - e, 120);
+    const int up = min(BITS - e, 120);
     *inv = __uint_as_float((uint32_t)(127 - up) << 23);
     return __uint_as_float((uint32_t)(127 + up) << 23);
 }
 // bytes 0..3: the signed digits of W = w rounded to nearest (cut off, the weights' errors would all have one sign)
 __device__ __forceinline__ uint32_t four_digits(float w) { return ((uint32_t)(int)rintf(w) + 0x00808080u) ^ 0x00808080u; }
+// sums of at most 128 products of two bytes stay below 2^21, so two neighbouring digits' sums join in an int
 __device__ __forceinline__ float join_four(const v4i &d) {
-    return fmaf(fmaf(fmaf((float)d.w, 256.f, (float)d.z), 256.f, (float)d.y), 256.f, (float)d.x);
+    return fmaf((float)(d.z + d.w * 256), 65536.f, (float)(d.x + d.y * 256));
 }
-// Where a lane reads its piece of the A operand: digit row lane % 4 if its matrix row belongs to its lane group, else
-// zeros.  digits: this head's four rows in the wave's LDS area; zeros: kDigitRow zero bytes.
-__device__ __forceinline__ const uint8_t *a_piece(const uint8_t *digits, const uint8_t *zeros, int lane) {
-    const int row = lane & 15;
-    return (row >> 2) == (lane >> 4) ? digits + (row & 3) * kDigitRow : zeros;
-}
-__device__ __forceinline__ v4i a_step(const uint8_t *piece, int pos) { return *reinterpret_cast<const v4i *>(piece + pos); }
-__device__ __forceinline__ v4i b_step(const uint32_t (&w)[16], int step) {
-    const v4i r = {(int)w[4 * step], (int)w[4 * step + 1], (int)w[4 * step + 2], (int)w[4 * step + 3]};
-    return r;
-}
-// where this lane's word of digits goes after the transposition: row lane % 4, columns 4 (lane / 4) .. + 3
-__device__ __forceinline__ uint32_t *digit_slot(uint8_t *digits, int lane) {
-    return reinterpret_cast<uint32_t *>(digits + (lane & 3) * kDigitRow + (lane & ~3));
+// adds the products of word W of a slice with the weights of its four positions (see above) to the lane's digit sums
+template <int W>
+__device__ __forceinline__ void add_products(v4i &d, uint32_t digits, uint32_t word) {
+    d = __builtin_amdgcn_mfma_i32_4x4x4i8((int)digits, (int)word, d, 4, W, 0);
 }
 
 // ---- K block: lane = token; its two slices are channels 0..63 and 64..127 ------------------------------------------
-// hdr32: the record (LDS or global); digits: this wave's LDS weight area.  Leaves scale * q.k' of this lane's token in
+// hdr32: the record (LDS or global).  Leaves scale * q.k' of this lane's token in
 // score[].  LB: the table width the kernel is compiled for (see DecodeMode).
 template <int G, int LB, class F>
-__device__ __forceinline__ void k_block(const uint32_t *hdr32, const char *lut, uint32_t mask, uint8_t *digits,
-                                        const uint8_t *zeros, const float (&qreg)[G][2], float two_eb, float bias,
-                                        float scale, int lane, int kmm, float (&score)[G], F &&record_done) {
+__device__ __forceinline__ void k_block(const uint32_t *hdr32, const char *lut, uint32_t mask, const float (&qreg)[G][2],
+                                        float two_eb, float bias, float scale, int lane, int kmm, float (&score)[G],
+                                        F &&record_done) {
     static_assert(G < kTileMinG, "groups of 4 and 8 take the tile path");
     // lane c holds the weights of channels c and c + 64.  kmm = bytes of the {min,max} pairs in the header: 512 (one pair
     // per channel) or 16 (BlockQuant: one pair for the whole block)
     const bool per_channel = kmm == kMinMaxBytesK;
     const uint32_t mm0 = hdr32[per_channel ? lane : 0], mm1 = hdr32[per_channel ? lane + 64 : 0];
+    const uint32_t sb = hdr32[kmm / 4 + lane];  // bit counts of slices 2*lane and 2*lane+1
+    const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
+    const Unit *units = payload_units(hdr32 + (kmm + 2 * kSlices) / 4);
+    Quad<DecodeMode<LB>::J> qd;
+    qd.open(units, start, sb & 0xffffu, sb >> 16);
     const float mn0 = h2f(mm0 & 0xffffu), mn1 = h2f(mm1 & 0xffffu);
     const float st0 = two_eb * (h2f(mm0 >> 16) - mn0), st1 = two_eb * (h2f(mm1 >> 16) - mn1);
     const QuadTranspose transpose(lane);
     float cst[G], inv[G];
-#pragma unroll
-    for (int g = 0; g < G; g++) {
-        const float w0 = qreg[g][0] * st0, w1 = qreg[g][1] * st1;
-        const float f = dot_scale(fmaxf(fabsf(w0), fabsf(w1)), &inv[g]);
-        uint32_t *slot = digit_slot(digits + g * 4 * kDigitRow, lane);
-        slot[0] = transpose(four_digits(w0 * f));
-        slot[kSliceLen / 4] = transpose(four_digits(w1 * f));
-        // the constant part of the dot product is shared by all tokens of the block
-        cst[g] = qreg[g][0] * fmaf(bias, st0, mn0) + qreg[g][1] * fmaf(bias, st1, mn1);
-    }
-    const uint32_t sb = hdr32[kmm / 4 + lane];  // bit counts of slices 2*lane and 2*lane+1
-    const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
-    const uint32_t *wm1 = hdr32 + (kmm + 2 * kSlices) / 4 - 1;
-    Quad<DecodeMode<LB>::J> qd;
-    wave_sync();
-    qd.open(wm1, start, sb & 0xffffu, sb >> 16);
-    ChainSyms<DecodeMode<LB>::kLookupsPerChain> syms;
-    SliceWords pw;
-    const uint8_t *piece[G];
+    uint32_t digits[G][2];  // of the channels of either slice
     v4i d[G];
 #pragma unroll
     for (int g = 0; g < G; g++) {
-        piece[g] = a_piece(digits + g * 4 * kDigitRow, zeros, lane);
+        const float w0 = qreg[g][0] * st0, w1 = qreg[g][1] * st1;
+        const float f = int_scale<30>(fmaxf(fabsf(w0), fabsf(w1)), &inv[g]);
+        digits[g][0] = transpose(four_digits(w0 * f));
+        digits[g][1] = transpose(four_digits(w1 * f));
+        // the constant part of the dot product is shared by all tokens of the block
+        cst[g] = wave_sum(qreg[g][0] * fmaf(bias, st0, mn0) + qreg[g][1] * fmaf(bias, st1, mn1));
         d[g] = v4i{0, 0, 0, 0};
     }
-    auto products = [&](int ks) {
+    decode_words<LB>(qd, units, lut, mask, [&](auto slice, auto index, uint32_t word) {
 #pragma unroll
-        for (int g = 0; g < G; g++) {
-            d[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_step(piece[g], 16 * ks), b_step(pw.a, ks), d[g], 0, 0, 0);
-            d[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_step(piece[g], kSliceLen + 16 * ks), b_step(pw.b, ks), d[g], 0, 0, 0);
-        }
-    };
-    constexpr int kP = tile_first_span(DecodeMode<LB>::kSymsPerWindow);
-    decode_span<LB, 0, kP>(qd, wm1, lut, mask, syms, pw);
-    products(0);
-    products(3);
-    decode_span<LB, kP, kHalf>(qd, wm1, lut, mask, syms, pw);
+        for (int g = 0; g < G; g++) add_products<decltype(index)::value>(d[g], digits[g][decltype(slice)::value], word);
+    });
     wave_sync();
     record_done();
-    products(1);
-    products(2);
 #pragma unroll
-    for (int g = 0; g < G; g++) score[g] = scale * fmaf(inv[g], join_four(d[g]), wave_sum(cst[g]));
+    for (int g = 0; g < G; g++) score[g] = scale * fmaf(inv[g], join_four(d[g]), cst[g]);
 }
 
 // ---- V block: lane = channels 2*lane and 2*lane+1 (its two slices) -------------------------------------------------
 // p[g] = softmax numerator of token `lane`.  kLate: another wave is still computing them; they are fetched with
 // numerators(p) once the whole block has been decoded, and all products follow.
 template <int G, int LB, bool kLate, class F, class N>
-__device__ __forceinline__ void v_block(const uint32_t *hdr32, const char *lut, uint32_t mask, uint8_t *digits,
-                                        const uint8_t *zeros, float (&p)[G], float two_eb, float bias, int lane,
-                                        Soft<G> &st, F &&record_done, N &&numerators) {
+__device__ __forceinline__ void v_block(const uint32_t *hdr32, const char *lut, uint32_t mask, float (&p)[G], float two_eb,
+                                        float bias, int lane, Soft<G> &st, F &&record_done, N &&numerators) {
     static_assert(G < kTileMinG, "groups of 4 and 8 take the tile path");
     // lane t holds the folded weight p_t * step_t of token t
     const uint32_t mm = hdr32[lane];
+    const uint32_t sb = hdr32[kMinMaxBytesV / 4 + lane];
+    const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
+    const Unit *units = payload_units(hdr32 + kHdrBytesV / 4);
+    Quad<DecodeMode<LB>::J> qd;
+    qd.open(units, start, sb & 0xffffu, sb >> 16);
     const float mn = h2f(mm & 0xffffu);
     const float step = two_eb * (h2f(mm >> 16) - mn);
     const QuadTranspose transpose(lane);
     float inv[G];
+    uint32_t digits[G];
+    v4i d[G][2];
     auto weights = [&] {
 #pragma unroll
         for (int g = 0; g < G; g++) {
             const float w = p[g] * step;
-            const float f = dot_scale(w, &inv[g]);
-            *digit_slot(digits + g * 4 * kDigitRow, lane) = transpose(four_digits(w * f));
+            const float f = int_scale<30>(w, &inv[g]);
+            digits[g] = transpose(four_digits(w * f));
             st.bv[g] = fmaf(p[g], fmaf(bias, step, mn), st.bv[g]);
+            d[g][0] = d[g][1] = v4i{0, 0, 0, 0};
         }
     };
-    if constexpr (!kLate) weights();
-    const uint32_t sb = hdr32[kMinMaxBytesV / 4 + lane];
-    const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
-    const uint32_t *wm1 = hdr32 + kHdrBytesV / 4 - 1;
-    Quad<DecodeMode<LB>::J> qd;
-    wave_sync();
-    qd.open(wm1, start, sb & 0xffffu, sb >> 16);
-    ChainSyms<DecodeMode<LB>::kLookupsPerChain> syms;
-    SliceWords pw;
-    const uint8_t *piece[G];
-    v4i d[G][2];
+    auto products = [&](auto slice, auto index, uint32_t word) {
 #pragma unroll
-    for (int g = 0; g < G; g++) {
-        piece[g] = a_piece(digits + g * 4 * kDigitRow, zeros, lane);
-        d[g][0] = d[g][1] = v4i{0, 0, 0, 0};
-    }
-    auto products = [&](int ks) {
-#pragma unroll
-        for (int g = 0; g < G; g++) {
-            const v4i a = a_step(piece[g], 16 * ks);
-            d[g][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b_step(pw.a, ks), d[g][0], 0, 0, 0);
-            d[g][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b_step(pw.b, ks), d[g][1], 0, 0, 0);
-        }
+        for (int g = 0; g < G; g++) add_products<decltype(index)::value>(d[g][decltype(slice)::value], digits[g], word);
     };
-    constexpr int kP = tile_first_span(DecodeMode<LB>::kSymsPerWindow);
-    decode_span<LB, 0, kP>(qd, wm1, lut, mask, syms, pw);
     if constexpr (!kLate) {
-        products(0);
-        products(3);
-    }
-    decode_span<LB, kP, kHalf>(qd, wm1, lut, mask, syms, pw);
-    wave_sync();
-    record_done();
-    if constexpr (kLate) {
+        weights();
+        decode_words<LB>(qd, units, lut, mask, products);
+        wave_sync();
+        record_done();
+    } else {
+        SliceWords pw;
+        decode_block<LB>(qd, units, lut, mask, pw);
+        wave_sync();
+        record_done();
         numerators(p);
         weights();
-        wave_sync();
-        products(0);
-        products(3);
+        static_for<0, 16>([&](auto w) {
+            products(std::integral_constant<int, 0>(), w, pw.a[decltype(w)::value]);
+            products(std::integral_constant<int, 1>(), w, pw.b[decltype(w)::value]);
+        });
     }
-    products(1);
-    products(2);
 #pragma unroll
     for (int g = 0; g < G; g++) {
         st.acc[g][0] = fmaf(inv[g], join_four(d[g][0]), st.acc[g][0]);
@@ -302,32 +260,35 @@ __device__ __forceinline__ void v_block(const uint32_t *hdr32, const char *lut, 
 // Rare path: a record larger than the LDS staging area is decoded straight from global memory.  Kept out of line so
 // that it costs the common path no registers.
 template <int G, int LB>
-__device__ __noinline__ void k_block_global(const uint32_t *rec, const char *lut, uint32_t mask, uint8_t *digits,
-                                            const uint8_t *zeros, const float (&qreg)[G][2], float two_eb, float bias,
-                                            float scale, int lane, int kmm, float (&score)[G]) {
-    k_block<G, LB>(rec, lut, mask, digits, zeros, qreg, two_eb, bias, scale, lane, kmm, score, [] {});
+__device__ __noinline__ void k_block_global(const uint32_t *rec, const char *lut, uint32_t mask, const float (&qreg)[G][2],
+                                            float two_eb, float bias, float scale, int lane, int kmm, float (&score)[G]) {
+    k_block<G, LB>(rec, lut, mask, qreg, two_eb, bias, scale, lane, kmm, score, [] {});
 }
 template <int G, int LB>
-__device__ __noinline__ void v_block_global(const uint32_t *rec, const char *lut, uint32_t mask, uint8_t *digits,
-                                            const uint8_t *zeros, const float (&p)[G], float two_eb, float bias, int lane,
-                                            Soft<G> &st) {
+__device__ __noinline__ void v_block_global(const uint32_t *rec, const char *lut, uint32_t mask, const float (&p)[G],
+                                            float two_eb, float bias, int lane, Soft<G> &st) {
     float pc[G];
 #pragma unroll
     for (int g = 0; g < G; g++) pc[g] = p[g];
-    v_block<G, LB, false>(rec, lut, mask, digits, zeros, pc, two_eb, bias, lane, st, [] {}, [](float (&)[G]) {});
+    v_block<G, LB, false>(rec, lut, mask, pc, two_eb, bias, lane, st, [] {}, [](float (&)[G]) {});
 }
 
 // ---- groups of 4 and 8 query heads, tile path ---------------------------------------------------------------------
 // With several query heads per KV head the update of the accumulators is a matrix product, (heads x symbols) weights
 // times the decoded block, and the decode itself is the same for all heads.  The wave therefore only packs the
 // decoded symbols, four table entries to a register -- less work than one conversion and one FMA per symbol and
-// head -- and multiplies them with the folded weights on v_mfma_i32_32x32x16_i8, whose result tiles (32 rows of
+// head -- and multiplies them with the folded weights on v_mfma_i32_32x32x32_i8, whose result tiles (32 rows of
 // weights x 32 columns) give the path its name:
-//   * a register of packed symbols is an MFMA operand as it is, with no conversion; the operand wants 32 columns x 16 positions from 64 lanes that hold
+//   * a register of packed symbols is an MFMA operand as it is, with no conversion; the operand wants 32 columns x 32 positions from 64 lanes that hold
 //     one slice each, which one v_permlane32_swap_b32 per register arranges (step_operands);
 //   * a weight w is scaled by a per-block power of two to an integer W below 2^22 and split into three signed bytes,
 //     W = sum_j d_j 256^j; row 4 * head + j of the A operand holds digit j, the products are exact in int32, and the
 //     digit rows of a head land in the same lane of the result, where they are recombined in fp32;
+//   * the products run once the whole block is decoded: 32 registers hold it, and the result tiles take the place of the
+//     stream readers.  With products after each half every digit sum was recombined twice (16 x 8 heads x 8192 tokens, groups
+//     of 4: 60.4 -> 57.4 us a step, with the fourth wave per SIMD that then fits; 8 x 8 heads x 16384, groups of 8: 71.3 ->
+//     65.5; code words of up to 10 bits, whose kernels of groups of 8 could hold two waves per SIMD before and hold three now,
+//     8 x 8 heads x 8192: 56.0 -> 47.8);
 //   * with more than 128 levels the table holds symbol - 128: sum_c W_c (s_c - 128) misses 128 * sum_c W_c, which joins
 //     the constant term of the block.
 // Lane l of the result tiles holds column l % 32 (token of a K block, channel of a V block) for the heads
@@ -367,34 +328,53 @@ __device__ __forceinline__ float half_sum(float v, bool upper) {
     return upper ? hi : lo;
 }
 
-// The B operands of v_mfma_i32_32x32x16_i8 for one step of 16 positions (words w[0..3] of a slice) straight from
-// registers.  Lane l of the operand supplies column l % 32 and positions 8 (l / 32) .. +7.  With one slice per lane and
-// 64 lanes there are two column tiles: tile 0 wants words 0, 1 of lanes 0..31 in its lower half and words 2, 3 of the
-// same lanes in its upper half, tile 1 words 0, 1 of lanes 32..63 in its lower half and their words 2, 3 in its upper
-// half -- which is what v_permlane32_swap_b32 makes of (word 0, word 2) and of (word 1, word 3).
+// The B operands of v_mfma_i32_32x32x32_i8 for one step of 32 positions (words w[8 STEP] .. of a slice) straight from
+// registers.  Lane l of the operand supplies column l % 32 and positions 16 (l / 32) .. +15.  With one slice per lane and
+// 64 lanes there are two column tiles: tile 0 wants words 0..3 of lanes 0..31 in its lower half and words 4..7 of the
+// same lanes in its upper half, tile 1 words 0..3 of lanes 32..63 in its lower half and their words 4..7 in its upper
+// half -- which is what v_permlane32_swap_b32 makes of (word i, word 4 + i).
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void step_operands(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, long &tile0, long &tile1) {
-    const v2u r0 = __builtin_amdgcn_permlane32_swap(w0, w2, false, false);
-    const v2u r1 = __builtin_amdgcn_permlane32_swap(w1, w3, false, false);
-    tile0 = (long)(((unsigned long long)r1.x << 32) | r0.x);
-    tile1 = (long)(((unsigned long long)r1.y << 32) | r0.y);
+__device__ __forceinline__ void step_operands(const uint32_t (&w)[16], int step, v4i &tile0, v4i &tile1) {
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const v2u r = __builtin_amdgcn_permlane32_swap(w[8 * step + i], w[8 * step + 4 + i], false, false);
+        tile0[i] = (int)r.x;
+        tile1[i] = (int)r.y;
+    }
+}
+// v[i] summed over the 32 lanes of this lane's half of the wave, in every lane.  The values are folded together while the
+// lanes are: one register is left after the steps inside a row of 16 that take as many as one value alone would.
+template <int HL>
+__device__ __forceinline__ void half_sums(float (&v)[HL], int lane) {
+    static_assert(HL == 2 || HL == 4);
+    constexpr int kRor8 = 0x128;
+    float m[2];
+#pragma unroll
+    for (int i = 0; i < HL; i += 2) {  // lanes 0..3 and 8..11 of a row go on with v[i], the others with v[i + 1]
+        const float a = v[i] + dpp_f<kDppHalfMirror>(v[i]), b = v[i + 1] + dpp_f<kDppHalfMirror>(v[i + 1]);
+        m[i / 2] = (lane & 4) ? b : a;
+    }
+    float r = m[0] + dpp_f<kRor8>(m[0]);
+    if constexpr (HL == 4) {
+        const float b = m[1] + dpp_f<kRor8>(m[1]);
+        r = (lane & 8) ? b : r;
+    }
+    r += dpp_f<kDppXor1>(r);
+    r += dpp_f<kDppXor2>(r);  // lane 4 i: the row's sum of v[i]
+    const v2u two = __builtin_amdgcn_permlane16_swap(__float_as_uint(r), __float_as_uint(r), false, false);
+    r = __uint_as_float(two.x) + __uint_as_float(two.y);
+    v[0] = dpp_f<0x150>(r);  // row_newbcast
+    v[1] = dpp_f<0x154>(r);
+    if constexpr (HL == 4) {
+        v[2] = dpp_f<0x158>(r);
+        v[3] = dpp_f<0x15c>(r);
+    }
 }
 
-// power-of-two factor that brings the largest weight of the wave into [2^21, 2^22) (1 if all are zero); *inv = 1/f
-__device__ __forceinline__ float int_scale(float amax, float *inv) {
-    const float m = wave_max(amax);
-    int e = 0;
-    if (m > 0.f) (void)frexpf(m, &e);  // m = f * 2^e, f in [0.5, 1)
-    const int up = min(22 - e, 120);
-    *inv = ldexpf(1.f, -up);
-    return m > 0.f ? ldexpf(1.f, up) : 1.f;
-}
-// |W| <= 2^22 as d2 2^16 + d1 2^8 + d0 with signed bytes d_j: bytes 0..2 of the result
-__device__ __forceinline__ uint32_t signed_digits(int W) { return ((uint32_t)W + 0x00008080u) ^ 0x00008080u; }
 // Rounding to an integer inside the multiplication: for |a * b| <= 2^22, fma(a, b, 1.5 * 2^23) is rounded (to nearest,
 // ties to even) at unit spacing, and its bit pattern is kMagicBits + W with W = rint(a * b), also across the binade
 // boundary at W = 2^22.  One instruction instead of a product, a rounding and a conversion; W stays implicit:
-//   magic_digits(bits) = signed_digits(W), and sums of W are sums of bit patterns minus n * kMagicBits.
+//   magic_digits(bits): bytes 0..2 are the signed digits d_j of W = d2 2^16 + d1 2^8 + d0, and sums of W are sums of bit patterns minus n * kMagicBits.
 constexpr float kMagic = 12582912.f;          // 1.5 * 2^23
 constexpr uint32_t kMagicBits = 0x4B400000u;  // its bit pattern
 __device__ __forceinline__ uint32_t magic_round(float a, float b) { return __float_as_uint(fmaf(a, b, kMagic)); }
@@ -407,14 +387,10 @@ __device__ __forceinline__ void transpose_digits(uint32_t a, uint32_t b, uint32_
     o[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
     o[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
 }
-__device__ __forceinline__ long lds_pair(const uint8_t *p) {
-    const uint32_t *w = reinterpret_cast<const uint32_t *>(p);
-    return (long)(((unsigned long long)w[1] << 32) | w[0]);
-}
-// the digit sums of one head, rows 4 i .. 4 i + 2 of a result tile, as one number
+// the digit sums of one head, rows 4 i .. 4 i + 2 of a result tile, as one number (see join_four)
 template <int I>
 __device__ __forceinline__ float join_digits(const v16i &d) {
-    return fmaf(fmaf((float)d[4 * I + 2], 256.f, (float)d[4 * I + 1]), 256.f, (float)d[4 * I]);
+    return fmaf((float)d[4 * I + 2], 65536.f, (float)(d[4 * I] + d[4 * I + 1] * 256));
 }
 template <int HL>
 __device__ __forceinline__ void join_all(const v16i &d, float (&out)[HL]) {
@@ -425,15 +401,16 @@ __device__ __forceinline__ void join_all(const v16i &d, float (&out)[HL]) {
         out[HL > 2 ? 3 : 0] = join_digits<3>(d);
     }
 }
-// Bytes per row of the A operand while it is laid out in the tile area.  Only the three digit rows of every head are
-// stored: row 4 * head + digit of the operand sits at row a_row() of the area; the operand's remaining rows are zero.
-constexpr int kARowK = kARowBytes, kARowV = kBT + 4;
-// x = row of the A operand that a lane supplies -> its row in the area (rows without a digit read a neighbour's and
-// are cleared afterwards)
-template <int G>
-__device__ __forceinline__ int a_row(int x) {
-    const int xr = min(x, 4 * G - 1);
-    return 3 * (xr >> 2) + min(xr & 3, 2);
+// Bytes per row of the A operand while it is laid out in the tile area: whole 16-byte reads, eight neighbouring rows in
+// different banks.  Only the three digit rows of every head are
+// stored: row 4 * head + digit of the operand sits at row 3 * head + digit of the area; the lanes of the operand's remaining rows
+// read zeros instead.
+constexpr int kARowK = kARowBytes, kARowV = kBT + 16;
+// where lane l = (x, hv) of the operand reads: row x, byte 16 hv of every step of 32
+template <int G, int ROW>
+__device__ __forceinline__ const v4i *a_row(const uint8_t *tile, const uint8_t *zeros, int x, int hv) {
+    const uint8_t *row = (x & 3) == 3 || x >= 4 * G ? zeros : tile + (3 * (x >> 2) + (x & 3)) * ROW;
+    return reinterpret_cast<const v4i *>(row + 16 * hv);
 }
 
 // How far a score may exceed the softmax reference before the state is rescaled.  The numerators of a block then
@@ -449,7 +426,7 @@ constexpr float kLazyMax = 2.f;
 // request the next record, whose loads then travel while few registers are live.
 template <int G, int LB, class F>
 __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *lut, uint32_t mask2, uint8_t *tile,
-                                             const float *qf, float two_eb, float bias, float scale, int lane, int kmm,
+                                             const uint8_t *zeros, const float *qf, float two_eb, float bias, float scale, int lane, int kmm,
                                              TileSoft<G> &ts, float (&p)[G / 2][2], F &&record_done) {
     constexpr int HL = G / 2;
     // everything derived from the lane number is recomputed per block (a few instructions) instead of being kept in
@@ -460,7 +437,6 @@ __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *
     const bool per_channel = kmm == kMinMaxBytesK;
     // the A operand: folded weights q_c * step_c as integers, heads l/32 + 2i, channels 4 (l%32) .. +3
     float cst[HL], inv;
-    long a[8];
     {
         float mn[4], stp[4];
 #pragma unroll
@@ -480,7 +456,7 @@ __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *
             }
             amax = fmaxf(amax, qmax * stp[c]);
         }
-        const float f = int_scale(amax, &inv);
+        const float f = int_scale<22>(amax, &inv);
 #pragma unroll
         for (int c = 0; c < 4; c++) stp[c] *= f;   // exact: f is a power of two
 #pragma unroll
@@ -500,62 +476,42 @@ __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *
             const int head = hv + 2 * i;
 #pragma unroll
             for (int j = 0; j < 3; j++) *reinterpret_cast<uint32_t *>(tile + (3 * head + j) * kARowK + 4 * x) = rows[j];
-            cst[i] = half_sum(qm, upper);
+            cst[i] = qm;
         }
-        wave_sync();
-#pragma unroll
-        for (int ks = 0; ks < 8; ks++) {
-            a[ks] = lds_pair(tile + a_row<G>(x) * kARowK + 16 * ks + 8 * hv);
-            if ((x & 3) == 3 || x >= 4 * G) a[ks] = 0;  // rows that hold no digit
-        }
-        wave_sync();
+        half_sums<HL>(cst, lane);
     }
     const uint32_t sb = hdr32[kmm / 4 + lane];  // bit counts of slices 2*lane and 2*lane+1
     const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
-    const uint32_t *wm1 = hdr32 + (kmm + 2 * kSlices) / 4 - 1;
+    const Unit *units = payload_units(hdr32 + (kmm + 2 * kSlices) / 4);
     Quad<DecodeMode<LB>::J> qd;
-    qd.open(wm1, start, sb & 0xffffu, sb >> 16);
-    constexpr bool kBoth = tile_halves_at_once(G, LB) == 2;  // one recombination per block instead of one per half
+    qd.open(units, start, sb & 0xffffu, sb >> 16);
     float sc[HL][2];
-    v16i d[2];  // result tiles: tokens 0..31 and 32..63
-    ChainSyms<DecodeMode<LB>::kLookupsPerChain> syms;
-    SliceWords pw;  // lane = token: slice a = its channels 0..63, slice b = its channels 64..127
-    // one step of 16 channels of either slice: steps 0..3 are channels 0..63, steps 4..7 channels 64..127
-    // fresh: the result tiles start at zero (the matrix instruction takes the constant as its addend: no register
-    // is cleared)
-    auto products = [&](int ks, bool fresh) {
+    {
+        SliceWords pw;  // lane = token: slice a = its channels 0..63, slice b = its channels 64..127
+        decode_block<LB>(qd, units, lut, mask2, pw);
+        wave_sync();
+        const v4i *row = a_row<G, kARowK>(tile, zeros, x, hv);  // read here: no register holds it during the decode
+        v4i a[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++) a[ks] = row[2 * ks];
+        record_done();
         const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        long t0, t1;
-        step_operands(pw.a[4 * ks], pw.a[4 * ks + 1], pw.a[4 * ks + 2], pw.a[4 * ks + 3], t0, t1);
-        d[0] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a[ks], t0, fresh ? zero : d[0], 0, 0, 0);
-        d[1] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a[ks], t1, fresh ? zero : d[1], 0, 0, 0);
-        step_operands(pw.b[4 * ks], pw.b[4 * ks + 1], pw.b[4 * ks + 2], pw.b[4 * ks + 3], t0, t1);
-        d[0] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a[4 + ks], t0, d[0], 0, 0, 0);
-        d[1] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a[4 + ks], t1, d[1], 0, 0, 0);
-    };
-    auto join = [&](bool first) {
+        v16i d[2];  // result tiles: tokens 0..31 and 32..63
+#pragma unroll
+        for (int ks = 0; ks < 4; ks++) {  // steps of 32 channels
+            v4i t0, t1;
+            step_operands(ks < 2 ? pw.a : pw.b, ks & 1, t0, t1);
+            d[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks], t0, ks ? d[0] : zero, 0, 0, 0);
+            d[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks], t1, ks ? d[1] : zero, 0, 0, 0);
+        }
 #pragma unroll
         for (int t = 0; t < 2; t++) {
             float v[HL];
             join_all<HL>(d[t], v);
 #pragma unroll
-            for (int i = 0; i < HL; i++) sc[i][t] = first ? v[i] : sc[i][t] + v[i];
+            for (int i = 0; i < HL; i++) sc[i][t] = v[i];
         }
-    };
-    constexpr int kP = tile_first_span(DecodeMode<LB>::kSymsPerWindow);
-    // a half of a block is 16 symbols of every chain: the up chains deliver step h, the down chains step 3 - h
-    // The products of the first half run while the second half is decoded (no fence in between: everything is in
-    // registers).
-    decode_span<LB, 0, kP>(qd, wm1, lut, mask2, syms, pw);
-    products(0, true);
-    products(3, false);
-    if constexpr (!kBoth) join(true);
-    decode_span<LB, kP, kHalf>(qd, wm1, lut, mask2, syms, pw);
-    wave_sync();
-    record_done();
-    products(1, !kBoth);
-    products(2, false);
-    join(kBoth);
+    }
     // Online softmax with a reference value m that only moves when it has to: the state is rescaled (a maximum over
     // the tokens of every head, six multiplications per head) only when some score of the block exceeds its head's m
     // by more than kLazyMax, which after the first blocks of a sequence split is rare.  Until then the numerators are
@@ -592,13 +548,12 @@ __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *
 // V block.  p: softmax numerators of tokens l%32 and 32 + l%32 for this lane's heads.  kLate: see v_block.
 template <int G, int LB, bool kLate, class F, class N>
 __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *lut, uint32_t mask2, uint8_t *tile,
-                                             float (&p)[G / 2][2], float two_eb, float bias, int lane,
+                                             const uint8_t *zeros, float (&p)[G / 2][2], float two_eb, float bias, int lane,
                                              TileSoft<G> &ts, F &&record_done, N &&numerators) {
     constexpr int HL = G / 2;
     asm volatile("" : "+v"(lane));
     const int x = lane & 31, hv = lane >> 5;
     float inv;
-    long a[4];
     uint32_t minmax[2];
     if constexpr (kLate) {  // the record's staging area may be reused before the weights are made
         minmax[0] = hdr32[x];
@@ -618,7 +573,7 @@ __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *
             pmax[0] = fmaxf(pmax[0], p[i][0]);
             pmax[1] = fmaxf(pmax[1], p[i][1]);
         }
-        const float f = int_scale(fmaxf(pmax[0] * stp[0], pmax[1] * stp[1]), &inv);
+        const float f = int_scale<22>(fmaxf(pmax[0] * stp[0], pmax[1] * stp[1]), &inv);
         stp[0] *= f;   // exact: f is a power of two
         stp[1] *= f;
 #pragma unroll
@@ -636,13 +591,6 @@ __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *
             if constexpr (kBiased<LB>) ts.bv[i] = fmaf(bias * inv, (float)(int)(wbits - 2u * kMagicBits), ts.bv[i]);
             ts.bv[i] += fmaf(p[i][0], mn[0], p[i][1] * mn[1]);
         }
-        wave_sync();
-#pragma unroll
-        for (int ks = 0; ks < 4; ks++) {
-            a[ks] = lds_pair(tile + a_row<G>(x) * kARowV + 16 * ks + 8 * hv);
-            if ((x & 3) == 3 || x >= 4 * G) a[ks] = 0;
-        }
-        wave_sync();
     };
     if constexpr (!kLate) weights();
     // lane = channels lane (slice a) and 64 + lane (slice b), so that a result tile of 32 channels is one slice of 32
@@ -651,76 +599,61 @@ __device__ __forceinline__ void v_tile_block(const uint32_t *hdr32, const char *
     const uint32_t abits = bits16[lane], bbits = bits16[kSliceLen + lane];
     const uint32_t start_a = wave_excl_scan(abits, lane);
     const uint32_t start_b = (uint32_t)__builtin_amdgcn_readlane((int)(start_a + abits), 63) + wave_excl_scan(bbits, lane);
-    const uint32_t *wm1 = hdr32 + kHdrBytesV / 4 - 1;
+    const Unit *units = payload_units(hdr32 + kHdrBytesV / 4);
     Quad<DecodeMode<LB>::J> qd;
-    qd.open2(wm1, start_a, abits, start_b, bbits);
-    constexpr bool kBoth = tile_halves_at_once(G, LB) == 2;
-    v16i d[4];  // result tiles: channels 0..31, 32..63 (slice a), 64..95, 96..127 (slice b)
-    ChainSyms<DecodeMode<LB>::kLookupsPerChain> syms;
+    qd.open2(units, start_a, abits, start_b, bbits);
     SliceWords pw;
-    // one step of 16 tokens of both slices
-    auto products = [&](int ks, bool fresh) {   // fresh: the result tiles start at zero
-        const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        long t0, t1;
-        step_operands(pw.a[4 * ks], pw.a[4 * ks + 1], pw.a[4 * ks + 2], pw.a[4 * ks + 3], t0, t1);
-        d[0] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a[ks], t0, fresh ? zero : d[0], 0, 0, 0);
-        d[1] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a[ks], t1, fresh ? zero : d[1], 0, 0, 0);
-        step_operands(pw.b[4 * ks], pw.b[4 * ks + 1], pw.b[4 * ks + 2], pw.b[4 * ks + 3], t0, t1);
-        d[2] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a[ks], t0, fresh ? zero : d[2], 0, 0, 0);
-        d[3] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a[ks], t1, fresh ? zero : d[3], 0, 0, 0);
-    };
-    auto join = [&] {
-#pragma unroll
-        for (int ct = 0; ct < 4; ct++) {
-            float v[HL];
-            join_all<HL>(d[ct], v);
-#pragma unroll
-            for (int i = 0; i < HL; i++) ts.acc[i][ct] = fmaf(inv, v[i], ts.acc[i][ct]);
-        }
-    };
-    constexpr int kP = tile_first_span(DecodeMode<LB>::kSymsPerWindow);
-    decode_span<LB, 0, kP>(qd, wm1, lut, mask2, syms, pw);
-    if constexpr (!kLate) {
-        products(0, true);
-        products(3, false);
-        if constexpr (!kBoth) join();
-    }
-    decode_span<LB, kP, kHalf>(qd, wm1, lut, mask2, syms, pw);
+    decode_block<LB>(qd, units, lut, mask2, pw);
     wave_sync();
     record_done();
     if constexpr (kLate) {
         numerators(p);
         weights();
-        products(0, true);
-        products(3, false);
+        wave_sync();
     }
-    products(1, !kBoth && !kLate);
-    products(2, false);
-    join();
+    const v4i *row = a_row<G, kARowV>(tile, zeros, x, hv);
+    const v4i a[2] = {row[0], row[2]};
+#pragma unroll
+    for (int sl = 0; sl < 2; sl++) {  // result tiles: channels 0..31, 32..63 (slice a), 64..95, 96..127 (slice b)
+        const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        v16i d[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) {  // steps of 32 tokens
+            v4i t0, t1;
+            step_operands(sl ? pw.b : pw.a, ks, t0, t1);
+            d[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks], t0, ks ? d[0] : zero, 0, 0, 0);
+            d[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks], t1, ks ? d[1] : zero, 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+            float v[HL];
+            join_all<HL>(d[t], v);
+#pragma unroll
+            for (int i = 0; i < HL; i++) ts.acc[i][2 * sl + t] = fmaf(inv, v[i], ts.acc[i][2 * sl + t]);
+        }
+    }
 }
 
 // Rare path: a record larger than the LDS staging area (one that an append flushed after the host last looked at the
 // record sizes) is decoded straight from global memory, out of line.
 template <int G, int LB>
 __device__ __noinline__ void k_tile_block_global(const uint32_t *rec, const char *lut, uint32_t mask2, uint8_t *tile,
-                                                 const float *qf, float two_eb, float bias, float scale, int lane, int kmm,
+                                                 const uint8_t *zeros, const float *qf, float two_eb, float bias, float scale, int lane, int kmm,
                                                  TileSoft<G> &ts, float (&p)[G / 2][2]) {
-    k_tile_block<G, LB>(rec, lut, mask2, tile, qf, two_eb, bias, scale, lane, kmm, ts, p, [] {});
+    k_tile_block<G, LB>(rec, lut, mask2, tile, zeros, qf, two_eb, bias, scale, lane, kmm, ts, p, [] {});
 }
 template <int G, int LB>
 __device__ __noinline__ void v_tile_block_global(const uint32_t *rec, const char *lut, uint32_t mask2, uint8_t *tile,
-                                                 const float (&p)[G / 2][2], float two_eb, float bias, int lane,
+                                                 const uint8_t *zeros, const float (&p)[G / 2][2], float two_eb, float bias, int lane,
                                                  TileSoft<G> &ts) {
     float pc[G / 2][2];
 #pragma unroll
     for (int i = 0; i < G / 2; i++) { pc[i][0] = p[i][0]; pc[i][1] = p[i][1]; }
-    v_tile_block<G, LB, false>(rec, lut, mask2, tile, pc, two_eb, bias, lane, ts, [] {}, [](float (&)[G / 2][2]) {});
+    v_tile_block<G, LB, false>(rec, lut, mask2, tile, zeros, pc, two_eb, bias, lane, ts, [] {}, [](float (&)[G / 2][2]) {});
 }
 
 // A wave's softmax state parked in LDS, G * 128 + 3 * G floats: o[g][channel] then {m, l, bv} per head with l and bv
-// already summed over the lanes.  The state crosses the call of the out-of-line buffered-token code this way (through
-// a reference it would cross in scratch memory, i.e. through the memory system: microseconds on the critical path of
-// the wave that finishes last), and the tile path changes its layout this way.
+// already summed over the lanes: the buffered tokens are merged into it there, and the tile path changes its layout this way.
 template <int G>
 __device__ __forceinline__ void soft_to_area(const Soft<G> &st, float *area, int lane) {
     wave_sync();
@@ -792,7 +725,8 @@ __device__ __forceinline__ void tile_state_to_area(const TileSoft<G> &ts, float 
 // instead of the buffer, and the lanes that read it store it into its buffer slot for the launches to come: one
 // wave of the grid per (batch, head) owns that row, so there is one writer and no reader of the slot in this launch.
 // The result is merged into the wave's parked state (`area`, see soft_to_area).
-// Out of line: it runs once, after the decode loop, and must not weigh on that loop's registers.
+// Inline: the decode loop leaves room for it.  Out of line it saved and restored the registers that a callee has to keep, through
+// scratch memory (4 x 8 heads x 9000 tokens, 1024 of them buffered, groups of 8: 29.3 -> 27.6 us).
 constexpr int kUnitTokens = 16;
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -838,7 +772,7 @@ __device__ __forceinline__ float max_over_rows(float v) {  // over the four rows
 }
 
 template <int G>
-__device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens, int B, int H, int b, int h,
+__device__ __forceinline__ void buffered_tokens(const uint16_t *res, int res_tokens, int B, int H, int b, int h,
                                              int res_head, int n_res, int first_unit, int unit_step,
                                              const uint16_t *q0, float scale, int lane, const uint16_t *k_new,
                                              const uint16_t *v_new, int new_row, float *area) {
@@ -960,10 +894,9 @@ __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens
     wave_sync();
 }
 
-// One workgroup per CU, as many waves as the registers allow per SIMD (fused_waves_per_simd): 4 (128 VGPRs), 3 (168)
-// or 2 (256).  The host may launch fewer waves per workgroup (short sequences,
+// One workgroup per CU, as many waves as the registers allow per SIMD (fused_waves_per_simd): 4 (128 VGPRs) or 3 (168).  The host may launch fewer waves per workgroup (short sequences,
 // large staging areas).
-template <int G, int LB> struct MaxWaves { static constexpr int value = 4 * fused_waves_per_simd(G, LB); };
+template <int G, int LB, bool kPaired> struct MaxWaves { static constexpr int value = fused_max_waves(G, kPaired); };
 
 // LB = the table width the kernel is compiled for (>= longest code word of both codebooks), see DecodeMode.
 //
@@ -974,21 +907,21 @@ template <int G, int LB> struct MaxWaves { static constexpr int value = 4 * fuse
 // behind them take the buffered tokens.  The V waves hold the state, the K waves end empty-handed.
 // 1 head x 1024 tokens 9.4 -> 7.9 us a step, 96 tokens appended to 2000 (8 heads, groups of 4) 1424 -> 1134 us.
 template <int G, int LB, bool kPaired>
-__global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_kernel(FusedArgs a) {
+__global__ __launch_bounds__((64 * MaxWaves<G, LB, kPaired>::value), 1) void fused_attn_kernel(FusedArgs a) {
     using M = DecodeMode<LB>;
     constexpr bool kTile = G >= kTileMinG;  // packed symbols in registers, int8 MFMA
     __shared__ __attribute__((aligned(16))) uint8_t lut_s[2][M::kTableBytes];
     __shared__ __attribute__((aligned(16))) float qf[kTile ? G * kD : 4];
-    __shared__ __attribute__((aligned(16))) uint8_t zeros[kTile ? 16 : kDigitRow];  // lanes that hold no digit row read it
+    __shared__ __attribute__((aligned(16))) uint8_t zeros[kTile ? kD : 16];  // tile path: the A operand's rows without a digit
     __shared__ uint32_t ready[kPaired ? 16 : 1];  // paired: wave w's numerators are in its record area
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // per wave: staging area + weights
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // per wave: staging area; tile path: + weights
     const int tid = threadIdx.x, lane = tid & 63, n_threads = blockDim.x;
     // the wave number and everything derived from it (block numbers, table entries, record addresses) are scalars
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_waves = __builtin_amdgcn_readfirstlane(n_threads >> 6);
     uint8_t *stage = smem + (size_t)wave * a.stage_bytes;
     constexpr int kWeightBytes = (int)fused_weight_bytes(G);
-    // the wave's weight area: digit rows of the A operand
+    // the wave's weight area (tile path): digit rows of the A operand
     uint8_t *tile = smem + (size_t)n_waves * a.stage_bytes + (size_t)wave * kWeightBytes;
     const char *lutK = reinterpret_cast<const char *>(&lut_s[0][0]);
     const char *lutV = reinterpret_cast<const char *>(&lut_s[1][0]);
@@ -1006,7 +939,7 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     const int j0 = split * a.blocks_per_split;
     const int j1 = min(j0 + a.blocks_per_split, a.n_blocks);
     const BlockEntry *tabK = a.table + (size_t)bh * a.max_blocks, *tabV = tabK + (size_t)a.n_bh * a.max_blocks;
-    const uint32_t stage16 = (uint32_t)a.stage_bytes / 16 - 1;  // one unit of slack for the streams' look-ahead
+    const uint32_t stage16 = (uint32_t)(a.stage_bytes - kStreamSlack) / 16;  // the streams' look-ahead stays inside
     const uint32_t *stage32 = reinterpret_cast<const uint32_t *>(stage);
 
     // Prologue: everything the first block needs is requested before anything is waited for -- the Block Offsets Array
@@ -1054,10 +987,10 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
                 dst[1] = make_float4(h2f(qv[k].z & 0xffffu), h2f(qv[k].z >> 16), h2f(qv[k].w & 0xffffu), h2f(qv[k].w >> 16));
             }
         }
+        if (tid < kD / 4) reinterpret_cast<uint32_t *>(zeros)[tid] = 0;
     } else {
 #pragma unroll
         for (int gg = 0; gg < G; gg++) { qreg[gg][0] = h2f(qh[gg][0]); qreg[gg][1] = h2f(qh[gg][1]); }
-        if (tid < kDigitRow / 4) reinterpret_cast<uint32_t *>(zeros)[tid] = 0;
     }
     if constexpr (kPaired) {
         if (tid < 16) ready[tid] = 0;
@@ -1091,12 +1024,12 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             if constexpr (kTile) {
                 float p[kQ0][2];
                 if (staged) {
-                    k_tile_block<G, LB>(stage32, lutK, maskK, tile, qf, a.two_eb[0], a.bias[0], a.scale, lane,
+                    k_tile_block<G, LB>(stage32, lutK, maskK, tile, zeros, qf, a.two_eb[0], a.bias[0], a.scale, lane,
                                         a.k_minmax_bytes, ts, p, [] {});
                 } else {
                     TileSoft<G> ts_tmp = ts;  // copies keep the hot state in registers
                     float p_tmp[kQ0][2];
-                    k_tile_block_global<G, LB>(rec32, lutK, maskK, tile, qf, a.two_eb[0], a.bias[0], a.scale, lane,
+                    k_tile_block_global<G, LB>(rec32, lutK, maskK, tile, zeros, qf, a.two_eb[0], a.bias[0], a.scale, lane,
                                                a.k_minmax_bytes, ts_tmp, p_tmp);
                     ts = ts_tmp;
 #pragma unroll
@@ -1112,13 +1045,13 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             } else {
                 float score[G];
                 if (staged) {
-                    k_block<G, LB>(stage32, lutK, maskK, tile, zeros, qreg, a.two_eb[0], a.bias[0], a.scale, lane,
+                    k_block<G, LB>(stage32, lutK, maskK, qreg, a.two_eb[0], a.bias[0], a.scale, lane,
                                    a.k_minmax_bytes, score, [] {});
                 } else {
                     float q_tmp[G][2], s_tmp[G];
 #pragma unroll
                     for (int gg = 0; gg < G; gg++) { q_tmp[gg][0] = qreg[gg][0]; q_tmp[gg][1] = qreg[gg][1]; }
-                    k_block_global<G, LB>(rec32, lutK, maskK, tile, zeros, q_tmp, a.two_eb[0], a.bias[0], a.scale, lane,
+                    k_block_global<G, LB>(rec32, lutK, maskK, q_tmp, a.two_eb[0], a.bias[0], a.scale, lane,
                                           a.k_minmax_bytes, s_tmp);
 #pragma unroll
                     for (int gg = 0; gg < G; gg++) score[gg] = s_tmp[gg];
@@ -1153,14 +1086,14 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
                     }
                 };
                 if (staged) {
-                    v_tile_block<G, LB, true>(stage32, lutV, maskV, tile, p, a.two_eb[1], a.bias[1], lane, ts, [] {}, numerators);
+                    v_tile_block<G, LB, true>(stage32, lutV, maskV, tile, zeros, p, a.two_eb[1], a.bias[1], lane, ts, [] {}, numerators);
                 } else {
                     numerators(p);
                     TileSoft<G> ts_tmp = ts;
                     float p_tmp[kQ0][2];
 #pragma unroll
                     for (int i = 0; i < kQ0; i++) { p_tmp[i][0] = p[i][0]; p_tmp[i][1] = p[i][1]; }
-                    v_tile_block_global<G, LB>(rec32, lutV, maskV, tile, p_tmp, a.two_eb[1], a.bias[1], lane, ts_tmp);
+                    v_tile_block_global<G, LB>(rec32, lutV, maskV, tile, zeros, p_tmp, a.two_eb[1], a.bias[1], lane, ts_tmp);
                     ts = ts_tmp;
                 }
             } else {
@@ -1175,14 +1108,14 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
                     }
                 };
                 if (staged) {
-                    v_block<G, LB, true>(stage32, lutV, maskV, tile, zeros, p, a.two_eb[1], a.bias[1], lane, st, [] {}, numerators);
+                    v_block<G, LB, true>(stage32, lutV, maskV, p, a.two_eb[1], a.bias[1], lane, st, [] {}, numerators);
                 } else {
                     numerators(p);
                     Soft<G> st_tmp = st;
                     float p_tmp[G];
 #pragma unroll
                     for (int gg = 0; gg < G; gg++) p_tmp[gg] = p[gg];
-                    v_block_global<G, LB>(rec32, lutV, maskV, tile, zeros, p_tmp, a.two_eb[1], a.bias[1], lane, st_tmp);
+                    v_block_global<G, LB>(rec32, lutV, maskV, p_tmp, a.two_eb[1], a.bias[1], lane, st_tmp);
                     st = st_tmp;
                 }
             }
@@ -1208,12 +1141,12 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         auto next_v = [&] { if (v_staged) stage_record(recV, eV.size16, stage, lane); };
         if constexpr (kTile) {
             if (k_staged) {
-                k_tile_block<G, LB>(stage32, lutK, maskK, tile, qf, a.two_eb[0], a.bias[0], a.scale, lane, a.k_minmax_bytes,
+                k_tile_block<G, LB>(stage32, lutK, maskK, tile, zeros, qf, a.two_eb[0], a.bias[0], a.scale, lane, a.k_minmax_bytes,
                                      ts, pt, next_v);
             } else {
                 TileSoft<G> ts_tmp = ts;
                 float p_tmp[kQ0][2];
-                k_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, tile, qf, a.two_eb[0],
+                k_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, tile, zeros, qf, a.two_eb[0],
                                             a.bias[0], a.scale, lane, a.k_minmax_bytes, ts_tmp, p_tmp);
                 ts = ts_tmp;
 #pragma unroll
@@ -1222,12 +1155,12 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
             }
         } else {
         if (k_staged) {
-            k_block<G, LB>(stage32, lutK, maskK, tile, zeros, qreg, a.two_eb[0], a.bias[0], a.scale, lane, a.k_minmax_bytes, score, next_v);
+            k_block<G, LB>(stage32, lutK, maskK, qreg, a.two_eb[0], a.bias[0], a.scale, lane, a.k_minmax_bytes, score, next_v);
         } else {  // larger than the staging area: decode from global memory (copies keep the hot state in registers)
             float q_tmp[G][2], s_tmp[G];
 #pragma unroll
             for (int gg = 0; gg < G; gg++) { q_tmp[gg][0] = qreg[gg][0]; q_tmp[gg][1] = qreg[gg][1]; }
-            k_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, tile, zeros, q_tmp, a.two_eb[0],
+            k_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recK), lutK, maskK, q_tmp, a.two_eb[0],
                                   a.bias[0], a.scale, lane, a.k_minmax_bytes, s_tmp);
 #pragma unroll
             for (int gg = 0; gg < G; gg++) score[gg] = s_tmp[gg];
@@ -1249,26 +1182,26 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
         auto next_k = [&] { if (next_staged) stage_record(a.payload + (size_t)eKn.off16 * 16, eKn.size16, stage, lane); };
         if constexpr (kTile) {
             if (v_staged) {
-                v_tile_block<G, LB, false>(stage32, lutV, maskV, tile, pt, a.two_eb[1], a.bias[1], lane, ts, next_k, no_numerators);
+                v_tile_block<G, LB, false>(stage32, lutV, maskV, tile, zeros, pt, a.two_eb[1], a.bias[1], lane, ts, next_k, no_numerators);
             } else {
                 TileSoft<G> ts_tmp = ts;
                 float p_tmp[kQ0][2];
 #pragma unroll
                 for (int i = 0; i < kQ0; i++) { p_tmp[i][0] = pt[i][0]; p_tmp[i][1] = pt[i][1]; }
-                v_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, tile, p_tmp, a.two_eb[1],
+                v_tile_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, tile, zeros, p_tmp, a.two_eb[1],
                                             a.bias[1], lane, ts_tmp);
                 ts = ts_tmp;
                 next_k();
             }
         } else {
         if (v_staged) {
-            v_block<G, LB, false>(stage32, lutV, maskV, tile, zeros, p, a.two_eb[1], a.bias[1], lane, st, next_k, no_numerators);
+            v_block<G, LB, false>(stage32, lutV, maskV, p, a.two_eb[1], a.bias[1], lane, st, next_k, no_numerators);
         } else {
             Soft<G> st_tmp = st;
             float p_tmp[G];
 #pragma unroll
             for (int gg = 0; gg < G; gg++) p_tmp[gg] = p[gg];
-            v_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, tile, zeros, p_tmp, a.two_eb[1],
+            v_block_global<G, LB>(reinterpret_cast<const uint32_t *>(recV), lutV, maskV, p_tmp, a.two_eb[1],
                                   a.bias[1], lane, st_tmp);
             st = st_tmp;
             next_k();
@@ -1293,7 +1226,7 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB>::value), 1) void fused_attn_k
     }
 
     // The record area is free now: the tile path changes the layout of its state through it, and a wave with buffered
-    // tokens parks its state there across the out-of-line call.
+    // tokens parks its state there.
     if (!kPaired || is_v) {  // a K wave of a pair has no state, and its area may still be read
         float *area = reinterpret_cast<float *>(stage);
         bool parked = false;
@@ -1387,7 +1320,7 @@ static hipError_t launch_fused_gn(const FusedArgs &a, int n_waves, size_t lds, h
         if (e != hipSuccess) return e;
         attr_set = lds;
     }
-    if (n_waves < 1 || n_waves > MaxWaves<G, LB>::value) return hipErrorInvalidValue;
+    if (n_waves < 1 || n_waves > MaxWaves<G, LB, kPaired>::value) return hipErrorInvalidValue;
     if (ev0) (void)hipEventRecord(ev0, s);
     hipLaunchKernelGGL((fused_attn_kernel<G, LB, kPaired>), dim3(a.n_splits * a.n_bh), dim3(64 * n_waves), lds, s, a);
     if (ev1) (void)hipEventRecord(ev1, s);

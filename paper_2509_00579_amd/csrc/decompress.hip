@@ -67,7 +67,7 @@ struct BlockOfWave {
         // A record larger than the staging area (the host sizes it from the largest record, so only a corrupted table gets
         // here) is not decoded: its block is NaN, so that it cannot pass for data, and the next synchronising call, or the
         // next decompression that is queued once this one has run, fails.
-        if (size16 >= (uint32_t)a.stage_bytes / 16) {
+        if (size16 > (uint32_t)(a.stage_bytes - kStreamSlack) / 16) {  // stage_bytes is at least kStreamSlack
             if (lane == 0) {
                 atomicOr(&g.ctrl->fault, kFaultStageSmall);
                 __hip_atomic_store(a.host_refused, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -114,7 +114,6 @@ __global__ __launch_bounds__(64 * kDecWaves, 4) void decompress_kernel(DecompArg
     if (!busy) return;
     const uint32_t *hdr32 = reinterpret_cast<const uint32_t *>(stage);
     const char *lut = reinterpret_cast<const char *>(lut_s);
-    ChainSyms<M::kLookupsPerChain> syms;
     SliceWords pw;
     Quad<M::J> qd;
     const float two_eb = g.two_eb[WHICH];
@@ -126,9 +125,9 @@ __global__ __launch_bounds__(64 * kDecWaves, 4) void decompress_kernel(DecompArg
         for (int k = 0; k < 8; k++) mm[k] = hdr32[g.k_units == 1 ? 0 : c0 + k];
         const uint32_t sb = hdr32[g.k_minmax_bytes / 4 + lane];
         const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
-        const uint32_t *wm1 = hdr32 + (g.k_minmax_bytes + 2 * kSlices) / 4 - 1;
-        qd.open(wm1, start, sb & 0xffffu, sb >> 16);
-        decode_span<LB, 0, kHalf>(qd, wm1, lut, a.mask2, syms, pw);
+        const Unit *units = payload_units(hdr32 + (g.k_minmax_bytes + 2 * kSlices) / 4);
+        qd.open(units, start, sb & 0xffffu, sb >> 16);
+        decode_block<LB>(qd, units, lut, a.mask2, pw);
         wave_sync();  // every lane is done with the record
         uint4 *mine = reinterpret_cast<uint4 *>(stage + lane * kDecRow);
 #pragma unroll
@@ -143,9 +142,9 @@ __global__ __launch_bounds__(64 * kDecWaves, 4) void decompress_kernel(DecompArg
         const uint32_t abits = bits16[lane], bbits = bits16[kSliceLen + lane];  // slices: channels lane and 64 + lane
         const uint32_t start_a = wave_excl_scan(abits, lane);
         const uint32_t start_b = (uint32_t)__builtin_amdgcn_readlane((int)(start_a + abits), 63) + wave_excl_scan(bbits, lane);
-        const uint32_t *wm1 = hdr32 + kHdrBytesV / 4 - 1;
-        qd.open2(wm1, start_a, abits, start_b, bbits);
-        decode_span<LB, 0, kHalf>(qd, wm1, lut, a.mask2, syms, pw);
+        const Unit *units = payload_units(hdr32 + kHdrBytesV / 4);
+        qd.open2(units, start_a, abits, start_b, bbits);
+        decode_block<LB>(qd, units, lut, a.mask2, pw);
         wave_sync();
         const QuadTranspose transpose(lane);
         uint8_t *mine = stage + (lane & 3) * kDecRow + (lane & ~3);
@@ -229,9 +228,9 @@ __global__ __launch_bounds__(64 * kDecWaves) void tree_walk_kernel(DecompArgs a)
     const int mmb = which == 0 ? g.k_minmax_bytes : kMinMaxBytesV;
     const uint32_t sb = hdr32[mmb / 4 + lane];
     const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
-    const uint32_t *wm1 = hdr32 + (mmb + 2 * kSlices) / 4 - 1;
+    const Unit *units = payload_units(hdr32 + (mmb + 2 * kSlices) / 4);
     Quad<1> qd;
-    qd.open(wm1, start, sb & 0xffffu, sb >> 16);
+    qd.open(units, start, sb & 0xffffu, sb >> 16);
     // All four chains of the lane walk one bit per step; a window gives 31 bits, then every reader moves on by
     // 31.  A chain stops emitting after its 32 symbols; the wave runs until every chain of every lane is done.
     // K: lane = token, chains au/ad = channels 0..63 (up / down), bu/bd = channels 64..127
@@ -250,8 +249,12 @@ __global__ __launch_bounds__(64 * kDecWaves) void tree_walk_kernel(DecompArgs a)
     // damaged table
     bool more = true;
     for (int round = 0; round < 16 && more; round++) {
-        uint32_t w0 = qd.au.window(wm1) >> 1, w1 = qd.ad.window(wm1) >> 1;
-        uint32_t w2 = qd.bu.window(wm1) >> 1, w3 = qd.bd.window(wm1) >> 1;
+        uint32_t w0, w1, w2, w3, behind;
+        qd.au.bits(w0, behind);
+        qd.ad.bits(w1, behind);
+        qd.bu.bits(w2, behind);
+        qd.bd.bits(w3, behind);
+        w0 >>= 1; w1 >>= 1; w2 >>= 1; w3 >>= 1;
 #pragma unroll 1
         for (int k = 0; k < kWindowBits; k++) {
             const int i0 = tw[0].count, i1 = tw[1].count, i2 = tw[2].count, i3 = tw[3].count;
@@ -261,10 +264,10 @@ __global__ __launch_bounds__(64 * kDecWaves) void tree_walk_kernel(DecompArgs a)
             emit(3, tw[3].step(tree, w3 & 1u), i3);
             w0 >>= 1; w1 >>= 1; w2 >>= 1; w3 >>= 1;
         }
-        qd.au.advance(wm1, kWindowBits);
-        qd.ad.advance(wm1, kWindowBits);
-        qd.bu.advance(wm1, kWindowBits);
-        qd.bd.advance(wm1, kWindowBits);
+        qd.au.advance(units, kWindowBits);
+        qd.ad.advance(units, kWindowBits);
+        qd.bu.advance(units, kWindowBits);
+        qd.bd.advance(units, kWindowBits);
         const bool mine = tw[0].count < kHalf || tw[1].count < kHalf || tw[2].count < kHalf || tw[3].count < kHalf;
         more = __any(mine);
     }

@@ -6,6 +6,8 @@
 
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "kvcomp_internal.h"
 
 namespace kvc {
@@ -66,59 +68,92 @@ __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, int lane) {
     return inc + before - v;
 }
 
+template <int A, int B, class F>
+__device__ __forceinline__ void static_for(F &&f) {  // f(integral constant) for A .. B-1
+    if constexpr (A < B) {
+        f(std::integral_constant<int, A>());
+        static_for<A + 1, B>(f);
+    }
+}
+
 // A slice holds two decode chains (see the record layout): symbols 0..31 are read upwards from the slice start,
 // symbols 63..32 downwards from the slice end.
-//   wm1   payload words, pointer moved back by one word: payload bit x is bit x + 32 of wm1
+//   units   the payload as 8-byte units, pointer moved back by one unit: payload bit x is bit x + 64 of units
 // A window is 32 bits whose lowest J bits are don't-cares and whose bits J.. are the next unread stream bits in
 // reading order, i.e. the stream already scaled to the byte offset of a table entry of 2^J bytes (J = 1: 16-bit
 // entries, one symbol each; J = 2: 32-bit entries that deliver two symbols).
-// (Unaligned 4-byte LDS reads at byte granularity, and re-reading both words of every window, were tried: slower.)
 //
-// Readers keep a 64-bit piece {hi,lo} of the stream in registers plus the next word in reading direction, fetched
-// one window ahead: one 4-byte LDS read per window, off the critical path (only table lookups depend on each other).
+// A reader gives 64 bits at a time, two windows: the second one starts where the first one's code words end, which one
+// funnel shift arranges, so positions and registers move on once per two windows.  It keeps the unit that holds its position,
+// the one behind it in reading direction for the bits that reach over, and a third one on its way: one aligned 8-byte LDS
+// read per two windows, off the critical path (only table lookups depend on each other).
+// The LDS pipe is the busiest unit of the decoders and the streams were a third of its work: a 4-byte gather of 64 lanes from
+// a record costs the pipe of a CU 2.5 ns, an aligned 8-byte one 2.2, two 4-byte halves in one ds_read2_b32 4.9, an 8-byte
+// one at an odd word 27 (lane by lane), and a chain of 32 symbols takes five aligned ones where it took nine of 4 bytes.
+struct __attribute__((aligned(8))) Unit { uint32_t lo, hi; };
+// payload: first word behind a record's header, 16-byte aligned.  The readers look at up to 16 bytes in front of it and, for
+// lookups that are never made, up to kStreamSlack bytes behind the record.
+__device__ __forceinline__ const Unit *payload_units(const uint32_t *payload) { return reinterpret_cast<const Unit *>(payload) - 1; }
+// From word `odd` of a and b on: words 0, 1 and words 1, 2 shifted by the position's low five bits
+__device__ __forceinline__ void unit_bits(const Unit &a, const Unit &b, uint32_t P, uint32_t &lo, uint32_t &hi) {
+    const bool odd = (P & 32u) != 0;
+    const uint32_t x0 = odd ? a.hi : a.lo, x1 = odd ? b.lo : a.hi, x2 = odd ? b.hi : b.lo;
+    lo = __builtin_amdgcn_alignbit(x1, x0, P);
+    hi = __builtin_amdgcn_alignbit(x2, x1, P);
+}
 template <int J>
 struct UpReader {
-    uint32_t P, idx, lo, hi, nx;  // P = (next unread payload bit) + 32 - J = window start in wm1 bit coordinates
-    __device__ __forceinline__ void open(const uint32_t *wm1, uint32_t first_bit) {
-        P = first_bit + (uint32_t)(32 - J);
-        idx = P >> 5;
-        lo = wm1[idx];
-        hi = wm1[idx + 1];
-        nx = wm1[idx + 2];
+    uint32_t P;       // (next unread payload bit) + 64 - J = start of the 64 bits in unit coordinates
+    Unit a, b, next;  // units P / 64, P / 64 + 1, P / 64 + 2
+    __device__ __forceinline__ void open(const Unit *units, uint32_t first_bit) {
+        P = first_bit + (uint32_t)(64 - J);
+        const Unit *u = units + (P >> 6);
+        a = u[0];
+        b = u[1];
+        next = u[2];
     }
-    __device__ __forceinline__ uint32_t window(const uint32_t *) const { return __builtin_amdgcn_alignbit(hi, lo, P); }
-    __device__ __forceinline__ void advance(const uint32_t *wm1, uint32_t used) {  // used <= 32 - J
+    // window at the position, and the 32 stream bits behind it
+    __device__ __forceinline__ void bits(uint32_t &first, uint32_t &second) const { unit_bits(a, b, P, first, second); }
+    __device__ __forceinline__ void advance(const Unit *units, uint32_t used) {  // used < 64
+        const uint32_t old = P >> 6;
         P += used;
-        const uint32_t nidx = P >> 5;
-        const bool adv = nidx != idx;
-        lo = adv ? hi : lo;
-        hi = adv ? nx : hi;
-        idx = nidx;
-        nx = wm1[nidx + 2];
+        const uint32_t now = P >> 6;
+        const bool adv = now != old;
+        a.lo = adv ? b.lo : a.lo;
+        a.hi = adv ? b.hi : a.hi;
+        b.lo = adv ? next.lo : b.lo;
+        b.hi = adv ? next.hi : b.hi;
+        next = units[now + 2];
     }
 };
 template <int J>
 struct DownReader {
-    uint32_t P, idx, lo, hi, pv;  // P = (one past the next unread payload bit) + J: the window [P, P+32) of wm1 ends J
-                                  // bits above the next unread bit; bit-reversed it reads downwards
-    __device__ __forceinline__ void open(const uint32_t *wm1, uint32_t end_bit) {
+    uint32_t P;       // (one past the next unread payload bit) + J: the 64 bits [P, P + 64) of units end J bits above the
+                      // next unread bit; bit-reversed they read downwards
+    Unit a, b, next;  // units P / 64, P / 64 + 1, P / 64 - 1
+    __device__ __forceinline__ void open(const Unit *units, uint32_t end_bit) {
         P = end_bit + (uint32_t)J;
-        idx = P >> 5;
-        lo = wm1[idx];
-        hi = wm1[idx + 1];
-        pv = wm1[(int)idx - 1];
+        const Unit *u = units + (P >> 6);
+        a = u[0];
+        b = u[1];
+        next = u[-1];
     }
-    __device__ __forceinline__ uint32_t window(const uint32_t *) const {
-        return __builtin_bitreverse32(__builtin_amdgcn_alignbit(hi, lo, P));
+    __device__ __forceinline__ void bits(uint32_t &first, uint32_t &second) const {
+        uint32_t lo, hi;
+        unit_bits(a, b, P, lo, hi);
+        first = __builtin_bitreverse32(hi);
+        second = __builtin_bitreverse32(lo);
     }
-    __device__ __forceinline__ void advance(const uint32_t *wm1, uint32_t used) {  // used <= 32 - J
+    __device__ __forceinline__ void advance(const Unit *units, uint32_t used) {  // used < 64
+        const uint32_t old = P >> 6;
         P -= used;
-        const uint32_t nidx = P >> 5;
-        const bool adv = nidx != idx;
-        hi = adv ? lo : hi;
-        lo = adv ? pv : lo;
-        idx = nidx;
-        pv = wm1[(int)nidx - 1];
+        const uint32_t now = P >> 6;
+        const bool adv = now != old;
+        b.lo = adv ? a.lo : b.lo;
+        b.hi = adv ? a.hi : b.hi;
+        a.lo = adv ? next.lo : a.lo;
+        a.hi = adv ? next.hi : a.hi;
+        next = units[(int)now - 1];
     }
 };
 
@@ -126,7 +161,7 @@ struct DownReader {
 // mask = ((1 << bits) - 1) << 1.  J = 2: 32-bit entries of the pair table, indexed by the next 12 stream bits
 // (mask = 0xfff << 2): byte 0 = length of two consecutive code words together, byte 1 = first symbol, byte 2 = second
 // symbol.  Lookups per window * index width <= 31 - J from four lookups on, else <= 32 - J, is the caller's promise.
-// The four chains of one lane (two slices x two directions) advance together, CNT lookups each.  The four lookups of a
+// The four chains of one lane (two slices x two directions) advance together.  The four lookups of a
 // round are issued back to back before any of their results is used: a wave then waits for the LDS once per round, not
 // once per lookup.  (Left to itself the compiler runs the chains of some blocks one after the other.)
 template <int J>
@@ -134,36 +169,37 @@ struct Quad {
     UpReader<J> au, bu;
     DownReader<J> ad, bd;
     // a = [a0, a0 + abits), b follows it
-    __device__ __forceinline__ void open(const uint32_t *wm1, uint32_t a0, uint32_t abits, uint32_t bbits) {
-        au.open(wm1, a0);
-        ad.open(wm1, a0 + abits);
-        bu.open(wm1, a0 + abits);
-        bd.open(wm1, a0 + abits + bbits);
+    __device__ __forceinline__ void open(const Unit *units, uint32_t a0, uint32_t abits, uint32_t bbits) {
+        au.open(units, a0);
+        ad.open(units, a0 + abits);
+        bu.open(units, a0 + abits);
+        bd.open(units, a0 + abits + bbits);
     }
     // the same for two slices that do not follow each other in the record
-    __device__ __forceinline__ void open2(const uint32_t *wm1, uint32_t a0, uint32_t abits, uint32_t b0, uint32_t bbits) {
-        au.open(wm1, a0);
-        ad.open(wm1, a0 + abits);
-        bu.open(wm1, b0);
-        bd.open(wm1, b0 + bbits);
+    __device__ __forceinline__ void open2(const Unit *units, uint32_t a0, uint32_t abits, uint32_t b0, uint32_t bbits) {
+        au.open(units, a0);
+        ad.open(units, a0 + abits);
+        bu.open(units, b0);
+        bd.open(units, b0 + bbits);
     }
     __device__ __forceinline__ static uint32_t entry(const char *lut, uint32_t at) {
         if constexpr (J == 1) return *reinterpret_cast<const uint16_t *>(lut + at);
         else return *reinterpret_cast<const uint32_t *>(lut + at);
     }
-    template <int CNT>
-    __device__ __forceinline__ void step(const uint32_t *wm1, const char *lut, uint32_t mask, uint32_t (&fau)[CNT],
-                                         uint32_t (&fad)[CNT], uint32_t (&fbu)[CNT], uint32_t (&fbd)[CNT]) {
+    // CNT lookups of every chain in its window w; tot: what of it they used, only its low five bits are to be looked at
+    // (without the sentinel the symbols are above them).  got(K0 + k, entries) as soon as lookup k is there.
+    template <int CNT, int K0, class F>
+    __device__ __forceinline__ static void window(const char *lut, uint32_t mask, uint32_t (&w)[4], uint32_t (&tot)[4], F &&got) {
         // From four lookups on the bits used are counted by a one in bit 31 of the window that the shifts move down (CNT
         // code words leave it untouched); for fewer it is cheaper to add up the entries' length bytes.
         constexpr bool kSentinel = CNT >= 4;
-        uint32_t w[4] = {au.window(wm1), ad.window(wm1), bu.window(wm1), bd.window(wm1)}, tot[4] = {0, 0, 0, 0};
-        if constexpr (kSentinel) {
 #pragma unroll
-            for (int c = 0; c < 4; c++) w[c] |= 0x80000000u;
+        for (int c = 0; c < 4; c++) {
+            tot[c] = 0;
+            if constexpr (kSentinel) w[c] |= 0x80000000u;
         }
-#pragma unroll
-        for (int k = 0; k < CNT; k++) {
+        static_for<0, CNT>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
             uint32_t at[4], e[4];
 #pragma unroll
             for (int c = 0; c < 4; c++) at[c] = w[c] & mask;
@@ -175,14 +211,48 @@ struct Quad {
                 if (kSentinel || k + 1 < CNT) w[c] >>= (e[c] & 31u);
                 if (!kSentinel) tot[c] += e[c];
             }
-            fau[k] = e[0]; fad[k] = e[1]; fbu[k] = e[2]; fbd[k] = e[3];
+            got(std::integral_constant<int, K0 + k>(), e);
+        });
+        if constexpr (kSentinel) {
+#pragma unroll
+            for (int c = 0; c < 4; c++) tot[c] = (uint32_t)__builtin_clz(w[c]);
+        }
+    }
+    // C1 lookups of every chain in the first window and C2 (0: none) in the second; got(k, entries of au, ad, bu, bd)
+    template <int C1, int C2, class F>
+    __device__ __forceinline__ void step(const Unit *units, const char *lut, uint32_t mask, F &&got) {
+        uint32_t w[4], first[4], rest[4], tot[4];
+        au.bits(first[0], rest[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        ad.bits(first[1], rest[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        bu.bits(first[2], rest[2]);
+        __builtin_amdgcn_sched_barrier(0);
+        bd.bits(first[3], rest[3]);
+#pragma unroll
+        for (int c = 0; c < 4; c++) w[c] = first[c];
+        window<C1, 0>(lut, mask, w, tot, got);
+        if constexpr (C2 > 0) {
+            uint32_t tot2[4];
+#pragma unroll
+            for (int c = 0; c < 4; c++) w[c] = __builtin_amdgcn_alignbit(rest[c], first[c], tot[c]);
+            window<C2, C1>(lut, mask, w, tot2, got);
+#pragma unroll
+            for (int c = 0; c < 4; c++) tot[c] += tot2[c];
         }
 #pragma unroll
-        for (int c = 0; c < 4; c++) tot[c] = kSentinel ? (uint32_t)__builtin_clz(w[c]) : tot[c] & 0xffu;
-        au.advance(wm1, tot[0]);
-        ad.advance(wm1, tot[1]);
-        bu.advance(wm1, tot[2]);
-        bd.advance(wm1, tot[3]);
+        for (int c = 0; c < 4; c++) tot[c] &= 0xffu;
+        // one chain after the other: the selects then all take their condition from VCC, where an instruction is one issue slot
+        // and not two
+        __builtin_amdgcn_sched_barrier(0);
+        au.advance(units, tot[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        ad.advance(units, tot[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        bu.advance(units, tot[2]);
+        __builtin_amdgcn_sched_barrier(0);
+        bd.advance(units, tot[3]);
+        __builtin_amdgcn_sched_barrier(0);
     }
 };
 
@@ -200,79 +270,72 @@ struct DecodeMode {
     static constexpr int kIndexBits = kPair ? kPairIndexBits : LB;
     static constexpr int kSymsPerLookup = kPair ? 2 : 1;
     static constexpr int kLookupsPerWindow = (32 - J) / kIndexBits;       // pair table: 2; 7, 8, 10, 12 bits: 4, 3, 3, 2
-    static constexpr int kSymsPerWindow = kSymsPerLookup * kLookupsPerWindow;
-    static constexpr int kLookupsPerChain = kHalf / kSymsPerLookup;
     static constexpr int kTableBytes = (kPair ? 4 : 2) << kIndexBits;     // per tensor
 };
 
-// bytes 1 of four table entries (the symbols) as one word, first entry in the lowest byte
-__device__ __forceinline__ uint32_t pack_syms(uint32_t e0, uint32_t e1, uint32_t e2, uint32_t e3) {
-    const uint32_t lo = __builtin_amdgcn_perm(e1, e0, 0x0c0c0501u), hi = __builtin_amdgcn_perm(e3, e2, 0x0c0c0501u);
-    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+// A word of four consecutive symbols of a chain grows by one table entry at a time.  AT: number of the entry's first symbol
+// inside the word; kDown: the chain is read downwards, so that its first symbol belongs into the highest byte.
+template <int SYMS, int AT, bool kDown>
+__device__ __forceinline__ uint32_t add_syms(uint32_t word, uint32_t e) {
+    if constexpr (AT == 0) return e;  // as it came: its symbols are in bytes 1 (and 2)
+    if constexpr (SYMS == 2) return __builtin_amdgcn_perm(e, word, kDown ? 0x01020506u : 0x06050201u);
+    // one symbol an entry: word holds AT of them, the first still in byte 1 for AT = 1
+    if constexpr (AT == 1) return __builtin_amdgcn_perm(e, word, kDown ? 0x0c0c0105u : 0x0c0c0501u);
+    if constexpr (AT == 2) return __builtin_amdgcn_perm(e, word, kDown ? 0x0c010005u : 0x0c050100u);
+    return __builtin_amdgcn_perm(e, word, kDown ? 0x02010005u : 0x05020100u);
 }
-// the same from two entries of the pair table (bytes 1 and 2 of each are two consecutive symbols): e0's symbols in
-// the two lowest bytes; and with the four symbols in the opposite order (a chain that was read downwards)
-__device__ __forceinline__ uint32_t pack_pairs(uint32_t e0, uint32_t e1) { return __builtin_amdgcn_perm(e1, e0, 0x06050201u); }
-__device__ __forceinline__ uint32_t pack_pairs_rev(uint32_t e0, uint32_t e1) { return __builtin_amdgcn_perm(e1, e0, 0x01020506u); }
 
-// The table entries of a lane's four chains while they wait to be packed (fully unrolled code: an entry lives in a
-// register from its lookup to the packing of its word).  NE entries per chain: 32 one-symbol or 16 two-symbol ones.
-template <int NE>
-struct ChainSyms {
-    uint32_t au[NE], ad[NE], bu[NE], bd[NE];
-};
 // The decoded symbols of the lane's two slices, four per word, in ascending position inside the slice:
 // word j of a slice holds positions 4j .. 4j+3.  The up chain delivers words 0, 1, .. and the down chain 15, 14, ..
 struct SliceWords {
     uint32_t a[16], b[16];
 };
-// Decodes symbols S0 .. S1-1 of this lane's four chains (whole windows from S0 on; the last window of a chain may be
-// short) and packs every word whose four symbols are there.
-template <int LB, int S0, int S1>
-__device__ __forceinline__ void decode_span(Quad<DecodeMode<LB>::J> &qd, const uint32_t *wm1, const char *lut, uint32_t mask,
-                                            ChainSyms<DecodeMode<LB>::kLookupsPerChain> &e, SliceWords &p) {
+// Decodes this lane's four chains and packs every word as soon as its four symbols are there: word(slice, index, value), the
+// first two as integral constants.
+template <int LB, class F>
+__device__ __forceinline__ void decode_words(Quad<DecodeMode<LB>::J> &qd, const Unit *units, const char *lut, uint32_t mask,
+                                             F &&word) {
     using M = DecodeMode<LB>;
-    constexpr int SP = M::kSymsPerLookup, NL = M::kLookupsPerWindow, NS = M::kSymsPerWindow;
-    static_assert(S0 % NS == 0 && S0 < S1 && S1 <= kHalf && (S1 % NS == 0 || S1 == kHalf), "whole windows");
-    auto pack_words = [&](int w0, int w1) {
+    using std::integral_constant;
+    constexpr int SP = M::kSymsPerLookup, NL = M::kLookupsPerWindow, kLookups = kHalf / SP;
+    uint32_t part[4];
+    // C1 + C2 lookups from number K on
+    auto take = [&](auto kc, auto c1, auto c2) {
+        constexpr int K = decltype(kc)::value, C1 = decltype(c1)::value, C2 = decltype(c2)::value;
+        qd.template step<C1, C2>(units, lut, mask, [&](auto lc, const uint32_t (&e)[4]) {
+            constexpr int first = (K + decltype(lc)::value) * SP, at = first % 4, w = first / 4;
 #pragma unroll
-        for (int w = w0; w < w1; w++) {
-            if constexpr (SP == 1) {
-                p.a[w] = pack_syms(e.au[4 * w], e.au[4 * w + 1], e.au[4 * w + 2], e.au[4 * w + 3]);
-                p.a[15 - w] = pack_syms(e.ad[4 * w + 3], e.ad[4 * w + 2], e.ad[4 * w + 1], e.ad[4 * w]);
-                p.b[w] = pack_syms(e.bu[4 * w], e.bu[4 * w + 1], e.bu[4 * w + 2], e.bu[4 * w + 3]);
-                p.b[15 - w] = pack_syms(e.bd[4 * w + 3], e.bd[4 * w + 2], e.bd[4 * w + 1], e.bd[4 * w]);
-            } else {
-                p.a[w] = pack_pairs(e.au[2 * w], e.au[2 * w + 1]);
-                p.a[15 - w] = pack_pairs_rev(e.ad[2 * w], e.ad[2 * w + 1]);
-                p.b[w] = pack_pairs(e.bu[2 * w], e.bu[2 * w + 1]);
-                p.b[15 - w] = pack_pairs_rev(e.bd[2 * w], e.bd[2 * w + 1]);
+            for (int c = 0; c < 4; c++)
+                part[c] = c & 1 ? add_syms<SP, at, true>(part[c], e[c]) : add_syms<SP, at, false>(part[c], e[c]);
+            // packed here and now: left to itself the compiler packs after the last lookup and keeps every entry until then
+            if constexpr (at > 0 && (at + SP) % 2 == 0) asm volatile("" : "+v"(part[0]), "+v"(part[1]), "+v"(part[2]), "+v"(part[3]));
+            if constexpr (at + SP == 4) {
+                constexpr integral_constant<int, 0> a;
+                constexpr integral_constant<int, 1> b;
+                constexpr integral_constant<int, w> up;
+                constexpr integral_constant<int, 15 - w> down;
+                word(a, up, part[0]);
+                word(a, down, part[1]);
+                word(b, up, part[2]);
+                word(b, down, part[3]);
             }
-        }
+        });
     };
-    constexpr int kFull = (S1 - S0) / NS, kTailSyms = (S1 - S0) - kFull * NS, kTail = kTailSyms / SP;
-    static_assert(kTailSyms % SP == 0, "a span ends on a whole table entry");
-#pragma unroll
-    for (int r = 0; r < kFull; r++) {
-        uint32_t fau[NL], fad[NL], fbu[NL], fbd[NL];
-        qd.template step<NL>(wm1, lut, mask, fau, fad, fbu, fbd);
-        const int s = S0 + r * NS;
-#pragma unroll
-        for (int k = 0; k < NL; k++) {
-            e.au[s / SP + k] = fau[k]; e.ad[s / SP + k] = fad[k]; e.bu[s / SP + k] = fbu[k]; e.bd[s / SP + k] = fbd[k];
-        }
-        pack_words(s / 4, (s + NS) / 4);
-    }
-    if constexpr (kTail > 0) {
-        uint32_t fau[kTail ? kTail : 1], fad[kTail ? kTail : 1], fbu[kTail ? kTail : 1], fbd[kTail ? kTail : 1];
-        qd.template step<(kTail ? kTail : 1)>(wm1, lut, mask, fau, fad, fbu, fbd);
-        constexpr int s = S0 + kFull * NS;
-#pragma unroll
-        for (int k = 0; k < kTail; k++) {
-            e.au[s / SP + k] = fau[k]; e.ad[s / SP + k] = fad[k]; e.bu[s / SP + k] = fbu[k]; e.bd[s / SP + k] = fbd[k];
-        }
-        pack_words(s / 4, (s + kTailSyms) / 4);
-    }
+    constexpr int kSteps = (kLookups + 2 * NL - 1) / (2 * NL);  // two windows each; the last one may be short
+    static_for<0, kSteps>([&](auto r) {
+        constexpr int K = decltype(r)::value * 2 * NL, n = kLookups - K < 2 * NL ? kLookups - K : 2 * NL;
+        constexpr int C1 = n < NL ? n : NL;
+        take(integral_constant<int, K>(), integral_constant<int, C1>(), integral_constant<int, n - C1>());
+    });
+}
+// the same into registers
+template <int LB>
+__device__ __forceinline__ void decode_block(Quad<DecodeMode<LB>::J> &qd, const Unit *units, const char *lut, uint32_t mask,
+                                             SliceWords &p) {
+    decode_words<LB>(qd, units, lut, mask, [&](auto slice, auto index, uint32_t v) {
+        if constexpr (decltype(slice)::value == 0) p.a[decltype(index)::value] = v;
+        else p.b[decltype(index)::value] = v;
+    });
 }
 // the 4 x 4 bytes of a quad of lanes transposed: lane q of the result holds byte q of the four lanes' words, lane 0's in
 // the lowest byte

@@ -437,11 +437,11 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     const int longest = std::max(g.lut_bits[0], g.lut_bits[1]);
     const size_t lds_fixed = fused_lds_fixed(g.G, longest);
     int stage = ctx->tune_stage;
-    if (stage <= 0) stage = (int)align_up((size_t)ctx->max_size16 * 16 + 16, 256);
+    if (stage <= 0) stage = (int)align_up((size_t)ctx->max_size16 * 16 + kStreamSlack, 256);
     stage = std::max(stage, 4608);
     stage = (int)align_up(stage, 16);
     const size_t per_wave_rest = fused_weight_bytes(g.G);
-    const int reg_waves = 4 * fused_waves_per_simd(g.G, fused_table_bits(longest));
+    const int reg_waves = 4 * fused_waves_per_simd(g.G);
     int max_waves = reg_waves;
     if (ctx->tune_waves > 0) max_waves = std::min(max_waves, ctx->tune_waves);
     max_waves = std::max(1, std::min(max_waves, (int)((kLdsBytesPerCU - lds_fixed) / ((size_t)stage + per_wave_rest))));
@@ -677,7 +677,7 @@ static kvcomp_status decompress_impl(kvcomp_ctx *ctx, int which, void *d_out, in
         st = check_flags(ctx, s);
         if (st) return st;
     }
-    const int stage = (int)align_up((size_t)ctx->max_size16 * 16 + 16, 256);
+    const int stage = (int)align_up((size_t)ctx->max_size16 * 16 + kStreamSlack, 256);
     HIP_TRY(launch_decompress(ctx->geo, which, static_cast<uint16_t *>(d_out), ctx->n_blocks, ctx->res_head, ctx->n_res,
                               seq_stride, stage, tree_walk, ctx->h_refused_dev, s));
     return KVCOMP_OK;

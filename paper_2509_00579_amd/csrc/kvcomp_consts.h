@@ -30,6 +30,10 @@ constexpr int kHdrBytesV = kMinMaxBytesV + 2 * kSlices;   // 512
 constexpr int kMaxPayloadBytes = kTile * kLutBits / 8;  // 12288
 constexpr int kMaxRecordBytes = kHdrBytesK + kMaxPayloadBytes + 16;
 
+// A decoder's stream readers may read this far behind a record (values that decode nothing): room behind it in every staging
+// area, and behind the last record of the arena.
+constexpr int kStreamSlack = 32;
+
 // Block Offsets Array entry (Section 3): where the record of a 2D block lives, in 16-byte units from the start of
 // the payload arena, and how long it is.
 struct BlockEntry {

@@ -72,30 +72,23 @@ constexpr int kCUs = 256;  // compute units of the MI355X
 constexpr int kXCDs = 8;   // accelerator dies, each with its own L2; workgroups are dealt to them round-robin
 // Groups of 4 and 8 query heads: a wave packs the decoded symbols of a block into registers and multiplies them with the
 // weights of all heads on int8 MFMA.  A wave's LDS area next to its staging area holds the A operand while it is laid
-// out: three digit rows per head, 128 + 4 bytes each.
-constexpr int kARowBytes = kD + 4;
+// out: three digit rows per head, 128 + 16 bytes each.
+constexpr int kARowBytes = kD + 16;
 constexpr int tile_bytes(int G) { return 3 * G * kARowBytes; }
-// Both groups multiply after every half of a block (16 symbols of every decode chain), so that the products of the
-// first half run while the second half is decoded, and recombine the result tiles after each half.  Groups of 8 on the
-// kernels with two waves per SIMD (single-symbol tables), where registers are plentiful, keep the integer accumulators
-// across both halves and recombine once.  2 = recombine once.
-constexpr int tile_halves_at_once(int G, int table_bits) { return G >= 8 && table_bits > 6 ? 2 : 1; }
-// Waves of the fused kernel per SIMD, as the registers allow: groups of 4 and 8 query heads trade occupancy for
-// registers.  One workgroup per CU holds them all (4 SIMDs: up to 16 waves).
-// The pair-table kernels (longest code word <= 6 bits) keep fewer table entries in flight and fit one wave more.
-constexpr int fused_waves_per_simd(int G, int table_bits) {
-    return table_bits <= 6 ? (G >= 4 ? 3 : 4) : (G >= 8 ? 2 : G >= 4 ? 3 : 4);
-}
+// Waves of the fused kernel per SIMD, as the registers allow: groups of 8 query heads hold more state.  One workgroup per CU
+// holds them all (4 SIMDs: up to 16 waves).
+constexpr int fused_waves_per_simd(int G) { return G >= 8 ? 3 : 4; }
+// Waves of a workgroup that the kernels are compiled for.  Those with a wave per record are launched with twelve at most.
+constexpr int fused_max_waves(int G, bool paired) { return paired ? 12 : 4 * fused_waves_per_simd(G); }
 // Table width a decode kernel is compiled for, given the longest code word in use.  6: code words of up to 6 bits,
 // decoded two at a time with the pair table (the fused kernel only; the stand-alone decompressor uses its 7-bit build).
 constexpr int fused_table_bits(int longest) {
     return longest <= 6 ? 6 : longest <= 7 ? 7 : longest <= 8 ? 8 : longest <= 10 ? 10 : 12;
 }
 constexpr int kLdsBytesPerCU = 160 * 1024;
-// Bytes of one wave's LDS area next to its staging area, in which the A operand is laid out.  Groups of 1 and 2 heads:
-// four digit rows per head; 16 bytes of padding put the rows into different banks.
-constexpr int kDigitRow = kD + 16;
-constexpr size_t fused_weight_bytes(int G) { return G >= 4 ? (size_t)tile_bytes(G) : (size_t)G * 4 * kDigitRow; }
+// Bytes of one wave's LDS area next to its staging area, in which the A operand is laid out (groups of 1 and 2 heads make
+// theirs in registers).
+constexpr size_t fused_weight_bytes(int G) { return G >= 4 ? (size_t)tile_bytes(G) : 0; }
 // LDS of one fused-kernel workgroup apart from the per-wave areas: the two decode tables, the query rows, the merge flag.
 constexpr size_t fused_lds_fixed(int G, int longest) {
     return (fused_table_bits(longest) == 6 ? (size_t)2 * kPairTableEntries * 4 : (size_t)4 << fused_table_bits(longest)) +

@@ -1246,6 +1246,45 @@ def test_block_quant_k(gpu, oracle, H, Hq, max_len):
     gc.close()
 
 
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("limit", [6, 7, 8, 10, 12])
+def test_streams_of_short_and_of_very_unequal_slices(gpu, oracle, G, limit):
+    """Codes with probability 2^-(k+1) in every block: the shortest code words of every table width, so that a chain's 32
+    symbols end inside the first 64-bit unit or two of its stream, next to slices with every long code word; whole rows and
+    columns of code 0, whose slices are as short as a slice can be, at both ends of the records too."""
+    _say(f"short and unequal slices, code words of up to {limit} bits, {G} query heads per KV head")
+    B, H, S = 1, 2, 64 * 9
+    rng = np.random.default_rng(41 + limit)
+    Kx, Vx = W.make_kv(B, H, S, 41)
+    for X, unit_axis in ((Kx, "token"), (Vx, "channel")):
+        geo = np.minimum(rng.geometric(0.5, size=X.shape) - 1, 50).astype(np.float16)
+        long_rows = rng.random((B, S, 1, 128)) < (0.1 if limit <= 8 else 0.01)   # rare enough for the longest code words
+        geo = np.where(long_rows, rng.integers(0, 51, X.shape), np.minimum(geo, 12)).astype(np.float16)
+        geo[:, 60:64] = 0               # the last tokens (K: the last slices) of the first block
+        geo[..., 120:] = 0              # the last channels (V: the last slices) of every block
+        if unit_axis == "token":        # every K unit (channel over a block's tokens) spans [0, 50] -> code == value
+            geo[:, 0::64], geo[:, 1::64] = 0, 50
+        else:                           # every V unit (token over the channels) too
+            geo[..., 0], geo[..., 1] = 0, 50
+        X[...] = geo
+    oc = oracle.OracleCache(B, H, G * H, S + 64, 1e-2, 1e-2, 0, limit)
+    gc = gpu.KVCompCache(B, H, G * H, S + 64, 1e-2, 1e-2, max_code_len=limit)
+    oc.build_codebook(Kx, Vx)
+    gc.build_codebook(_dev(Kx), _dev(Vx))
+    assert all(int(oc.len[w][:51].min()) <= 3 and int(oc.len[w].max()) == limit for w in (K, V))
+    oc.compress_blocks(Kx, Vx)
+    gc.compress_blocks(_dev(Kx), _dev(Vx))
+    for which in (K, V):
+        got = gc.decompress(which, S).cpu().numpy()
+        np.testing.assert_array_equal(got.view(np.uint16), oc.decompress(which).view(np.uint16))
+    q = W.make_queries(B, G * H, 1, 41)[0]
+    want = oc.attn_decode(q, 1e-3)
+    _attn_close(gc.attn_decode(_dev(q), 1e-3).cpu().numpy(), want)
+    gc.set_tuning(n_splits=1, stage_bytes=4608)    # one wave after the other, and long records from global memory
+    _attn_close(gc.attn_decode(_dev(q), 1e-3).cpu().numpy(), want)
+    gc.close()
+
+
 @pytest.mark.parametrize("B,H,S,k_mode,max_len", [(2, 2, 200, 0, 7), (1, 3, 333, 1, 10), (1, 1, 64, 0, 12)])
 def test_stand_alone_decompression(gpu, oracle, B, H, S, k_mode, max_len):
     """The decompressed cache (blocks reconstructed in fp16, then the buffered tokens) is bit-identical to the
