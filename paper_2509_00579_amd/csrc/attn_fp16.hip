@@ -51,7 +51,7 @@ __device__ __forceinline__ void merge_waves_and_splits(float (&comb)[kBWaves][G]
         }
     }
     if (gridDim.x > 1)
-        finish_splits<G>(partials, counters + bh, b * Hq + h * G, (int)gridDim.x, out, tid, 64 * kBWaves, &comb[0][0][0],
+        finish_splits<G, false>(partials, counters + bh, b * Hq + h * G, (int)gridDim.x, out, tid, 64 * kBWaves, &comb[0][0][0],
                          split_stride);
 }
 

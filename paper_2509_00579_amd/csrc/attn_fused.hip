@@ -310,21 +310,13 @@ struct TileSoft {
     }
 };
 
-// maximum / sum over the 32 lanes of this lane's half of the wave
+// maximum over the 32 lanes of this lane's half of the wave
 __device__ __forceinline__ float half_max(float v, bool upper) {
     v = fmaxf(v, dpp_f<kDppXor1>(v));
     v = fmaxf(v, dpp_f<kDppXor2>(v));
     v = fmaxf(v, dpp_f<kDppHalfMirror>(v));
     v = fmaxf(v, dpp_f<kDppMirror>(v));
     const float lo = fmaxf(bcast(v, 0), bcast(v, 16)), hi = fmaxf(bcast(v, 32), bcast(v, 48));
-    return upper ? hi : lo;
-}
-__device__ __forceinline__ float half_sum(float v, bool upper) {
-    v += dpp_f<kDppXor1>(v);
-    v += dpp_f<kDppXor2>(v);
-    v += dpp_f<kDppHalfMirror>(v);
-    v += dpp_f<kDppMirror>(v);
-    const float lo = bcast(v, 0) + bcast(v, 16), hi = bcast(v, 32) + bcast(v, 48);
     return upper ? hi : lo;
 }
 
@@ -652,59 +644,56 @@ __device__ __noinline__ void v_tile_block_global(const uint32_t *rec, const char
     v_tile_block<G, LB, false>(rec, lut, mask2, tile, zeros, pc, two_eb, bias, lane, ts, [] {}, [](float (&)[G / 2][2]) {});
 }
 
-// A wave's softmax state parked in LDS, G * 128 + 3 * G floats: o[g][channel] then {m, l, bv} per head with l and bv
-// already summed over the lanes: the buffered tokens are merged into it there, and the tile path changes its layout this way.
+// A wave's softmax state parked in LDS for the merge of the workgroup's waves: o[g][channel] in the wave's own staging area,
+// its reference m and, summed over the lanes, l and bv (what every channel's o is short of) in ml[m, l, bv][g][wave].  The
+// buffered tokens are merged into it there, and the tile path changes its layout this way.
+constexpr int kMergeWaves = 16;
 template <int G>
-__device__ __forceinline__ void soft_to_area(const Soft<G> &st, float *area, int lane) {
+__device__ __forceinline__ float *merge_word(float *ml, int word, int g, int wave) {
+    return ml + (word * G + g) * kMergeWaves + wave;
+}
+template <int G>
+__device__ __forceinline__ void soft_to_area(const Soft<G> &st, float *area, float *ml, int wave, int lane) {
     wave_sync();
 #pragma unroll
     for (int g = 0; g < G; g++) {
-        area[g * kD + 2 * lane] = st.acc[g][0];
-        area[g * kD + 2 * lane + 1] = st.acc[g][1];
+        *reinterpret_cast<float2 *>(area + g * kD + 2 * lane) = make_float2(st.acc[g][0], st.acc[g][1]);
         const float l = wave_sum(st.l[g]), bv = wave_sum(st.bv[g]);
         if (lane == 0) {
-            area[G * kD + 3 * g] = st.m[g];
-            area[G * kD + 3 * g + 1] = l;
-            area[G * kD + 3 * g + 2] = bv;
+            *merge_word<G>(ml, 0, g, wave) = st.m[g];
+            *merge_word<G>(ml, 1, g, wave) = l;
+            *merge_word<G>(ml, 2, g, wave) = bv;
         }
     }
     wave_sync();
 }
-// lane = channels 2*lane, 2*lane+1 of every head; l and bv in lane 0 only
+// the tile path's state: lane l holds column l % 32, heads l / 32 + 2 i
 template <int G>
-__device__ __forceinline__ void area_to_soft(const float *area, int lane, Soft<G> &st) {
-    wave_sync();
-#pragma unroll
-    for (int g = 0; g < G; g++) {
-        st.acc[g][0] = area[g * kD + 2 * lane];
-        st.acc[g][1] = area[g * kD + 2 * lane + 1];
-        st.m[g] = area[G * kD + 3 * g];
-        st.l[g] = lane == 0 ? area[G * kD + 3 * g + 1] : 0.f;
-        st.bv[g] = lane == 0 ? area[G * kD + 3 * g + 2] : 0.f;
-    }
-    wave_sync();
-}
-// the tile path's state (lane l: column l % 32, heads l / 32 + 2 i) into the area
-template <int G>
-__device__ __forceinline__ void tile_state_to_area(const TileSoft<G> &ts, float *area, int lane) {
+__device__ __forceinline__ void soft_to_area(const TileSoft<G> &ts, float *area, float *ml, int wave, int lane) {
     constexpr int HL = G / 2;
     const int x = lane & 31, hv = lane >> 5;
     wave_sync();
+    float l[HL], bv[HL];
 #pragma unroll
     for (int i = 0; i < HL; i++) {
         const int head = hv + 2 * i;
 #pragma unroll
         for (int ct = 0; ct < 4; ct++) area[head * kD + 32 * ct + x] = ts.acc[i][ct];
-        const float l = half_sum(ts.l[i], hv != 0), bv = half_sum(ts.bv[i], hv != 0);
+        l[i] = ts.l[i];
+        bv[i] = ts.bv[i];
+    }
+    half_sums<HL>(l, lane);
+    half_sums<HL>(bv, lane);
+#pragma unroll
+    for (int i = 0; i < HL; i++) {
         if (x == 0) {
-            area[G * kD + 3 * head] = ts.m[i];
-            area[G * kD + 3 * head + 1] = l;
-            area[G * kD + 3 * head + 2] = bv;
+            *merge_word<G>(ml, 0, hv + 2 * i, wave) = ts.m[i];
+            *merge_word<G>(ml, 1, hv + 2 * i, wave) = l[i];
+            *merge_word<G>(ml, 2, hv + 2 * i, wave) = bv[i];
         }
     }
     wave_sync();
 }
-
 
 // The buffered fp16 tokens (Section 3.2.3: the newest vectors take part too), in units of 16 tokens; this wave takes
 // units first_unit, first_unit + unit_step, ...  Token r of the buffer (oldest = 0) sits in slot
@@ -724,7 +713,7 @@ __device__ __forceinline__ void tile_state_to_area(const TileSoft<G> &ts, float 
 // When the append of the newest token is fused into the launch (new_row >= 0), its row comes from k_new / v_new
 // instead of the buffer, and the lanes that read it store it into its buffer slot for the launches to come: one
 // wave of the grid per (batch, head) owns that row, so there is one writer and no reader of the slot in this launch.
-// The result is merged into the wave's parked state (`area`, see soft_to_area).
+// The result is merged into the wave's parked state (`area` and `ml`, see soft_to_area).
 // Inline: the decode loop leaves room for it.  Out of line it saved and restored the registers that a callee has to keep, through
 // scratch memory (4 x 8 heads x 9000 tokens, 1024 of them buffered, groups of 8: 29.3 -> 27.6 us).
 constexpr int kUnitTokens = 16;
@@ -775,7 +764,7 @@ template <int G>
 __device__ __forceinline__ void buffered_tokens(const uint16_t *res, int res_tokens, int B, int H, int b, int h,
                                              int res_head, int n_res, int first_unit, int unit_step,
                                              const uint16_t *q0, float scale, int lane, const uint16_t *k_new,
-                                             const uint16_t *v_new, int new_row, float *area) {
+                                             const uint16_t *v_new, int new_row, float *area, float *ml, int wave) {
     const size_t res_tensor = (size_t)B * res_tokens * H * kD;
     const int n_units = (n_res + kUnitTokens - 1) / kUnitTokens;
     const int col = lane & 15, grp = lane >> 4;
@@ -871,13 +860,13 @@ __device__ __forceinline__ void buffered_tokens(const uint16_t *res, int res_tok
     l = fold_rows(l, l);
     float fa = 1.f, fb = 0.f;
     if (col < G) {
-        float *ml = area + G * kD + 3 * col;
-        const float ma = ml[0], mx = fmaxf(ma, m);
+        float *pm = merge_word<G>(ml, 0, col, wave), *pl = merge_word<G>(ml, 1, col, wave), *pb = merge_word<G>(ml, 2, col, wave);
+        const float ma = *pm, mx = fmaxf(ma, m);
         fa = ma == -INFINITY ? 0.f : __expf(ma - mx);  // 0 for a state that is still empty
         fb = m == -INFINITY ? 0.f : __expf(m - mx);
-        const float l1 = fmaf(ml[1], fa, l * fb), bv1 = ml[2] * fa;
+        const float l1 = fmaf(*pl, fa, l * fb), bv1 = *pb * fa;
         wave_sync();
-        if (grp == 0) { ml[0] = mx; ml[1] = l1; ml[2] = bv1; }
+        if (grp == 0) { *pm = mx; *pl = l1; *pb = bv1; }
     }
     // fold the four rows: lane (grp, col) ends up with channels 8 col + 2 grp, +1 of all tokens
     for_heads<G>([&](auto gc) {
@@ -914,6 +903,7 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB, kPaired>::value), 1) void fus
     __shared__ __attribute__((aligned(16))) float qf[kTile ? G * kD : 4];
     __shared__ __attribute__((aligned(16))) uint8_t zeros[kTile ? kD : 16];  // tile path: the A operand's rows without a digit
     __shared__ uint32_t ready[kPaired ? 16 : 1];  // paired: wave w's numerators are in its record area
+    __shared__ float merge_ml[3 * G * kMergeWaves];  // see soft_to_area
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // per wave: staging area; tile path: + weights
     const int tid = threadIdx.x, lane = tid & 63, n_threads = blockDim.x;
     // the wave number and everything derived from it (block numbers, table entries, record addresses) are scalars
@@ -1230,89 +1220,73 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB, kPaired>::value), 1) void fus
     }
     }
 
-    // The record area is free now: the tile path changes the layout of its state through it, and a wave with buffered
-    // tokens parks its state there.
+    // The record area is free now: the wave's state is parked there, and the buffered tokens join it.
     if (!kPaired || is_v) {  // a K wave of a pair has no state, and its area may still be read
         float *area = reinterpret_cast<float *>(stage);
-        bool parked = false;
-        if constexpr (kTile) {
-            tile_state_to_area<G>(ts, area, lane);
-            parked = true;
-        }
+        if constexpr (kTile) soft_to_area<G>(ts, area, merge_ml, wave, lane);
+        else soft_to_area<G>(st, area, merge_ml, wave, lane);
         // the buffered fp16 tokens in units of 16: unit u goes to split n_splits-1 - u % n_splits (the last split is the
         // short one), there to the waves in turn, starting after the wave that took the split's last block
         if (a.n_res > 0) {
             // 0 for the wave whose turn the next block would be; paired: for the first wave behind the pairs
             const int turn = kPaired ? wave - 2 * n_pairs : j - j1, takers = kPaired ? n_waves - 2 * n_pairs : n_waves;
             const int first = a.n_splits - 1 - split + a.n_splits * turn;
-            if (turn >= 0 && first * kUnitTokens < a.n_res) {
-                if (!parked) soft_to_area<G>(st, area, lane);
-                parked = true;
+            if (turn >= 0 && first * kUnitTokens < a.n_res)
                 buffered_tokens<G>(a.res, a.res_tokens, a.B, a.H, b, h, a.res_head, a.n_res, first, takers * a.n_splits,
-                                   q0, a.scale, lane, a.k_new, a.v_new, a.new_row, area);
-            }
-        }
-        if (parked) area_to_soft<G>(area, lane, st);
-        wave_sync();
-
-        // merge the waves of this workgroup into one partial (o[128], m, l) per query head
-        float *comb = reinterpret_cast<float *>(stage);  // this wave's own staging area: G * 130 floats
-#pragma unroll
-        for (int gg = 0; gg < G; gg++) {
-            const float l = wave_sum(st.l[gg]);
-            const float bv = wave_sum(st.bv[gg]);
-            comb[gg * kPartialStride + 2 * lane] = st.acc[gg][0] + bv;
-            comb[gg * kPartialStride + 2 * lane + 1] = st.acc[gg][1] + bv;
-            if (lane == 0) {
-                comb[gg * kPartialStride + kD] = st.m[gg];
-                comb[gg * kPartialStride + kD + 1] = l;
-            }
+                                   q0, a.scale, lane, a.k_new, a.v_new, a.new_row, area, merge_ml, wave);
         }
     }
     __syncthreads();
+    // Merge the waves of this workgroup into one partial (o[128], m, l) per query head, a wave per head: lane w holds wave w's
+    // m, l and bv, so the weights are there after one reduction; then every lane adds up two channels.  A thread per channel
+    // that read every wave's m, l and o and kept a running maximum, with the states turned into another layout before, took
+    // 1.8 us for groups of 8 and 12 waves.
     const int row0 = b * a.Hq + h * G;
     // the thread number is rebuilt from the lane and the (scalar) wave number: nothing of the prologue has to stay
     // in a register, or be spilled, across the decode loop for the sake of the merge
     const int tid_m = lane + 64 * wave, nt_m = 64 * n_waves;
-    for (int i = tid_m; i < G * kD; i += nt_m) {
-        const int gg = i / kD, c = i - gg * kD;
-        float M_ = -INFINITY, L = 0.f, O = 0.f;
-        for (int w0 = kPaired ? n_pairs : 0; w0 < n_waves; w0 += 4) {  // the LDS reads of four waves' states at a time
-            float mw[4], lw[4], ow[4], mx = M_;
+    for (int gg = wave; gg < G; gg += n_waves) {
+        const int w0 = kPaired ? n_pairs : 0;
+        float2 o[4];
+        auto request = [&](int w) {  // the LDS reads of four waves' states at a time
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                o[k] = reinterpret_cast<const float2 *>(smem + (size_t)min(w + k, n_waves - 1) * a.stage_bytes)[gg * (kD / 2) + lane];
+        };
+        request(w0);  // travels behind the weights
+        float mw = -INFINITY, lw = 0.f, bw = 0.f;
+        if (lane >= w0 && lane < n_waves) {
+            mw = *merge_word<G>(merge_ml, 0, gg, lane);
+            lw = *merge_word<G>(merge_ml, 1, gg, lane);
+            bw = *merge_word<G>(merge_ml, 2, gg, lane);
+        }
+        const float M_ = wave_max(mw);
+        const uint32_t live = (uint32_t)__builtin_amdgcn_ballot_w64(mw != -INFINITY);  // the others had nothing to do
+        const float f = mw == -INFINITY ? 0.f : __expf(mw - M_);
+        const float L = wave_sum(mw == -INFINITY ? 0.f : lw * f);
+        float O0 = wave_sum(mw == -INFINITY ? 0.f : bw * f), O1 = O0;
+        for (int w = w0; w < n_waves; w += 4) {
+            if (w > w0) request(w);
 #pragma unroll
             for (int k = 0; k < 4; k++) {
-                const float *cw = reinterpret_cast<const float *>(smem + (size_t)min(w0 + k, n_waves - 1) * a.stage_bytes) +
-                                  gg * kPartialStride;
-                mw[k] = w0 + k < n_waves ? cw[kD] : -INFINITY;
-                lw[k] = cw[kD + 1];
-                ow[k] = cw[c];
-                mx = fmaxf(mx, mw[k]);
+                if (!((live >> (w + k)) & 1u)) continue;  // uniform; no lane beyond the last wave is live
+                const float fw = bcast(f, w + k);
+                O0 = fmaf(fw, o[k].x, O0);
+                O1 = fmaf(fw, o[k].y, O1);
             }
-            // the loads stay together, in front of the branches (selects or loads behind them cost groups of 8 0.6 us)
-            asm volatile("" : "+v"(lw[0]), "+v"(lw[1]), "+v"(lw[2]), "+v"(lw[3]), "+v"(ow[0]), "+v"(ow[1]), "+v"(ow[2]), "+v"(ow[3]));
-            if (mx == -INFINITY) continue;  // waves that had nothing to do
-            const float f0 = __expf(M_ - mx);
-            L *= f0;
-            O *= f0;
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                if (w0 + k >= n_waves) break;  // uniform.  A copy of the last wave's sums: 0 times them is NaN if they are Inf
-                const float f = __expf(mw[k] - mx);  // 0 for a wave that had nothing to do
-                L = fmaf(lw[k], f, L);
-                O = fmaf(ow[k], f, O);
-            }
-            M_ = mx;
         }
         if (a.n_splits == 1) {
-            a.out[(size_t)(row0 + gg) * kD + c] = O / L;
+            a.out[(size_t)(row0 + gg) * kD + 2 * lane] = O0 / L;
+            a.out[(size_t)(row0 + gg) * kD + 2 * lane + 1] = O1 / L;
         } else {
             float *dst = a.partials + ((size_t)(row0 + gg) * kMaxSplits + split) * kPartialStride;
-            store_agent(dst + c, O);
-            if (c == 0) { store_agent(dst + kD, M_); store_agent(dst + kD + 1, L); }
+            store_agent(dst + 2 * lane, O0);
+            store_agent(dst + 2 * lane + 1, O1);
+            if (lane == 0) { store_agent(dst + kD, M_); store_agent(dst + kD + 1, L); }
         }
     }
-    if (a.n_splits > 1) finish_splits<G>(a.partials, a.counters + bh, row0, a.n_splits, a.out, tid_m, nt_m,
-                                           reinterpret_cast<float *>(smem));
+    if (a.n_splits > 1) finish_splits<G, true>(a.partials, a.counters + bh, row0, a.n_splits, a.out, tid_m, nt_m,
+                                               reinterpret_cast<float *>(smem));
 }
 
 template <int G, int LB, bool kPaired>

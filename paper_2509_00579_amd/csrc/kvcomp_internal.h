@@ -89,10 +89,11 @@ constexpr int kLdsBytesPerCU = 160 * 1024;
 // Bytes of one wave's LDS area next to its staging area, in which the A operand is laid out (groups of 1 and 2 heads make
 // theirs in registers).
 constexpr size_t fused_weight_bytes(int G) { return G >= 4 ? (size_t)tile_bytes(G) : 0; }
-// LDS of one fused-kernel workgroup apart from the per-wave areas: the two decode tables, the query rows, the merge flag.
+// LDS of one fused-kernel workgroup apart from the per-wave areas: the two decode tables, the query rows, what the waves leave
+// for their merge, the merge flag.
 constexpr size_t fused_lds_fixed(int G, int longest) {
     return (fused_table_bits(longest) == 6 ? (size_t)2 * kPairTableEntries * 4 : (size_t)4 << fused_table_bits(longest)) +
-           (size_t)G * kD * 4 + 512;
+           (size_t)G * (kD * 4 + 3 * 16 * 4) + 512;
 }
 
 // Unsigned division by a number that the host knows: x / d = mulhi(x, mul) >> shift for x < 2^31 (round-up method); d = 1

@@ -35,7 +35,8 @@ __device__ __forceinline__ float load_agent(const float *p) {
 // Few heads over a long cache have the most splits.  us a step, before -> now: 1 head x 32768 tokens (128 splits) groups
 // of 1 18.0 -> 10.7, of 8 34.4 -> 22.8; 8 heads x 16384 (32) 16.0 -> 15.0 and 24.1 -> 21.5; 8 heads x 2048 (8) 8.6 -> 8.5
 // and 13.5 -> 12.1; fp16 kernel, groups of 8, 2 heads x 16384 (64) 30.9 -> 20.3, 8 x 8 heads x 16384 (4) 105.4 -> 103.3.
-template <int G>
+// kPairs: the partials are 8-byte aligned, and a lane takes two neighbouring channels with one load.
+template <int G, bool kPairs>
 __device__ __forceinline__ void finish_splits(float *partials, uint32_t *counter, int row0, int n_splits, float *out,
                                               int tid, int nt, float *scratch, int split_stride = kMaxSplits) {
     static_assert(kMaxSplits <= 128, "a lane holds the state of two splits");
@@ -52,6 +53,7 @@ __device__ __forceinline__ void finish_splits(float *partials, uint32_t *counter
     if (!s_last) return;
     constexpr int kBatch = 16;  // ranges shorter than this only add their own merge
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = nt >> 6;
+    const int c0 = kPairs ? 2 * lane : lane, c1 = kPairs ? c0 + 1 : lane + 64;  // this lane's channels
     const int ranges = min(max(n_waves / G, 1), (n_splits + kBatch - 1) / kBatch);
     const int per = (n_splits + ranges - 1) / ranges;
     for (int item = wave; item < G * ranges; item += n_waves) {  // one round, unless there are fewer waves than heads
@@ -71,7 +73,14 @@ __device__ __forceinline__ void finish_splits(float *partials, uint32_t *counter
 #pragma unroll
             for (int k = 0; k < kBatch; k++) {
                 o[k][0] = o[k][1] = 0.f;
-                if (s + k < n) {
+                if (s + k >= n) continue;
+                if constexpr (kPairs) {
+                    const unsigned long long two = __hip_atomic_load(
+                        reinterpret_cast<const unsigned long long *>(p + (s + k) * kPartialStride + 2 * lane), __ATOMIC_RELAXED,
+                        __HIP_MEMORY_SCOPE_AGENT);
+                    o[k][0] = __uint_as_float((uint32_t)two);
+                    o[k][1] = __uint_as_float((uint32_t)(two >> 32));
+                } else {
                     o[k][0] = load_agent(p + (s + k) * kPartialStride + lane);
                     o[k][1] = load_agent(p + (s + k) * kPartialStride + lane + 64);
                 }
@@ -91,10 +100,9 @@ __device__ __forceinline__ void finish_splits(float *partials, uint32_t *counter
         for (int s = 0; s < n; s += kBatch) {
             if (s) request(s);
 #pragma unroll
-            for (int k = 0; k < kBatch; k++) {
+            for (int k = 0; k < kBatch; k++) {  // without branches: the loads are waited for once
                 const int at = (s + k) & 63;
-                const float w0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f0), at));
-                const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f1), at));
+                const float w0 = bcast(f0, at), w1 = bcast(f1, at);
                 const float w = s + k < 64 ? w0 : w1;
                 const bool live = ((s + k < 64 ? live0 : live1) >> at) & 1;
                 O0 = fmaf(w, live ? o[k][0] : 0.f, O0);
@@ -102,12 +110,12 @@ __device__ __forceinline__ void finish_splits(float *partials, uint32_t *counter
             }
         }
         if (ranges == 1) {
-            out[(size_t)(row0 + g) * kD + lane] = O0 / L;
-            out[(size_t)(row0 + g) * kD + lane + 64] = O1 / L;
+            out[(size_t)(row0 + g) * kD + c0] = O0 / L;
+            out[(size_t)(row0 + g) * kD + c1] = O1 / L;
         } else {
             float *c = scratch + item * kPartialStride;  // item = wave here
-            c[lane] = O0;
-            c[lane + 64] = O1;
+            c[c0] = O0;
+            c[c1] = O1;
             if (lane == 0) { c[kD] = mx; c[kD + 1] = L; }
         }
     }
