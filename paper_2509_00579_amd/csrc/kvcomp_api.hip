@@ -449,26 +449,35 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
         stage = (int)((kLdsBytesPerCU - lds_fixed - per_wave_rest) / 16 * 16);  // one wave, records above it from global memory
     const int wgs_per_cu = std::max(1, std::min(reg_waves / max_waves,
                                                 (int)(kLdsBytesPerCU / (lds_fixed + max_waves * ((size_t)stage + per_wave_rest)))));
+    const int bh = g.B * g.H, units = (ctx->n_res + 15) / 16;
+    // A wave for each record of a pair where the wave slots would be empty.  It is the shorter chain against the SIMDs'
+    // sharing, so it ends at three waves per SIMD: 32 heads in 8 splits of n pairs, one query head per KV head, code words
+    // of up to 6 bits, n = 1 2 4 6 7 8: 8.9 8.8 9.7 11.3 12.4 13.0 us against 12.4 11.1 11.0 12.6 12.7 13.2; groups of 4,
+    // n = 2 4 6: 12.2 11.5 13.4 against 17.1 14.3 16.4; groups of 8: 16.6 14.7 16.7 against 24.5 19.4 20.5; groups of 1 with
+    // code words of up to 10 bits, n = 5 6: 12.0 12.5 against 14.2 14.3, groups of 2: 12.5 13.1 against 15.1 15.3.
+    const int paired_waves = std::min(max_waves, fused_max_waves(g.G, true));
     int n_splits = ctx->tune_splits;
-    if (n_splits <= 0) {  // measured with a wave per pair, not again with one per record
-        const int bh = g.B * g.H;
+    if (n_splits <= 0) {
         const int by_chip = std::max(1, kCUs * wgs_per_cu / bh);
-        const int by_work = std::max(1, (ctx->n_blocks + 3) / 4);  // at least one block pair per SIMD of the CU
-        n_splits = std::min(by_chip, by_work);
+        const auto in_splits_of = [&](int pairs) { return (ctx->n_blocks + pairs - 1) / pairs; };
+        // At least one block pair per SIMD of the CU.  Fewer leave each wave more of the LDS pipe, but there are more partials to
+        // merge: two or three pairs pay while there are few splits.  us a step with 2, 3 and 4 pairs a split: 1 head x 16
+        // blocks 7.5 7.7 8.1, x 64 blocks 8.0 8.2 8.3, x 128 8.7 8.5 8.7; 8 heads, groups of 4, x 16 8.9 8.9 9.2, x 31 9.8 9.4
+        // 9.4, groups of 8, x 8 9.3 9.4 9.7, x 31 11.0 10.5 10.4; 32 heads x 8 8.0 7.9 8.3, x 16 8.6 8.4 8.6, x 31 10.4 10.1
+        // 9.1, groups of 8, x 16 10.9 10.5 10.5, x 31 20.2 17.6 11.2 (beyond one workgroup per CU).
+        int by_work = in_splits_of(4);
+        if (in_splits_of(2) <= 32 && in_splits_of(2) * bh <= 64) by_work = in_splits_of(2);
+        else if (in_splits_of(3) <= 8 && in_splits_of(3) * bh <= kCUs) by_work = in_splits_of(3);
+        // One split has nothing to merge across workgroups.  In 1 and in 2 splits, 4 5 6 blocks: 8 heads 6.1 7.0 7.6 against 7.2
+        // 7.5 7.6; groups of 8 7.8 9.0 9.5 against 9.2 9.4 9.5.
+        if (2 * ctx->n_blocks + units <= paired_waves) by_work = 1;
+        n_splits = std::min(by_chip, std::max(by_work, 1));
     }
     n_splits = std::max(1, std::min({n_splits, (int)kMaxSplits, std::max(ctx->n_blocks, 1)}));
     // waves of a workgroup: as many as its split has block pairs and units of buffered tokens (a short sequence leaves wave
     // slots empty rather than CUs); the kernel gives the units to the waves without a block first
     const int bps = ctx->n_blocks > 0 ? (ctx->n_blocks + n_splits - 1) / n_splits : 0;
-    const int units = (ctx->n_res + 15) / 16, units_per_split = (units + n_splits - 1) / n_splits;
-    // A wave for each record of a pair where the wave slots would be empty.  It is the shorter chain against the SIMDs'
-    // sharing, so it ends at three waves per SIMD: 32 heads in 8 splits of n pairs, one query head per KV head, code words
-    // of up to 6 bits, n = 1 2 4 6 7 8: 8.9 8.8 9.7 11.3 12.4 13.0 us against 12.4 11.1 11.0 12.6 12.7 13.2; groups of 4,
-    // n = 2 4 6: 12.2 11.5 13.4 against 17.1 14.3 16.4; groups of 8: 16.6 14.7 16.7 against 24.5 19.4 20.5.  Groups of 1 and
-    // 2 with longer code words end at two waves per SIMD: n = 4 6 8: 12.1 15.3 20.0 against 12.9 14.9 15.7.  Their kernels are
-    // compiled for the same sixteen waves as the unpaired ones, and a whole decoded block beside the lookups in flight does not
-    // fit the 128 registers of that (17 to 31 spilled); eight waves could have 256 each.
-    const int paired_waves = std::min(max_waves, fused_table_bits(longest) == 6 || g.G >= 4 ? 12 : 8);
+    const int units_per_split = (units + n_splits - 1) / n_splits;
     const bool paired = bps > 0 && 2 * bps + units_per_split <= paired_waves;
     // Sixteen waves (groups of 1 and 2) that have more than one pair each but not two leave a last round of a few waves that
     // cannot fill the LDS pipe; twelve spread it better.  32 heads in 8 splits of n pairs, groups of 1, 16 against 12 waves,
@@ -481,7 +490,9 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     // 47.4 46.9; groups of 4 with 4, 8, 12: 255 10.3 9.2 11.0, 4000 88 48.4 50.0.  Groups of 8 have more work per load: 255
     // tokens 14.4 12.9 13.8, 1000 33.6 26.4 26.6, 4000 136 83 75.5.
     if (ctx->tune_waves <= 0 && ctx->n_blocks == 0 && g.G <= 4) max_waves = std::min(max_waves, 8);
-    const int n_waves = std::max(1, std::min(max_waves, (paired ? 2 : 1) * bps + units_per_split));
+    // at least a wave per query head of the group: the merges give every head a wave (8 heads x 8 blocks in 4 splits, groups of
+    // 8: 10.5 -> 9.3 us)
+    const int n_waves = std::min(paired ? paired_waves : max_waves, std::max(g.G, (paired ? 2 : 1) * bps + units_per_split));
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (ctx->profiling) {
         if (ctx->events_used + 2 > ctx->events.size()) {
