@@ -1264,15 +1264,16 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB, kPaired>::value), 1) void fus
         const uint32_t live = (uint32_t)__builtin_amdgcn_ballot_w64(mw != -INFINITY);  // the others had nothing to do
         const float f = mw == -INFINITY ? 0.f : __expf(mw - M_);
         const float L = wave_sum(mw == -INFINITY ? 0.f : lw * f);
-        float O0 = wave_sum(mw == -INFINITY ? 0.f : bw * f), O1 = O0;
+        float O0 = 0.f, O1 = 0.f;
         for (int w = w0; w < n_waves; w += 4) {
             if (w > w0) request(w);
 #pragma unroll
             for (int k = 0; k < 4; k++) {
                 if (!((live >> (w + k)) & 1u)) continue;  // uniform; no lane beyond the last wave is live
-                const float fw = bcast(f, w + k);
-                O0 = fmaf(fw, o[k].x, O0);
-                O1 = fmaf(fw, o[k].y, O1);
+                // o and bv nearly cancel (min + step * code): their sum is formed before anything else is added
+                const float fw = bcast(f, w + k), bv = bcast(bw, w + k);
+                O0 = fmaf(fw, o[k].x + bv, O0);
+                O1 = fmaf(fw, o[k].y + bv, O1);
             }
         }
         if (a.n_splits == 1) {
