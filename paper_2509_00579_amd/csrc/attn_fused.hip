@@ -714,8 +714,11 @@ __device__ __forceinline__ void soft_to_area(const TileSoft<G> &ts, float *area,
 // instead of the buffer, and the lanes that read it store it into its buffer slot for the launches to come: one
 // wave of the grid per (batch, head) owns that row, so there is one writer and no reader of the slot in this launch.
 // The result is merged into the wave's parked state (`area` and `ml`, see soft_to_area).
-// Inline: the decode loop leaves room for it.  Out of line it saved and restored the registers that a callee has to keep, through
-// scratch memory (4 x 8 heads x 9000 tokens, 1024 of them buffered, groups of 8: 29.3 -> 27.6 us).
+// Inline: the decode loops leave room for it, and out of line it saves and restores the registers that a callee has to keep,
+// through scratch memory (4 x 8 heads x 9000 tokens, 1024 of them buffered, groups of 8: 29.3 -> 27.6 us).  Called by the kernels
+// with a wave per record for code words beyond 6 bits only: they have one unit or two and the registers of twelve waves.  Called
+// from kernels of sixteen waves it has 128 registers and spills (4 x 8 heads, groups of 4, 1000 buffered tokens and no block: 30
+// us where inline takes 17).
 constexpr int kUnitTokens = 16;
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -761,7 +764,7 @@ __device__ __forceinline__ float max_over_rows(float v) {  // over the four rows
 }
 
 template <int G>
-__device__ __forceinline__ void buffered_tokens(const uint16_t *res, int res_tokens, int B, int H, int b, int h,
+__device__ __forceinline__ void buffered_units(const uint16_t *res, int res_tokens, int B, int H, int b, int h,
                                              int res_head, int n_res, int first_unit, int unit_step,
                                              const uint16_t *q0, float scale, int lane, const uint16_t *k_new,
                                              const uint16_t *v_new, int new_row, float *area, float *ml, int wave) {
@@ -881,6 +884,15 @@ __device__ __forceinline__ void buffered_tokens(const uint16_t *res, int res_tok
         *at = make_float2(fmaf(old.x, a, o0 * c), fmaf(old.y, a, o1 * c));
     });
     wave_sync();
+}
+
+template <int G>
+__device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens, int B, int H, int b, int h,
+                                             int res_head, int n_res, int first_unit, int unit_step,
+                                             const uint16_t *q0, float scale, int lane, const uint16_t *k_new,
+                                             const uint16_t *v_new, int new_row, float *area, float *ml, int wave) {
+    buffered_units<G>(res, res_tokens, B, H, b, h, res_head, n_res, first_unit, unit_step, q0, scale, lane, k_new, v_new, new_row,
+                      area, ml, wave);
 }
 
 // One workgroup per CU, as many waves as the registers allow per SIMD (fused_waves_per_simd): 4 (128 VGPRs) or 3 (168).  The host may launch fewer waves per workgroup (short sequences,
@@ -1231,9 +1243,15 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB, kPaired>::value), 1) void fus
             // 0 for the wave whose turn the next block would be; paired: for the first wave behind the pairs
             const int turn = kPaired ? wave - 2 * n_pairs : j - j1, takers = kPaired ? n_waves - 2 * n_pairs : n_waves;
             const int first = a.n_splits - 1 - split + a.n_splits * turn;
-            if (turn >= 0 && first * kUnitTokens < a.n_res)
-                buffered_tokens<G>(a.res, a.res_tokens, a.B, a.H, b, h, a.res_head, a.n_res, first, takers * a.n_splits,
-                                   q0, a.scale, lane, a.k_new, a.v_new, a.new_row, area, merge_ml, wave);
+            if (turn >= 0 && first * kUnitTokens < a.n_res) {
+                const int step = takers * a.n_splits;
+                if constexpr (DecodeMode<LB>::kPair || !kPaired)
+                    buffered_units<G>(a.res, a.res_tokens, a.B, a.H, b, h, a.res_head, a.n_res, first, step, q0, a.scale, lane,
+                                      a.k_new, a.v_new, a.new_row, area, merge_ml, wave);
+                else
+                    buffered_tokens<G>(a.res, a.res_tokens, a.B, a.H, b, h, a.res_head, a.n_res, first, step, q0, a.scale, lane,
+                                       a.k_new, a.v_new, a.new_row, area, merge_ml, wave);
+            }
         }
     }
     __syncthreads();

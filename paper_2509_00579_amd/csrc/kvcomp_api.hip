@@ -430,8 +430,8 @@ kvcomp_status kvcomp_append_token(kvcomp_ctx *ctx, const void *d_k_new, const vo
 static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, float *d_out, const uint16_t *k_new,
                                const uint16_t *v_new, hipStream_t s) {
     const Geo &g = ctx->geo;
-    // Work split: one workgroup per CU, holding as many waves as the registers allow per SIMD (16, 12 or 8 for groups
-    // of 1-2, 4, 8 query heads) and the LDS has room for (decode tables + a staging area per wave); the grid is one
+    // Work split: one workgroup per CU, holding as many waves as the registers allow per SIMD (16, or 12 for groups
+    // of 8 query heads) and the LDS has room for (decode tables + a staging area per wave); the grid is one
     // round of workgroups, every wave owning whole block pairs.  Per-workgroup costs (tables, split merge) are then
     // paid once per CU, and the waves of a head's split merge through LDS.
     const int longest = std::max(g.lut_bits[0], g.lut_bits[1]);
@@ -479,11 +479,11 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     const int bps = ctx->n_blocks > 0 ? (ctx->n_blocks + n_splits - 1) / n_splits : 0;
     const int units_per_split = (units + n_splits - 1) / n_splits;
     const bool paired = bps > 0 && 2 * bps + units_per_split <= paired_waves;
-    // Sixteen waves (groups of 1 and 2) that have more than one pair each but not two leave a last round of a few waves that
-    // cannot fill the LDS pipe; twelve spread it better.  32 heads in 8 splits of n pairs, groups of 1, 16 against 12 waves,
-    // n = 16 18 20 24 28 30 34 64: 21.4 23.4 24.7 27.1 28.8 31.0 32.3 51.5 against 21.7 22.6 23.4 26.2 28.2 30.2 32.4 52.0 us;
-    // the same with code words of up to 12 bits (n = 20: 30.8 against 29.5) and for groups of 2.  Groups of 4 and 8 have
-    // twelve waves at most and gain less, each length at another number.
+    // Sixteen waves that have more than one pair each but not two leave a last round of a few waves that cannot fill the LDS
+    // pipe; twelve spread it a little better.  32 heads in 8 splits of n pairs, 16 against 12 waves, n = 16 18 20 24 28 31 34 64:
+    // groups of 1 19.3 21.7 22.3 24.2 26.2 28.0 29.0 45.1 against 20.0 21.2 21.5 23.8 26.5 28.1 30.2 46.6 us; groups of 4 20.1
+    // 22.7 23.2 25.2 27.4 29.7 31.4 48.7 against 20.9 22.5 22.9 25.4 27.1 29.8 32.6 50.7; groups of 2 with code words of up to
+    // 10 bits, n = 18 20 28 31: 28.6 29.2 35.5 38.8 against 28.4 28.8 35.2 38.8.
     if (ctx->tune_waves <= 0 && max_waves == 16 && bps > 16 && bps < 32) max_waves = 12;
     // Buffered tokens only: two waves per SIMD for groups of 1, 2 and 4.  More only get in each other's way; 4, 8, 12 and 16
     // waves of groups of 1, 32 heads: 255 tokens 8.0 7.6 9.4 10.7 us, 1000 tokens 19.2 13.7 16.1 17.7, 4000 tokens 75.8 42.7
