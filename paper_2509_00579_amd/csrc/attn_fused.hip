@@ -84,10 +84,11 @@ struct Soft {
     }
     // s: this lane's score.  Returns its softmax numerator.  The reference m is the same in all lanes and moves only when
     // a score exceeds it by more than kLazyMaxDot (m = -inf before the first block): most blocks then need no maximum
-    // over the wave and no rescaling of the sums.
+    // over the wave and no rescaling of the sums.  The test is written so that a NaN passes it: a first block whose tokens all
+    // score -Inf or NaN gets its reference too.
     __device__ __forceinline__ float update(int g, float s) {
-        if (__builtin_amdgcn_ballot_w64(s - m[g] > kLazyMaxDot) != 0) {
-            const float mnew = fmaxf(m[g], wave_max(s));
+        if (__builtin_amdgcn_ballot_w64(!(s - m[g] <= kLazyMaxDot)) != 0) {
+            const float mnew = fmaxf(fmaxf(m[g], wave_max(s)), kLowestRef);
             const float alpha = __expf(m[g] - mnew);
             l[g] *= alpha;
             bv[g] *= alpha;
@@ -515,12 +516,13 @@ __device__ __forceinline__ void k_tile_block(const uint32_t *hdr32, const char *
         const float sk = scale * cst[i];
         sc[i][0] = fmaf(si, sc[i][0], sk);
         sc[i][1] = fmaf(si, sc[i][1], sk);
-        over = fmaxf(over, fmaxf(sc[i][0], sc[i][1]) - ts.m[i]);   // m = -inf before the first block: +inf
+        // m = -inf before the first block: +inf, whatever the scores are
+        over = fmaxf(over, fmaxf(fmaxf(sc[i][0], sc[i][1]), kLowestRef) - ts.m[i]);
     }
     if (__builtin_amdgcn_ballot_w64(over > kLazyMax) != 0) {
 #pragma unroll
         for (int i = 0; i < HL; i++) {
-            const float mnew = fmaxf(ts.m[i], half_max(fmaxf(sc[i][0], sc[i][1]), upper));
+            const float mnew = fmaxf(fmaxf(ts.m[i], half_max(fmaxf(sc[i][0], sc[i][1]), upper)), kLowestRef);
             const float alpha = __expf(ts.m[i] - mnew);
             ts.l[i] *= alpha;
             ts.bv[i] *= alpha;
@@ -815,7 +817,7 @@ __device__ __forceinline__ void buffered_units(const uint16_t *res, int res_toke
 #pragma unroll
         for (int i = 0; i < 4; i++)
             s[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, rk[i]), __builtin_bit_cast(v8h, qb[i]), v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        float p[4], mu = -INFINITY;
+        float p[4], mu = kLowestRef;
 #pragma unroll
         for (int r = 0; r < 4; r++) p[r] = (s[0][r] + s[1][r]) + (s[2][r] + s[3][r]);
 #pragma unroll
@@ -824,9 +826,8 @@ __device__ __forceinline__ void buffered_units(const uint16_t *res, int res_toke
             mu = fmaxf(mu, p[r]);
         }
         const float mnew = fmaxf(m, max_over_rows(mu));
-        const float ref = mnew == -INFINITY ? 0.f : mnew;  // so far every token scored -inf: numerators of 0
         if (u != first_unit && __builtin_amdgcn_ballot_w64(mnew > m) != 0) {
-            const float alpha = __expf(m - ref);
+            const float alpha = __expf(m - mnew);
             l *= alpha;
             for_heads<G>([&](auto gc) {
                 constexpr int g = decltype(gc)::value;
@@ -838,7 +839,7 @@ __device__ __forceinline__ void buffered_units(const uint16_t *res, int res_toke
         m = mnew;
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-            p[r] = __expf(p[r] - ref);
+            p[r] = __expf(p[r] - mnew);
             l += p[r];
         }
         row_operand(p[0], p[1], p[2], p[3]);
@@ -865,8 +866,8 @@ __device__ __forceinline__ void buffered_units(const uint16_t *res, int res_toke
     if (col < G) {
         float *pm = merge_word<G>(ml, 0, col, wave), *pl = merge_word<G>(ml, 1, col, wave), *pb = merge_word<G>(ml, 2, col, wave);
         const float ma = *pm, mx = fmaxf(ma, m);
-        fa = ma == -INFINITY ? 0.f : __expf(ma - mx);  // 0 for a state that is still empty
-        fb = m == -INFINITY ? 0.f : __expf(m - mx);
+        fa = __expf(ma - mx);  // 0 for a state that is still empty
+        fb = __expf(m - mx);
         const float l1 = fmaf(*pl, fa, l * fb), bv1 = *pb * fa;
         wave_sync();
         if (grp == 0) { *pm = mx; *pl = l1; *pb = bv1; }

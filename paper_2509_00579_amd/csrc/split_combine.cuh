@@ -15,6 +15,12 @@
 
 namespace kvc {
 
+// The lowest reference of a softmax state that has met a token.  A maximum over tokens that all score -Inf or NaN is -Inf (fmaxf
+// passes a NaN over), and against a reference of -Inf the numerators of the former would be NaN, while a state with the latter
+// would look like one that has met nothing.  Against this one they are 0 and NaN.  So a reference of -Inf says that a state holds
+// nothing, to every merge, and a NaN score makes its head's output NaN whatever wave or split it is in.
+constexpr float kLowestRef = -3.402823466e38f;
+
 __device__ __forceinline__ void store_agent(float *p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -89,7 +95,7 @@ __device__ __forceinline__ void finish_splits(float *partials, uint32_t *counter
         request(0);
         float mx = fmaxf(m0, m1);
         mx = wave_max(mx);
-        // a split that had nothing to do, or whose tokens all score -inf (m = -inf), takes no part, whatever its words are
+        // a split that had nothing to do (m = -inf) takes no part, whatever its words are
         if (m0 == -INFINITY) l0 = 0.f;
         if (m1 == -INFINITY) l1 = 0.f;
         const unsigned long long live0 = __builtin_amdgcn_ballot_w64(m0 != -INFINITY),

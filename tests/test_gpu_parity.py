@@ -539,6 +539,63 @@ def test_units_that_score_minus_infinity_for_one_head_only(gpu, oracle, G):
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 @pytest.mark.parametrize("limit", [6, 12])
+@pytest.mark.parametrize("blocks", [0, 1, 2, 3, 9])
+def test_a_buffered_token_that_scores_nan(gpu, oracle, G, limit, blocks):
+    """A NaN in the K of the newest token, or Infs of both signs there, makes the output NaN: alone in its unit of 16 and with one
+    token beside it, on a wave of its own and on one with blocks, in every split."""
+    _say(f"a buffered token that scores NaN, groups of {G}, code words of up to {limit} bits, {blocks} blocks")
+    B, H = 1, 2
+    q = W.make_queries(B, G * H, 1, 67)[0]
+    q[..., 30:32] = 1.0
+    for buffered in (0, 1, 16, 17):            # in front of the token
+        n = 64 * blocks + buffered
+        Kx, Vx = W.make_kv(B, H, max(n, 64), 67)
+        kn, vn = W.make_new_tokens(B, H, 2, 67)
+        for bad in ((np.nan, 0.0), (np.inf, -np.inf)):
+            gc = gpu.KVCompCache(B, H, G * H, 64 * 10, 1e-2, 1e-2, max_code_len=limit)
+            gc.build_codebook(_dev(Kx), _dev(Vx))
+            if n:
+                gc.compress_blocks(_dev(Kx[:, :n]), _dev(Vx[:, :n]))
+            kn[0, ..., 30:32] = bad
+            for t in range(2):                 # the token appended inside the launch, then one behind it
+                assert np.isnan(gc.append_attn_decode(_dev(kn[t]), _dev(vn[t]), _dev(q), SCALE).cpu().numpy()).all()
+                for n_splits in (1, 2):
+                    for waves in (0, 1, 2, 3, 4, 5, 8):
+                        gc.set_tuning(n_splits=n_splits, waves=waves)
+                        out = gc.attn_decode(_dev(q), SCALE).cpu().numpy()
+                        assert np.isnan(out).all(), (buffered, bad, t, n_splits, waves)
+                gc.set_tuning()
+            gc.close()
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("blocks", [2, 9])
+def test_blocks_that_score_minus_infinity(gpu, G, blocks):
+    """Blocks whose tokens all score -Inf (a scale that overflows) take no part, first blocks of a wave and of a split among them:
+    the output is the mean of V over the blocks that score 0, whose V is the same for every token and exact."""
+    _say(f"blocks that score -Inf, groups of {G}, {blocks} blocks")
+    B, H, S = 1, 2, 64 * blocks
+    rng = np.random.default_rng(68)
+    Kx, Vx = np.zeros((B, S, H, 128), np.float16), rng.standard_normal((B, S, H, 128)).astype(np.float16)
+    q = rng.standard_normal((B, G * H, 128)).astype(np.float16)
+    q[..., 5] = -2.0
+    for live in (0, blocks - 1):
+        Kx[..., 5] = 1.0
+        Kx[:, 64 * live:64 * (live + 1), :, 5] = 0.0
+        Vx[:, 64 * live:64 * (live + 1)] = (np.arange(128) % 2).astype(np.float16)   # the two ends of every token's range
+        gc = gpu.KVCompCache(B, H, G * H, S, 1e-2, 1e-2)
+        gc.build_codebook(_dev(Kx), _dev(Vx))
+        gc.compress_blocks(_dev(Kx), _dev(Vx))
+        for n_splits in (0, 1, 2, blocks):
+            for waves in (0, 1, 2, 3, 8):
+                gc.set_tuning(n_splits=n_splits, waves=waves)
+                out = gc.attn_decode(_dev(q), 3e38).cpu().numpy()
+                np.testing.assert_allclose(out, np.broadcast_to(np.arange(128) % 2, out.shape), rtol=0, atol=1e-5)
+        gc.close()
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("limit", [6, 12])
 def test_a_wave_for_each_record_of_a_pair(gpu, oracle, G, limit):
     _say(f"K and V records of a pair on two waves, and on one; groups of {G}, code words of up to {limit} bits")
     B, H = 1, 2
