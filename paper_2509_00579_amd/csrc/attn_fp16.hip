@@ -136,7 +136,7 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_kernel(int B, i
             for (int i = 1; i < 16; i++) ml = fmaxf(ml, s[g][i]);
             ml = fmaxf(ml, __shfl_xor(ml, 16));
             ml = fmaxf(ml, __shfl_xor(ml, 32));
-            const float mnew = fmaxf(m[g], ml);
+            const float mnew = fmaxf(fmaxf(m[g], ml), kLowestRef);
             const float alpha = __expf(m[g] - mnew);
             m[g] = mnew;
             float ps = 0.f;
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
     if (t0 < t_end) load_k(t0);
     for (; t0 < t_end; t0 += 64 * kBWaves) {
         load_v(t0);
-        float s[16], ml = -INFINITY;
+        float s[16], ml = kLowestRef;
 #pragma unroll
         for (int tt = 0; tt < 4; tt++) {
             const uint4 k4[4] = {kv[tt * 4], kv[tt * 4 + 1], kv[tt * 4 + 2], kv[tt * 4 + 3]};
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(64 * kBWaves, 2) void baseline_attn_gqa_kernel(
         if (__builtin_amdgcn_ballot_w64(ml - m > kLazyMaxFp16) != 0) {
             ml = fmaxf(ml, __shfl_xor(ml, 16));
             ml = fmaxf(ml, __shfl_xor(ml, 32));
-            const float mnew = fmaxf(m, ml);  // finite: the tile holds at least one token
+            const float mnew = fmaxf(m, ml);  // not -inf
             const float alpha = __expf(m - mnew);
             m = mnew;
             lsum *= alpha;

@@ -1166,6 +1166,31 @@ def test_fp16_attention_of_splits_that_score_minus_infinity(gpu, G, n_splits, de
         assert np.abs(out[0, g] - ref).max() <= 1e-5, g
 
 
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("n_splits,first,last", [(1, 0, 64), (1, 64, 128), (1, 192, 256), (1, 256, 500), (2, 0, 64), (2, 256, 512),
+                                                 (20, 256 * 3, 256 * 19), (20, 256 * 19, 256 * 20)])
+def test_fp16_attention_of_tiles_that_score_minus_infinity_or_nan(gpu, G, n_splits, first, last):
+    """Tiles of 64 tokens and splits of 256, a wave's first and later ones: tokens with score -Inf take no part, and NaN scores make
+    the output NaN."""
+    B, H, S = 1, 2, 256 * n_splits + (300 if n_splits == 1 else 0)
+    rng = np.random.default_rng(n_splits + G + first)
+    Kx, Vx = (rng.standard_normal((B, S, H, 128)).astype(np.float16) for _ in range(2))
+    q = rng.standard_normal((B, H * G, 128)).astype(np.float16)
+    q[..., 17] = 1.0
+    live = np.ones(S, bool)
+    live[first:last] = False
+    k64, v64, q64 = (x.astype(np.float64) for x in (Kx[0, live], Vx[0, live], q[0]))
+    attn = gpu.BaselineFp16Attention(B, H, H * G)
+    Kx[:, ~live, :, 17] = -np.inf
+    out = attn(_dev(Kx), _dev(Vx), _dev(q), 0.125, n_splits=n_splits).cpu().numpy()
+    for g in range(H * G):
+        s = k64[:, g // G] @ q64[g] / 8
+        p = np.exp(s - s.max())
+        assert np.abs(out[0, g] - p @ v64[:, g // G] / p.sum()).max() <= 1e-5, g
+    Kx[:, ~live, :, 17] = np.nan
+    assert np.isnan(attn(_dev(Kx), _dev(Vx), _dev(q), 0.125, n_splits=n_splits).cpu().numpy()).all()
+
+
 def test_config1_full_size_sampled(gpu, oracle):
     """The benchmark workload (32 heads x 4096 tokens) in the launch configuration bench.py times."""
     w = W.CONFIGS["c1"]
