@@ -78,8 +78,10 @@ inline Layout make_layout(const kvcomp_config &c) {
     L.res = at; at += align_up(2 * (size_t)c.batch * buffer_tokens(c) * c.n_kv_heads * kD * 2, 256);
     L.partials = at; at += align_up((size_t)c.batch * c.n_q_heads * kMaxSplits * kPartialStride * 4, 256);
     L.payload = at;
+    // placements leave kStreamSlack bytes behind the last record: a record that is decoded where it lies is read beyond its end
+    static_assert(kStreamSlack <= 256, "the spare bytes hold it");
     const size_t pay = BH * (size_t)L.max_blocks * (worst_k + worst_v) + 256;
-    L.payload_cap16 = pay / 16;
+    L.payload_cap16 = (pay - kStreamSlack) / 16;
     at += align_up(pay, 256);
     L.total = at;
     return L;
