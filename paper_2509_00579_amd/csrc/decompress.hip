@@ -5,6 +5,7 @@
 //     x' = fp16( min + float(code) * width ),   binary32 multiply, binary32 add, one rounding.
 #include "huff_decode.cuh"
 #include "kvcomp_internal.h"
+#include "tree_walk.cuh"
 
 namespace kvc {
 
@@ -185,25 +186,8 @@ __global__ __launch_bounds__(64 * kDecWaves, 4) void decompress_kernel(DecompArg
 }
 
 // ---- the paper's bit-serial decoder, kept for an A/B on this hardware ----------------------------------------------
-// One chain of the bit-serial decoder of Section 3.3.1: one stream bit per step, node = tree[node][bit], a symbol
-// is emitted and the walk restarts at the root when a leaf is reached; no branch depends on the data.
-struct TreeWalk {
-    int node, count;  // current inner node, symbols emitted so far
-    __device__ __forceinline__ void init() { node = 0; count = 0; }
-    // returns the symbol (>= 0) if this bit completed a code word of a chain that still has symbols to give, else -1
-    __device__ __forceinline__ int step(const int16_t *tree, uint32_t bit) {
-        const int next = tree[node * 2 + (int)bit];
-        const bool leaf = next < 0, live = count < kHalf;
-        node = leaf ? 0 : next;
-        const int sym = (leaf && live) ? ~next : -1;
-        count += (leaf && live) ? 1 : 0;
-        return sym;
-    }
-};
-
 constexpr int kTreeRow = kD + 8;  // padded row of the code tile (bytes; keeps 8-byte reads aligned)
 __global__ __launch_bounds__(64 * kDecWaves) void tree_walk_kernel(DecompArgs a) {
-    constexpr int kWindowBits = 31;  // stream bits per window
     __shared__ __attribute__((aligned(16))) uint16_t tree_s[512];
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // per wave: the record, then the code tile
     const Geo &g = a.g;
@@ -229,48 +213,16 @@ __global__ __launch_bounds__(64 * kDecWaves) void tree_walk_kernel(DecompArgs a)
     const uint32_t sb = hdr32[mmb / 4 + lane];
     const uint32_t start = wave_excl_scan((sb & 0xffffu) + (sb >> 16), lane);
     const Unit *units = payload_units(hdr32 + (mmb + 2 * kSlices) / 4);
-    Quad<1> qd;
-    qd.open(units, start, sb & 0xffffu, sb >> 16);
-    // All four chains of the lane walk one bit per step; a window gives 31 bits, then every reader moves on by
-    // 31.  A chain stops emitting after its 32 symbols; the wave runs until every chain of every lane is done.
-    // K: lane = token, chains au/ad = channels 0..63 (up / down), bu/bd = channels 64..127
-    // V: lane = channels 2*lane (au/ad) and 2*lane+1 (bu/bd), symbol index = token
-    const int16_t *tree = reinterpret_cast<const int16_t *>(tree_s);
-    TreeWalk tw[4];
-#pragma unroll
-    for (int c = 0; c < 4; c++) tw[c].init();
-    auto emit = [&](int c, int sym, int idx) {  // chain c emitted its idx-th symbol
-        if (sym < 0) return;
-        const int pos = (c & 1) ? kSliceLen - 1 - idx : idx;  // chains 1 and 3 read downwards
-        if (which == 0) tile[lane * kTreeRow + (c >> 1) * kSliceLen + pos] = (uint8_t)sym;
-        else tile[pos * kTreeRow + 2 * lane + (c >> 1)] = (uint8_t)sym;
-    };
-    // 32 symbols of at most 12 bits need at most 13 windows of 31 bits: the bound also ends the loop on a
-    // damaged table
-    bool more = true;
-    for (int round = 0; round < 16 && more; round++) {
-        uint32_t w0, w1, w2, w3, behind;
-        qd.au.bits(w0, behind);
-        qd.ad.bits(w1, behind);
-        qd.bu.bits(w2, behind);
-        qd.bd.bits(w3, behind);
-        w0 >>= 1; w1 >>= 1; w2 >>= 1; w3 >>= 1;
-#pragma unroll 1
-        for (int k = 0; k < kWindowBits; k++) {
-            const int i0 = tw[0].count, i1 = tw[1].count, i2 = tw[2].count, i3 = tw[3].count;
-            emit(0, tw[0].step(tree, w0 & 1u), i0);
-            emit(1, tw[1].step(tree, w1 & 1u), i1);
-            emit(2, tw[2].step(tree, w2 & 1u), i2);
-            emit(3, tw[3].step(tree, w3 & 1u), i3);
-            w0 >>= 1; w1 >>= 1; w2 >>= 1; w3 >>= 1;
-        }
-        qd.au.advance(units, kWindowBits);
-        qd.ad.advance(units, kWindowBits);
-        qd.bu.advance(units, kWindowBits);
-        qd.bd.advance(units, kWindowBits);
-        const bool mine = tw[0].count < kHalf || tw[1].count < kHalf || tw[2].count < kHalf || tw[3].count < kHalf;
-        more = __any(mine);
-    }
+    // K: lane = token, chains 0 and 1 = channels 0..63 (up / down), 2 and 3 = channels 64..127
+    // V: lane = channels 2*lane (chains 0 and 1) and 2*lane+1, symbol index = token
+    walk_chains(units, reinterpret_cast<const int16_t *>(tree_s), start, sb & 0xffffu, sb >> 16,
+                [&](int c, int sym, int idx) {  // chain c emitted its idx-th symbol
+                    if (sym < 0) return;
+                    const int pos = (c & 1) ? kSliceLen - 1 - idx : idx;  // chains 1 and 3 read downwards
+                    if (which == 0) tile[lane * kTreeRow + (c >> 1) * kSliceLen + pos] = (uint8_t)sym;
+                    else tile[pos * kTreeRow + 2 * lane + (c >> 1)] = (uint8_t)sym;
+                },
+                [](bool mine) { return __any(mine) != 0; });
     wave_sync();
     // dequantize and write: instruction i covers tokens 4 i + lane / 16, channels 8 (lane % 16) .. + 7 (four rows)
     const int c0 = (lane & 15) * 8, sub = lane >> 4;

@@ -1,8 +1,8 @@
 // CPU-only check program, built by tests/test_stream_bounds.py with -fsanitize=address,undefined: the stream readers and the
-// decoders of huff_decode.cuh, compiled for the CPU lane by lane, over records of the oracle's encoder that end kStreamSlack
-// bytes in front of the end of their allocation.  Every read behind that (or in front of the record) is a sanitizer report, and
-// every code has to come out.  The arena's layout is checked to leave as much behind the last record that fits.
-// Exit status 0 = all checks passed.
+// decoders of huff_decode.cuh and tree_walk.cuh, compiled for the CPU lane by lane, over records of the oracle's encoder that
+// end kStreamSlack bytes in front of the end of their allocation.  Every read behind that (or in front of the record) is a
+// sanitizer report, and every code has to come out.  The arena's layout is checked to leave as much behind the last record
+// that fits.  Exit status 0 = all checks passed.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -11,6 +11,7 @@
 
 #include "../../paper_2509_00579_amd/csrc/host_logic.h"
 #include "../../paper_2509_00579_amd/csrc/huff_decode.cuh"
+#include "../../paper_2509_00579_amd/csrc/tree_walk.cuh"
 
 extern "C" {
 size_t orc_encode_block(int which, int k_mode, const uint8_t *codes, const uint16_t *minmax, const uint8_t *len,
@@ -90,6 +91,22 @@ static void decode(const Record &r, const Book &book, const std::vector<uint8_t>
     }
 }
 
+// the bit-serial walk, as long as the slowest lane of a wave may keep the others going
+static void walk(const Record &r, const Book &book, const std::vector<uint8_t> &codes) {
+    for (int lane = 0; lane < 64; lane++) {
+        const int sa = 2 * lane;
+        int emitted = 0;
+        walk_chains(r.units(), book.tree.data(), r.start(sa), r.bits(sa), r.bits(sa + 1),
+                    [&](int c, int sym, int idx) {
+                        if (sym < 0) return;
+                        CHECK(sym == codes[code_at(r.which, sa + (c >> 1), (c & 1) ? kSliceLen - 1 - idx : idx)]);
+                        emitted++;
+                    },
+                    [](bool) { return true; });
+        CHECK(emitted == 2 * kSliceLen);
+    }
+}
+
 static void records(std::mt19937_64 &rng) {
     int cases = 0;
     for (int round = 0; round < 120; round++) {
@@ -123,6 +140,7 @@ static void records(std::mt19937_64 &rng) {
         if (book.bits <= 8) decode<8>(r, book, codes);
         if (book.bits <= 10) decode<10>(r, book, codes);
         decode<12>(r, book, codes);
+        walk(r, book, codes);
         cases++;
     }
     std::printf("records: %d\n", cases);

@@ -1,6 +1,6 @@
 """How far the decoders' stream readers read, under AddressSanitizer and UndefinedBehaviorSanitizer on the CPU:
-tests/sanitize/streams.cc compiles them from huff_decode.cuh (tests/sanitize/shim stands in for HIP's headers) and runs them
-over records that are followed by the slack they are promised and by nothing else."""
+tests/sanitize/streams.cc compiles them from huff_decode.cuh and tree_walk.cuh (tests/sanitize/shim stands in for HIP's
+headers) and runs them over records that are followed by the slack they are promised and by nothing else."""
 import pathlib
 import shutil
 import subprocess
