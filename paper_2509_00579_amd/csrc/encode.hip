@@ -199,14 +199,15 @@ __global__ __launch_bounds__(kPlaceThreads) void place_scan_kernel(Geo g, int n_
     }
     // The host only starts a placement that fits the arena.  A replay of a captured flush without the eager calls in
     // between (which the interface forbids) would advance the tail on every replay: a placement that would run past
-    // the arena sets a fault bit, points its entries at the arena start (so that later readers stay in bounds) and
-    // leaves the tail where it is; the write pass then writes nothing.
+    // the arena sets a fault bit, leaves its entries empty and the tail where it is; the write pass then writes nothing,
+    // and while the bit is up no placement finds room.  An entry of a record that was never written would have a reader take
+    // whatever is there for bit counts, and one that is too long for a staging area be followed far out of the arena.
     const uint32_t tail0 = g.ctrl->tail_base;
-    if ((unsigned long long)tail0 + need > (unsigned long long)g.payload_cap16) {
+    if ((g.ctrl->fault & kFaultArenaFull) || (unsigned long long)tail0 + need > (unsigned long long)g.payload_cap16) {
 #pragma unroll
         for (int k = 0; k < kPlacePerThread; k++) {
             const int i = c0 + k * kPlaceThreads + tid;
-            if (i < it.n_items) it.entry(i)->off16 = 0;
+            if (i < it.n_items) *it.entry(i) = {0, 0};
         }
         if (blockIdx.x == 0 && tid == 0) atomicOr(&g.ctrl->fault, kFaultArenaFull);
         return;
@@ -325,11 +326,11 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
     }
     __syncthreads();
     // a placement that would run past the arena: as in place_scan_kernel
-    const bool fits = (unsigned long long)tail0 + sh.need <= (unsigned long long)g.payload_cap16;
+    const bool fits = !(g.ctrl->fault & kFaultArenaFull) && (unsigned long long)tail0 + sh.need <= (unsigned long long)g.payload_cap16;
 #pragma unroll
     for (int k = 0; k < REGS; k++) {
         const int i = k * THREADS + tid;
-        if (k * THREADS < n_items && i < n_items) *entry(i) = {fits ? tail0 + sh.tot[k * kWaves + wave] + at[k] : 0u, size[k]};
+        if (k * THREADS < n_items && i < n_items) *entry(i) = fits ? BlockEntry{tail0 + sh.tot[k * kWaves + wave] + at[k], size[k]} : BlockEntry{0, 0};
     }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) biggest = max(biggest, (uint32_t)__shfl_xor(biggest, m));

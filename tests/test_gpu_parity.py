@@ -1049,6 +1049,39 @@ def test_flush_replayed_past_the_arena_is_refused(gpu):
     gc.close()
 
 
+@pytest.mark.parametrize("B,H", [(1, 1), (25, 16)])
+def test_blocks_that_found_no_room_have_empty_entries(gpu, B, H):
+    """The same with few records (placed by the last workgroup) and with many (placed by launches): until the fault is reported,
+    no block that was refused has an entry that a reader would follow, and no later one is admitted."""
+    import torch
+    _say(f"entries of refused blocks, {B} x {H} heads")
+    Kx, Vx = W.make_kv(B, H, 128, 38)
+    gc = gpu.KVCompCache(B, H, H, 192, 1e-2, 1e-2)
+    dK, dV = _dev(Kx), _dev(Vx)
+    gc.build_codebook(dK, dV)
+    gc.compress_blocks(dK[:, :64].contiguous(), dV[:, :64].contiguous())
+    kn, vn = W.make_new_tokens(B, H, 64, 38)
+    dkn, dvn, zero = _dev(kn), _dev(vn), torch.zeros((B, H, 128), dtype=torch.float16, device="cuda:0")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for t in range(64):
+            gc.append_token(dkn[t], dvn[t])
+    for _ in range(16):
+        graph.replay()
+    torch.cuda.synchronize()
+    for which, b, h in ((K, 0, 0), (V, 0, 0), (V, B - 1, H - 1)):
+        assert gc.block_entry(which, b, h, 1) == (0, 0)
+    for t in range(64):       # smaller records, which would fit
+        gc.append_token(zero, zero)
+    for which, b, h in ((K, 0, 0), (V, 0, 0), (V, B - 1, H - 1)):
+        assert gc.block_entry(which, b, h, 2) == (0, 0)
+    with pytest.raises(gpu.KvcompError) as e:
+        gc.stats()
+    assert e.value.status == gpu.ERR_CAPACITY
+    gc.close()
+
+
 @pytest.mark.parametrize("B,H,Hq,S", [(1, 2, 2, 1000), (2, 2, 8, 300), (1, 1, 8, 64), (1, 4, 8, 4100)])
 def test_fp16_baseline_attention(gpu, oracle, B, H, Hq, S):
     """The uncompressed comparison kernel (Section 4.3) against the oracle's attention on the raw fp16 values
