@@ -461,13 +461,19 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
         const int by_chip = std::max(1, kCUs * wgs_per_cu / bh);
         const auto in_splits_of = [&](int pairs) { return (ctx->n_blocks + pairs - 1) / pairs; };
         // At least one block pair per SIMD of the CU.  Fewer leave each wave more of the LDS pipe, but there are more partials to
-        // merge: two or three pairs pay while there are few splits.  us a step with 2, 3 and 4 pairs a split: 1 head x 16
-        // blocks 7.5 7.7 8.1, x 64 blocks 8.0 8.2 8.3, x 128 8.7 8.5 8.7; 8 heads, groups of 4, x 16 8.9 8.9 9.2, x 31 9.8 9.4
-        // 9.4, groups of 8, x 8 9.3 9.4 9.7, x 31 11.0 10.5 10.4; 32 heads x 8 8.0 7.9 8.3, x 16 8.6 8.4 8.6, x 31 10.4 10.1
-        // 9.1, groups of 8, x 16 10.9 10.5 10.5, x 31 20.2 17.6 11.2 (beyond one workgroup per CU).
+        // merge: two or three pairs pay while there are few splits, for groups of 4 and 8 as many as one pass of a head's merge
+        // takes (16).  us a step with 2, 3 and 4 pairs a split, code words of up to 6 bits:
+        //   1 head, groups of 1: 16 blocks 7.7 8.0 8.3, 64 8.2 8.3 8.4, 128 8.9 8.7 8.8
+        //           groups of 4: 32 8.9 9.0 9.4, 40 9.6 9.0 9.3, 64 10.1 9.9 9.6;  of 8: 40 10.7 10.2 10.3, 64 11.5 11.4 10.8
+        //   4 heads x 40: groups of 1 8.6 8.2 8.4, of 4 10.1 9.3 9.5, of 8 11.5 10.6 10.5
+        //   8 heads, groups of 4: 16 9.0 9.0 9.2, 31 9.9 9.6 9.6;  of 8: 8 9.4 9.6 9.8, 31 11.1 10.7 10.5
+        //   32 heads, groups of 1: 8 7.9 8.0 8.3, 16 8.8 8.6 8.8, 31 10.7 10.2 9.3
+        //             groups of 8: 16 11.0 10.6 10.7, 31 20.2 17.8 11.5 (beyond one workgroup per CU)
         int by_work = in_splits_of(4);
-        if (in_splits_of(2) <= 32 && in_splits_of(2) * bh <= 64) by_work = in_splits_of(2);
-        else if (in_splits_of(3) <= 8 && in_splits_of(3) * bh <= kCUs) by_work = in_splits_of(3);
+        if (in_splits_of(2) <= (g.G >= 4 ? 16 : 32) && in_splits_of(2) * bh <= 64) by_work = in_splits_of(2);
+        else if ((in_splits_of(3) <= 8 && in_splits_of(3) * bh <= kCUs) ||
+                 (in_splits_of(3) <= 16 && in_splits_of(3) * bh <= (g.G >= 8 ? 32 : 64)))
+            by_work = in_splits_of(3);
         // One split has nothing to merge across workgroups.  In 1 and in 2 splits, 4 5 6 blocks: 8 heads 6.1 7.0 7.6 against 7.2
         // 7.5 7.6; groups of 8 7.8 9.0 9.5 against 9.2 9.4 9.5.
         if (2 * ctx->n_blocks + units <= paired_waves) by_work = 1;
