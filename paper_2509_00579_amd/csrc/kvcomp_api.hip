@@ -486,11 +486,20 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     const int units_per_split = (units + n_splits - 1) / n_splits;
     const bool paired = bps > 0 && 2 * bps + units_per_split <= paired_waves;
     // Sixteen waves that have more than one pair each but not two leave a last round of a few waves that cannot fill the LDS
-    // pipe; twelve spread it a little better.  32 heads in 8 splits of n pairs, 16 against 12 waves, n = 16 18 20 24 28 31 34 64:
-    // groups of 1 19.3 21.7 22.3 24.2 26.2 28.0 29.0 45.1 against 20.0 21.2 21.5 23.8 26.5 28.1 30.2 46.6 us; groups of 4 20.1
-    // 22.7 23.2 25.2 27.4 29.7 31.4 48.7 against 20.9 22.5 22.9 25.4 27.1 29.8 32.6 50.7; groups of 2 with code words of up to
-    // 10 bits, n = 18 20 28 31: 28.6 29.2 35.5 38.8 against 28.4 28.8 35.2 38.8.
-    if (ctx->tune_waves <= 0 && max_waves == 16 && bps > 16 && bps < 32) max_waves = 12;
+    // pipe; twelve spread it a little better.  32 heads in 8 splits of n pairs, 16 against 12 waves, n = 18 20 24 28 31:
+    //   groups of 1, up to 6 bits 21.8 22.4 24.1 25.9 27.9 against 21.3 21.7 23.7 26.3 28.1 us, 12 bits 29.6 30.3 33.5 37.4 40.7
+    //   against 28.8 29.3 32.9 36.8 39.8;  groups of 2, 10 bits 28.8 29.6 32.5 35.7 38.9 against 28.6 29.0 32.3 35.3 38.7
+    //   groups of 4, 6 bits, 2e-2 (largest record 5408 bytes) 23.0 23.4 25.5 27.7 30.1 against 22.7 23.1 25.7 27.4 30.0
+    // From 32 pairs on sixteen are the faster (n = 34 64: 29.3 45.3 against 30.5 46.7, groups of 4 31.7 49.2 against 32.8 51.1).
+    // Thirteen to fifteen, where the LDS has no room for more (groups of 4 with records above 6224 bytes), load the SIMDs unevenly,
+    // too: a round is four waves on some and three on the others.  Twelve instead, up to two rounds and a half, where that
+    // leaves the busiest SIMD fewer pairs: groups of 4, 6 bits, 1e-2 (6528 bytes), 15 against 12 waves, n = 16 20 24 28 31 32:
+    // 23.4 25.6 27.9 30.3 32.2 32.4 against 22.1 24.0 26.8 28.6 31.3 31.5; otherwise the two are within 2 % (n = 18 22: 23.9 26.0
+    // and 23.6 26.2), and beyond fifteen are the faster (n = 33 64: 32.5 53.1 against 33.8 53.7).
+    const auto busiest = [&](int waves) { return bps / waves * ((waves + 3) / 4) + (bps % waves + 3) / 4; };  // pairs of a SIMD
+    if (ctx->tune_waves <= 0 && ((max_waves == 16 && bps > 16 && bps < 32) ||
+                                 (max_waves > 12 && bps > 12 && bps <= 32 && busiest(12) < busiest(max_waves))))
+        max_waves = 12;
     // Buffered tokens only: two waves per SIMD for groups of 1, 2 and 4.  More only get in each other's way; 4, 8, 12 and 16
     // waves of groups of 1, 32 heads: 255 tokens 8.0 7.6 9.4 10.7 us, 1000 tokens 19.2 13.7 16.1 17.7, 4000 tokens 75.8 42.7
     // 47.4 46.9; groups of 4 with 4, 8, 12: 255 10.3 9.2 11.0, 4000 88 48.4 50.0.  Groups of 8 have more work per load: 255

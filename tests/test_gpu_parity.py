@@ -612,6 +612,25 @@ def test_a_wave_for_each_record_of_a_pair(gpu, oracle, G, limit):
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("rel", [1e-2, 2e-2])
+def test_pairs_of_a_split_on_twelve_to_sixteen_waves(gpu, oracle, G, rel):
+    """One split with as many block pairs as the rules for its waves go by: groups of 4 have room for fifteen waves at 1e-2 and for
+    sixteen at 2e-2, groups of 1 and 2 for sixteen."""
+    _say(f"one split of up to 33 pairs, groups of {G}, bound {rel}")
+    q = W.make_queries(1, G, 1, 69)[0]
+    for blocks in (12, 13, 15, 16, 17, 20, 31, 32, 33):
+        _, _, oc, gc = _both(gpu, oracle, 1, 1, G, 64 * 12, 64 * blocks + 21, 64 * 40, rel, rel, 69, 6)
+        if G == 4 and blocks == 33:
+            room = (160 * 1024 - 32768 - 4 * (512 + 192) - 512) // (gc.stats()["max_record_bytes"] + 32 + 12 * 144)
+            assert room == 15 if rel == 1e-2 else room >= 16
+        ref = oc.attn_decode(q, SCALE)
+        for waves in (0, 12, 13, 14, 15, 16):
+            gc.set_tuning(n_splits=1, waves=waves)
+            _attn_close(gc.attn_decode(_dev(q), SCALE).cpu().numpy(), ref)
+        gc.close()
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_query_at_any_element_of_a_larger_tensor(gpu, oracle, G):
     """The query may start at any fp16 element: blocks and buffered tokens give the same bits as from an aligned copy."""
     import torch
