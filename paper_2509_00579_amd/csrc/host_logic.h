@@ -87,6 +87,16 @@ inline Layout make_layout(const kvcomp_config &c) {
     return L;
 }
 
+// A wave's staging area in the fused kernel, given the largest record that the host knows of.  Not a byte more than its streams'
+// look-ahead asks for, except where a flush has been queued since the host looked: the blocks that it compressed may hold a
+// slightly longer record, and one that does not fit is decoded from global memory in every step from then on (8 heads x 1024
+// tokens and a flushed record 16 bytes above the prompt's largest: 10.3 instead of 9.0 us a step for groups of 4, 12.2 instead of
+// 10.0 for groups of 8).
+constexpr int kStageGrowth = 128;
+inline int stage_bytes_for(uint32_t max_size16, bool may_have_grown) {
+    return std::max((int)(max_size16 * 16) + kStreamSlack + (may_have_grown ? kStageGrowth : 0), 4608);
+}
+
 // ---- Huffman codebook (Section 3.1.2), canonical and length-limited --------------------------------------------
 // Two-queue construction over leaves sorted by (count, symbol); on equal weight a leaf is taken before a merged
 // node and merged nodes leave in creation order, which fixes the code lengths uniquely.

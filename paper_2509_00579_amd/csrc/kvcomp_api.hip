@@ -437,7 +437,7 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     const int longest = std::max(g.lut_bits[0], g.lut_bits[1]);
     const size_t lds_fixed = fused_lds_fixed(g.G, longest);
     int stage = ctx->tune_stage;
-    if (stage <= 0) stage = (int)(ctx->max_size16 * 16) + kStreamSlack;
+    if (stage <= 0) stage = stage_bytes_for(ctx->max_size16, ctx->flushed || ctx->flush_anytime);
     stage = std::max(stage, 4608);
     stage = (int)align_up(stage, 16);
     const size_t per_wave_rest = fused_weight_bytes(g.G);

@@ -2,7 +2,7 @@
 // decoders of huff_decode.cuh and tree_walk.cuh, compiled for the CPU lane by lane, over records of the oracle's encoder that
 // end kStreamSlack bytes in front of the end of their allocation.  Every read behind that (or in front of the record) is a
 // sanitizer report, and every code has to come out.  The arena's layout is checked to leave as much behind the last record
-// that fits.  Exit status 0 = all checks passed.
+// that fits, and a staging area to hold the records that it may meet.  Exit status 0 = all checks passed.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -163,10 +163,20 @@ static void arena() {
     std::printf("arenas: %d\n", cases);
 }
 
+static void staging() {
+    for (uint32_t size16 = 0; size16 <= (uint32_t)kMaxRecordBytes / 16; size16++) {
+        const int known = stage_bytes_for(size16, false), flushed = stage_bytes_for(size16, true);
+        CHECK(known % 16 == 0 && flushed % 16 == 0);
+        CHECK((known - kStreamSlack) / 16 >= (int)size16);           // the largest record fits
+        CHECK((flushed - kStreamSlack) / 16 >= (int)size16 + 8);     // and behind a flush one that is 128 bytes longer
+    }
+}
+
 int main() {
     std::mt19937_64 rng(20250908);
     records(rng);
     arena();
+    staging();
     std::printf("streams driver: ok\n");
     return 0;
 }
