@@ -986,9 +986,12 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB, kPaired>::value), 1) void fus
         for (int k = 0; k < G / 4; k++) {
             const int i = tid + k * n_threads;
             float4 *dst = reinterpret_cast<float4 *>(qf + 8 * i);
+            // An Inf in a query makes its head's output NaN, as any score with it is +-Inf or NaN; the maximum that scales the weights
+            // of all heads passes over a NaN, and would leave the other heads no bits beside an Inf.
+            auto value = [](uint32_t bits) { const float x = h2f(bits); return fmaf(x, 0.f, x); };
             if (i < G * kD / 8) {
-                dst[0] = make_float4(h2f(qv[k].x & 0xffffu), h2f(qv[k].x >> 16), h2f(qv[k].y & 0xffffu), h2f(qv[k].y >> 16));
-                dst[1] = make_float4(h2f(qv[k].z & 0xffffu), h2f(qv[k].z >> 16), h2f(qv[k].w & 0xffffu), h2f(qv[k].w >> 16));
+                dst[0] = make_float4(value(qv[k].x & 0xffffu), value(qv[k].x >> 16), value(qv[k].y & 0xffffu), value(qv[k].y >> 16));
+                dst[1] = make_float4(value(qv[k].z & 0xffffu), value(qv[k].z >> 16), value(qv[k].w & 0xffffu), value(qv[k].w >> 16));
             }
         }
         if (tid < kD / 4) reinterpret_cast<uint32_t *>(zeros)[tid] = 0;

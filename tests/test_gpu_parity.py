@@ -569,6 +569,28 @@ def test_a_buffered_token_that_scores_nan(gpu, oracle, G, limit, blocks):
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("limit", [6, 12])
+def test_a_query_that_is_not_finite_spoils_its_own_head_only(gpu, oracle, G, limit):
+    """An Inf or a NaN in the query of one head: that head's output is NaN, the others' are what they are without it."""
+    _say(f"queries that are not finite, groups of {G}, code words of up to {limit} bits")
+    B, H, S = 1, 2, 64 * 9 + 21
+    _, _, oc, gc = _both(gpu, oracle, B, H, G * H, S, S, S, 1e-2, 1e-2, 70, limit)
+    q = W.make_queries(B, G * H, 1, 70)[0]
+    ref = oc.attn_decode(q, SCALE)
+    for head in {0, G - 1, G}:
+        for bad in (np.inf, -np.inf, np.nan):
+            qb = q.copy()
+            qb[0, head, 77] = bad
+            others = np.arange(G * H) != head
+            for n_splits, waves in ((0, 0), (1, 1), (1, 3), (2, 0)):
+                gc.set_tuning(n_splits=n_splits, waves=waves)
+                out = gc.attn_decode(_dev(qb), SCALE).cpu().numpy()
+                assert np.isnan(out[0, head]).all(), (head, bad, n_splits, waves)
+                _attn_close(out[0, others], ref[0, others])
+    gc.close()
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
 @pytest.mark.parametrize("blocks", [2, 9])
 def test_blocks_that_score_minus_infinity(gpu, G, blocks):
     """Blocks whose tokens all score -Inf (a scale that overflows) take no part, first blocks of a wave and of a split among them:
