@@ -1428,16 +1428,26 @@ def test_streams_of_short_and_of_very_unequal_slices(gpu, oracle, G, limit):
     oc.build_codebook(Kx, Vx)
     gc.build_codebook(_dev(Kx), _dev(Vx))
     assert all(int(oc.len[w][:51].min()) <= 3 and int(oc.len[w].max()) == limit for w in (K, V))
+    for j in (3, 6):                # two blocks of any code: records longer than a small staging area
+        for X in (Kx, Vx):
+            X[:, 64 * j:64 * (j + 1)] = rng.integers(0, 51, (B, 64, H, 128))
+        Kx[:, 64 * j], Kx[:, 64 * j + 1] = 0, 50
+        Vx[:, 64 * j:64 * (j + 1), :, 0], Vx[:, 64 * j:64 * (j + 1), :, 1] = 0, 50
     oc.compress_blocks(Kx, Vx)
     gc.compress_blocks(_dev(Kx), _dev(Vx))
+    sizes = [[gc.block_entry(w, 0, 1, j)[1] * 16 for j in range(9)] for w in (K, V)]
+    assert all(z[j] > 4608 for z in sizes for j in (3, 6))
+    assert limit == 6 or all(min(z) < 4608 - 32 for z in sizes)    # and records that fit it beside them
     for which in (K, V):
         got = gc.decompress(which, S).cpu().numpy()
         np.testing.assert_array_equal(got.view(np.uint16), oc.decompress(which).view(np.uint16))
     q = W.make_queries(B, G * H, 1, 41)[0]
     want = oc.attn_decode(q, 1e-3)
     _attn_close(gc.attn_decode(_dev(q), 1e-3).cpu().numpy(), want)
-    gc.set_tuning(n_splits=1, stage_bytes=4608)    # one wave after the other, and long records from global memory
-    _attn_close(gc.attn_decode(_dev(q), 1e-3).cpu().numpy(), want)
+    for waves in (0, 1, 3):                        # a wave for each pair, nine and three pairs one after the other
+        for stage_bytes in (0, 4608):              # records staged whatever their length, and long ones from global memory
+            gc.set_tuning(n_splits=1, waves=waves, stage_bytes=stage_bytes)
+            _attn_close(gc.attn_decode(_dev(q), 1e-3).cpu().numpy(), want)
     gc.close()
 
 
