@@ -12,8 +12,8 @@
 //    symbol lock-step (same trip count for every lane, no divergence), so the dequantization weight of the current
 //    symbol is the same for the whole wave and the products with it fit the matrix cores: int8 codes times the signed
 //    byte digits of integer weights, exact in int32 (groups of 1 and 2 query heads: "a dot product per lane"; groups of 4
-//    and 8: "tile path").  The table is indexed by as many stream bits as the longest code word of the codebook, and one
-//    32-bit window serves several symbols (floor(31 / table width)) with no refill test in between;
+//    and 8: "tile path").  The table is indexed by as many stream bits as the longest code word of the codebook, or by
+//    twelve for two symbols at a time, and one 32-bit window serves several lookups with no refill test in between (DecodeMode);
 //  * the dequantization is folded into the weights: q.k' = sum_c q_c min_c + sum_c (q_c step_c) code_tc, and
 //    p.v'  = sum_t p_t min_t + sum_t (p_t step_t) code_tc;
 //  * K and V of a block are handled by the same wave back to back with an online softmax, so scores never go to
@@ -717,10 +717,7 @@ __device__ __forceinline__ void soft_to_area(const TileSoft<G> &ts, float *area,
 // wave of the grid per (batch, head) owns that row, so there is one writer and no reader of the slot in this launch.
 // The result is merged into the wave's parked state (`area` and `ml`, see soft_to_area).
 // Inline: the decode loops leave room for it, and out of line it saves and restores the registers that a callee has to keep,
-// through scratch memory (4 x 8 heads x 9000 tokens, 1024 of them buffered, groups of 8: 29.3 -> 27.6 us).  Called by the kernels
-// with a wave per record for code words beyond 6 bits only: they have one unit or two and the registers of twelve waves.  Called
-// from kernels of sixteen waves it has 128 registers and spills (4 x 8 heads, groups of 4, 1000 buffered tokens and no block: 30
-// us where inline takes 17).
+// through scratch memory (4 x 8 heads x 9000 tokens, 1024 of them buffered, groups of 8: 29.3 -> 27.6 us).
 constexpr int kUnitTokens = 16;
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -887,6 +884,9 @@ __device__ __forceinline__ void buffered_units(const uint16_t *res, int res_toke
     wave_sync();
 }
 
+// The same out of line, for the kernels with a wave per record for code words beyond 6 bits: they have one unit or two, and the
+// registers of twelve waves.  Called from kernels of sixteen waves it would have 128 registers and spill (4 x 8 heads, groups of 4,
+// 1000 buffered tokens and no block: 30 us where inline takes 17).
 template <int G>
 __device__ __noinline__ void buffered_tokens(const uint16_t *res, int res_tokens, int B, int H, int b, int h,
                                              int res_head, int n_res, int first_unit, int unit_step,
@@ -949,7 +949,8 @@ __global__ __launch_bounds__((64 * MaxWaves<G, LB, kPaired>::value), 1) void fus
     // together, so the workgroup starts after two trips to memory (entry, record).  The entries are loaded without a branch
     // and last: their wait is everyone's, and the barrier behind it, which is there for the tables and the query, waits for no
     // record.  Every wave then waits for its own: all records of a launch's first round are requested at once (23 MB for 32
-    // heads x 32768 tokens), and the first ones arrive 2 us before the last.
+    // heads x 32768 tokens), and the first ones arrive 2 us before the last.  (With more than 128 levels the tables are biased
+    // behind that barrier, and the second barrier which that takes does wait for the records.)
     const int n_pairs = a.blocks_per_split;
     const bool is_v = kPaired && wave >= n_pairs;
     int j = j0 + wave;

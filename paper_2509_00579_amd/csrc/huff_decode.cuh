@@ -89,7 +89,8 @@ __device__ __forceinline__ void static_for(F &&f) {  // f(integral constant) for
 // read per two windows, off the critical path (only table lookups depend on each other).
 // The LDS pipe is the busiest unit of the decoders and the streams were a third of its work: a 4-byte gather of 64 lanes from
 // a record costs the pipe of a CU 2.5 ns, an aligned 8-byte one 2.2, two 4-byte halves in one ds_read2_b32 4.9, an 8-byte
-// one at an odd word 27 (lane by lane), and a chain of 32 symbols takes five aligned ones where it took nine of 4 bytes.
+// one at an odd word 27 (lane by lane), and a chain of 32 symbols takes five aligned ones where it took nine of 4 bytes (with
+// the pair table and tables of 7 bits; tables of 8 and 10 bits seven for twelve, of 12 bits nine for seventeen).
 struct __attribute__((aligned(8))) Unit { uint32_t lo, hi; };
 // payload: first word behind a record's header, 16-byte aligned.  The readers look at up to 16 bytes in front of it and, for
 // lookups that are never made, up to kStreamSlack bytes behind the record.

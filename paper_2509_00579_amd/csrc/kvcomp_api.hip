@@ -451,10 +451,11 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
                                                 (int)(kLdsBytesPerCU / (lds_fixed + max_waves * ((size_t)stage + per_wave_rest)))));
     const int bh = g.B * g.H, units = (ctx->n_res + 15) / 16;
     // A wave for each record of a pair where the wave slots would be empty.  It is the shorter chain against the SIMDs'
-    // sharing, so it ends at three waves per SIMD: 32 heads in 8 splits of n pairs, one query head per KV head, code words
-    // of up to 6 bits, n = 1 2 4 6 7 8: 8.9 8.8 9.7 11.3 12.4 13.0 us against 12.4 11.1 11.0 12.6 12.7 13.2; groups of 4,
-    // n = 2 4 6: 12.2 11.5 13.4 against 17.1 14.3 16.4; groups of 8: 16.6 14.7 16.7 against 24.5 19.4 20.5; groups of 1 with
-    // code words of up to 10 bits, n = 5 6: 12.0 12.5 against 14.2 14.3, groups of 2: 12.5 13.1 against 15.1 15.3.
+    // sharing, so it ends at three waves per SIMD.  32 heads in 8 splits of n pairs, a wave per record against a wave per pair, us a
+    // step, n = 2 4 6:
+    //   up to 6 bits, groups of 1  8.9 9.7 11.2 against 10.9 10.9 12.1,  of 2  9.5 10.3 11.8 against 11.5 11.4 12.9
+    //                 groups of 4 10.0 10.9 12.5 against 13.1 12.2 13.6, of 8 11.0 11.9 13.6 against 15.4 14.7 14.9
+    //   up to 10 bits, groups of 1 9.8 10.9 13.0 against 12.5 12.5 14.6, of 8 12.1 13.1 15.4 against 17.5 17.2 18.1
     const int paired_waves = std::min(max_waves, fused_max_waves(g.G, true));
     int n_splits = ctx->tune_splits;
     if (n_splits <= 0) {
@@ -500,10 +501,10 @@ static kvcomp_status attn_impl(kvcomp_ctx *ctx, const void *d_q, float scale, fl
     if (ctx->tune_waves <= 0 && ((max_waves == 16 && bps > 16 && bps < 32) ||
                                  (max_waves > 12 && bps > 12 && bps <= 32 && busiest(12) < busiest(max_waves))))
         max_waves = 12;
-    // Buffered tokens only: two waves per SIMD for groups of 1, 2 and 4.  More only get in each other's way; 4, 8, 12 and 16
-    // waves of groups of 1, 32 heads: 255 tokens 8.0 7.6 9.4 10.7 us, 1000 tokens 19.2 13.7 16.1 17.7, 4000 tokens 75.8 42.7
-    // 47.4 46.9; groups of 4 with 4, 8, 12: 255 10.3 9.2 11.0, 4000 88 48.4 50.0.  Groups of 8 have more work per load: 255
-    // tokens 14.4 12.9 13.8, 1000 33.6 26.4 26.6, 4000 136 83 75.5.
+    // Buffered tokens only: two waves per SIMD for groups of 1, 2 and 4.  More only get in each other's way.  us a step with 4, 8, 12
+    // and 16 waves, 32 heads x 255, 1000 and 4000 tokens: groups of 1 7.3 6.2 6.6 6.8, 18.9 12.4 13.4 14.1, 76.5 42.9 45.9 44.0; of
+    // 4 8.6 7.1 7.7 7.9, 22.3 14.9 15.8 16.5, 88.6 47.3 48.1 46.8.  Groups of 8 (4, 8, 12) have more work per load: 10.8 8.8 9.4,
+    // 27.8 21.9 20.9, 104 67.5 64.9.
     if (ctx->tune_waves <= 0 && ctx->n_blocks == 0 && g.G <= 4) max_waves = std::min(max_waves, 8);
     // at least a wave per query head of the group: the merges give every head a wave (8 heads x 8 blocks in 4 splits, groups of
     // 8: 10.5 -> 9.3 us)
