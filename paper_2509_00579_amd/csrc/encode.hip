@@ -282,6 +282,7 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
     constexpr int kWaves = THREADS / 64, kTotals = PlaceShared<THREADS, REGS>::kTotals, kPerLane = PlaceShared<THREADS, REGS>::kPerLane;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t tail0 = g.ctrl->tail16;  // only the last workgroup moves it
+    const bool full = (g.ctrl->fault & kFaultArenaFull) != 0;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);  // this wave's sizes have arrived
     __syncthreads();
@@ -326,7 +327,7 @@ __device__ __forceinline__ void place_if_last(const Geo &g, BlockEntry *rows, in
     }
     __syncthreads();
     // a placement that would run past the arena: as in place_scan_kernel
-    const bool fits = !(g.ctrl->fault & kFaultArenaFull) && (unsigned long long)tail0 + sh.need <= (unsigned long long)g.payload_cap16;
+    const bool fits = !full && (unsigned long long)tail0 + sh.need <= (unsigned long long)g.payload_cap16;
 #pragma unroll
     for (int k = 0; k < REGS; k++) {
         const int i = k * THREADS + tid;
